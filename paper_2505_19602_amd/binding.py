@@ -7,6 +7,10 @@ happens here.  Where a tensor's shape depends on how many rows a call keeps
 (idx [S,H,keep]), the binding works the number out only to check that shape
 before the call; what it returns is always the value the library wrote, and
 the two are asserted equal.
+
+The usual call takes none of the checks below: _marshal (csrc/marshal.cpp) does them in native
+code and crosses into C at once.  Only arguments that it does not take come back here (it
+answers None), to raise the error that names what is wrong or to be converted.
 """
 from __future__ import annotations
 
@@ -71,6 +75,11 @@ class Shape:
 
 
 _lib: Optional[ctypes.CDLL] = None
+_fast = None      # the _marshal module, bound to the loaded library's entry points
+
+# entry points in the order of struct Entry in csrc/marshal.cpp
+_MARSHALLED = ("scalekv_step", "scalekv_step_static", "scalekv_step_append_first", "scalekv_score", "scalekv_select",
+               "scalekv_select_window", "scalekv_select_positional", "scalekv_compact", "scalekv_attend", "scalekv_asi")
 
 
 def lib_path() -> str:
@@ -81,7 +90,7 @@ def lib_path() -> str:
 
 def lib() -> ctypes.CDLL:
     """Load libscalekv.so (built in-tree by paper_2505_19602_amd/build.py)."""
-    global _lib
+    global _lib, _fast
     if _lib is None:
         path = lib_path()
         if not os.path.exists(path):
@@ -92,6 +101,13 @@ def lib() -> ctypes.CDLL:
         L.scalekv_version.restype = ctypes.c_char_p
         for name in _STATUS_SYMBOLS:
             getattr(L, name).restype = ctypes.c_int
+        try:
+            from . import _marshal
+        except ImportError as exc:
+            raise ImportError(f"{HERE}/_marshal.so is missing or was built for another torch: run "
+                              "`python -m paper_2505_19602_amd.build` (there is no fallback path)") from exc
+        _marshal.bind(*[ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in _MARSHALLED])
+        _fast = _marshal
         _lib = L
     return _lib
 
@@ -103,6 +119,19 @@ def version() -> str:
 def _check(status: int) -> None:
     if status != 0:
         raise ScaleKVError(status, lib().scalekv_last_error().decode())
+
+
+def _marshaller():
+    if _fast is None:
+        lib()
+    return _fast
+
+
+def _checked(r: int) -> int:
+    """What _marshal returned: the call's own result, or a status as its negative."""
+    if r < 0:
+        _check(-r)
+    return r
 
 
 def _stream() -> ctypes.c_void_p:
@@ -154,6 +183,10 @@ def _ws(ws: Optional[torch.Tensor]):
 def score(shape: Shape, q_win: torch.Tensor, k: torch.Tensor, cache_len: int,
           log_scores: torch.Tensor, ws: torch.Tensor) -> None:
     """scalekv_score: q_win [S,H,n_win,d], k cache [S,H,cap,d] -> log_scores [S,H,cache_len] fp32."""
+    r = _marshaller().score(shape, q_win, k, cache_len, log_scores, ws)
+    if r is not None:
+        _checked(r)
+        return
     n_win = q_win.shape[2]
     _dense(q_win, shape, n_win, "q_win")
     if tuple(log_scores.shape) != (shape.n_seq, shape.n_head, cache_len) or log_scores.dtype != torch.float32 \
@@ -167,6 +200,9 @@ def score(shape: Shape, q_win: torch.Tensor, k: torch.Tensor, cache_len: int,
 
 def select(shape: Shape, scores: torch.Tensor, cache_len: int, budget: int, idx: torch.Tensor) -> int:
     """scalekv_select: scores [S,H,cache_len] fp32 -> idx [S,H,keep] int32; returns keep."""
+    r = _marshaller().select(shape, scores, cache_len, budget, idx)
+    if r is not None:
+        return _checked(r)
     if scores.dtype != torch.float32 or not scores.is_cuda or not scores.is_contiguous() \
             or tuple(scores.shape) != (shape.n_seq, shape.n_head, cache_len):
         raise ScaleKVError(1, "scores must be a contiguous fp32 device tensor [S,H,cache_len]")
@@ -186,6 +222,9 @@ def compact(shape: Shape, k_src: torch.Tensor, v_src: torch.Tensor, cache_len: i
             idx: Optional[torch.Tensor], keep: int, k_cur: Optional[torch.Tensor],
             v_cur: Optional[torch.Tensor], k_dst: torch.Tensor, v_dst: torch.Tensor) -> int:
     """scalekv_compact; returns keep + n_cur."""
+    r = _marshaller().compact(shape, k_src, v_src, cache_len, idx, keep, k_cur, v_cur, k_dst, v_dst)
+    if r is not None:
+        return _checked(r)
     n_cur = 0 if k_cur is None else k_cur.shape[2]
     if k_cur is not None:
         _dense(k_cur, shape, n_cur, "k_cur")
@@ -205,6 +244,10 @@ def compact(shape: Shape, k_src: torch.Tensor, v_src: torch.Tensor, cache_len: i
 def attend(shape: Shape, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, kv_len: int,
            out: torch.Tensor) -> None:
     """scalekv_attend: q [S,H,n_q,d], caches k/v (first kv_len rows) -> out [S,H,n_q,d]."""
+    r = _marshaller().attend(shape, q, k, v, kv_len, out)
+    if r is not None:
+        _checked(r)
+        return
     n_q = q.shape[2]
     _dense(q, shape, n_q, "q")
     _dense(out, shape, n_q, "out")
@@ -218,6 +261,10 @@ def step(shape: Shape, q: torch.Tensor, k_cur: torch.Tensor, v_cur: torch.Tensor
          k_dst: torch.Tensor, v_dst: torch.Tensor, out: torch.Tensor,
          idx_out: Optional[torch.Tensor], ws: Optional[torch.Tensor]) -> int:
     """scalekv_step; returns the new cache length keep + n_cur."""
+    r = _marshaller().step(shape, q, k_cur, v_cur, win_idx, k_src, v_src, cache_len, budget, k_dst, v_dst, out,
+                           idx_out, ws)
+    if r is not None:
+        return _checked(r)
     n_cur = q.shape[2]
     _dense(q, shape, n_cur, "q"); _dense(k_cur, shape, n_cur, "k_cur"); _dense(v_cur, shape, n_cur, "v_cur")
     _dense(out, shape, n_cur, "out")
@@ -245,6 +292,10 @@ def step_static(shape: Shape, q: torch.Tensor, k_cur: torch.Tensor, v_cur: torch
                 idx_out: Optional[torch.Tensor]) -> int:
     """scalekv_step_static: the step with the library's own fixed scratch array instead of a
     caller workspace (allocates nothing); returns the new cache length."""
+    r = _marshaller().step_static(shape, q, k_cur, v_cur, win_idx, k_src, v_src, cache_len, budget, k_dst, v_dst, out,
+                                  idx_out)
+    if r is not None:
+        return _checked(r)
     n_cur = q.shape[2]
     _dense(q, shape, n_cur, "q"); _dense(k_cur, shape, n_cur, "k_cur"); _dense(v_cur, shape, n_cur, "v_cur")
     _dense(out, shape, n_cur, "out")
@@ -270,85 +321,67 @@ class PreparedStep:
     the small scales where a call's own work is a few microseconds.  Holds references to
     its tensors so the pointers stay valid."""
 
-    __slots__ = ("_args", "_keep", "new_len", "_refs", "_fn")
+    __slots__ = ("_call", "new_len", "_refs")
 
     def __init__(self, shape: Shape, q, k_cur, v_cur, win_idx, k_src, v_src, cache_len, budget,
                  k_dst, v_dst, out, idx_out, ws):
-        n_cur = q.shape[2]
-        _dense(q, shape, n_cur, "q"); _dense(k_cur, shape, n_cur, "k_cur"); _dense(v_cur, shape, n_cur, "v_cur")
-        _dense(out, shape, n_cur, "out")
-        keep = max(0, min(int(budget), int(cache_len)))
-        if idx_out is not None:
-            if idx_out.dtype != torch.int32 or not idx_out.is_cuda or not idx_out.is_contiguous() \
-                    or tuple(idx_out.shape) != (shape.n_seq, shape.n_head, keep):
-                raise ScaleKVError(1, f"idx_out must be a contiguous int32 device tensor [S,H,{keep}]")
-        win = (ctypes.c_int32 * max(1, len(win_idx)))(*[int(w) for w in win_idx])
-        cs = shape.c()
-        a, b = _kv(k_src, shape, "k_src"), _kv(v_src, shape, "v_src")
-        c, d = _kv(k_dst, shape, "k_dst"), _kv(v_dst, shape, "v_dst")
-        wp, wb = _ws(ws)
-        new_len = ctypes.c_int32(-1)
-        self._refs = (cs, win, a, b, c, d, new_len, q, k_cur, v_cur, k_src, v_src, k_dst, v_dst, out, idx_out, ws)
-        self._args = [ctypes.byref(cs), _ptr(q), _ptr(k_cur), _ptr(v_cur), ctypes.c_int32(n_cur), win,
-                      ctypes.c_int32(len(win_idx)), ctypes.byref(a), ctypes.byref(b), ctypes.c_int32(cache_len),
-                      ctypes.c_int32(budget), ctypes.byref(c), ctypes.byref(d), ctypes.byref(new_len), _ptr(out),
-                      _ptr(idx_out), wp, wb, None]
-        self._keep = keep
+        win, cache_len, budget = [int(w) for w in win_idx], int(cache_len), int(budget)
+        self._refs = (q, k_cur, v_cur, k_src, v_src, k_dst, v_dst, out, idx_out, ws)
+        self._call = _marshaller().prepare_step(shape, q, k_cur, v_cur, win, k_src, v_src, cache_len, budget, k_dst,
+                                                v_dst, out, idx_out, ws)
+        n_cur, keep = q.shape[2], max(0, min(budget, cache_len))
         self.new_len = keep + n_cur
-        self._fn = lib().scalekv_step
+        if self._call is None:
+            shape.c()
+            for t, name in ((q, "q"), (k_cur, "k_cur"), (v_cur, "v_cur"), (out, "out")):
+                _dense(t, shape, n_cur, name)
+            _idx_tensor(idx_out, shape, keep, "idx_out")
+            for t, name in ((k_src, "k_src"), (v_src, "v_src"), (k_dst, "k_dst"), (v_dst, "v_dst")):
+                _kv(t, shape, name)
+            _ws(ws)
+            raise ScaleKVError(1, "cache_len and budget must fit 32 bits")
 
     def __call__(self, stream_ptr: Optional[int] = None) -> int:
         """Enqueue on `stream_ptr` (a hipStream_t as int) or on torch's current stream."""
-        args = self._args
-        args[-1] = ctypes.c_void_p(stream_ptr if stream_ptr is not None
-                                   else torch.cuda.current_stream().cuda_stream)
-        status = self._fn(*args)
-        if status != 0:
-            _check(status)
-        assert self._refs[6].value == self.new_len, "the binding's shape check and the library disagree on keep"
-        return self.new_len
+        r = self._call(stream_ptr)
+        if r < 0:
+            _check(-r)
+        assert r == self.new_len, "the binding's shape check and the library disagree on keep"
+        return r
 
 
 class PreparedAppendFirst:
     """One scalekv_step_append_first call with every argument already marshalled (see
     PreparedStep).  `keep` and `moved` are known on the host before anything runs."""
 
-    __slots__ = ("_args", "keep", "moved", "_refs", "_fn")
+    __slots__ = ("_call", "keep", "moved", "_refs")
 
     def __init__(self, shape: Shape, q, k_cur, v_cur, win_idx, pool_w, k_cache, v_cache, cache_len, budget,
                  k_next, v_next, out, idx_out, ws):
+        win, pool_w, cache_len, budget = [int(w) for w in win_idx], int(pool_w), int(cache_len), int(budget)
+        self._refs = (q, k_cur, v_cur, k_cache, v_cache, k_next, v_next, out, idx_out, ws)
+        self._call = _marshaller().prepare_append_first(shape, q, k_cur, v_cur, win, pool_w, k_cache, v_cache,
+                                                        cache_len, budget, k_next, v_next, out, idx_out, ws)
         n_cur = q.shape[2]
-        _dense(q, shape, n_cur, "q"); _dense(k_cur, shape, n_cur, "k_cur"); _dense(v_cur, shape, n_cur, "v_cur")
-        _dense(out, shape, n_cur, "out")
-        total = int(cache_len) + n_cur
-        self.keep = len(win_idx) + max(0, min(int(budget), total - len(win_idx)))
+        total = cache_len + n_cur
+        self.keep = len(win) + max(0, min(budget, total - len(win)))
         self.moved = self.keep < total
-        _idx_tensor(idx_out, shape, self.keep, "idx_out")
-        win = (ctypes.c_int32 * max(1, len(win_idx)))(*[int(w) for w in win_idx])
-        cs = shape.c()
-        a, b = _kv(k_cache, shape, "k_cache"), _kv(v_cache, shape, "v_cache")
-        c = _kv(k_next, shape, "k_next") if k_next is not None else None
-        d = _kv(v_next, shape, "v_next") if v_next is not None else None
-        wp, wb = _ws(ws)
-        keep_out, moved = ctypes.c_int32(-1), ctypes.c_int32(-1)
-        self._refs = (cs, win, a, b, c, d, keep_out, moved, q, k_cur, v_cur, k_cache, v_cache, k_next, v_next, out,
-                      idx_out, ws)
-        self._args = [ctypes.byref(cs), _ptr(q), _ptr(k_cur), _ptr(v_cur), ctypes.c_int32(n_cur), win,
-                      ctypes.c_int32(len(win_idx)), ctypes.c_int32(pool_w), ctypes.byref(a), ctypes.byref(b),
-                      ctypes.c_int32(cache_len), ctypes.c_int32(budget),
-                      ctypes.byref(c) if c is not None else None, ctypes.byref(d) if d is not None else None,
-                      ctypes.byref(keep_out), ctypes.byref(moved), _ptr(out), _ptr(idx_out), wp, wb, None]
-        self._fn = lib().scalekv_step_append_first
+        if self._call is None:
+            shape.c()
+            for t, name in ((q, "q"), (k_cur, "k_cur"), (v_cur, "v_cur"), (out, "out")):
+                _dense(t, shape, n_cur, name)
+            _idx_tensor(idx_out, shape, self.keep, "idx_out")
+            for t, name in ((k_cache, "k_cache"), (v_cache, "v_cache"), (k_next, "k_next"), (v_next, "v_next")):
+                if t is not None:
+                    _kv(t, shape, name)
+            _ws(ws)
+            raise ScaleKVError(1, "pool_w, cache_len and budget must fit 32 bits")
 
     def __call__(self, stream_ptr: Optional[int] = None) -> int:
-        args = self._args
-        args[-1] = ctypes.c_void_p(stream_ptr if stream_ptr is not None
-                                   else torch.cuda.current_stream().cuda_stream)
-        status = self._fn(*args)
-        if status != 0:
-            _check(status)
-        assert self._refs[6].value == self.keep and bool(self._refs[7].value) == self.moved, \
-            "the binding's shape check and the library disagree on keep / moved"
+        r = self._call(stream_ptr)
+        if r < 0:
+            _check(-r)
+        assert r == 2 * self.keep + self.moved, "the binding's shape check and the library disagree on keep / moved"
         return self.keep
 
 
@@ -381,6 +414,9 @@ def _idx_tensor(t: Optional[torch.Tensor], shape: Shape, keep: int, name: str) -
 def select_window(shape: Shape, log_scores: torch.Tensor, cache_len: int, budget: int,
                   forced: Sequence[int], pool_w: int, idx: torch.Tensor) -> int:
     """scalekv_select_window: forced positions + top-budget of the rest by pooled score; returns keep."""
+    r = _marshaller().select_window(shape, log_scores, cache_len, budget, forced, pool_w, idx)
+    if r is not None:
+        return _checked(r)
     if log_scores.dtype != torch.float32 or not log_scores.is_cuda or not log_scores.is_contiguous() \
             or tuple(log_scores.shape) != (shape.n_seq, shape.n_head, cache_len):
         raise ScaleKVError(1, "log_scores must be a contiguous fp32 device tensor [S,H,cache_len]")
@@ -402,6 +438,11 @@ def step_append_first(shape: Shape, q: torch.Tensor, k_cur: torch.Tensor, v_cur:
                       ws: Optional[torch.Tensor]):
     """scalekv_step_append_first; returns (keep, moved): the next cache has `keep` rows and
     lives in k_next/v_next if `moved`, else still in k_cache/v_cache."""
+    r = _marshaller().append_first(shape, q, k_cur, v_cur, win_idx, pool_w, k_cache, v_cache, cache_len, budget,
+                                   k_next, v_next, out, idx_out, ws)
+    if r is not None:
+        _checked(r)
+        return r >> 1, bool(r & 1)
     n_cur = q.shape[2]
     _dense(q, shape, n_cur, "q"); _dense(k_cur, shape, n_cur, "k_cur"); _dense(v_cur, shape, n_cur, "v_cur")
     _dense(out, shape, n_cur, "out")
@@ -430,6 +471,10 @@ def asi(shape: Shape, q_samp: torch.Tensor, k: torch.Tensor, hist_len: int, cur_
         terms: torch.Tensor, asi_out: Optional[torch.Tensor], ws: torch.Tensor) -> None:
     """scalekv_asi: q_samp [S,H,n_samp,d], k cache (history rows then the current map) ->
     terms [S,H,n_samp,2] fp32 and, if given, asi_out [3] fp32 (two means and their product)."""
+    r = _marshaller().asi(shape, q_samp, k, hist_len, cur_len, top_k, terms, asi_out, ws)
+    if r is not None:
+        _checked(r)
+        return
     n_samp = q_samp.shape[2]
     _dense(q_samp, shape, n_samp, "q_samp")
     if terms.dtype != torch.float32 or not terms.is_cuda or not terms.is_contiguous() \
@@ -496,6 +541,9 @@ def pyramid_budgets(n_layer: int, b_uniform: int, b_last: int) -> list:
 
 def select_positional(shape: Shape, cache_len: int, n_sink: int, n_recent: int, idx: torch.Tensor) -> int:
     """scalekv_select_positional: first n_sink and last n_recent positions -> idx [S,H,keep]; returns keep."""
+    r = _marshaller().select_positional(shape, cache_len, n_sink, n_recent, idx)
+    if r is not None:
+        return _checked(r)
     sink = max(0, min(int(n_sink), int(cache_len)))
     keep = sink + max(0, min(int(n_recent), int(cache_len) - sink))
     _idx_tensor(idx, shape, keep, "idx")

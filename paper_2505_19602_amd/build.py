@@ -8,6 +8,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libscalekv.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")   # the binding's argument marshalling, a Python extension module
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -22,18 +23,38 @@ def sources():
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(MARSHAL):
         return True
-    t = os.path.getmtime(LIB)
-    deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + \
+    t = min(os.path.getmtime(LIB), os.path.getmtime(MARSHAL))
+    deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + [os.path.join(CSRC, "marshal.cpp")] + \
         glob.glob(os.path.join(HERE, "..", "include", "*.h"))
     return any(os.path.getmtime(d) > t for d in deps)
 
 
+def build_marshal() -> str:
+    """Compile csrc/marshal.cpp (host code only) against this interpreter and its torch."""
+    import sysconfig
+    import torch
+    base = os.path.dirname(torch.__file__)
+    inc = [os.path.join(base, "include"), os.path.join(base, "include", "torch", "csrc", "api", "include"),
+           sysconfig.get_paths()["include"], os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")]
+    libs = os.path.join(base, "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    cmd += [f"-isystem{i}" for i in inc] + [os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL, f"-L{libs}",
+            f"-Wl,-rpath,{libs}", "-ltorch_python", "-ltorch_cpu", "-ltorch", "-lc10", "-lc10_hip"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ (marshal.cpp) failed:\n" + res.stderr[-4000:])
+    return MARSHAL
+
+
 def build(force: bool = True, verbose: bool = False) -> str:
-    """Compile every HIP source into one shared library.  Returns its path."""
+    """Compile every HIP source into one shared library, and the binding's extension module
+    beside it.  Returns the library's path."""
     if not force and not is_stale():
         return LIB
+    build_marshal()
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     cmd = [hipcc] + HIPCC_FLAGS + sources() + ["-o", LIB]
     if verbose:
