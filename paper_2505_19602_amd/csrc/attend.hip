@@ -1,14 +1,12 @@
 // Unmasked attention of the current token map over [retained cache ; current
 // map] (Sec. 3.1 / 3.3): out[t] = sum_i softmax_i(q_t . k_i * sm_scale) v_i.
 //
-// Two kernels:
-//  * attend_mfma_kernel   bf16, flash-style: K/V tiles staged through LDS, bf16
-//    MFMA 32x32x16 for both products, fp32 online softmax.  The products are
-//    formed transposed (S^T = K Q^T, O^T = V^T P^T) so that one lane owns one
-//    query column: the softmax statistics are per-lane scalars and P^T leaves
-//    the first product already in the register layout the second one consumes.
-//  * attend_simple_kernel fp32 (and any case the MFMA kernel is not built for):
-//    plain FMA, fp32 throughout.
+// attend_mfma_kernel: bf16, flash-style: K/V tiles staged through LDS, bf16
+// MFMA 32x32x16 for both products, fp32 online softmax.  The products are
+// formed transposed (S^T = K Q^T, O^T = V^T P^T) so that one lane owns one
+// query column: the softmax statistics are per-lane scalars and P^T leaves
+// the first product already in the register layout the second one consumes.
+// (attend_f32.hip: fp32.  attend_pipe.hip: bf16, head_dim 128, large maps.)
 #include "common.h"
 
 namespace scalekv {
@@ -17,96 +15,6 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-
-// =====================================================================
-// fp32 / generic kernel.  256 threads: 32 query rows x 8 lanes per row.
-// =====================================================================
-template <typename T, int D>
-__global__ __launch_bounds__(256) void attend_simple_kernel(
-    const T* __restrict__ q, int n_q, const T* __restrict__ k, long long k_seq_stride,
-    long long k_head_stride, const T* __restrict__ v, long long v_seq_stride,
-    long long v_head_stride, int kv_len, int n_head, float sm_scale, T* __restrict__ out) {
-  constexpr int BQ = 32, BK = 32, G = 8, CPT = D / G;  // CPT output columns per thread
-  __shared__ float qs[BQ][D + 1];
-  __shared__ float ks[BK][D + 1];
-  __shared__ float vs[BK][D];
-  __shared__ float ps[BQ][BK + 1];
-
-  const int unit = SCALEKV_WG_Y;
-  const int seq = unit / n_head, head = unit - seq * n_head;
-  const int tid = threadIdx.x, r = tid / G, g = tid % G;
-  const int q0 = SCALEKV_WG_X * BQ;
-  const T* qu = q + (long long)unit * n_q * D;
-  const T* ku = k + seq * k_seq_stride + head * k_head_stride;
-  const T* vu = v + seq * v_seq_stride + head * v_head_stride;
-
-  auto ld = [](const T* p) -> float {
-    if constexpr (sizeof(T) == 4) return *(const float*)p;
-    else return bf16_bits_to_float(*(const uint16_t*)p);
-  };
-
-  for (int e = tid; e < BQ * D; e += 256) {
-    const int rr = e / D, c = e - rr * D;
-    qs[rr][c] = (q0 + rr < n_q) ? ld(qu + (long long)(q0 + rr) * D + c) : 0.f;
-  }
-  float acc[CPT];
-#pragma unroll
-  for (int c = 0; c < CPT; ++c) acc[c] = 0.f;
-  float m = -INFINITY, l = 0.f;
-
-  for (int t0 = 0; t0 < kv_len; t0 += BK) {
-    __syncthreads();
-    for (int e = tid; e < BK * D; e += 256) {
-      const int rr = e / D, c = e - rr * D;
-      const bool ok = t0 + rr < kv_len;
-      ks[rr][c] = ok ? ld(ku + (long long)(t0 + rr) * D + c) : 0.f;
-      vs[rr][c] = ok ? ld(vu + (long long)(t0 + rr) * D + c) : 0.f;
-    }
-    __syncthreads();
-    float s[BK / G];
-    float mx = m;
-#pragma unroll
-    for (int jj = 0; jj < BK / G; ++jj) {
-      const int j = g + G * jj;
-      float dot = 0.f;
-      for (int c = 0; c < D; ++c) dot = fmaf(qs[r][c], ks[j][c], dot);
-      s[jj] = (t0 + j < kv_len) ? dot * sm_scale : -INFINITY;
-      mx = fmaxf(mx, s[jj]);
-    }
-#pragma unroll
-    for (int off = 1; off < G; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-    const float alpha = expf(m - mx);  // m == -inf on the first tile -> 0
-    float rs = 0.f;
-#pragma unroll
-    for (int jj = 0; jj < BK / G; ++jj) {
-      const float p = expf(s[jj] - mx);
-      ps[r][g + G * jj] = p;
-      rs += p;
-    }
-#pragma unroll
-    for (int off = 1; off < G; off <<= 1) rs += __shfl_xor(rs, off);
-    l = l * alpha + rs;
-    m = mx;
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < CPT; ++c) acc[c] *= alpha;
-    for (int j = 0; j < BK; ++j) {
-      const float p = ps[r][j];
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) acc[c] = fmaf(p, vs[j][g + G * c], acc[c]);
-    }
-  }
-  if (q0 + r < n_q) {
-    const float inv = 1.f / l;
-    T* o = out + ((long long)unit * n_q + q0 + r) * D;
-#pragma unroll
-    for (int c = 0; c < CPT; ++c) {
-      const float val = acc[c] * inv;
-      if constexpr (sizeof(T) == 4) ((float*)o)[g + G * c] = val;
-      else ((uint16_t*)o)[g + G * c] = (uint16_t)float_to_bf16_bits(val);
-    }
-  }
-}
 
 // =====================================================================
 // bf16 MFMA kernel.
@@ -404,20 +312,8 @@ hipError_t launch_attend(int dtype, int n_seq, int n_head, int d, const void* q,
                          KvView v, int kv_len, float sm_scale, void* out, hipStream_t stream) {
   const int n_unit = n_seq * n_head;
   if (n_q <= 0 || n_unit <= 0) return hipSuccess;
-  if (dtype == 0) {
-    dim3 grid((n_q + 31) / 32, n_unit);
-    if (d == 128)
-      hipLaunchKernelGGL((attend_simple_kernel<float, 128>), grid, dim3(256), 0, stream,
-                         (const float*)q, n_q, (const float*)k.ptr, k.seq_stride, k.head_stride,
-                         (const float*)v.ptr, v.seq_stride, v.head_stride, kv_len, n_head,
-                         sm_scale, (float*)out);
-    else
-      hipLaunchKernelGGL((attend_simple_kernel<float, 64>), grid, dim3(256), 0, stream,
-                         (const float*)q, n_q, (const float*)k.ptr, k.seq_stride, k.head_stride,
-                         (const float*)v.ptr, v.seq_stride, v.head_stride, kv_len, n_head,
-                         sm_scale, (float*)out);
-    return hipGetLastError();
-  }
+  if (dtype == 0)
+    return launch_attend_f32(n_unit, n_head, d, q, n_q, k, v, kv_len, sm_scale, out, stream);
   const float scale_log2e = sm_scale * 1.4426950408889634f;
   const uint16_t* qp = (const uint16_t*)q;
   const uint16_t* kp = (const uint16_t*)k.ptr;

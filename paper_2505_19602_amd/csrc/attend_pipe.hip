@@ -111,7 +111,6 @@ __device__ unsigned long long g_timeline[kTimelineMaxWg * kTimelineWords];
 #define SCALEKV_STAMP(name)
 #endif
 constexpr float kBlockSumLimit = 0x1p100f;  // largest row-sum share a block may add unchecked
-constexpr int kXcds = 8;
 
 // Three-input max as one instruction and without the NaN-quieting pre-pass the
 // compiler puts in front of fmaxf on values it has not produced itself.
@@ -188,13 +187,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   unsigned char* const k_lds = smem;
   unsigned char* const v_lds = smem + kStages * kTileBytes;
 
-  // Consecutive workgroup ids go round-robin over the XCDs.  Renumber so that the ids an
-  // XCD receives are consecutive: all query tiles of a unit then share one L2.
-  int wg = SCALEKV_WG_X;
-  {
-    const int per = n_wg / kXcds, full = per * kXcds;  // the tail (< 8 groups) keeps its ids
-    if (wg < full) wg = (wg % kXcds) * per + wg / kXcds;
-  }
+  const int wg = xcd_order(SCALEKV_WG_X, n_wg);  // all query tiles of a unit share one L2
   const int unit = wg / n_qtile, qtile = wg - unit * n_qtile;
   const int seq = unit / n_head, head = unit - seq * n_head;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;

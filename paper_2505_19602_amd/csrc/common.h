@@ -108,6 +108,9 @@ hipError_t launch_compact(int dtype, int n_seq, int n_head, int d, KvView k_src,
                           int n_cur, KvView k_dst, KvView v_dst, hipStream_t stream);
 hipError_t launch_attend(int dtype, int n_seq, int n_head, int d, const void* q, int n_q, KvView k,
                          KvView v, int kv_len, float sm_scale, void* out, hipStream_t stream);
+// the fp32 part of launch_attend
+hipError_t launch_attend_f32(int n_unit, int n_head, int d, const void* q, int n_q, KvView k, KvView v,
+                             int kv_len, float sm_scale, void* out, hipStream_t stream);
 
 // bf16, head_dim 128 only: the pipelined kernel used when n_q is large.  Keys and values are the
 // first len1 rows of the caches k, v followed by the len2 rows of the dense tensors k2, v2
@@ -136,6 +139,14 @@ inline bool attend_uses_pipe(int dtype, int d, int n_q) { return dtype == 1 && d
 #define SCALEKV_WG_Y ((int)blockIdx.y)
 #define SCALEKV_WG_Z ((int)blockIdx.z)
 #endif
+// Consecutive workgroup ids go round-robin over the eight XCDs, each with an L2 of its own.  This
+// renumbers them so that the ids an XCD receives are consecutive (the tail, fewer than eight, keeps
+// its ids): workgroups that read the same rows then share an L2.
+constexpr int kXcds = 8;
+__device__ __forceinline__ int xcd_order(int wg, int n_wg) {
+  const int per = n_wg / kXcds;
+  return wg < per * kXcds ? wg % kXcds * per + wg / kXcds : wg;
+}
 // Shared by the two MFMA attention kernels: the key row fed to MFMA row i of the first product
 // is row pi32(i) of the 32-key block (bits 2 and 3 swapped), which makes the registers of an
 // S^T block the B operand of the second product; and the number of log2 units a row maximum may
