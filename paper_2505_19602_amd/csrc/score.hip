@@ -14,80 +14,97 @@
 namespace scalekv {
 namespace {
 
-constexpr int kThreads = kScoreChunk;  // one key per thread
+constexpr int kThreads = kScoreChunk;  // bf16 kernel: 64 keys per wave
 
-// Generic logits kernel (fp32 or bf16 storage, plain FMA).  Window queries sit
-// in LDS as fp32 and are broadcast to every thread; each thread walks its own
-// key row in 16-byte vectors.
-template <typename T, int D>
-__global__ __launch_bounds__(kThreads) void score_logits_kernel(
-    const T* __restrict__ q, long long q_unit_stride, WindowRows rows, int n_win,
-    const T* __restrict__ k, long long k_seq_stride, long long k_head_stride, int n_head,
+// fp32 logits kernel, plain FMA in channel order.  16 waves per 256-key chunk: wave w takes keys
+// 64 (w % 4) .. +63, one per lane, and window rows 4 (w / 4) .. +3, so that a chunk has four times
+// the waves of a thread-per-key form and a row costs a thread 4 instead of 16 fma per channel.
+// The chunk's keys come through LDS, 32 channels at a time, as whole 128-byte pieces (a thread
+// walking its own row in global memory touches 64 lines per instruction); the next piece is
+// requested before this one is used.  LDS rows are 36 floats apart: an odd number of 16-byte
+// units, no bank conflicts.  The window queries are wave-uniform and arrive as scalars.  Bound by
+// latency at the sizes in use: 585 keys x 32 units (96 workgroups), 22 us thread-per-key.
+template <int D>
+__global__ __launch_bounds__(1024) void score_logits_f32_kernel(
+    const float* __restrict__ q, long long q_unit_stride, WindowRows rows, int n_win,
+    const float* __restrict__ k, long long k_seq_stride, long long k_head_stride, int n_head,
     int cache_len, float sm_scale, ScoreWorkspace ws) {
-  constexpr int EPV = Elem<T>::kPerVec;
-  __shared__ float qs[kMaxWindow][D];
-  __shared__ float red_max[kThreads / 64][kMaxWindow];
-  __shared__ float red_sum[kThreads / 64][kMaxWindow];
+  constexpr int kPiece = 32, kStride = kPiece + 4, kRows = 4;
+  __shared__ __attribute__((aligned(16))) float ks[kScoreChunk * kStride];
+  __shared__ float red_max[kScoreChunk / 64][kMaxWindow];
+  __shared__ float red_sum[kScoreChunk / 64][kMaxWindow];
 
   const int unit = SCALEKV_WG_Y;
   const int seq = unit / n_head, head = unit - seq * n_head;
-  const int tid = threadIdx.x;
-  const T* qu = q + unit * q_unit_stride;
-  for (int e = tid; e < kMaxWindow * D; e += kThreads) {
-    const int j = e / D, c = e - j * D;
-    float val = 0.f;
-    if (j < n_win) {
-      if constexpr (sizeof(T) == 4) val = ((const float*)qu)[(long long)rows.row[j] * D + c];
-      else val = bf16_bits_to_float(((const uint16_t*)qu)[(long long)rows.row[j] * D + c]);
-    }
-    qs[j][c] = val;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int group = wave & 3, row0 = kRows * (wave >> 2);
+  const int key0 = SCALEKV_WG_X * kScoreChunk;
+  const float* ku = k + seq * k_seq_stride + head * k_head_stride;
+  const float* qr[kRows];
+#pragma unroll
+  for (int j = 0; j < kRows; ++j) {
+    int row = 0;
+#pragma unroll
+    for (int t = 0; t < kMaxWindow; ++t) row = t == row0 + j ? rows.row[t] : row;  // (an index would put rows into LDS)
+    qr[j] = q + unit * q_unit_stride + (long long)row * D;
   }
-  __syncthreads();
 
-  const int key = SCALEKV_WG_X * kThreads + tid;
+  static_assert(kScoreChunk * kPiece / 4 == 2 * 1024, "two 16-byte vectors per thread and piece");
+  constexpr int kPer = kPiece / 4;
+  const int ld_key = tid / kPer, ld_c = 4 * (tid % kPer);  // and the same 128 keys on
+  const float* ld_a = ku + (long long)min(key0 + ld_key, cache_len - 1) * D + ld_c;  // clamp: legal address, value unused
+  const float* ld_b = ku + (long long)min(key0 + ld_key + 128, cache_len - 1) * D + ld_c;
+  float4 stage_a = *(const float4*)ld_a, stage_b = *(const float4*)ld_b;
+  float acc[kRows] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+  for (int c0 = 0; c0 < D; c0 += kPiece) {
+    __syncthreads();  // the previous piece has been used
+    *(float4*)(ks + ld_key * kStride + ld_c) = stage_a;
+    *(float4*)(ks + (ld_key + 128) * kStride + ld_c) = stage_b;
+    __syncthreads();
+    if (c0 + kPiece < D) {
+      stage_a = *(const float4*)(ld_a + c0 + kPiece);
+      stage_b = *(const float4*)(ld_b + c0 + kPiece);
+    }
+    const float* krow = ks + (64 * group + lane) * kStride;
+#pragma unroll
+    for (int c = 0; c < kPiece; c += 4) {
+      const float4 kv = *(const float4*)(krow + c);
+#pragma unroll
+      for (int j = 0; j < kRows; ++j) {
+        acc[j] = fmaf(qr[j][c0 + c], kv.x, acc[j]);
+        acc[j] = fmaf(qr[j][c0 + c + 1], kv.y, acc[j]);
+        acc[j] = fmaf(qr[j][c0 + c + 2], kv.z, acc[j]);
+        acc[j] = fmaf(qr[j][c0 + c + 3], kv.w, acc[j]);
+      }
+    }
+  }
+
+  const int key = key0 + 64 * group + lane;
   const bool valid = key < cache_len;
-  const int krow = valid ? key : cache_len - 1;  // clamp: load something legal, ignore it later
-  const uint4* kv = (const uint4*)(k + seq * k_seq_stride + head * k_head_stride +
-                                   (long long)krow * D);
-  float acc[kMaxWindow];
 #pragma unroll
-  for (int j = 0; j < kMaxWindow; ++j) acc[j] = 0.f;
-#pragma unroll 4
-  for (int c0 = 0; c0 < D / EPV; ++c0) {
-    float kf[EPV];
-    Elem<T>::unpack(kv[c0], kf);
+  for (int j = 0; j < kRows; ++j) acc[j] *= sm_scale;
+  if (valid)
+    *(float4*)(ws.logits + ((long long)unit * ws.len_pad + key) * kMaxWindow + row0) =
+        make_float4(acc[0], acc[1], acc[2], acc[3]);
 #pragma unroll
-    for (int e = 0; e < EPV; ++e) {
-#pragma unroll
-      for (int j = 0; j < kMaxWindow; ++j) acc[j] = fmaf(qs[j][c0 * EPV + e], kf[e], acc[j]);
-    }
-  }
-
-  float* lg = ws.logits + ((long long)unit * ws.len_pad + key) * kMaxWindow;
-  const int lane = tid & 63, wave = tid >> 6;
-  if (valid) {
-#pragma unroll
-    for (int j4 = 0; j4 < kMaxWindow; j4 += 4)
-      *(float4*)(lg + j4) = make_float4(acc[j4] * sm_scale, acc[j4 + 1] * sm_scale,
-                                        acc[j4 + 2] * sm_scale, acc[j4 + 3] * sm_scale);
-  }
-#pragma unroll
-  for (int j = 0; j < kMaxWindow; ++j) {
-    const float x = valid ? acc[j] * sm_scale : -INFINITY;
+  for (int j = 0; j < kRows; ++j) {
+    const float x = valid ? acc[j] : -INFINITY;
     float m = x;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
     float e = valid ? expf(x - m) : 0.f;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) e += __shfl_xor(e, off);
-    if (lane == 0) { red_max[wave][j] = m; red_sum[wave][j] = e; }
+    if (lane == 0) { red_max[group][row0 + j] = m; red_sum[group][row0 + j] = e; }
   }
   __syncthreads();
   if (tid < kMaxWindow) {
     float m = -INFINITY;
-    for (int w = 0; w < kThreads / 64; ++w) m = fmaxf(m, red_max[w][tid]);
+    for (int w = 0; w < kScoreChunk / 64; ++w) m = fmaxf(m, red_max[w][tid]);
     float ssum = 0.f;
-    for (int w = 0; w < kThreads / 64; ++w)
+    for (int w = 0; w < kScoreChunk / 64; ++w)
       if (red_max[w][tid] > -INFINITY) ssum += red_sum[w][tid] * expf(red_max[w][tid] - m);
     float* part = ws.partial + ((long long)unit * ws.n_chunk + SCALEKV_WG_X) * 2 * kMaxWindow;
     part[tid] = m;
@@ -144,22 +161,6 @@ __global__ __launch_bounds__(256) void score_finalize_kernel(int n_win, int cach
   log_scores[unit * score_unit_stride + key] = score_log_sum(ws, unit, key, n_win, row_shift);
 }
 
-template <typename T>
-hipError_t launch_logits_t(int n_seq, int n_head, int d, const void* q, long long q_unit_stride,
-                           WindowRows rows, int n_win, KvView k, int cache_len, float sm_scale,
-                           ScoreWorkspace ws, hipStream_t stream) {
-  dim3 grid(ws.n_chunk, n_seq * n_head);
-  if (d == 128)
-    hipLaunchKernelGGL((score_logits_kernel<T, 128>), grid, dim3(kThreads), 0, stream,
-                       (const T*)q, q_unit_stride, rows, n_win, (const T*)k.ptr, k.seq_stride,
-                       k.head_stride, n_head, cache_len, sm_scale, ws);
-  else
-    hipLaunchKernelGGL((score_logits_kernel<T, 64>), grid, dim3(kThreads), 0, stream, (const T*)q,
-                       q_unit_stride, rows, n_win, (const T*)k.ptr, k.seq_stride, k.head_stride,
-                       n_head, cache_len, sm_scale, ws);
-  return hipGetLastError();
-}
-
 }  // namespace
 
 hipError_t launch_score_logits(int dtype, int n_seq, int n_head, int d, const void* q,
@@ -167,10 +168,16 @@ hipError_t launch_score_logits(int dtype, int n_seq, int n_head, int d, const vo
                                int cache_len, float sm_scale, ScoreWorkspace ws,
                                hipStream_t stream) {
   if (cache_len <= 0 || n_seq * n_head <= 0) return hipSuccess;
-  if (dtype == 0)
-    return launch_logits_t<float>(n_seq, n_head, d, q, q_unit_stride, rows, n_win, k, cache_len,
-                                  sm_scale, ws, stream);
   dim3 grid(ws.n_chunk, n_seq * n_head);
+  if (dtype == 0) {
+    if (d == 128)
+      hipLaunchKernelGGL((score_logits_f32_kernel<128>), grid, dim3(1024), 0, stream, (const float*)q, q_unit_stride,
+                         rows, n_win, (const float*)k.ptr, k.seq_stride, k.head_stride, n_head, cache_len, sm_scale, ws);
+    else
+      hipLaunchKernelGGL((score_logits_f32_kernel<64>), grid, dim3(1024), 0, stream, (const float*)q, q_unit_stride,
+                         rows, n_win, (const float*)k.ptr, k.seq_stride, k.head_stride, n_head, cache_len, sm_scale, ws);
+    return hipGetLastError();
+  }
   if (d == 128)
     hipLaunchKernelGGL((score_logits_mfma_kernel<128>), grid, dim3(kThreads), 0, stream,
                        (const uint16_t*)q, q_unit_stride, rows, n_win, (const uint16_t*)k.ptr,
