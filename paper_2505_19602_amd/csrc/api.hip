@@ -409,17 +409,21 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
   };
   const int U = shape->n_seq * shape->n_head;
   const int32_t* idx = nullptr;  // identity unless a ranking is needed
-  const bool pipe = attend_uses_pipe(shape->dtype, shape->head_dim, n_cur);
+  const bool pipe = attend_uses_pipe(shape->dtype, shape->head_dim, U, n_cur, keep + n_cur);
+  const bool small = small_tile_rows(shape->dtype, U, n_cur, keep + n_cur) > 0;
+  const bool one_launch = small && ranks && cache_len <= kShortLen;  // the attention kernel ranks as well
   bool pruned = false;           // the ranking kernel has already written the destination caches
+  WindowRows rows;
+  for (int j = 0; j < kMaxWindow; ++j) rows.row[j] = ranks && j < n_win ? win_idx[j] : 0;
   SCALEKV_HIP(mark(0), "event record");
-  if (ranks) {
+  if (one_launch) {
+    SCALEKV_HIP(mark(1), "event record");
+  } else if (ranks) {
     const WsLayout w = ws_layout(shape, cache_len);
     const ScoreWorkspace sw = score_ws(w, ws);
     float* scores = reinterpret_cast<float*>(static_cast<char*>(ws) + w.scores_off);
     int32_t* idx_ws = idx_out ? idx_out
                               : reinterpret_cast<int32_t*>(static_cast<char*>(ws) + w.idx_off);
-    WindowRows rows;
-    for (int j = 0; j < kMaxWindow; ++j) rows.row[j] = j < n_win ? win_idx[j] : 0;
     // One launch for the whole ranking where it pays (enough units to fill the chip, or short
     // caches): the selection kernel streams the keys itself.  Then event 1 coincides with event 0.
     // The same workgroup then prunes its unit as well: the kept rows go to the destination
@@ -429,7 +433,7 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
     hipError_t one = launch_score_select(shape->dtype, shape->n_seq, shape->n_head, shape->head_dim, q,
                                          (long long)n_cur * shape->head_dim, rows, n_win,
                                          view(k_src), cache_len, resolve_scale(shape), sw, keep,
-                                         idx_ws, nullptr, &prune, st);
+                                         idx_ws, nullptr, small ? nullptr : &prune, st);
     if (one == hipErrorNotSupported) {
       SCALEKV_HIP(launch_score_logits(shape->dtype, shape->n_seq, shape->n_head, shape->head_dim, q,
                                       (long long)n_cur * shape->head_dim, rows, n_win, view(k_src),
@@ -450,7 +454,7 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
     } else {
       SCALEKV_HIP(one, "score + select + prune launch");
       SCALEKV_HIP(mark(1), "event record");   // after the launch: the stages up to the pruning share it
-      pruned = true;
+      pruned = !small;
     }
     idx = idx_ws;
   } else {
@@ -464,7 +468,7 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
   // behind the kept rows itself (it is bound by the matrix pipe, the copy by the HBM, so the
   // two overlap); for the other shapes the pruning appends them.
   const bool fused_append = pipe;
-  if (!pruned)
+  if (!pruned && !small)
     SCALEKV_HIP(launch_compact(shape->dtype, shape->n_seq, shape->n_head, shape->head_dim,
                                view(k_src), view(v_src), idx, keep, k_cur, v_cur,
                                fused_append ? 0 : n_cur, view(k_dst), view(v_dst), st),
@@ -476,6 +480,21 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
                                    ev ? static_cast<hipEvent_t>(ev[3]) : nullptr,
                                    ev ? static_cast<hipEvent_t>(ev[4]) : nullptr),
                 "attend launch");
+  } else if (small) {
+    // one kernel prunes, appends and attends (and ranks, if the cache is short)
+    SmallStep s{};
+    s.n_unit = U; s.n_head = shape->n_head; s.d = shape->head_dim;
+    s.q = q; s.n_q = n_cur; s.out = out;
+    s.k = view(k_src); s.v = view(v_src); s.k_cur = k_cur; s.v_cur = v_cur;
+    s.len1 = keep; s.len2 = n_cur; s.idx = idx;
+    s.k_dst = view(k_dst); s.v_dst = view(v_dst); s.copy_kept = true;
+    s.sm_scale = resolve_scale(shape);
+    if (one_launch) {
+      s.cache_len = cache_len; s.rows = rows; s.n_win = n_win; s.idx_out = idx_out;
+    }
+    SCALEKV_HIP(mark(3), "event record");
+    SCALEKV_HIP(launch_step_small(s, st), "step launch");
+    SCALEKV_HIP(mark(4), "event record");
   } else {
     SCALEKV_HIP(mark(3), "event record");
     SCALEKV_HIP(launch_attend(shape->dtype, shape->n_seq, shape->n_head, shape->head_dim, q, n_cur,
@@ -632,8 +651,9 @@ scalekv_status scalekv_step_append_first(const scalekv_shape* shape, const void*
   SCALEKV_HIP(mark(0), "event record");
   // 1. the map's K/V join the cache: rows [cache_len, cache_len + n_cur) of every unit (the
   //    pipelined attention kernel does this itself, overlapped with its own work)
-  const bool fused_append = attend_uses_pipe(shape->dtype, d, n_cur);
-  if (!fused_append) {
+  const bool fused_append = attend_uses_pipe(shape->dtype, shape->head_dim, U, n_cur, len);
+  const bool small = small_tile_rows(shape->dtype, U, n_cur, len) > 0;
+  if (!fused_append && !small) {
     const long long tail = (long long)cache_len * d * elem_bytes(shape);
     KvView kt{static_cast<const char*>(k_cache->ptr) + tail, k_cache->seq_stride,
               k_cache->head_stride};
@@ -651,6 +671,17 @@ scalekv_status scalekv_step_append_first(const scalekv_shape* shape, const void*
                                    ev ? static_cast<hipEvent_t>(ev[1]) : nullptr,
                                    ev ? static_cast<hipEvent_t>(ev[2]) : nullptr),
                 "attend launch");
+  } else if (small) {
+    SmallStep s{};
+    s.n_unit = U; s.n_head = shape->n_head; s.d = d;
+    s.q = q; s.n_q = n_cur; s.out = out;
+    s.k = view(k_cache); s.v = view(v_cache); s.k_cur = k_cur; s.v_cur = v_cur;
+    s.len1 = cache_len; s.len2 = n_cur;
+    s.k_dst = view(k_cache); s.v_dst = view(v_cache); s.copy_kept = false;  // the append alone
+    s.sm_scale = resolve_scale(shape);
+    SCALEKV_HIP(mark(1), "event record");
+    SCALEKV_HIP(launch_step_small(s, st), "attend launch");
+    SCALEKV_HIP(mark(2), "event record");
   } else {
     SCALEKV_HIP(mark(1), "event record");
     SCALEKV_HIP(launch_attend(shape->dtype, shape->n_seq, shape->n_head, d, q, n_cur, view(k_cache),

@@ -314,13 +314,21 @@ hipError_t launch_attend(int dtype, int n_seq, int n_head, int d, const void* q,
   if (n_q <= 0 || n_unit <= 0) return hipSuccess;
   if (dtype == 0)
     return launch_attend_f32(n_unit, n_head, d, q, n_q, k, v, kv_len, sm_scale, out, stream);
+  if (small_tile_rows(dtype, n_unit, n_q, kv_len) > 0) {
+    SmallStep s{};
+    s.n_unit = n_unit; s.n_head = n_head; s.d = d;
+    s.q = q; s.n_q = n_q; s.out = out;
+    s.k = k; s.v = v; s.len1 = kv_len;
+    s.sm_scale = sm_scale;
+    return launch_step_small(s, stream);
+  }
   const float scale_log2e = sm_scale * 1.4426950408889634f;
   const uint16_t* qp = (const uint16_t*)q;
   const uint16_t* kp = (const uint16_t*)k.ptr;
   const uint16_t* vp = (const uint16_t*)v.ptr;
   uint16_t* op = (uint16_t*)out;
   if (d == 128) {
-    if (attend_uses_pipe(dtype, d, n_q))
+    if (attend_uses_pipe(dtype, d, n_unit, n_q, kv_len))
       return launch_attend_pipe(n_unit, n_head, q, n_q, k, v, kv_len, nullptr, nullptr, 0, false,
                                 sm_scale, out, stream);
     return launch_mfma<128, 1>(dim3((n_q + 127) / 128, n_unit), stream, qp, n_q, kp, k, vp, v,

@@ -9,6 +9,7 @@ namespace scalekv {
 
 constexpr int kMaxWindow = 16;     // window rows held per unit by the score kernels
 constexpr int kScoreChunk = 256;   // cached keys handled per workgroup in the score kernels
+constexpr int kShortLen = 1536;    // longest cache that one workgroup ranks in LDS (rank_short.h)
 constexpr int kLogitPad = 64;      // logits row stride is the cache length rounded up to this
 
 // A cache viewed by kernels: base pointer plus strides in elements.
@@ -112,7 +113,49 @@ hipError_t launch_attend(int dtype, int n_seq, int n_head, int d, const void* q,
 hipError_t launch_attend_f32(int n_unit, int n_head, int d, const void* q, int n_q, KvView k, KvView v,
                              int kv_len, float sm_scale, void* out, hipStream_t stream);
 
-// bf16, head_dim 128 only: the pipelined kernel used when n_q is large.  Keys and values are the
+// bf16 attention for small work, with the pruning and, for short caches, the ranking in the same
+// launch (step_small.hip).
+struct SmallStep {
+  int n_unit, n_head, d;
+  const void* q;            // [U, n_q, d]
+  int n_q;
+  void* out;                // [U, n_q, d]
+  // keys: len1 rows of the source cache (rows idx[t], or row t), then len2 rows of k_cur / v_cur
+  KvView k, v;
+  const void *k_cur, *v_cur;
+  int len1, len2;
+  const int32_t* idx;       // [U, len1]; NULL: the first len1 rows
+  KvView k_dst, v_dst;      // ptr NULL: no cache is written
+  bool copy_kept;           // the len1 rows are written as well, not only the len2 behind them
+  float sm_scale;
+  // cache_len > 0 (at most kShortLen): rank the cache_len rows of k with the window queries and keep len1
+  // of them (0 < len1 < cache_len); idx is not used, idx_out (may be NULL) receives the rows
+  int cache_len;
+  WindowRows rows;
+  int n_win;
+  int32_t* idx_out;
+};
+hipError_t launch_step_small(const SmallStep& s, hipStream_t stream);
+// Query rows per workgroup of that kernel for n_q bf16 queries over kv keys, 0 where the other kernels
+// are the better ones.  A workgroup of it fills a compute unit, and its time grows with the rows it
+// carries, so: the fewest rows with which the chip's 256 compute units take the launch in one round.
+// Measured against ranking + pruning + pipelined attention (us, d 128; units, queries, cached, kept):
+//   16 rows:   16 x 144, 340, 80: 16.5 / 26.2       16 x 144, 5000, 5000: 60 / 117
+//   32 rows:   32 x 256, 380, 82: 21.5 / 28.9       16 x 400, 1500, 1500: 29 / 48
+//   64 rows:   16 x 1024, 820, 390: 51 / 59         64 x 256, 380, 82: 26.5 / 30.1
+//   128 rows:  256 x 128, 300, 60: 28.3 / 30.2      128 x 256, 380, 82: 33.5 / 33.6
+//              128 x 144, 5000, 5000: 294 / 217     (longer than 320 keys: not worth it)
+// More units than compute units: two rounds are paid, which only maps of up to 16 queries stand
+// (320 x 4, 65, 65: 10.8 / 20.8;  512 x 16, 69, 14: 22.1 / 22.7;  320 x 36, 85, 21: 26 / 23).
+inline int small_tile_rows(int dtype, int n_unit, int n_q, int kv) {
+  if (dtype != 1) return 0;
+  constexpr int kComputeUnits = 256;
+  for (int rows = 16; rows <= 128; rows *= 2)
+    if ((long long)n_unit * ((n_q + rows - 1) / rows) <= kComputeUnits) return rows < 128 || kv <= 320 ? rows : 0;
+  return n_q <= 16 ? 16 : 0;
+}
+
+// bf16, head_dim 128 only: the pipelined kernel used when there is enough work for it.  Keys and values are the
 // first len1 rows of the caches k, v followed by the len2 rows of the dense tensors k2, v2
 // ([U, len2, d]; may be NULL when len2 == 0).  With `append` the kernel also copies k2, v2 into
 // rows [len1, len1 + len2) of the caches, which must have room for them.  `start` / `stop`
@@ -123,7 +166,9 @@ hipError_t launch_attend_pipe(int n_unit, int n_head, const void* q, int n_q, Kv
                               float sm_scale, void* out, hipStream_t stream,
                               hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 // whether launch_attend would take the pipelined kernel for this shape
-inline bool attend_uses_pipe(int dtype, int d, int n_q) { return dtype == 1 && d == 128 && n_q > 128; }
+inline bool attend_uses_pipe(int dtype, int d, int n_unit, int n_q, int kv) {
+  return dtype == 1 && d == 128 && small_tile_rows(dtype, n_unit, n_q, kv) == 0;
+}
 
 // ---- device helpers ----
 // Workgroup coordinates as the kernels read them.  A build with SCALEKV_REVERSE_WG
@@ -147,7 +192,25 @@ __device__ __forceinline__ int xcd_order(int wg, int n_wg) {
   const int per = n_wg / kXcds;
   return wg < per * kXcds ? wg % kXcds * per + wg / kXcds : wg;
 }
-// Shared by the two MFMA attention kernels: the key row fed to MFMA row i of the first product
+// Butterflies over the four rows of 16 lanes of a wave: lanes l and l^16, then l and l^32, in
+// registers.  The swap hands every lane {own value, partner's value} in some order; maximum and
+// sum do not care which is which.
+__device__ __forceinline__ void swap16(float x, float& a, float& b) {
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap32(float x, float& a, float& b) {
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float xor16_max(float x) { float a, b; swap16(x, a, b); return fmaxf(a, b); }
+__device__ __forceinline__ float xor32_max(float x) { float a, b; swap32(x, a, b); return fmaxf(a, b); }
+__device__ __forceinline__ float xor16_sum(float x) { float a, b; swap16(x, a, b); return a + b; }
+__device__ __forceinline__ float xor32_sum(float x) { float a, b; swap32(x, a, b); return a + b; }
+
+// In the 32x32 MFMA attention kernel the key row fed to MFMA row i of the first product
 // is row pi32(i) of the 32-key block (bits 2 and 3 swapped), which makes the registers of an
 // S^T block the B operand of the second product; and the number of log2 units a row maximum may
 // grow before the running offset is moved and the accumulators are rescaled.
@@ -191,16 +254,9 @@ __device__ __forceinline__ float score_row_shift(const ScoreWorkspace& ws, int u
     z += part[c * 2 * kMaxWindow + kMaxWindow + j] * expf(part[c * 2 * kMaxWindow + j] - m);
   return m + logf(z);
 }
-// log s_i = logsumexp_j(logit[i][j] - shift_j) for one key; row_shift lives in LDS.
-__device__ __forceinline__ float score_log_sum(const ScoreWorkspace& ws, int unit, int key, int n_win,
-                                               const float* row_shift) {
-  const float* lg = ws.logits + ((long long)unit * ws.len_pad + key) * kMaxWindow;
-  float la[kMaxWindow];
-#pragma unroll
-  for (int j4 = 0; j4 < kMaxWindow; j4 += 4) {
-    const float4 x = *(const float4*)(lg + j4);
-    la[j4] = x.x; la[j4 + 1] = x.y; la[j4 + 2] = x.z; la[j4 + 3] = x.w;
-  }
+// log s_i = logsumexp_j(logit[i][j] - shift_j) from the n_win logits of one key
+template <typename Shift>
+__device__ __forceinline__ float log_sum_rows(float (&la)[kMaxWindow], int n_win, const Shift& row_shift) {
   float top = -INFINITY;
 #pragma unroll
   for (int j = 0; j < kMaxWindow; ++j) {
@@ -211,6 +267,18 @@ __device__ __forceinline__ float score_log_sum(const ScoreWorkspace& ws, int uni
 #pragma unroll
   for (int j = 0; j < kMaxWindow; ++j) acc += j < n_win ? expf(la[j] - top) : 0.f;
   return top + logf(acc);
+}
+// the same for one key of the workspace; row_shift lives in LDS
+__device__ __forceinline__ float score_log_sum(const ScoreWorkspace& ws, int unit, int key, int n_win,
+                                               const float* row_shift) {
+  const float* lg = ws.logits + ((long long)unit * ws.len_pad + key) * kMaxWindow;
+  float la[kMaxWindow];
+#pragma unroll
+  for (int j4 = 0; j4 < kMaxWindow; j4 += 4) {
+    const float4 x = *(const float4*)(lg + j4);
+    la[j4] = x.x; la[j4 + 1] = x.y; la[j4 + 2] = x.z; la[j4 + 3] = x.w;
+  }
+  return log_sum_rows(la, n_win, row_shift);
 }
 
 // round-to-nearest-even float -> bf16 bits (NaN kept quiet)

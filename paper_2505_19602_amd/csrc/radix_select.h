@@ -30,6 +30,18 @@ __device__ __forceinline__ uint32_t wave_prefix_sum(uint32_t x, int lane) {
   return x + (lane >= 16 ? t0 : 0u) + (lane >= 32 ? t1 : 0u) + (lane >= 48 ? t2 : 0u);
 }
 
+// log of the average of exp(v[i + t]), |t| <= r, positions outside [0, len) counting as zero
+template <typename Load>
+__device__ __forceinline__ float pooled_log(Load v, int i, int len, int r) {
+  const int a = max(i - r, 0), b = min(i + r, len - 1);
+  float m = -INFINITY;
+  for (int t = a; t <= b; ++t) m = fmaxf(m, v(t));
+  if (!(m > -INFINITY)) return -INFINITY;
+  float acc = 0.f;
+  for (int t = a; t <= b; ++t) acc += expf(v(t) - m);
+  return m + logf(acc) - logf((float)(2 * r + 1));
+}
+
 constexpr int kRadixHistWords = 4 * 256;  // LDS scratch of radix_kth_largest: one histogram per pass
 
 // Among the n keys key_at(0..n-1) finds T, the key of the k-th largest (1 <= k <= n), in four
@@ -96,6 +108,63 @@ __device__ __forceinline__ void radix_kth_largest(KeyAt key_at, int n, uint32_t 
     prefix |= (uint32_t)__builtin_amdgcn_readlane(digit_sel, owner) << shift;
     remaining = __builtin_amdgcn_readlane(rem_sel, owner);
     mask |= 255u << shift;
+  }
+  T = prefix;
+  need_eq = remaining;
+}
+
+// The same search for keys whose bits from `bits` up (1 <= bits <= 32) are all those of any_key: the
+// first digit ends at the highest bit that differs, and the search ends as soon as the bin it has
+// narrowed down to is wanted whole.  Then T is one less than the bin's smallest possible key and
+// need_eq is 0: "above T" are exactly the k largest.  hist (kRadixHistWords words) has been cleared
+// and a barrier passed.  Keys of real scores spread over the first digit's bins this way, so the
+// lanes add one by one.
+template <int THREADS, typename KeyAt>
+__device__ __forceinline__ void radix_kth_largest_from(KeyAt key_at, int n, uint32_t k, int bits, uint32_t any_key,
+                                                       uint32_t* hist, uint32_t& T, uint32_t& need_eq) {
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  uint32_t mask = bits < 32 ? ~0u << bits : 0u;
+  uint32_t prefix = any_key & mask, remaining = k;
+  for (int pass = 0;; ++pass) {
+    const int width = min(bits, 8);
+    const int shift = bits - width;
+    const uint32_t digit_mask = (1u << width) - 1u;
+    uint32_t* h = hist + 256 * pass;
+    for (int i = tid; i < n; i += THREADS) {
+      const uint32_t kk = key_at(i);
+      if ((kk & mask) == prefix) atomicAdd(&h[(kk >> shift) & digit_mask], 1u);
+    }
+    __syncthreads();
+    // lane L owns bins 4L..4L+3 (see radix_kth_largest)
+    const uint4 own = *reinterpret_cast<const uint4*>(h + 4 * lane);
+    const uint32_t mine = own.x + own.y + own.z + own.w;
+    const uint32_t upto = wave_prefix_sum(mine, lane);
+    uint32_t above = __builtin_amdgcn_readlane(upto, 63) - upto;
+    const uint32_t hh[4] = {own.w, own.z, own.y, own.x};
+    uint32_t digit_sel = 0, rem_sel = 0, size_sel = 0;
+    bool found = false;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      if (above < remaining && remaining <= above + hh[b]) {
+        found = true;
+        digit_sel = 4 * lane + (3 - b);
+        rem_sel = remaining - above;
+        size_sel = hh[b];
+      }
+      above += hh[b];
+    }
+    const int owner = __builtin_ctzll(__builtin_amdgcn_ballot_w64(found));
+    prefix |= (uint32_t)__builtin_amdgcn_readlane(digit_sel, owner) << shift;
+    remaining = __builtin_amdgcn_readlane(rem_sel, owner);
+    mask |= digit_mask << shift;
+    bits = shift;
+    if (bits == 0) break;
+    if (remaining == (uint32_t)__builtin_amdgcn_readlane(size_sel, owner) && prefix != 0) {
+      T = prefix - 1;
+      need_eq = 0;
+      return;
+    }
   }
   T = prefix;
   need_eq = remaining;

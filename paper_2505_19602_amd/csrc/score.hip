@@ -131,7 +131,7 @@ __global__ __launch_bounds__(kThreads) void score_logits_mfma_kernel(
   score_load_window<D>(q + unit * q_unit_stride, rows, n_win, qf);
   float m, e;
   score_wave_logits<D, NT>(ku, qf, SCALEKV_WG_X * kScoreChunk + wave * (16 * NT), cache_len, sm_scale,
-                           ws.logits + (long long)unit * ws.len_pad * kMaxWindow, m, e);
+                           ws.logits + (long long)unit * ws.len_pad * kMaxWindow, kMaxWindow, m, e);
   if (lane < kMaxWindow) { red_max[wave][lane] = m; red_sum[wave][lane] = e; }
   __syncthreads();
   if (tid < kMaxWindow) {

@@ -21,22 +21,26 @@ template <int D>
 __device__ __forceinline__ void score_load_window(const uint16_t* qu, const WindowRows& rows, int n_win,
                                                   score_bf16x8 (&qf)[D / 32]) {
   const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
+  // (chosen among the sixteen scalars: indexing the array by lane is a load of its own in front of the rows)
+  int row = 0;
+#pragma unroll
+  for (int j = 0; j < kMaxWindow; ++j) row = i == j ? rows.row[j] : row;
 #pragma unroll
   for (int sl = 0; sl < D / 32; ++sl) {
     uint4 raw = make_uint4(0, 0, 0, 0);
-    if (i < n_win) raw = *(const uint4*)(qu + (long long)rows.row[i] * D + 32 * sl + 8 * g);
+    if (i < n_win) raw = *(const uint4*)(qu + (long long)row * D + 32 * sl + 8 * g);
     qf[sl] = __builtin_bit_cast(score_bf16x8, raw);
   }
 }
 
 // Logits (scaled) of keys key0 .. key0 + 16 NT - 1 of one unit against the window rows: written
-// key-major to logits_unit[key * kMaxWindow + row] for keys below cache_len.  On return every
+// key-major to logits_unit[key * stride + row] (global memory or LDS) for keys below cache_len.  On return every
 // lane holds, for its window row l%16, m = the maximum of those logits over the wave's valid
 // keys (-inf if none) and e = the sum of exp(logit - m) over them.
 template <int D, int NT>
 __device__ __forceinline__ void score_wave_logits(const uint16_t* ku, const score_bf16x8 (&qf)[D / 32],
                                                   int key0, int cache_len, float sm_scale,
-                                                  float* logits_unit, float& m, float& e) {
+                                                  float* logits_unit, int stride, float& m, float& e) {
   constexpr int NSL = D / 32;
   const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
   score_bf16x8 kf[NT][NSL];
@@ -60,12 +64,11 @@ __device__ __forceinline__ void score_wave_logits(const uint16_t* ku, const scor
       const int key = key0 + 16 * t + 4 * g + v;
       c[t][v] = key < cache_len ? c[t][v] * sm_scale : -INFINITY;
       m = fmaxf(m, c[t][v]);
-      if (key < cache_len) logits_unit[(long long)key * kMaxWindow + i] = c[t][v];
+      if (key < cache_len) logits_unit[key * stride + i] = c[t][v];
     }
   }
   // row statistics of window row i over this wave's keys
-  m = fmaxf(m, __shfl_xor(m, 16));
-  m = fmaxf(m, __shfl_xor(m, 32));
+  m = xor32_max(xor16_max(m));
   e = 0.f;
   if (m > -INFINITY) {
 #pragma unroll
@@ -73,8 +76,7 @@ __device__ __forceinline__ void score_wave_logits(const uint16_t* ku, const scor
 #pragma unroll
       for (int v = 0; v < 4; ++v) e += expf(c[t][v] - m);
   }
-  e += __shfl_xor(e, 16);
-  e += __shfl_xor(e, 32);
+  e = xor32_sum(xor16_sum(e));
 }
 
 }  // namespace scalekv

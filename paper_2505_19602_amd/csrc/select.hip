@@ -13,6 +13,7 @@
 // largest key, and `keep` counts them.
 #include "common.h"
 #include "radix_select.h"
+#include "rank_short.h"
 #include "score_mfma.h"
 
 namespace scalekv {
@@ -22,20 +23,6 @@ constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
 constexpr int kLdsKeys = 12288;  // units up to this many scores keep their keys in LDS
 static_assert(kLdsKeys == 12288, "score_select_fits() in common.h states the same limit");
-
-// FUSED: the scores are not read but formed here from the logits workspace (the score
-// finalisation), so the fused step neither writes nor re-reads them.
-// log of the average of exp(v[i + t]), |t| <= r, positions outside [0, len) counting as zero
-template <typename Load>
-__device__ __forceinline__ float pooled_log(Load v, int i, int len, int r) {
-  const int a = max(i - r, 0), b = min(i + r, len - 1);
-  float m = -INFINITY;
-  for (int t = a; t <= b; ++t) m = fmaxf(m, v(t));
-  if (!(m > -INFINITY)) return -INFINITY;
-  float acc = 0.f;
-  for (int t = a; t <= b; ++t) acc += expf(v(t) - m);
-  return m + logf(acc) - logf((float)(2 * r + 1));
-}
 
 // What the kernel needs to form the logits itself (SCORE_D != 0): bf16 storage only.
 struct ScoreInputs {
@@ -59,6 +46,47 @@ struct ScoreInputs {
   const uint16_t* v_cur;
   int n_app;
 };
+
+// Pruning of one unit by one workgroup: the kept rows (and, if asked, the map's rows behind them)
+// into the destination.
+template <int D, int THREADS>
+__device__ __forceinline__ void prune_unit(const ScoreInputs& si, int unit, int keep, const int32_t* list) {
+  typedef unsigned int vec4 __attribute__((ext_vector_type(4)));
+  constexpr int VPR = D * 2 / 16;  // 16-byte vectors per row
+  constexpr int kFly = 4;          // vectors in flight per thread and tensor
+  const int tid = threadIdx.x;
+  const int seq = unit / si.n_head, head = unit - seq * si.n_head;
+  const vec4* ksrc = (const vec4*)(si.k + seq * si.k_seq_stride + head * si.k_head_stride);
+  const vec4* vsrc = (const vec4*)(si.v_src + seq * si.v_seq_stride + head * si.v_head_stride);
+  vec4* kdst = (vec4*)(si.k_dst + seq * si.kd_seq_stride + head * si.kd_head_stride);
+  vec4* vdst = (vec4*)(si.v_dst + seq * si.vd_seq_stride + head * si.vd_head_stride);
+  const vec4* kcur = (const vec4*)(si.k_cur + (long long)unit * si.n_app * D);
+  const vec4* vcur = (const vec4*)(si.v_cur + (long long)unit * si.n_app * D);
+  const int total = (keep + si.n_app) * VPR;
+#pragma unroll 1
+  for (int f0 = tid; f0 < total; f0 += THREADS * kFly) {
+    vec4 a[kFly], b[kFly];
+#pragma unroll
+    for (int u = 0; u < kFly; ++u) {
+      // (lanes past the end re-read the last vector and store nothing: a branch around the loads
+      // costs the kernel 30 registers)
+      const int f = min(f0 + u * THREADS, total - 1);
+      const int row = f / VPR, c = f % VPR;
+      const bool kept = row < keep;
+      const long long o = (long long)(kept ? list[row] : row - keep) * VPR + c;
+      a[u] = __builtin_nontemporal_load((kept ? ksrc : kcur) + o);
+      b[u] = __builtin_nontemporal_load((kept ? vsrc : vcur) + o);
+    }
+#pragma unroll
+    for (int u = 0; u < kFly; ++u) {
+      const int f = f0 + u * THREADS;
+      if (f < total) {
+        __builtin_nontemporal_store(a[u], kdst + f);
+        __builtin_nontemporal_store(b[u], vdst + f);
+      }
+    }
+  }
+}
 
 // SCORE_D = 64 / 128: the whole ranking step of Sec. 3.3 in one kernel.  The workgroup first
 // streams the unit's cached keys itself (16 waves x 32 keys per round, logits to the workspace,
@@ -112,7 +140,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MIN_WA
       float m_run = -INFINITY, e_run = 0.f;
       for (int key0 = wave * (16 * NT); key0 < cache_len; key0 += kWaves * 16 * NT) {
         float m, e;
-        score_wave_logits<SCORE_D, NT>(ku, qf, key0, cache_len, si.sm_scale, logits_unit, m, e);
+        score_wave_logits<SCORE_D, NT>(ku, qf, key0, cache_len, si.sm_scale, logits_unit, kMaxWindow, m, e);
         const float m_new = fmaxf(m_run, m);   // m is finite: the round has at least one valid key
         e_run = e_run * expf(m_run - m_new) + e * expf(m - m_new);
         m_run = m_new;
@@ -194,47 +222,38 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MIN_WA
   // ---- pruning: the kept rows (and, if asked, the map's rows behind them) into the destination
   if constexpr (SCORE_D != 0) {
     if (si.k_dst != nullptr) {
-      typedef unsigned int vec4 __attribute__((ext_vector_type(4)));
-      constexpr int VPR = SCORE_D * 2 / 16;  // 16-byte vectors per row
-      constexpr int kFly = 4;                // vectors in flight per thread and tensor
       __syncthreads();  // the unit's index list is complete (written by this workgroup)
-      const int seq = unit / si.n_head, head = unit - seq * si.n_head;
-      const vec4* ksrc = (const vec4*)(si.k + seq * si.k_seq_stride + head * si.k_head_stride);
-      const vec4* vsrc = (const vec4*)(si.v_src + seq * si.v_seq_stride + head * si.v_head_stride);
-      vec4* kdst = (vec4*)(si.k_dst + seq * si.kd_seq_stride + head * si.kd_head_stride);
-      vec4* vdst = (vec4*)(si.v_dst + seq * si.vd_seq_stride + head * si.vd_head_stride);
-      const vec4* kcur = (const vec4*)(si.k_cur + (long long)unit * si.n_app * SCORE_D);
-      const vec4* vcur = (const vec4*)(si.v_cur + (long long)unit * si.n_app * SCORE_D);
-      const int total = (keep + si.n_app) * VPR;
-      for (int f0 = tid; f0 < total; f0 += kThreads * kFly) {
-        vec4 a[kFly], b[kFly];
-#pragma unroll
-        for (int u = 0; u < kFly; ++u) {
-          const int f = f0 + u * kThreads;
-          if (f < total) {
-            const int row = f / VPR, c = f % VPR;
-            if (row < keep) {
-              const long long o = (long long)out[row] * VPR + c;
-              a[u] = __builtin_nontemporal_load(ksrc + o);
-              b[u] = __builtin_nontemporal_load(vsrc + o);
-            } else {
-              const long long o = (long long)(row - keep) * VPR + c;
-              a[u] = __builtin_nontemporal_load(kcur + o);
-              b[u] = __builtin_nontemporal_load(vcur + o);
-            }
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < kFly; ++u) {
-          const int f = f0 + u * kThreads;
-          if (f < total) {
-            __builtin_nontemporal_store(a[u], kdst + f);
-            __builtin_nontemporal_store(b[u], vdst + f);
-          }
-        }
-      }
+      prune_unit<SCORE_D, kThreads>(si, unit, keep, out);
     }
   }
+}
+
+// The same for short caches (rank_short.h): nothing but the index list leaves the compute unit
+// between the keys and the pruned rows.  EXTRAS: forced positions and pooling may be asked for.
+// 256 units, 546 cached rows, 246 kept: 30.6 us with select_kernel, 26.3 here; 16-256 units, 70-400 rows: 13-17 -> 8-13 us.
+template <int D, int THREADS, bool EXTRAS>
+__global__ __launch_bounds__(THREADS) void rank_short_kernel(int cache_len, int keep, int32_t* __restrict__ idx,
+                                                             int n_win, SelectExtras ex, ScoreInputs si) {
+  extern __shared__ __attribute__((aligned(16))) float short_logits[];
+  __shared__ RankShortLds lds;
+  const int unit = SCALEKV_WG_X;
+  const int seq = unit / si.n_head, head = unit - seq * si.n_head;
+  rank_short<D, THREADS, EXTRAS>(si.q + unit * si.q_unit_stride, si.rows, n_win,
+                                 si.k + seq * si.k_seq_stride + head * si.k_head_stride, cache_len, keep, si.sm_scale,
+                                 ex, short_logits, lds, idx + (long long)unit * keep);
+  if (si.k_dst != nullptr) prune_unit<D, THREADS>(si, unit, keep, lds.list);
+}
+
+template <int D, int THREADS, bool EXTRAS>
+hipError_t launch_short(int n_unit, int cache_len, int keep, int32_t* idx, int n_win, const SelectExtras& ex,
+                        const ScoreInputs& si, hipStream_t stream) {
+  static std::atomic<uint64_t> configured{0};  // LDS above 64 KB per workgroup has to be asked for
+  const hipError_t e = allow_dynamic_lds((const void*)rank_short_kernel<D, THREADS, EXTRAS>,
+                                         rank_short_logit_bytes(kShortLen), configured);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((rank_short_kernel<D, THREADS, EXTRAS>), dim3(n_unit), dim3(THREADS),
+                     rank_short_logit_bytes(cache_len), stream, cache_len, keep, idx, n_win, ex, si);
+  return hipGetLastError();
 }
 
 __global__ void iota_kernel(int32_t* __restrict__ idx, int keep, long long total) {
@@ -325,6 +344,16 @@ hipError_t launch_score_select(int dtype, int n_seq, int n_head, int d, const vo
     si.n_app = prune->k_cur ? prune->n_app : 0;
   }
   constexpr int kComputeUnits = 256;  // MI355X
+  if (cache_len <= kShortLen) {
+    const bool plain = ex.n_forced == 0 && ex.pool_w == 1;
+#define SCALEKV_SHORT(T)                                                                             \
+  (d == 128 ? plain ? launch_short<128, T, false>(n_unit, cache_len, keep, idx, n_win, ex, si, stream) \
+                    : launch_short<128, T, true>(n_unit, cache_len, keep, idx, n_win, ex, si, stream)  \
+   : plain ? launch_short<64, T, false>(n_unit, cache_len, keep, idx, n_win, ex, si, stream)           \
+           : launch_short<64, T, true>(n_unit, cache_len, keep, idx, n_win, ex, si, stream))
+    return n_unit > kComputeUnits ? SCALEKV_SHORT(512) : SCALEKV_SHORT(1024);
+#undef SCALEKV_SHORT
+  }
   if (d == 128 && n_unit > kComputeUnits)
     hipLaunchKernelGGL((select_kernel<true, true, 128, 8>), dim3(n_unit), dim3(kThreads), 0, stream, nullptr,
                        0, cache_len, keep, idx, ws, n_win, ex, si);

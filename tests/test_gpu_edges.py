@@ -7,7 +7,7 @@ import torch
 import oracle
 import paper_2505_19602_amd as skv
 import workloads as W
-from parity_util import check_output, units
+from parity_util import check_indices, check_output, units
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -52,3 +52,61 @@ def test_score_f32_edges(d, L, n_win):
     torch.cuda.synchronize()
     _, ref = oracle.score(units(qw), units(k)[:, :L])
     assert np.abs(ls.cpu().numpy().reshape(S * H, L).astype(np.float64) - ref).max() < 2e-4
+
+
+def _step_against_oracle(S, H, d, L, budget, n_cur, n_win, pick, seed, dup=1, with_idx=True):
+    """One step; units `pick` followed by the oracle.  dup > 1: cached rows repeat in runs of that length (ties)."""
+    dtype = torch.bfloat16
+    shape = skv.Shape(S, H, d, dtype)
+    keep = min(budget, L)
+    mk = lambda i, n, scale=1.0: _rand(100 * seed + i, (S, H, n, d), dtype, scale)
+    q, kc, vc, vs = mk(0, n_cur, 1.5), mk(1, n_cur), mk(2, n_cur), mk(3, L + 2)
+    ks = mk(4, (L + 2 + dup - 1) // dup, 1.5).repeat_interleave(dup, 2)[:, :, : L + 2].contiguous()
+    ks[:, :, L:] = float("nan"); vs[:, :, L:] = float("nan")
+    win = list(range(n_cur - n_win, n_cur))
+    cap = keep + n_cur + 2
+    kd = torch.full((S, H, cap, d), 7.0, dtype=dtype, device=DEV); vd = torch.full_like(kd, 7.0)
+    out = torch.full((S, H, n_cur, d), float("nan"), dtype=dtype, device=DEV)
+    idx = torch.full((S, H, keep), -1, dtype=torch.int32, device=DEV) if with_idx else None
+    ws = torch.empty(skv.workspace_bytes(shape, max(L, 1), n_cur), dtype=torch.uint8, device=DEV)
+    assert skv.step(shape, q.to(DEV), kc.to(DEV), vc.to(DEV), win, ks.to(DEV), vs.to(DEV), L, budget, kd, vd, out, idx,
+                    ws) == keep + n_cur
+    torch.cuda.synchronize()
+    for t in (kd, vd):
+        assert torch.all(t[:, :, keep + n_cur:] == 7.0)
+    sub = lambda t: units(t)[pick]
+    kpart, vpart = sub(ks)[:, :L], sub(vs)[:, :L]
+    if keep and keep < L:
+        _, ls = oracle.score(sub(q)[:, win], kpart)
+        own = oracle.select(ls, budget)
+    else:
+        ls, own = np.zeros((len(pick), L)), np.tile(np.arange(keep), (len(pick), 1))
+    if with_idx:
+        got = idx.cpu().numpy().reshape(S * H, keep)[pick]
+        for u in range(len(pick)):
+            if dup == 1:
+                check_indices(got[u], ls[u], keep, own[u])
+            else:      # equal rows have equal scores: of a run that is cut, the lower rows are kept
+                assert np.array_equal(got[u], own[u])
+    else:
+        got = own
+    ref = oracle.step(sub(q), sub(kc), sub(vc), win, kpart, vpart, budget, force_idx=got)
+    assert np.array_equal(sub(kd)[:, : keep + n_cur].double().numpy(), ref["k_dst"])
+    assert np.array_equal(sub(vd)[:, : keep + n_cur].double().numpy(), ref["v_dst"])
+    check_output(sub(out), ref["out"], dtype, "step")
+
+
+# One-launch steps: groups of 32 keys, rounds of 512 keys, the longest cache ranked in LDS and the
+# first beyond it; 16-query blocks, several blocks per workgroup (many units), ties.
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("S,H,L,budget,n_cur,n_win,dup", [
+    (1, 2, 2, 1, 1, 1, 1), (1, 3, 31, 30, 15, 15, 1), (1, 2, 33, 1, 16, 16, 1), (2, 2, 64, 32, 17, 3, 1),
+    (1, 2, 511, 100, 40, 16, 1), (1, 2, 513, 512, 33, 16, 1), (1, 2, 1025, 77, 64, 16, 1), (1, 2, 1535, 400, 128, 16, 1),
+    (1, 2, 1536, 1535, 20, 16, 1), (1, 2, 1537, 500, 20, 16, 1), (4, 80, 200, 50, 128, 16, 1), (3, 100, 90, 20, 50, 16, 1),
+    (2, 140, 300, 60, 30, 16, 1), (1, 2, 300, 101, 20, 16, 5), (1, 2, 1200, 333, 36, 16, 7), (1, 1, 40, 13, 5, 5, 40),
+    (1, 2, 50, 50, 20, 16, 1), (1, 2, 40, 0, 20, 16, 1), (40, 20, 60, 60, 100, 16, 1),
+])
+def test_small_step_edges(d, S, H, L, budget, n_cur, n_win, dup):
+    print(f"small step d={d} S={S} H={H} L={L} budget={budget} n_cur={n_cur} n_win={n_win} dup={dup}", flush=True)
+    pick = sorted({0, S * H // 2, S * H - 1})
+    _step_against_oracle(S, H, d, L, budget, n_cur, n_win, pick, 1, dup)
