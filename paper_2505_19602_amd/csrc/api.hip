@@ -409,7 +409,7 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
   };
   const int U = shape->n_seq * shape->n_head;
   const int32_t* idx = nullptr;  // identity unless a ranking is needed
-  const bool pipe = attend_uses_pipe(shape->dtype, shape->head_dim, U, n_cur, keep + n_cur);
+  const bool pipe = attend_uses_pipe(shape->dtype, U, n_cur, keep + n_cur);
   const bool small = small_tile_rows(shape->dtype, U, n_cur, keep + n_cur) > 0;
   const bool one_launch = small && ranks && cache_len <= kShortLen;  // the attention kernel ranks as well
   bool pruned = false;           // the ranking kernel has already written the destination caches
@@ -475,7 +475,7 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
                 "compact launch");
   if (fused_append) {
     // events 3 and 4 ride on this kernel's dispatch: its own start and end
-    SCALEKV_HIP(launch_attend_pipe(U, shape->n_head, q, n_cur, view(k_dst), view(v_dst), keep, k_cur,
+    SCALEKV_HIP(launch_attend_pipe(U, shape->n_head, shape->head_dim, q, n_cur, view(k_dst), view(v_dst), keep, k_cur,
                                    v_cur, n_cur, true, resolve_scale(shape), out, st,
                                    ev ? static_cast<hipEvent_t>(ev[3]) : nullptr,
                                    ev ? static_cast<hipEvent_t>(ev[4]) : nullptr),
@@ -651,7 +651,7 @@ scalekv_status scalekv_step_append_first(const scalekv_shape* shape, const void*
   SCALEKV_HIP(mark(0), "event record");
   // 1. the map's K/V join the cache: rows [cache_len, cache_len + n_cur) of every unit (the
   //    pipelined attention kernel does this itself, overlapped with its own work)
-  const bool fused_append = attend_uses_pipe(shape->dtype, shape->head_dim, U, n_cur, len);
+  const bool fused_append = attend_uses_pipe(shape->dtype, U, n_cur, len);
   const bool small = small_tile_rows(shape->dtype, U, n_cur, len) > 0;
   if (!fused_append && !small) {
     const long long tail = (long long)cache_len * d * elem_bytes(shape);
@@ -666,7 +666,7 @@ scalekv_status scalekv_step_append_first(const scalekv_shape* shape, const void*
   // 2. the map attends over history and itself
   if (fused_append) {
     // events 1 and 2 ride on this kernel's dispatch: its own start and end
-    SCALEKV_HIP(launch_attend_pipe(U, shape->n_head, q, n_cur, view(k_cache), view(v_cache), cache_len,
+    SCALEKV_HIP(launch_attend_pipe(U, shape->n_head, shape->head_dim, q, n_cur, view(k_cache), view(v_cache), cache_len,
                                    k_cur, v_cur, n_cur, true, resolve_scale(shape), out, st,
                                    ev ? static_cast<hipEvent_t>(ev[1]) : nullptr,
                                    ev ? static_cast<hipEvent_t>(ev[2]) : nullptr),

@@ -1,4 +1,4 @@
-// bf16 MFMA attention for head_dim 128 and large query counts: the kernel that
+// bf16 MFMA attention for large query counts: the kernel that
 // carries almost all of the flops of the ScaleKV step (Sec. 3.1 / 3.3: the current
 // token map attends, unmasked, over the retained cache followed by its own keys).
 //
@@ -80,12 +80,33 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void glb_void;
 
-constexpr int D = 128;
 constexpr int BM = 128;              // query rows per workgroup: 4 waves x 32
 constexpr int TN = 64;               // keys per staged tile (two blocks of 32)
-constexpr int kRowBytes = D * 2;     // 256
-constexpr int kTileBytes = TN * kRowBytes;  // 16 KB
 constexpr int kStages = 2;
+
+// What depends on head_dim.  head_dim 64 halves the tiles and the accumulators, so that three
+// workgroups share a compute unit instead of two; per block of 32 keys its 8 MFMA (256 clocks) and
+// its softmax (16 fma, 16 exp2, 16 others: 260 clocks) are about equal, and the third wave per SIMD
+// lets the two pipes overlap.  (Two waves: 3-10 % slower; four: 18 registers spilled, 0.7 % faster
+// on the largest launches and 5-8 % slower on the others.)  4096 queries x 4420 keys x 256 units:
+// 1824 us, 651 TFLOP/s with the register-staged kernel this one replaced, 1264 us, 938 TFLOP/s now;
+// 1215 x 1648 x 60: 74 -> 51 us.
+// LDS rows are swizzled in 16-byte chunks so that operand reads are free of bank conflicts: chunk c of
+// row r sits in slot c ^ k_flip(r) of a K (or query) row and c ^ v_flip(r) of a V row.  Sixteen rows
+// of 256 bytes start in the same bank, of rows of 128 bytes every second.
+template <int D>
+struct Shape {
+  static constexpr int kRowBytes = D * 2;
+  static constexpr int kTileBytes = TN * kRowBytes;       // 16 KB (d 128), 8 KB
+  static constexpr int kSlabs = D / 16;                   // k-slabs of the first product
+  static constexpr int kBlocks = D / 32;                  // 32-channel blocks of the output
+  static constexpr int kChunks = D / 8;                   // 16-byte chunks per row
+  static constexpr int kRowsPerOp = 64 / kChunks;         // rows that one transfer of a wave covers
+  static constexpr int kOps = 16 / kRowsPerOp;            // transfers for a wave's 16 rows of a tile
+  static constexpr int kWavesPerSimd = D == 128 ? 2 : 3;
+  __device__ static constexpr int k_flip(int r) { return D == 128 ? r & 15 : r >> 1 & 7; }
+  __device__ static constexpr int v_flip(int r) { return D == 128 ? (r & 3) << 2 : (r >> 1 & 1) << 2; }
+};
 // Measurement-only builds (python -m paper_2505_19602_amd.build --variant ...; never the library
 // the tests or the bench's headline load): each takes one ingredient out of the kernel so that
 // its share of the running time can be read off a timing.  Their results are wrong on purpose.
@@ -98,9 +119,11 @@ constexpr int kStages = 2;
 //                             arrived, when it left the tile loop and when it ended (results stay
 //                             correct); scalekv_timeline_read() hands the records to the host
 #if defined(SCALEKV_ONE_WG_PER_CU)
+template <int D>
 constexpr int kLdsBytes = 96 * 1024;
 #else
-constexpr int kLdsBytes = 2 * kStages * kTileBytes;  // K stages then V stages: 64 KB
+template <int D>
+constexpr int kLdsBytes = 2 * kStages * Shape<D>::kTileBytes;  // K stages then V stages: 64 KB (d 128), 32 KB
 #endif
 #if defined(SCALEKV_TIMELINE)
 constexpr int kTimelineMaxWg = 8192;
@@ -172,7 +195,9 @@ __device__ __forceinline__ void dma16_xor(const unsigned char* base_uniform, uns
       : "m0", "memory");
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int D>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(Shape<D>::kWavesPerSimd, Shape<D>::kWavesPerSimd)))
 void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, long long k_seq_stride,
                         long long k_head_stride, uint16_t* v, long long v_seq_stride,
                         long long v_head_stride, int len1, const uint16_t* __restrict__ k2,
@@ -183,6 +208,8 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   unsigned long long t_first_tile = 0;
   const unsigned long long c_start = __builtin_readcyclecounter();
 #endif
+  using G = Shape<D>;
+  constexpr int kRowBytes = G::kRowBytes, kTileBytes = G::kTileBytes, NSL = G::kSlabs, NDB = G::kBlocks;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   unsigned char* const k_lds = smem;
   unsigned char* const v_lds = smem + kStages * kTileBytes;
@@ -201,17 +228,17 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   const int n_tile1 = (len1 + TN - 1) / TN;
   const int n_tile = n_tile1 + (len2 + TN - 1) / TN;
 
-  // ---- tile loader: per thread 4 K vectors and 4 V vectors of 16 bytes.
-  // Instruction p of wave w fills LDS rows 16w + 4p .. +3 (64 lanes x 16 B = 4 rows);
-  // the lane that lands in chunk slot s of row r fetches global chunk s ^ f(r), with
-  // f(r) = r & 15 for K and (r & 3) << 2 for V.  For this lane r = r0 + 4p with r0 & 15 =
-  // lane >> 4 < 4, so its K chunk is c0 ^ 4p with c0 = (lane & 15) ^ (lane >> 4) and its V
-  // chunk does not depend on p: one register pair serves all four instructions, the rest
-  // (1024 p bytes) rides in the instruction's immediate offset.
-  const int ld_row0 = 16 * wave + (lane >> 4);
+  // ---- tile loader: per thread kOps K vectors and kOps V vectors of 16 bytes (4 each, d 64: 2).
+  // Instruction p of wave w fills LDS rows 16w + kRowsPerOp p .. (64 lanes x 16 B = 4 rows, d 64: 8);
+  // the lane that lands in chunk slot s of row r fetches global chunk s ^ flip(r).  For this lane
+  // r = r0 + kRowsPerOp p, and both flips are linear: its K chunk is c0 ^ 4p with c0 the one for
+  // p = 0, and its V chunk does not depend on p.  One register pair serves all instructions, the
+  // rest (1024 p bytes) rides in the instruction's immediate offset.
+  const int ld_row = lane / G::kChunks;                                  // row inside an instruction
+  const int ld_row0 = 16 * wave + ld_row;
   const unsigned ld_krow = ld_row0 * kRowBytes;                          // K: row part
-  const unsigned ld_kchunk = 16 * ((lane & 15) ^ (lane >> 4));           // K: chunk part for p = 0
-  const unsigned ld_vofs = ld_row0 * kRowBytes + 16 * ((lane & 15) ^ ((lane >> 4) << 2));
+  const unsigned ld_kchunk = 16 * ((lane % G::kChunks) ^ G::k_flip(ld_row));  // K: chunk part for p = 0
+  const unsigned ld_vofs = ld_row0 * kRowBytes + 16 * ((lane % G::kChunks) ^ G::v_flip(ld_row));
   auto lds_addr = [](const unsigned char* p) -> unsigned {
     return (unsigned)(size_t)(const __attribute__((address_space(3))) unsigned char*)p;
   };
@@ -229,41 +256,43 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     const int valid = (second ? len2 : len1) - lt * TN;
     if (valid >= TN) {
       // the immediate offset moves the LDS destination along with the global source, which
-      // is exactly the 4 rows between a lane's consecutive transfers
+      // is exactly the kRowsPerOp rows between a lane's consecutive transfers
       dma16_xor<0>(kt, ld_krow, ld_kchunk, 0u, ks);
       dma16<0>(vt, ld_vofs, vs);
       dma16_xor<1024>(kt, ld_krow, ld_kchunk, 64u, ks);
       dma16<1024>(vt, ld_vofs, vs);
-      dma16_xor<2048>(kt, ld_krow, ld_kchunk, 128u, ks);
-      dma16<2048>(vt, ld_vofs, vs);
-      dma16_xor<3072>(kt, ld_krow, ld_kchunk, 192u, ks);
-      dma16<3072>(vt, ld_vofs, vs);
+      if constexpr (G::kOps == 4) {
+        dma16_xor<2048>(kt, ld_krow, ld_kchunk, 128u, ks);
+        dma16<2048>(vt, ld_vofs, vs);
+        dma16_xor<3072>(kt, ld_krow, ld_kchunk, 192u, ks);
+        dma16<3072>(vt, ld_vofs, vs);
+      }
     } else {
       // ragged last tile: rows past the end re-read the last valid row (finite data that
       // the mask turns into zero weight)
       const int last_row = valid - 1;
 #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const int back = max(ld_row0 + 4 * p - last_row, 0) * kRowBytes;
-        dma16<0>(kt, ld_krow + (ld_kchunk ^ (64 * p)) + 1024 * p - back, ks + 4 * p * kRowBytes);
-        dma16<0>(vt, ld_vofs + 1024 * p - back, vs + 4 * p * kRowBytes);
+      for (int p = 0; p < G::kOps; ++p) {
+        const int back = max(ld_row0 + G::kRowsPerOp * p - last_row, 0) * kRowBytes;
+        dma16<0>(kt, ld_krow + (ld_kchunk ^ (64 * p)) + 1024 * p - back, ks + 1024 * p);
+        dma16<0>(vt, ld_vofs + 1024 * p - back, vs + 1024 * p);
       }
     }
   };
 
   // ---- per-lane operand offsets inside a 32-key block (bytes)
-  int k_ofs[8];  // K operand, slab sl: row pi(j), chunk (2sl + h) ^ (row & 15)
+  int k_ofs[NSL];  // K operand, slab sl: row pi(j), chunk (2sl + h) ^ flip
   {
     const int row = pi32(j);
 #pragma unroll
-    for (int sl = 0; sl < 8; ++sl) k_ofs[sl] = row * kRowBytes + 16 * ((2 * sl + h) ^ (row & 15));
+    for (int sl = 0; sl < NSL; ++sl) k_ofs[sl] = row * kRowBytes + 16 * ((2 * sl + h) ^ G::k_flip(row));
   }
-  int v_ofs[4];  // V^T operand, channel block db: this lane's address role in the transposing load
+  int v_ofs[NDB];  // V^T operand, channel block db: this lane's address role in the transposing load
   {
     const int i = j & 15, g = i >> 2;
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
-      v_ofs[db] = (8 * h + g) * kRowBytes + 64 * (db ^ g) + 32 * (j >> 4) + 8 * (i & 3);
+    for (int db = 0; db < NDB; ++db)
+      v_ofs[db] = (8 * h + g) * kRowBytes + 64 * (db ^ (G::v_flip(g) >> 2)) + 32 * (j >> 4) + 8 * (i & 3);
   }
 
   // ---- Q fragments: B operand of the first product, resident for the whole kernel.  A lane's
@@ -272,31 +301,31 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   // go, whole and 16 bytes per lane, straight into LDS and are read from there once the first
   // tile has arrived.  They wait in the second stage, which is not in use before the first
   // barrier, each wave's rows exactly where the same wave will later put its share of the second
-  // tile (16 K rows and 16 V rows, 4 KB each): nobody else writes there, so no barrier is needed
+  // tile (16 K rows and 16 V rows): nobody else writes there, so no barrier is needed
   // before that tile is requested, only the wave's own reads must have returned.  Chunk c of row
-  // r sits in slot c ^ (r & 15), so that the fragment reads are free of bank conflicts.  Rows
+  // r sits in slot c ^ k_flip(r), so that the fragment reads are free of bank conflicts.  Rows
   // past the end of the map repeat its last row; nothing is stored for them.
-  bf16x8 qf[8];
+  bf16x8 qf[NSL];
   unsigned char* const q_stage_k = k_lds + kTileBytes + (16 * wave) * kRowBytes;  // query rows 0-15 of the wave
   unsigned char* const q_stage_v = v_lds + kTileBytes + (16 * wave) * kRowBytes;  // query rows 16-31
   {
     const unsigned qk = __builtin_amdgcn_readfirstlane(lds_addr(q_stage_k));
     const unsigned qv = __builtin_amdgcn_readfirstlane(lds_addr(q_stage_v));
 #pragma unroll
-    for (int p = 0; p < 8; ++p) {
-      const int r = 4 * p + (lane >> 4);
+    for (int p = 0; p < 2 * G::kOps; ++p) {
+      const int r = G::kRowsPerOp * p + ld_row;
       const unsigned row = (unsigned)min(q_base + r, n_q - 1);
-      dma16<0>((const unsigned char*)qu, row * kRowBytes + 16 * ((lane & 15) ^ (r & 15)),
-               (p < 4 ? qk : qv) + 4 * (p & 3) * kRowBytes);
+      dma16<0>((const unsigned char*)qu, row * kRowBytes + 16 * ((lane % G::kChunks) ^ G::k_flip(r)),
+               (p < G::kOps ? qk : qv) + 1024 * (p % G::kOps));
     }
   }
   auto read_q = [&]() __attribute__((always_inline)) {
     const unsigned char* row = (j < 16 ? q_stage_k : q_stage_v) + (j & 15) * kRowBytes;
 #pragma unroll
-    for (int s = 0; s < 8; ++s) qf[s] = *(const bf16x8*)(row + 16 * ((2 * s + h) ^ (j & 15)));
+    for (int s = 0; s < NSL; ++s) qf[s] = *(const bf16x8*)(row + 16 * ((2 * s + h) ^ G::k_flip(j & 15)));
   };
 
-  f32x16 o[4];
+  f32x16 o[NDB];
   float m_run;  // exponent offset
   float l_run;  // this lane's share of the row sum
   unsigned long long overflowed = 0;  // lanes whose block sum left the unchecked range
@@ -334,22 +363,22 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   };
 
   // ---- the phases of one block of 32 keys
-  auto fetch_k = [&](bf16x8 (&kf)[8], int ofs) {
+  auto fetch_k = [&](bf16x8 (&kf)[NSL], int ofs) {
 #pragma unroll
-    for (int sl = 0; sl < 8; ++sl) kf[sl] = load_k(ofs, sl);
+    for (int sl = 0; sl < NSL; ++sl) kf[sl] = load_k(ofs, sl);
   };
-  auto fetch_vt = [&](bf16x8 (&vf)[2][4], int ofs) {
+  auto fetch_vt = [&](bf16x8 (&vf)[2][NDB], int ofs) {
 #pragma unroll
     for (int sl = 0; sl < 2; ++sl)
 #pragma unroll
-      for (int db = 0; db < 4; ++db) vf[sl][db] = load_vt(ofs, sl, db);
+      for (int db = 0; db < NDB; ++db) vf[sl][db] = load_vt(ofs, sl, db);
   };
-  auto scores = [&](const bf16x8 (&kf)[8]) -> f32x16 {
+  auto scores = [&](const bf16x8 (&kf)[NSL]) -> f32x16 {
     f32x16 s;
 #pragma unroll
     for (int r = 0; r < 16; ++r) s[r] = 0.f;
 #pragma unroll
-    for (int sl = 0; sl < 8; ++sl) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[sl], qf[sl], s, 0, 0, 0);
+    for (int sl = 0; sl < NSL; ++sl) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[sl], qf[sl], s, 0, 0, 0);
     return s;
   };
   // softmax of the block's scores (register r = key 16(r/8) + 8h + r%8 of the block, which
@@ -357,7 +386,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   // O^T += V^T P^T
   // `tracked` (a std::bool_constant): follow the running maximum; otherwise keep m_run and
   // only watch for overflow.
-  auto softmax_pv = [&](auto tracked, f32x16& s, const bf16x8 (&vf)[2][4], bool mask, int first_key,
+  auto softmax_pv = [&](auto tracked, f32x16& s, const bf16x8 (&vf)[2][NDB], bool mask, int first_key,
                         int valid) __attribute__((always_inline)) {
     if (mask) {
       // (the lane half is taken from the lane number on the spot, so that the sixteen key
@@ -378,7 +407,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
         m_run = m_new;
         l_run *= alpha;
 #pragma unroll
-        for (int db = 0; db < 4; ++db)
+        for (int db = 0; db < NDB; ++db)
 #pragma unroll
           for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
       }
@@ -391,7 +420,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
 #pragma unroll
     for (int sl = 0; sl < 2; ++sl)
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
+      for (int db = 0; db < NDB; ++db)
         o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[sl][db], pf[sl], o[db], 0, 0, 0);
   };
 
@@ -402,7 +431,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   // its share of the next tile (so that tile may be read).  The fences stop the compiler
   // from sinking the requests back next to their uses.
   constexpr int kHalf = 32 * kRowBytes;
-  bf16x8 kf[8], vf[2][4];
+  bf16x8 kf[NSL], vf[2][NDB];
   // One tile (two blocks).  `ofs` / `next_ofs` are the byte offsets of this tile's and the
   // next tile's stage; in the main loop they are constants and fold into the LDS
   // instructions' offset fields.
@@ -440,7 +469,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   // before the second tile may overwrite them.
   auto pass = [&](auto tracked, auto first) __attribute__((always_inline)) {
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
     m_run = -INFINITY;
@@ -468,7 +497,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
       // inf or NaN in an accumulator (huge values times large unchecked weights): repeat tracked
       bool bad = false;
 #pragma unroll
-      for (int db = 0; db < 4; ++db)
+      for (int db = 0; db < NDB; ++db)
 #pragma unroll
         for (int r = 0; r < 16; ++r) bad |= !(fabsf(o[db][r]) < INFINITY);
       overflowed |= __builtin_amdgcn_ballot_w64(bad);
@@ -514,7 +543,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     const float l_tot = both_halves_sum(l_run);
     const float inv = 1.f / l_tot;
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const bf16x2 lo = {(__bf16)(o[db][4 * g] * inv), (__bf16)(o[db][4 * g + 1] * inv)};
@@ -530,10 +559,10 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     unsigned char* const obase = (unsigned char*)(out + ((long long)unit * n_q + q_base) * D);
 #pragma unroll
-    for (int p = 0; p < 8; ++p) {
-      const int r = 4 * p + (lane >> 4);
-      const u32x4 val = *(const u32x4*)(ostage + r * kOutRowStride + 16 * (lane & 15));
-      if (q_base + r < n_q) *(u32x4*)(obase + (long long)r * kRowBytes + 16 * (lane & 15)) = val;
+    for (int p = 0; p < 2 * G::kOps; ++p) {
+      const int r = G::kRowsPerOp * p + ld_row, c = 16 * (lane % G::kChunks);
+      const u32x4 val = *(const u32x4*)(ostage + r * kOutRowStride + c);
+      if (q_base + r < n_q) *(u32x4*)(obase + (long long)r * kRowBytes + c) = val;
     }
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -582,31 +611,41 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
 #endif
 }
 
-}  // namespace
-
-hipError_t launch_attend_pipe(int n_unit, int n_head, const void* q, int n_q, KvView k, KvView v,
-                              int len1, const void* k2, const void* v2, int len2, bool append,
-                              float sm_scale, void* out, hipStream_t stream, hipEvent_t start,
-                              hipEvent_t stop) {
+template <int D>
+hipError_t launch(int n_unit, int n_head, const void* q, int n_q, KvView k, KvView v, int len1, const void* k2,
+                  const void* v2, int len2, bool append, float sm_scale, void* out, hipStream_t stream,
+                  hipEvent_t start, hipEvent_t stop) {
   static std::atomic<uint64_t> configured{0};
-  const hipError_t e = allow_dynamic_lds((const void*)attend_pipe_kernel, kLdsBytes, configured);
+  const hipError_t e = allow_dynamic_lds((const void*)attend_pipe_kernel<D>, kLdsBytes<D>, configured);
   if (e != hipSuccess) return e;
   const float scale_log2e = sm_scale * 1.4426950408889634f;
   const int n_qtile = (n_q + BM - 1) / BM;
   const int n_wg = n_qtile * n_unit;
   if (start || stop)
-    hipExtLaunchKernelGGL(attend_pipe_kernel, dim3(n_wg), dim3(256), kLdsBytes, stream, start, stop, 0,
+    hipExtLaunchKernelGGL(attend_pipe_kernel<D>, dim3(n_wg), dim3(256), kLdsBytes<D>, stream, start, stop, 0,
                           (const uint16_t*)q, n_q, (uint16_t*)const_cast<void*>(k.ptr), k.seq_stride,
                           k.head_stride, (uint16_t*)const_cast<void*>(v.ptr), v.seq_stride,
                           v.head_stride, len1, (const uint16_t*)k2, (const uint16_t*)v2, len2,
                           append ? 1 : 0, n_head, n_qtile, n_wg, scale_log2e, (uint16_t*)out);
   else
-    hipLaunchKernelGGL(attend_pipe_kernel, dim3(n_wg), dim3(256), kLdsBytes, stream,
+    hipLaunchKernelGGL(attend_pipe_kernel<D>, dim3(n_wg), dim3(256), kLdsBytes<D>, stream,
                        (const uint16_t*)q, n_q, (uint16_t*)const_cast<void*>(k.ptr), k.seq_stride,
                        k.head_stride, (uint16_t*)const_cast<void*>(v.ptr), v.seq_stride,
                        v.head_stride, len1, (const uint16_t*)k2, (const uint16_t*)v2, len2,
                        append ? 1 : 0, n_head, n_qtile, n_wg, scale_log2e, (uint16_t*)out);
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_attend_pipe(int n_unit, int n_head, int d, const void* q, int n_q, KvView k, KvView v,
+                              int len1, const void* k2, const void* v2, int len2, bool append,
+                              float sm_scale, void* out, hipStream_t stream, hipEvent_t start,
+                              hipEvent_t stop) {
+  return d == 128 ? launch<128>(n_unit, n_head, q, n_q, k, v, len1, k2, v2, len2, append, sm_scale, out, stream,
+                                start, stop)
+                  : launch<64>(n_unit, n_head, q, n_q, k, v, len1, k2, v2, len2, append, sm_scale, out, stream,
+                               start, stop);
 }
 
 }  // namespace scalekv

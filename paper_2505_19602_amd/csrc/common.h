@@ -155,19 +155,19 @@ inline int small_tile_rows(int dtype, int n_unit, int n_q, int kv) {
   return n_q <= 16 ? 16 : 0;
 }
 
-// bf16, head_dim 128 only: the pipelined kernel used when there is enough work for it.  Keys and values are the
+// bf16: the pipelined kernel used when there is enough work for it.  Keys and values are the
 // first len1 rows of the caches k, v followed by the len2 rows of the dense tensors k2, v2
 // ([U, len2, d]; may be NULL when len2 == 0).  With `append` the kernel also copies k2, v2 into
 // rows [len1, len1 + len2) of the caches, which must have room for them.  `start` / `stop`
 // (either may be NULL): events that receive the kernel's own start and end times; they ride on
 // the kernel's dispatch, so unlike hipEventRecord they put no operation of their own on the stream.
-hipError_t launch_attend_pipe(int n_unit, int n_head, const void* q, int n_q, KvView k, KvView v,
+hipError_t launch_attend_pipe(int n_unit, int n_head, int d, const void* q, int n_q, KvView k, KvView v,
                               int len1, const void* k2, const void* v2, int len2, bool append,
                               float sm_scale, void* out, hipStream_t stream,
                               hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 // whether launch_attend would take the pipelined kernel for this shape
-inline bool attend_uses_pipe(int dtype, int d, int n_unit, int n_q, int kv) {
-  return dtype == 1 && d == 128 && small_tile_rows(dtype, n_unit, n_q, kv) == 0;
+inline bool attend_uses_pipe(int dtype, int n_unit, int n_q, int kv) {
+  return dtype == 1 && small_tile_rows(dtype, n_unit, n_q, kv) == 0;
 }
 
 // ---- device helpers ----
