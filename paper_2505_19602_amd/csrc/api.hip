@@ -767,7 +767,11 @@ scalekv_status scalekv_asi(const scalekv_shape* shape, const void* q_samp, int32
   const ScoreWorkspace sw = score_ws(w, ws);
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int U = shape->n_seq * shape->n_head;
-  for (int row0 = 0; row0 < n_samp; row0 += kMaxWindow) {
+  const hipError_t streamed =
+      launch_asi_stream(shape->dtype, shape->n_seq, shape->n_head, shape->head_dim, q_samp, n_samp, view(k), hist_len,
+                        len, top_k, resolve_scale(shape), ws, w.total, terms, st);
+  if (streamed != hipErrorNotSupported) SCALEKV_HIP(streamed, "asi launch");
+  for (int row0 = 0; streamed == hipErrorNotSupported && row0 < n_samp; row0 += kMaxWindow) {
     const int n_rows = std::min(kMaxWindow, n_samp - row0);
     WindowRows rows;
     for (int j = 0; j < kMaxWindow; ++j) rows.row[j] = row0 + (j < n_rows ? j : 0);

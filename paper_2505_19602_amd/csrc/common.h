@@ -102,6 +102,11 @@ hipError_t launch_positional(int n_unit, int cache_len, int n_sink, int keep, in
 // [0, hist_len), written to terms[((unit * n_samp) + row0 + row) * 2 + {0, 1}]
 hipError_t launch_asi_terms(int n_unit, ScoreWorkspace ws, int n_rows, int hist_len, int len,
                             int top_k, float* terms, int n_samp, int row0, hipStream_t stream);
+// Eq. 2 for all n_samp query rows of q ([U, n_samp, d]) without a workspace of logits: bf16 and top_k up to
+// 256, hipErrorNotSupported otherwise (or where ws_bytes does not hold the candidates)
+hipError_t launch_asi_stream(int dtype, int n_seq, int n_head, int d, const void* q, int n_samp, KvView k,
+                             int hist_len, int len, int top_k, float sm_scale, void* ws, size_t ws_bytes,
+                             float* terms, hipStream_t stream);
 // out[0], out[1] = means of the two columns of terms [n][2]; out[2] = their product
 hipError_t launch_asi_mean(const float* terms, long long n, float* out, hipStream_t stream);
 hipError_t launch_compact(int dtype, int n_seq, int n_head, int d, KvView k_src, KvView v_src,

@@ -110,3 +110,39 @@ def test_small_step_edges(d, S, H, L, budget, n_cur, n_win, dup):
     print(f"small step d={d} S={S} H={H} L={L} budget={budget} n_cur={n_cur} n_win={n_win} dup={dup}", flush=True)
     pick = sorted({0, S * H // 2, S * H - 1})
     _step_against_oracle(S, H, d, L, budget, n_cur, n_win, pick, 1, dup)
+
+
+# Streamed selectivity: rounds of 512 keys, lists that overflow and are cut (keys in ascending order of
+# their scores), ties at the threshold, several parts per unit, one and two blocks of 16 rows, history
+# within a round, K' at its limits and beyond (the route through the logits)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("S,H,n_samp,hist,cur,top_k,kind", [
+    (1, 2, 1, 1, 1, 1, "normal"), (1, 2, 16, 0, 40, 64, "normal"), (1, 2, 17, 511, 1, 64, "normal"),
+    (1, 2, 33, 513, 31, 200, "normal"), (1, 2, 16, 2000, 100, 256, "rising"), (1, 2, 5, 3000, 500, 64, "rising"),
+    (1, 2, 20, 1025, 0, 16, "ties"), (2, 2, 16, 1500, 600, 1500, "normal"), (1, 2, 16, 900, 50, 257, "normal"),
+    (1, 2, 16, 5000, 30, 255, "ties"), (3, 50, 8, 1100, 70, 0, "normal"), (9, 16, 32, 700, 400, 100, "rising"),
+])
+def test_asi_edges(d, S, H, n_samp, hist, cur, top_k, kind):
+    print(f"asi d={d} S={S} H={H} n_samp={n_samp} hist={hist} cur={cur} top_k={top_k} {kind}", flush=True)
+    dtype, n = torch.bfloat16, hist + cur
+    shape = skv.Shape(S, H, d, dtype)
+    q = _rand(7, (S, H, n_samp, d), dtype, 1.5)
+    k = _rand(8, (S, H, n, d), torch.float32)
+    if kind == "rising":       # scores of every query grow along the cache
+        q = (q.float() * 0.2 + 1.0).to(dtype)
+        k = k * 0.1 + torch.linspace(-0.5, 0.5, n)[None, None, :, None]
+    elif kind == "ties":
+        k = k.repeat_interleave(9, 2)[:, :, :n]
+    k = k.to(dtype)
+    terms = torch.full((S, H, n_samp, 2), float("nan"), device=DEV)
+    mean = torch.empty(3, device=DEV)
+    ws = torch.empty(skv.workspace_bytes(shape, n, n_samp), dtype=torch.uint8, device=DEV)
+    skv.asi(shape, q.to(DEV), k.to(DEV), hist, cur, top_k, terms, mean, ws)
+    again = torch.empty_like(terms)
+    skv.asi(shape, q.to(DEV), k.to(DEV), hist, cur, top_k, again, mean, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(terms, again)
+    pick = sorted({0, S * H - 1})
+    ref = np.stack(oracle.asi_terms(units(q)[pick], units(k)[pick], hist, top_k), -1)
+    got = terms.cpu().numpy().reshape(S * H, n_samp, 2)[pick].astype(np.float64)
+    assert np.abs(got - ref).max() < 2e-5
