@@ -440,8 +440,8 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
                                       cache_len, resolve_scale(shape), sw, st),
                   "score logits launch");
       SCALEKV_HIP(mark(1), "event record");
-      // the finalisation of the score is fused into the select; very long caches take the
-      // three-kernel route through the scores buffer
+      // the finalisation of the score is fused into the select; long caches take the three-kernel
+      // route through the scores buffer
       hipError_t fused = launch_select_from_logits(U, n_win, sw, cache_len, keep, idx_ws, nullptr, st);
       if (fused == hipErrorNotSupported) {
         SCALEKV_HIP(launch_score_finalize(U, n_win, cache_len, sw, scores, w.len_pad, st),

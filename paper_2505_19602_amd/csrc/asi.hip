@@ -47,15 +47,14 @@ __global__ __launch_bounds__(kThreads) void asi_terms_kernel(ScoreWorkspace ws, 
   __shared__ uint32_t keys[IN_LDS ? kLdsKeys : 1];
   __shared__ __attribute__((aligned(16))) uint32_t hist[kRadixHistWords];
   __shared__ float red[kWaves];
-  __shared__ float shift_s;
+  __shared__ float row_shift[kMaxWindow], stage[kStatChunks * 2 * kMaxWindow];
 
   const int row = SCALEKV_WG_X, unit = SCALEKV_WG_Y;
   const int tid = threadIdx.x;
   const float* lg = ws.logits + (long long)unit * ws.len_pad * kMaxWindow + row;
   auto logit = [&](int i) -> float { return lg[(long long)i * kMaxWindow]; };
-  if (tid == 0) shift_s = score_row_shift(ws, unit, row);  // max + log Z over all `len` keys
-  __syncthreads();
-  const float shift = shift_s;
+  score_row_shifts(ws, unit, kMaxWindow, stage, row_shift);  // max + log Z over all `len` keys
+  const float shift = row_shift[row];
 
   // attention mass on the current map: keys [hist_len, len)
   float part = 0.f;

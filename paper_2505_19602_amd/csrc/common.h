@@ -9,7 +9,7 @@ namespace scalekv {
 
 constexpr int kMaxWindow = 16;     // window rows held per unit by the score kernels
 constexpr int kScoreChunk = 256;   // cached keys handled per workgroup in the score kernels
-constexpr int kShortLen = 1536;    // longest cache that one workgroup ranks in LDS (rank_short.h)
+constexpr int kShortLen = 1536;    // longest cache that one workgroup ranks in LDS (rank.h)
 constexpr int kLogitPad = 64;      // logits row stride is the cache length rounded up to this
 
 // A cache viewed by kernels: base pointer plus strides in elements.
@@ -69,7 +69,8 @@ hipError_t launch_select(int n_unit, const float* scores, long long score_unit_s
                          int cache_len, int keep, int32_t* idx, const SelectExtras* extras,
                          hipStream_t stream);
 // select straight from the logits workspace (score finalisation fused in); returns
-// hipErrorNotSupported when the unit is too long for the fused kernel
+// hipErrorNotSupported for units of more than 2048 rows: one workgroup takes 4 us per 1024 rows for the
+// finalisation, as long as a launch of its own that spreads it over the chip
 hipError_t launch_select_from_logits(int n_unit, int n_win, ScoreWorkspace ws, int cache_len,
                                      int keep, int32_t* idx, const SelectExtras* extras,
                                      hipStream_t stream);
@@ -249,15 +250,38 @@ struct Elem<bf16_t> {
 };
 
 // ---- shared between the score finalisation and the fused select ----
-// Row normaliser of window row j: max_j + log Z_j from the per-chunk (max, sum exp) pairs.
-__device__ __forceinline__ float score_row_shift(const ScoreWorkspace& ws, int unit, int j) {
+// Row normalisers max_j + log Z_j of the window rows from the per-chunk (max, sum exp) pairs, into
+// row_shift[kMaxWindow] (LDS; 0 from n_win on), by the whole workgroup (at least 2 kMaxWindow threads).
+// The pairs of up to kStatChunks chunks come into LDS (stage) at once: a thread that walks them in
+// global memory pays a latency per chunk (14 us at 26 chunks).  A barrier at the end.
+constexpr int kStatChunks = 64;
+__device__ __forceinline__ void score_row_shifts(const ScoreWorkspace& ws, int unit, int n_win,
+                                                 float (&stage)[kStatChunks * 2 * kMaxWindow],
+                                                 float (&row_shift)[kMaxWindow]) {
   const float* part = ws.partial + (long long)unit * ws.n_chunk * 2 * kMaxWindow;
+  const int tid = threadIdx.x, j = tid;
   float m = -INFINITY;
-  for (int c = 0; c < ws.n_chunk; ++c) m = fmaxf(m, part[c * 2 * kMaxWindow + j]);
-  float z = 0.f;
-  for (int c = 0; c < ws.n_chunk; ++c)
-    z += part[c * 2 * kMaxWindow + kMaxWindow + j] * expf(part[c * 2 * kMaxWindow + j] - m);
-  return m + logf(z);
+  const bool staged = ws.n_chunk <= kStatChunks;
+  if (staged) {
+    for (int e = tid; e < ws.n_chunk * 2 * kMaxWindow; e += blockDim.x) stage[e] = part[e];
+    __syncthreads();
+  }
+  if (tid < kMaxWindow) {
+    float z = 0.f;
+    if (staged) {
+#pragma unroll 4
+      for (int c = 0; c < ws.n_chunk; ++c) m = fmaxf(m, stage[c * 2 * kMaxWindow + j]);
+#pragma unroll 4
+      for (int c = 0; c < ws.n_chunk; ++c)
+        z += stage[c * 2 * kMaxWindow + kMaxWindow + j] * expf(stage[c * 2 * kMaxWindow + j] - m);
+    } else {
+      for (int c = 0; c < ws.n_chunk; ++c) m = fmaxf(m, part[c * 2 * kMaxWindow + j]);
+      for (int c = 0; c < ws.n_chunk; ++c)
+        z += part[c * 2 * kMaxWindow + kMaxWindow + j] * expf(part[c * 2 * kMaxWindow + j] - m);
+    }
+    row_shift[j] = j < n_win ? m + logf(z) : 0.f;
+  }
+  __syncthreads();
 }
 // log s_i = logsumexp_j(logit[i][j] - shift_j) from the n_win logits of one key
 template <typename Shift>

@@ -1,0 +1,380 @@
+// Ranking of one unit's cache by one workgroup (Eq. 5 and the top-k of Sec. 3.3, bf16): logits, row
+// normalisers, log-scores, selection, index list.  rank_short: up to kShortLen rows, logits in LDS;
+// rank_long: logits in registers, beyond them in the workspace.
+//
+// For short caches nothing is bound by bandwidth; the time is a chain of memory latencies and
+// barriers.  The logits do not leave the compute unit (80 bytes of LDS a key: 16 window rows and a
+// pad against bank conflicts), every wave forms the row normalisers itself instead of waiting for
+// them, and the radix search skips the bits that all keys share and those that no longer matter:
+// the first digit starts at the highest bit in which the largest and the smallest key differ, and
+// the search ends as soon as the digit's bin is wanted whole.
+//
+// Every form selects the same rows bit for bit: groups of 32 keys belong to virtual waves group %
+// 16, whose running maximum and sum are merged in group order, then in wave order.
+#pragma once
+#include "common.h"
+#include "radix_select.h"
+#include "score_mfma.h"
+
+namespace scalekv {
+
+constexpr int kShortGroups = kShortLen / 32;
+constexpr int kLogitStride = 20;            // floats between the logits of consecutive keys in LDS
+constexpr int kVirtualWaves = 16;           // waves of the general ranking kernel
+
+struct RankShortLds {
+  __attribute__((aligned(16))) uint32_t hist[4 * 256];
+  float group_max[kShortGroups][kMaxWindow], group_sum[kShortGroups][kMaxWindow];
+  uint32_t keys[kShortLen];
+  int32_t list[kShortLen];                  // the selected rows, ascending
+  uint32_t wave_max[16], wave_min[16];
+  uint32_t count[2 * kShortLen / 64];       // per 64 keys: above the threshold, equal to it
+};
+// dynamic LDS for the logits
+inline int rank_short_logit_bytes(int len) { return round_up(len, 32) * kLogitStride * 4; }
+
+// Rows in ascending order: thread tid holds the keys kk[c] of rows tid + c THREADS < len.  Those above T
+// and the first need_eq equal to T go to list[] (LDS) and idx[], each if it is not NULL.  count: one word
+// of LDS per 64 rows.  One barrier; the caller's next one publishes the list.
+template <int THREADS, int PER>
+__device__ __forceinline__ void emit_selected(const uint32_t (&kk)[PER], int len, uint32_t T, uint32_t need_eq,
+                                              uint32_t* count, int32_t* list, int32_t* idx) {
+  constexpr int kWaves = THREADS / 64;
+  constexpr int PER_LANE = (PER * kWaves + 63) / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int n_slot = (len + 63) / 64;
+#pragma unroll
+  for (int c = 0; c < PER; ++c) {
+    const int slot = c * kWaves + wave;
+    if (slot < n_slot) {
+      const bool valid = tid + c * THREADS < len;
+      const uint32_t gt = __builtin_popcountll(__builtin_amdgcn_ballot_w64(valid && kk[c] > T));
+      const uint32_t eq = __builtin_popcountll(__builtin_amdgcn_ballot_w64(valid && kk[c] == T));
+      if (lane == 0) count[slot] = gt | eq << 16;  // (both sums stay below 2^16)
+    }
+  }
+  __syncthreads();
+  uint32_t before[PER_LANE], carry = 0;
+#pragma unroll
+  for (int x = 0; x < PER_LANE; ++x) {
+    const uint32_t mine = 64 * x + lane < n_slot ? count[64 * x + lane] : 0u;
+    const uint32_t upto = wave_prefix_sum(mine, lane);
+    before[x] = carry + upto - mine;
+    carry += __builtin_amdgcn_readlane(upto, 63);
+  }
+#pragma unroll
+  for (int c = 0; c < PER; ++c) {
+    const int slot = c * kWaves + wave;
+    if (slot < n_slot) {
+      uint32_t base = 0;
+#pragma unroll
+      for (int x = 0; x < PER_LANE; ++x)
+        if (slot / 64 == x) base = __builtin_amdgcn_readlane(before[x], slot % 64);
+      const int key = tid + c * THREADS;
+      const bool valid = key < len;
+      const unsigned long long gt = __builtin_amdgcn_ballot_w64(valid && kk[c] > T);
+      const unsigned long long eq = __builtin_amdgcn_ballot_w64(valid && kk[c] == T);
+      const unsigned long long below = ((unsigned long long)1 << lane) - 1;
+      const uint32_t g_before = (base & 0xffffu) + __builtin_popcountll(gt & below);
+      const uint32_t e_before = (base >> 16) + __builtin_popcountll(eq & below);
+      const bool take = (gt >> lane & 1) || ((eq >> lane & 1) && e_before < need_eq);
+      if (take) {
+        const uint32_t pos = g_before + min(e_before, need_eq);
+        if (list) list[pos] = key;
+        if (idx) idx[pos] = key;
+      }
+    }
+  }
+}
+
+// Largest and smallest of a value per thread, over the workgroup.  wave_max, wave_min: a word per wave.
+template <int THREADS>
+__device__ __forceinline__ void block_extremes(uint32_t& hi, uint32_t& lo, uint32_t* wave_max, uint32_t* wave_min) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    hi = max(hi, (uint32_t)__shfl_xor((int)hi, off));
+    lo = min(lo, (uint32_t)__shfl_xor((int)lo, off));
+  }
+  if ((threadIdx.x & 63) == 0) { wave_max[threadIdx.x >> 6] = hi; wave_min[threadIdx.x >> 6] = lo; }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < THREADS / 64; ++w) {
+    hi = max(hi, wave_max[w]);
+    lo = min(lo, wave_min[w]);
+  }
+}
+
+// Row normalisers max_j + log Z_j of all sixteen window rows, by one wave: lane (g, i) brings maximum and
+// sum of virtual waves 4g .. 4g+3 of row i and, in mm, the largest of those maxima.
+__device__ __forceinline__ void row_shifts(const float (&vm)[4], const float (&ve)[4], float mm,
+                                           float (&shift)[kMaxWindow]) {
+  const int i = threadIdx.x & 15;
+  mm = xor32_max(xor16_max(mm));
+  // the sum runs over the virtual waves in order: g = 0 hands its part to g = 1 and so on
+  float z = 0.f;
+#pragma unroll
+  for (int turn = 0; turn < 4; ++turn) {
+    float part = z;
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+      if (vm[x] > -INFINITY) part += ve[x] * expf(vm[x] - mm);
+    // after turn t the lanes of g = t hold the sum so far; everybody takes it from there
+    z = __shfl(part, 16 * turn + i);
+  }
+  const float s = mm + logf(z);
+#pragma unroll
+  for (int j = 0; j < kMaxWindow; ++j)
+    shift[j] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(s), j));
+}
+
+// From the log-scores to the selection.  own[c]: log-score of row tid + c THREADS.  `keys` (LDS, len words)
+// may hold other data until the first barrier if nothing is pooled; hist has been cleared.
+template <int THREADS, int PER, bool EXTRAS, typename Lds>
+__device__ __forceinline__ void select_scores(float (&own)[PER], int len, int keep, const SelectExtras& ex, Lds& lds,
+                                              int32_t* list, int32_t* idx) {
+  const int tid = threadIdx.x;
+  if constexpr (EXTRAS) {
+    if (ex.pool_w > 1) {
+      float* raw = reinterpret_cast<float*>(lds.keys);
+#pragma unroll
+      for (int c = 0; c < PER; ++c)
+        if (tid + c * THREADS < len) raw[tid + c * THREADS] = own[c];
+      __syncthreads();
+#pragma unroll
+      for (int c = 0; c < PER; ++c)
+        if (tid + c * THREADS < len)
+          own[c] = pooled_log([&](int t) { return raw[t]; }, tid + c * THREADS, len, (ex.pool_w - 1) / 2);
+      __syncthreads();
+    }
+  }
+  uint32_t kk[PER];
+  uint32_t hi = 0, lo = 0xffffffffu;
+#pragma unroll
+  for (int c = 0; c < PER; ++c) {
+    const int key = tid + c * THREADS;
+    kk[c] = 0;
+    if (key < len) {
+      kk[c] = order_key(own[c]);
+      if constexpr (EXTRAS) {
+        for (int j = 0; j < ex.n_forced; ++j)
+          if (ex.forced[j] == key) kk[c] = 0xffffffffu;
+      }
+      lds.keys[key] = kk[c];
+      hi = max(hi, kk[c]);
+      lo = min(lo, kk[c]);
+    }
+  }
+  block_extremes<THREADS>(hi, lo, lds.wave_max, lds.wave_min);
+  // keys above T are selected, and the first need_eq of those equal to it
+  uint32_t T, need_eq;
+  radix_kth_largest_from<THREADS>([&](int t) { return lds.keys[t]; }, len, (uint32_t)keep,
+                                  32 - __builtin_clz((hi ^ lo) | 1u), hi, lds.hist, T, need_eq);
+  emit_selected<THREADS, PER>(kk, len, T, need_eq, lds.count, list, idx);
+  __syncthreads();
+}
+
+// Leaves the `keep` selected rows in lds.list (0 < keep < len <= kShortLen) and, if idx is not
+// NULL, in idx.  All THREADS threads of the workgroup call it; `logits` may be overwritten
+// afterwards without a barrier.
+template <int D, int THREADS, bool EXTRAS>
+__device__ __forceinline__ void rank_short(const uint16_t* qu, const WindowRows& rows, int n_win,
+                                           const uint16_t* ku, int len, int keep, float sm_scale,
+                                           const SelectExtras& ex, float* logits, RankShortLds& lds,
+                                           int32_t* idx) {
+  constexpr int kWaves = THREADS / 64;
+  constexpr int kPer = (kShortLen + THREADS - 1) / THREADS;  // keys per thread
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int i = lane & 15, g = lane >> 4;
+  const int n_group = (len + 31) / 32;
+
+  // ---- logits of every key against the window rows, and per 32 keys the maximum and sum of
+  // exponentials of every window row
+  {
+    score_bf16x8 qf[D / 32];
+    score_load_window<D>(qu, rows, n_win, qf);
+    score_bf16x8 kf[2][D / 32];
+    if (wave < n_group) score_load_keys<D, 2>(ku, 32 * wave, len, kf);
+    for (int group = wave; group < n_group; group += kWaves) {
+      score_f32x4 c[2];
+      float m, e;
+      score_products<D, 2>(kf, qf, c);
+      if (group + kWaves < n_group) score_load_keys<D, 2>(ku, 32 * (group + kWaves), len, kf);
+      score_statistics<2>(c, 32 * group, len, sm_scale, m, e);
+      score_store_logits<2>(c, 32 * group, len, logits, kLogitStride);
+      if (lane < kMaxWindow) {
+        lds.group_max[group][lane] = m;
+        lds.group_sum[group][lane] = e;
+      }
+    }
+    for (int b = tid; b < 4 * 256; b += THREADS) lds.hist[b] = 0;
+  }
+  __syncthreads();
+
+  // ---- row normalisers, by every wave: lane (g, i) merges virtual waves 4g .. 4g+3 of row i
+  float shift[kMaxWindow];
+  {
+    float vm[4], ve[4];
+    float mm = -INFINITY;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      float m_run = -INFINITY, e_run = 0.f;
+      for (int group = 4 * g + x; group < n_group; group += kVirtualWaves) {
+        const float m = lds.group_max[group][i], e = lds.group_sum[group][i];
+        const float m_new = fmaxf(m_run, m);
+        e_run = e_run * expf(m_run - m_new) + e * expf(m - m_new);
+        m_run = m_new;
+      }
+      vm[x] = m_run;
+      ve[x] = e_run;
+      mm = fmaxf(mm, m_run);
+    }
+    row_shifts(vm, ve, mm, shift);
+  }
+
+  // ---- log-scores, as keys whose order is theirs
+  float own[kPer];
+#pragma unroll
+  for (int c = 0; c < kPer; ++c) {
+    const int key = tid + c * THREADS;
+    if (key < len) {
+      const float* lg = logits + key * kLogitStride;
+      float la[kMaxWindow];
+#pragma unroll
+      for (int j4 = 0; j4 < kMaxWindow; j4 += 4) {
+        const float4 x = *(const float4*)(lg + j4);
+        la[j4] = x.x; la[j4 + 1] = x.y; la[j4 + 2] = x.z; la[j4 + 3] = x.w;
+      }
+      own[c] = log_sum_rows(la, n_win, shift);
+    }
+  }
+  select_scores<THREADS, kPer, EXTRAS>(own, len, keep, ex, lds, lds.list, idx);
+}
+
+// ---- longer caches, 1024 threads, up to 1024 PER rows (PER = 4 or 12): the logits of the first rows stay
+// in registers (a wave's groups of 32 keys, one per round of 512; eight rounds, or six where rows
+// beyond them have to be provided for) until the row normalisers are known, and are then turned
+// through a piece of LDS per wave, two groups at a time, so that a lane has the sixteen logits of one
+// key.  Later rows go through the workspace.  Keeping them saves 64 bytes
+// written and read per key (more than an XCD's L2 holds for 32 units of 3350 keys) and their latency.
+// Bound by the HBM where there is a unit per compute unit, by the exponentials (two per key and
+// window row, through one compute unit's vector pipes) where there are fewer.
+constexpr int kLongInRegisters = 8 * 512;  // rows of PER = 4
+constexpr int kLongTurnBytes = 16 * 64 * kLogitStride * 4;  // dynamic LDS; afterwards the index list is there
+constexpr int kLongMaxPer = 12;
+static_assert(kLongInRegisters == 4 * 1024 && kLongMaxPer * 1024 * 4 <= kLongTurnBytes, "the index list fits");
+
+template <int PER>
+struct RankLongLds {
+  __attribute__((aligned(16))) uint32_t hist[4 * 256];
+  float wave_rowmax[16][kMaxWindow], wave_rowsum[16][kMaxWindow];
+  uint32_t keys[PER * 1024];
+  uint32_t wave_max[16], wave_min[16];
+  uint32_t count[PER * 16];
+};
+
+// Returns the index list (LDS, in place of `turn`).  logits_far: [len][kMaxWindow] of the unit.
+template <int D, int PER, bool EXTRAS>
+__device__ __forceinline__ const int32_t* rank_long(const uint16_t* qu, const WindowRows& rows, int n_win,
+                                                    const uint16_t* ku, int len, int keep, float sm_scale,
+                                                    const SelectExtras& ex, float* turn, float* logits_far,
+                                                    RankLongLds<PER>& lds, int32_t* idx) {
+  constexpr int kThreads = 1024;
+  constexpr bool kFar = PER > 4;
+  constexpr int kLongRounds = kFar ? 6 : 8;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int i = lane & 15, g = lane >> 4;
+  score_f32x4 c[kLongRounds][2];
+  float m_run = -INFINITY, e_run = 0.f;
+  auto join = [&](float m, float e) {
+    const float m_new = fmaxf(m_run, m);
+    e_run = e_run * expf(m_run - m_new) + e * expf(m - m_new);
+    m_run = m_new;
+  };
+  {
+    score_bf16x8 qf[D / 32], kf[2][D / 32];
+    score_load_window<D>(qu, rows, n_win, qf);
+    if (32 * wave < len) score_load_keys<D, 2>(ku, 32 * wave, len, kf);
+#pragma unroll
+    for (int r = 0; r < kLongRounds; ++r) {
+      const int key0 = 512 * r + 32 * wave;
+      if (key0 < len) {
+        score_products<D, 2>(kf, qf, c[r]);
+        __builtin_amdgcn_sched_barrier(0);
+        if ((kFar || r + 1 < kLongRounds) && key0 + 512 < len) score_load_keys<D, 2>(ku, key0 + 512, len, kf);
+        __builtin_amdgcn_sched_barrier(0);
+        float m, e;
+        score_statistics<2>(c[r], key0, len, sm_scale, m, e);
+        join(m, e);
+      }
+    }
+    if constexpr (kFar) {
+      for (int key0 = kLongRounds * 512 + 32 * wave; key0 < len; key0 += 512) {
+        score_f32x4 far[2];
+        score_products<D, 2>(kf, qf, far);
+        __builtin_amdgcn_sched_barrier(0);
+        if (key0 + 512 < len) score_load_keys<D, 2>(ku, key0 + 512, len, kf);
+        __builtin_amdgcn_sched_barrier(0);
+        float m, e;
+        score_statistics<2>(far, key0, len, sm_scale, m, e);
+        score_store_logits<2>(far, key0, len, logits_far, kMaxWindow);
+        join(m, e);
+      }
+    }
+  }
+  if (lane < kMaxWindow) {
+    lds.wave_rowmax[wave][lane] = m_run;
+    lds.wave_rowsum[wave][lane] = e_run;
+  }
+  lds.hist[tid] = 0;
+  __syncthreads();  // also makes the far logits visible to the whole workgroup
+  float shift[kMaxWindow];
+  {
+    float vm[4], ve[4], mm = -INFINITY;
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+      vm[x] = lds.wave_rowmax[4 * g + x][i];
+      ve[x] = lds.wave_rowsum[4 * g + x][i];
+      mm = fmaxf(mm, vm[x]);
+    }
+    row_shifts(vm, ve, mm, shift);
+  }
+  auto log_score = [&](const float* lg) -> float {
+    float la[kMaxWindow];
+#pragma unroll
+    for (int j4 = 0; j4 < kMaxWindow; j4 += 4) {
+      const float4 x = *(const float4*)(lg + j4);
+      la[j4] = x.x; la[j4 + 1] = x.y; la[j4 + 2] = x.z; la[j4 + 3] = x.w;
+    }
+    return log_sum_rows(la, n_win, shift);
+  };
+  float* const mine = turn + wave * (64 * kLogitStride);
+  float* const raw = reinterpret_cast<float*>(lds.keys);
+#pragma unroll
+  for (int r = 0; r < kLongRounds; r += 2) {
+    if (512 * r + 32 * wave < len) {
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) mine[(32 * x + 16 * t + 4 * g + v) * kLogitStride + i] = c[r + x][t][v];
+      const int key = 512 * (r + (lane >> 5)) + 32 * wave + (lane & 31);
+      const float ls = log_score(mine + lane * kLogitStride);
+      if (key < len) raw[key] = ls;
+    }
+  }
+  if constexpr (kFar)
+    for (int key = kLongRounds * 512 + tid; key < len; key += kThreads)
+      raw[key] = log_score(logits_far + (long long)key * kMaxWindow);
+  __syncthreads();
+  float own[PER];
+#pragma unroll
+  for (int x = 0; x < PER; ++x)
+    if (tid + x * kThreads < len) own[x] = raw[tid + x * kThreads];
+  __syncthreads();
+  int32_t* const list = reinterpret_cast<int32_t*>(turn);
+  select_scores<kThreads, PER, EXTRAS>(own, len, keep, ex, lds, list, idx);
+  return list;
+}
+
+}  // namespace scalekv

@@ -151,11 +151,10 @@ __global__ __launch_bounds__(256) void score_finalize_kernel(int n_win, int cach
                                                              ScoreWorkspace ws,
                                                              float* __restrict__ log_scores,
                                                              long long score_unit_stride) {
-  __shared__ float row_shift[kMaxWindow];  // max_j + log Z_j
+  __shared__ float row_shift[kMaxWindow], stage[kStatChunks * 2 * kMaxWindow];
   const int unit = SCALEKV_WG_Y;
   const int tid = threadIdx.x;
-  if (tid < kMaxWindow) row_shift[tid] = tid < n_win ? score_row_shift(ws, unit, tid) : 0.f;
-  __syncthreads();
+  score_row_shifts(ws, unit, n_win, stage, row_shift);
   const int key = SCALEKV_WG_X * 256 + tid;
   if (key >= cache_len) return;
   log_scores[unit * score_unit_stride + key] = score_log_sum(ws, unit, key, n_win, row_shift);

@@ -13,7 +13,7 @@
 // largest key, and `keep` counts them.
 #include "common.h"
 #include "radix_select.h"
-#include "rank_short.h"
+#include "rank.h"
 #include "score_mfma.h"
 
 namespace scalekv {
@@ -22,9 +22,9 @@ namespace {
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
 constexpr int kLdsKeys = 12288;  // units up to this many scores keep their keys in LDS
-static_assert(kLdsKeys == 12288, "score_select_fits() in common.h states the same limit");
+static_assert(kLdsKeys == 12288 && kLdsKeys == 1024 * kLongMaxPer, "score_select_fits() in common.h states the same limit");
 
-// What the kernel needs to form the logits itself (SCORE_D != 0): bf16 storage only.
+// What a kernel that ranks from the keys needs: bf16 storage only.
 struct ScoreInputs {
   const uint16_t* q;        // [U, *, D]; window queries are rows `rows` of every unit
   long long q_unit_stride;
@@ -88,102 +88,22 @@ __device__ __forceinline__ void prune_unit(const ScoreInputs& si, int unit, int 
   }
 }
 
-// SCORE_D = 64 / 128: the whole ranking step of Sec. 3.3 in one kernel.  The workgroup first
-// streams the unit's cached keys itself (16 waves x 32 keys per round, logits to the workspace,
-// running row maximum and sum of exponentials per wave), so that neither a second launch nor the
-// per-chunk statistics are needed; then it ranks as in the FUSED form.
-// MIN_WAVES = 8 holds the kernel to 64 registers so that two workgroups share a compute unit (one
-// streams keys while the other ranks): for launches with more units than compute units.  With
-// one workgroup per compute unit the unconstrained form (MIN_WAVES = 4) is a little faster.
-template <bool IN_LDS, bool FUSED, int SCORE_D, int MIN_WAVES = 4>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MIN_WAVES, 8))) void select_kernel(const float* __restrict__ scores,
-                                                          long long score_unit_stride,
-                                                          int cache_len, int keep,
-                                                          int32_t* __restrict__ idx,
-                                                          ScoreWorkspace ws, int n_win,
-                                                          SelectExtras ex, ScoreInputs si) {
-  static_assert(IN_LDS || !FUSED, "the fused form keeps its keys in LDS");
-  static_assert(FUSED || SCORE_D == 0, "forming the logits here implies the fused form");
-  constexpr int kPerThread = IN_LDS ? kLdsKeys / kThreads : 1;
-  __shared__ uint32_t keys[IN_LDS ? kLdsKeys : 1];
-  __shared__ float row_shift[kMaxWindow];
+// Units too long for their keys to stay in LDS: scores given, keys formed anew in each pass.
+__global__ __launch_bounds__(kThreads) void select_far_kernel(const float* __restrict__ scores, long long score_unit_stride,
+                                                              int cache_len, int keep, int32_t* __restrict__ idx,
+                                                              SelectExtras ex) {
   __shared__ __attribute__((aligned(16))) uint32_t hist[kRadixHistWords];
   __shared__ uint32_t wave_gt[kWaves], wave_eq[kWaves];
-  __shared__ float red_max[SCORE_D ? kWaves : 1][kMaxWindow], red_sum[SCORE_D ? kWaves : 1][kMaxWindow];
-
   const int unit = SCALEKV_WG_X;
   const int tid = threadIdx.x;
   const float* s = scores + unit * score_unit_stride;
   const int pool_r = (ex.pool_w - 1) / 2;
   auto key_at = [&](int i) -> uint32_t {
-    if constexpr (IN_LDS) {
-      return keys[i];
-    } else {
-      for (int j = 0; j < ex.n_forced; ++j)
-        if (ex.forced[j] == i) return 0xffffffffu;
-      if (pool_r > 0) return order_key(pooled_log([&](int t) { return s[t]; }, i, cache_len, pool_r));
-      return order_key(s[i]);
-    }
+    for (int j = 0; j < ex.n_forced; ++j)
+      if (ex.forced[j] == i) return 0xffffffffu;
+    if (pool_r > 0) return order_key(pooled_log([&](int t) { return s[t]; }, i, cache_len, pool_r));
+    return order_key(s[i]);
   };
-  if constexpr (IN_LDS) {
-    // log-scores into LDS (formed from the logits workspace when FUSED), pooled in place if
-    // asked for, then turned into keys
-    if constexpr (SCORE_D != 0) {
-      // Eq. 5, logits and row normalisers: every wave walks its share of the keys, 32 per round
-      constexpr int NT = 2;
-      const int lane = tid & 63, wave = tid >> 6;
-      const int seq = unit / si.n_head, head = unit - seq * si.n_head;
-      const uint16_t* ku = si.k + seq * si.k_seq_stride + head * si.k_head_stride;
-      float* logits_unit = ws.logits + (long long)unit * ws.len_pad * kMaxWindow;
-      score_bf16x8 qf[SCORE_D / 32];
-      score_load_window<SCORE_D>(si.q + unit * si.q_unit_stride, si.rows, n_win, qf);
-      float m_run = -INFINITY, e_run = 0.f;
-      for (int key0 = wave * (16 * NT); key0 < cache_len; key0 += kWaves * 16 * NT) {
-        float m, e;
-        score_wave_logits<SCORE_D, NT>(ku, qf, key0, cache_len, si.sm_scale, logits_unit, kMaxWindow, m, e);
-        const float m_new = fmaxf(m_run, m);   // m is finite: the round has at least one valid key
-        e_run = e_run * expf(m_run - m_new) + e * expf(m - m_new);
-        m_run = m_new;
-      }
-      if (lane < kMaxWindow) { red_max[wave][lane] = m_run; red_sum[wave][lane] = e_run; }
-      __syncthreads();   // also makes the logits visible to the whole workgroup
-      if (tid < kMaxWindow) {
-        float mm = -INFINITY;
-        for (int w = 0; w < kWaves; ++w) mm = fmaxf(mm, red_max[w][tid]);
-        float z = 0.f;
-        for (int w = 0; w < kWaves; ++w)
-          if (red_max[w][tid] > -INFINITY) z += red_sum[w][tid] * expf(red_max[w][tid] - mm);
-        row_shift[tid] = tid < n_win ? mm + logf(z) : 0.f;
-      }
-      __syncthreads();
-    } else if constexpr (FUSED) {
-      if (tid < kMaxWindow) row_shift[tid] = tid < n_win ? score_row_shift(ws, unit, tid) : 0.f;
-      __syncthreads();
-    }
-    float* raw = reinterpret_cast<float*>(keys);
-    for (int i = tid; i < cache_len; i += kThreads) {
-      if constexpr (FUSED) raw[i] = score_log_sum(ws, unit, i, n_win, row_shift);
-      else raw[i] = s[i];
-    }
-    __syncthreads();
-    float mine[kPerThread];
-#pragma unroll
-    for (int c = 0; c < kPerThread; ++c) {
-      const int i = tid + c * kThreads;
-      if (i < cache_len)
-        mine[c] = pool_r > 0 ? pooled_log([&](int t) { return raw[t]; }, i, cache_len, pool_r) : raw[i];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < kPerThread; ++c) {
-      const int i = tid + c * kThreads;
-      if (i < cache_len) keys[i] = order_key(mine[c]);
-    }
-    if (ex.n_forced > 0) {
-      __syncthreads();
-      if (tid < ex.n_forced) keys[ex.forced[tid]] = 0xffffffffu;
-    }
-  }
 
   // ---- radix select: T = key of the keep-th largest ----
   uint32_t T, need_eq;  // need_eq: how many keys equal to T are taken (>= 1)
@@ -218,17 +138,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(MIN_WA
       ++eq_seen;
     }
   }
-
-  // ---- pruning: the kept rows (and, if asked, the map's rows behind them) into the destination
-  if constexpr (SCORE_D != 0) {
-    if (si.k_dst != nullptr) {
-      __syncthreads();  // the unit's index list is complete (written by this workgroup)
-      prune_unit<SCORE_D, kThreads>(si, unit, keep, out);
-    }
-  }
 }
 
-// The same for short caches (rank_short.h): nothing but the index list leaves the compute unit
+// The whole ranking step of Sec. 3.3 and the pruning in one kernel, a workgroup per unit, for short caches
+// (rank.h): nothing but the index list leaves the compute unit
 // between the keys and the pruned rows.  EXTRAS: forced positions and pooling may be asked for.
 // 256 units, 546 cached rows, 246 kept: 30.6 us with select_kernel, 26.3 here; 16-256 units, 70-400 rows: 13-17 -> 8-13 us.
 template <int D, int THREADS, bool EXTRAS>
@@ -244,6 +157,34 @@ __global__ __launch_bounds__(THREADS) void rank_short_kernel(int cache_len, int 
   if (si.k_dst != nullptr) prune_unit<D, THREADS>(si, unit, keep, lds.list);
 }
 
+// The same for longer ones.  256 units, 3350 cached rows, 1622 kept: 138 us, 148 with every logit through
+// the workspace; 192 units, 2535 rows, ranking alone: 37 us against 46; 512 units, 2516 rows, 328 kept:
+// a step of 144 queries 189 -> 174 us.
+template <int D, int PER, bool EXTRAS>
+__global__ __launch_bounds__(1024) void rank_long_kernel(int cache_len, int keep, int32_t* __restrict__ idx, int n_win,
+                                                         SelectExtras ex, ScoreInputs si, ScoreWorkspace ws) {
+  extern __shared__ __attribute__((aligned(16))) float long_turn[];
+  __shared__ RankLongLds<PER> lds;
+  const int unit = SCALEKV_WG_X;
+  const int seq = unit / si.n_head, head = unit - seq * si.n_head;
+  const int32_t* list = rank_long<D, PER, EXTRAS>(
+      si.q + unit * si.q_unit_stride, si.rows, n_win, si.k + seq * si.k_seq_stride + head * si.k_head_stride, cache_len,
+      keep, si.sm_scale, ex, long_turn, ws.logits + (long long)unit * ws.len_pad * kMaxWindow, lds,
+      idx + (long long)unit * keep);
+  if (si.k_dst != nullptr) prune_unit<D, 1024>(si, unit, keep, list);
+}
+
+template <int D, int PER, bool EXTRAS>
+hipError_t launch_long(int n_unit, int cache_len, int keep, int32_t* idx, int n_win, const SelectExtras& ex,
+                       const ScoreInputs& si, ScoreWorkspace ws, hipStream_t stream) {
+  static std::atomic<uint64_t> configured{0};  // LDS above 64 KB per workgroup has to be asked for
+  const hipError_t e = allow_dynamic_lds((const void*)rank_long_kernel<D, PER, EXTRAS>, kLongTurnBytes, configured);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((rank_long_kernel<D, PER, EXTRAS>), dim3(n_unit), dim3(1024), kLongTurnBytes, stream, cache_len,
+                     keep, idx, n_win, ex, si, ws);
+  return hipGetLastError();
+}
+
 template <int D, int THREADS, bool EXTRAS>
 hipError_t launch_short(int n_unit, int cache_len, int keep, int32_t* idx, int n_win, const SelectExtras& ex,
                         const ScoreInputs& si, hipStream_t stream) {
@@ -253,6 +194,54 @@ hipError_t launch_short(int n_unit, int cache_len, int keep, int32_t* idx, int n
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((rank_short_kernel<D, THREADS, EXTRAS>), dim3(n_unit), dim3(THREADS),
                      rank_short_logit_bytes(cache_len), stream, cache_len, keep, idx, n_win, ex, si);
+  return hipGetLastError();
+}
+
+// Selection alone, for units whose keys fit in LDS (PER rows per thread): from scores, or
+// (FROM_LOGITS) from the logits and chunk statistics of the workspace, log-scores formed here.
+template <int PER>
+struct SelectLds {
+  __attribute__((aligned(16))) uint32_t hist[4 * 256];
+  uint32_t keys[PER * kThreads];
+  uint32_t wave_max[kWaves], wave_min[kWaves];
+  uint32_t count[PER * kWaves];
+};
+template <int PER, bool FROM_LOGITS>
+__global__ __launch_bounds__(kThreads) void select_lds_kernel(const float* __restrict__ scores, long long score_unit_stride,
+                                                              int cache_len, int keep, int32_t* __restrict__ idx,
+                                                              ScoreWorkspace ws, int n_win, SelectExtras ex) {
+  __shared__ SelectLds<PER> lds;
+  __shared__ float row_shift[kMaxWindow], stage[FROM_LOGITS ? kStatChunks * 2 * kMaxWindow : 1];
+  const int unit = SCALEKV_WG_X, tid = threadIdx.x;
+  lds.hist[tid] = 0;
+  if constexpr (FROM_LOGITS) score_row_shifts(ws, unit, n_win, stage, row_shift);
+  float own[PER];
+#pragma unroll
+  for (int c = 0; c < PER; ++c) {
+    const int key = tid + c * kThreads;
+    if (key < cache_len) {
+      if constexpr (FROM_LOGITS) own[c] = score_log_sum(ws, unit, key, n_win, row_shift);
+      else own[c] = scores[unit * score_unit_stride + key];
+    }
+  }
+  select_scores<kThreads, PER, true>(own, cache_len, keep, ex, lds, nullptr, idx + (long long)unit * keep);
+}
+
+template <bool FROM_LOGITS>
+hipError_t launch_select_lds(int n_unit, const float* scores, long long score_unit_stride, int cache_len, int keep,
+                             int32_t* idx, ScoreWorkspace ws, int n_win, const SelectExtras& ex, hipStream_t stream) {
+#define SCALEKV_SELECT(PER)                                                                                      \
+  hipLaunchKernelGGL((select_lds_kernel<PER, FROM_LOGITS>), dim3(n_unit), dim3(kThreads), 0, stream, scores,     \
+                     score_unit_stride, cache_len, keep, idx, ws, n_win, ex)
+  if (cache_len <= kThreads) SCALEKV_SELECT(1);
+  else if (cache_len <= 2 * kThreads) SCALEKV_SELECT(2);
+  else if constexpr (!FROM_LOGITS) {
+    if (cache_len <= 4 * kThreads) SCALEKV_SELECT(4);
+    else SCALEKV_SELECT(kLdsKeys / kThreads);
+  } else {
+    return hipErrorNotSupported;
+  }
+#undef SCALEKV_SELECT
   return hipGetLastError();
 }
 
@@ -297,13 +286,10 @@ hipError_t launch_select(int n_unit, const float* scores, long long score_unit_s
     return hipGetLastError();
   }
   const ScoreWorkspace none{nullptr, nullptr, 0, 0};
-  const ScoreInputs no_score{};
   if (cache_len <= kLdsKeys)
-    hipLaunchKernelGGL((select_kernel<true, false, 0>), dim3(n_unit), dim3(kThreads), 0, stream,
-                       scores, score_unit_stride, cache_len, keep, idx, none, 0, ex, no_score);
-  else
-    hipLaunchKernelGGL((select_kernel<false, false, 0>), dim3(n_unit), dim3(kThreads), 0, stream,
-                       scores, score_unit_stride, cache_len, keep, idx, none, 0, ex, no_score);
+    return launch_select_lds<false>(n_unit, scores, score_unit_stride, cache_len, keep, idx, none, 0, ex, stream);
+  hipLaunchKernelGGL(select_far_kernel, dim3(n_unit), dim3(kThreads), 0, stream, scores, score_unit_stride,
+                     cache_len, keep, idx, ex);
   return hipGetLastError();
 }
 
@@ -313,11 +299,8 @@ hipError_t launch_select_from_logits(int n_unit, int n_win, ScoreWorkspace ws, i
   SelectExtras ex{};
   ex.pool_w = 1;
   if (extras) ex = *extras;
-  if (cache_len > kLdsKeys) return hipErrorNotSupported;
   if (n_unit <= 0 || keep <= 0 || cache_len <= 0) return hipSuccess;
-  hipLaunchKernelGGL((select_kernel<true, true, 0>), dim3(n_unit), dim3(kThreads), 0, stream, nullptr,
-                     0, cache_len, keep, idx, ws, n_win, ex, ScoreInputs{});
-  return hipGetLastError();
+  return launch_select_lds<true>(n_unit, nullptr, 0, cache_len, keep, idx, ws, n_win, ex, stream);
 }
 
 hipError_t launch_score_select(int dtype, int n_seq, int n_head, int d, const void* q, long long q_unit_stride,
@@ -344,8 +327,8 @@ hipError_t launch_score_select(int dtype, int n_seq, int n_head, int d, const vo
     si.n_app = prune->k_cur ? prune->n_app : 0;
   }
   constexpr int kComputeUnits = 256;  // MI355X
+  const bool plain = ex.n_forced == 0 && ex.pool_w == 1;
   if (cache_len <= kShortLen) {
-    const bool plain = ex.n_forced == 0 && ex.pool_w == 1;
 #define SCALEKV_SHORT(T)                                                                             \
   (d == 128 ? plain ? launch_short<128, T, false>(n_unit, cache_len, keep, idx, n_win, ex, si, stream) \
                     : launch_short<128, T, true>(n_unit, cache_len, keep, idx, n_win, ex, si, stream)  \
@@ -354,16 +337,12 @@ hipError_t launch_score_select(int dtype, int n_seq, int n_head, int d, const vo
     return n_unit > kComputeUnits ? SCALEKV_SHORT(512) : SCALEKV_SHORT(1024);
 #undef SCALEKV_SHORT
   }
-  if (d == 128 && n_unit > kComputeUnits)
-    hipLaunchKernelGGL((select_kernel<true, true, 128, 8>), dim3(n_unit), dim3(kThreads), 0, stream, nullptr,
-                       0, cache_len, keep, idx, ws, n_win, ex, si);
-  else if (d == 128)
-    hipLaunchKernelGGL((select_kernel<true, true, 128>), dim3(n_unit), dim3(kThreads), 0, stream, nullptr,
-                       0, cache_len, keep, idx, ws, n_win, ex, si);
-  else
-    hipLaunchKernelGGL((select_kernel<true, true, 64>), dim3(n_unit), dim3(kThreads), 0, stream, nullptr,
-                       0, cache_len, keep, idx, ws, n_win, ex, si);
-  return hipGetLastError();
+#define SCALEKV_LONG(D, PER)                                                                           \
+  (plain ? launch_long<D, PER, false>(n_unit, cache_len, keep, idx, n_win, ex, si, ws, stream)       \
+         : launch_long<D, PER, true>(n_unit, cache_len, keep, idx, n_win, ex, si, ws, stream))
+  if (cache_len <= kLongInRegisters) return d == 128 ? SCALEKV_LONG(128, 4) : SCALEKV_LONG(64, 4);
+  return d == 128 ? SCALEKV_LONG(128, kLongMaxPer) : SCALEKV_LONG(64, kLongMaxPer);
+#undef SCALEKV_LONG
 }
 
 }  // namespace scalekv

@@ -1,6 +1,6 @@
 // bf16 attention for small work: where the pipelined kernel (attend_pipe.hip, 128 query rows per
 // workgroup) would leave most of the chip idle (small_tile_rows() in common.h).  The same launch
-// prunes and appends the cache, and where the cache is short enough (rank_short.h) it also ranks it:
+// prunes and appends the cache, and where the cache is short enough (rank.h) it also ranks it:
 // a whole step in one kernel.
 //
 // A step of this size is bound by latency: the launch, a chain of dependent loads, barriers, and how
@@ -25,7 +25,7 @@
 //   the A operand then is channel i of the same eight keys, which the transposing LDS load
 //   (ds_read_b64_tr_b16) delivers from V rows staged in LDS, 32 of them per wave.
 #include "common.h"
-#include "rank_short.h"
+#include "rank.h"
 
 namespace scalekv {
 namespace {

@@ -146,3 +146,17 @@ def test_asi_edges(d, S, H, n_samp, hist, cur, top_k, kind):
     ref = np.stack(oracle.asi_terms(units(q)[pick], units(k)[pick], hist, top_k), -1)
     got = terms.cpu().numpy().reshape(S * H, n_samp, 2)[pick].astype(np.float64)
     assert np.abs(got - ref).max() < 2e-5
+
+
+# Ranking in front of the pipelined attention (150 queries of 300 units, or 2049 queries): caches ranked in
+# LDS, in registers (rounds of 512 keys, two at a time) and beyond, with and without a unit per compute
+# unit; then the route for few units with long caches
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("S,H,L,budget,n_cur,dup", [
+    (1, 10, 1537, 3, 2049, 1), (1, 9, 2047, 2046, 2049, 1), (1, 9, 2049, 700, 2049, 6), (1, 9, 3585, 900, 2049, 1),
+    (1, 9, 4096, 4095, 2049, 1), (1, 9, 4095, 1, 2049, 4), (4, 40, 1600, 200, 300, 1), (4, 75, 700, 90, 150, 1),
+    (4, 75, 1700, 90, 150, 1), (1, 2, 4097, 800, 20, 1), (1, 2, 6400, 1000, 20, 3), (4, 16, 4100, 300, 900, 1),
+])
+def test_rank_edges(d, S, H, L, budget, n_cur, dup):
+    print(f"rank d={d} S={S} H={H} L={L} budget={budget} n_cur={n_cur} dup={dup}", flush=True)
+    _step_against_oracle(S, H, d, L, budget, n_cur, 16, sorted({0, S * H - 1}), 2, dup)
