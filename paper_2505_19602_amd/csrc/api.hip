@@ -411,7 +411,12 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
   const int32_t* idx = nullptr;  // identity unless a ranking is needed
   const bool pipe = attend_uses_pipe(shape->dtype, U, n_cur, keep + n_cur);
   const bool small = small_tile_rows(shape->dtype, U, n_cur, keep + n_cur) > 0;
-  const bool one_launch = small && ranks && cache_len <= kShortLen;  // the attention kernel ranks as well
+  // The attention kernel ranks as well.  Each of its workgroups reads the window's queries, while others may
+  // already be writing results: with out in the place of q the ranking is a launch of its own.
+  const uintptr_t q_lo = reinterpret_cast<uintptr_t>(q), out_lo = reinterpret_cast<uintptr_t>(out);
+  const uintptr_t q_bytes = (uintptr_t)((long long)U * n_cur * shape->head_dim * elem_bytes(shape));
+  const bool q_written = q_lo < out_lo + q_bytes && out_lo < q_lo + q_bytes;
+  const bool one_launch = small && ranks && cache_len <= kShortLen && !q_written;
   bool pruned = false;           // the ranking kernel has already written the destination caches
   WindowRows rows;
   for (int j = 0; j < kMaxWindow; ++j) rows.row[j] = ranks && j < n_win ? win_idx[j] : 0;

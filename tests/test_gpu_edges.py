@@ -160,3 +160,22 @@ def test_asi_edges(d, S, H, n_samp, hist, cur, top_k, kind):
 def test_rank_edges(d, S, H, L, budget, n_cur, dup):
     print(f"rank d={d} S={S} H={H} L={L} budget={budget} n_cur={n_cur} dup={dup}", flush=True)
     _step_against_oracle(S, H, d, L, budget, n_cur, 16, sorted({0, S * H - 1}), 2, dup)
+
+
+# out in the place of q: the workgroups of a unit must not read the window after a neighbour has written
+@pytest.mark.parametrize("d,L,budget,n_cur", [(64, 700, 90, 200), (128, 1536, 300, 128), (128, 90, 20, 16)])
+def test_small_step_writes_over_its_queries(d, L, budget, n_cur):
+    S, H, dtype = 1, 12, torch.bfloat16
+    print(f"out over q d={d} L={L} budget={budget} n_cur={n_cur}", flush=True)
+    shape = skv.Shape(S, H, d, dtype)
+    q, kc, vc, ks, vs = (_rand(60 + i, (S, H, n, d), dtype, 1.3).to(DEV) for i, n in enumerate((n_cur,) * 3 + (L,) * 2))
+    ws = torch.empty(skv.workspace_bytes(shape, L, n_cur), dtype=torch.uint8, device=DEV)
+    results = []
+    for over in (False, True):
+        out = q if over else torch.empty_like(q)
+        kd = torch.empty(S, H, budget + n_cur, d, dtype=dtype, device=DEV); vd = torch.empty_like(kd)
+        skv.step(shape, q, kc, vc, list(range(n_cur - 16, n_cur)), ks, vs, L, budget, kd, vd, out, None, ws)
+        torch.cuda.synchronize()
+        results.append((out, kd, vd))
+    for plain, over in zip(*results):
+        assert torch.equal(plain, over)
