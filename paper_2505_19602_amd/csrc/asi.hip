@@ -237,6 +237,10 @@ __global__ __launch_bounds__(kThreads) void asi_stream_kernel(AsiStream a) {
           eh[b] = fmaf(eh[b], alpha, h);
           ec[b] = fmaf(ec[b], alpha, u);
           m[b] = top;
+        } else {  // nothing but -inf and NaN (the maximum passes over NaN; the sums do not)
+#pragma unroll
+          for (int x = 0; x < 8; ++x)
+            if (c[b][x / 4][x % 4] != c[b][x / 4][x % 4]) eh[b] = c[b][x / 4][x % 4];
         }
       }
       if (lists_on && key0 < a.hist_len) {

@@ -85,7 +85,7 @@ __global__ __launch_bounds__(64 * kMaxSplit) void attend_f32_kernel(
   float m_run[QB], l_run[QB];
 #pragma unroll
   for (int b = 0; b < QB; ++b) {
-    m_run[b] = -INFINITY;
+    m_run[b] = kNoMaximum;
     l_run[b] = 0.f;
 #pragma unroll
     for (int t = 0; t < NO; ++t)

@@ -222,6 +222,9 @@ __device__ __forceinline__ float xor32_sum(float x) { float a, b; swap32(x, a, b
 // grow before the running offset is moved and the accumulators are rescaled.
 __device__ __forceinline__ int pi32(int i) { return (i & ~12) | ((i & 4) << 1) | ((i & 8) >> 1); }
 constexpr float kRescaleThreshold = 8.f;
+// Running maximum of a wave that has met no key yet, where the waves of a workgroup split the keys: finite, so
+// that a wave whose keys all have logits of -inf adds weights of zero and not NaN.
+constexpr float kNoMaximum = -__FLT_MAX__;
 
 __device__ __forceinline__ float bf16_bits_to_float(uint32_t bits16) {
   return __uint_as_float(bits16 << 16);

@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kThreads) void step_small_kernel(SmallArgs a) {
   float m_run[QB], l_run[QB];
 #pragma unroll
   for (int b = 0; b < QB; ++b) {
-    m_run[b] = -INFINITY;
+    m_run[b] = kNoMaximum;
     l_run[b] = 0.f;
 #pragma unroll
     for (int c = 0; c < NCB; ++c) o[b][c] = f32x4{0.f, 0.f, 0.f, 0.f};

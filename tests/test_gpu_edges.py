@@ -179,3 +179,36 @@ def test_small_step_writes_over_its_queries(d, L, budget, n_cur):
         results.append((out, kd, vd))
     for plain, over in zip(*results):
         assert torch.equal(plain, over)
+
+
+# keys whose logits are all -inf have weight zero, also where one wave meets nothing else
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("d,n_q", [(64, 20), (128, 33)])
+def test_attend_over_keys_of_weight_zero(dtype, d, n_q):
+    S, H, kv = 1, 2, 200
+    print(f"weight zero d={d} n_q={n_q} {dtype}", flush=True)
+    shape = skv.Shape(S, H, d, dtype)
+    q, k, v = (_rand(70 + i, (S, H, n, d), dtype) for i, n in enumerate((n_q, kv, kv)))
+    q[..., 0] = 1.0
+    keep = torch.ones(kv, dtype=torch.bool)
+    keep[16:32] = False; keep[64:96] = False
+    k[:, :, ~keep, 0] = float("-inf")
+    out = torch.empty(S, H, n_q, d, dtype=dtype, device=DEV)
+    skv.attend(shape, q.to(DEV), k.to(DEV), v.to(DEV), kv, out)
+    torch.cuda.synchronize()
+    ref = oracle.attend(units(q), units(k)[:, keep], units(v)[:, keep])
+    check_output(units(out), ref, dtype, "attend")
+
+
+# a key of NaN makes the selectivity NaN, also where a lane holds no other key
+@pytest.mark.parametrize("d", [64, 128])
+def test_asi_of_a_key_of_nan(d):
+    S, H, n_samp, hist, cur = 1, 2, 16, 512, 1
+    shape = skv.Shape(S, H, d, torch.bfloat16)
+    q, k = _rand(80, (S, H, n_samp, d), torch.bfloat16), _rand(81, (S, H, hist + cur, d), torch.bfloat16)
+    k[:, :, -1] = float("nan")
+    terms, mean = torch.zeros(S, H, n_samp, 2, device=DEV), torch.zeros(3, device=DEV)
+    ws = torch.empty(skv.workspace_bytes(shape, hist + cur, n_samp), dtype=torch.uint8, device=DEV)
+    skv.asi(shape, q.to(DEV), k.to(DEV), hist, cur, 64, terms, mean, ws)
+    torch.cuda.synchronize()
+    assert torch.isnan(terms).all() and torch.isnan(mean).all()
