@@ -119,6 +119,13 @@ bool dense_overlaps(const scalekv_shape* s, const void* p, long long rows, const
   return pl < kh && kl < ph;
 }
 
+// do two dense tensors [S, H, rows, d] overlap?
+bool dense_overlap(const scalekv_shape* s, const void* a, const void* b, long long rows) {
+  const uintptr_t al = reinterpret_cast<uintptr_t>(a), bl = reinterpret_cast<uintptr_t>(b);
+  const uintptr_t bytes = (uintptr_t)((long long)s->n_seq * s->n_head * rows * s->head_dim * elem_bytes(s));
+  return al < bl + bytes && bl < al + bytes;
+}
+
 KvView view(const scalekv_kv* kv) { return KvView{kv->ptr, kv->seq_stride, kv->head_stride}; }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -409,14 +416,16 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
   };
   const int U = shape->n_seq * shape->n_head;
   const int32_t* idx = nullptr;  // identity unless a ranking is needed
-  const bool pipe = attend_uses_pipe(shape->dtype, U, n_cur, keep + n_cur);
-  const bool small = small_tile_rows(shape->dtype, U, n_cur, keep + n_cur) > 0;
-  // The attention kernel ranks as well.  Each of its workgroups reads the window's queries, while others may
-  // already be writing results: with out in the place of q the ranking is a launch of its own.
-  const uintptr_t q_lo = reinterpret_cast<uintptr_t>(q), out_lo = reinterpret_cast<uintptr_t>(out);
-  const uintptr_t q_bytes = (uintptr_t)((long long)U * n_cur * shape->head_dim * elem_bytes(shape));
-  const bool q_written = q_lo < out_lo + q_bytes && out_lo < q_lo + q_bytes;
-  const bool one_launch = small && ranks && cache_len <= kShortLen && !q_written;
+  // The kernels that append while they attend read the map's K/V, and the one for small work the kept rows
+  // of the source, while other workgroups already store results: with out on top of any of them the new
+  // cache is written by a launch of its own and attended over.
+  const bool map_written = dense_overlap(shape, out, k_cur, n_cur) || dense_overlap(shape, out, v_cur, n_cur);
+  const bool src_written = keep > 0 && (dense_overlaps(shape, out, n_cur, k_src) || dense_overlaps(shape, out, n_cur, v_src));
+  const bool pipe = !map_written && attend_uses_pipe(shape->dtype, U, n_cur, keep + n_cur);
+  const bool small = !map_written && !src_written && small_tile_rows(shape->dtype, U, n_cur, keep + n_cur) > 0;
+  // The small kernel ranks as well.  Each of its workgroups reads the window's queries: with out in the place
+  // of q the ranking is a launch of its own.
+  const bool one_launch = small && ranks && cache_len <= kShortLen && !dense_overlap(shape, q, out, n_cur);
   bool pruned = false;           // the ranking kernel has already written the destination caches
   WindowRows rows;
   for (int j = 0; j < kMaxWindow; ++j) rows.row[j] = ranks && j < n_win ? win_idx[j] : 0;
@@ -655,9 +664,10 @@ scalekv_status scalekv_step_append_first(const scalekv_shape* shape, const void*
   const int d = shape->head_dim;
   SCALEKV_HIP(mark(0), "event record");
   // 1. the map's K/V join the cache: rows [cache_len, cache_len + n_cur) of every unit (the
-  //    pipelined attention kernel does this itself, overlapped with its own work)
-  const bool fused_append = attend_uses_pipe(shape->dtype, U, n_cur, len);
-  const bool small = small_tile_rows(shape->dtype, U, n_cur, len) > 0;
+  //    bf16 attention kernels do this themselves, unless out lies on top of the map's K/V)
+  const bool map_written = dense_overlap(shape, out, k_cur, n_cur) || dense_overlap(shape, out, v_cur, n_cur);
+  const bool fused_append = !map_written && attend_uses_pipe(shape->dtype, U, n_cur, len);
+  const bool small = !map_written && small_tile_rows(shape->dtype, U, n_cur, len) > 0;
   if (!fused_append && !small) {
     const long long tail = (long long)cache_len * d * elem_bytes(shape);
     KvView kt{static_cast<const char*>(k_cache->ptr) + tail, k_cache->seq_stride,

@@ -181,6 +181,36 @@ def test_small_step_writes_over_its_queries(d, L, budget, n_cur):
         assert torch.equal(plain, over)
 
 
+# out on top of the map's keys or values, or of the source cache: all of them are read before it is stored
+@pytest.mark.parametrize("d,H,L,budget,n_cur", [(64, 12, 700, 90, 200), (128, 12, 90, 20, 16), (128, 12, 40, 40, 100),
+                                                (128, 6, 1600, 200, 120), (64, 40, 300, 60, 1100)])
+@pytest.mark.parametrize("over", ["k_cur", "v_cur", "k_src"])
+def test_step_writes_over_its_inputs(over, d, H, L, budget, n_cur):
+    dtype = torch.bfloat16
+    print(f"out over {over} d={d} H={H} L={L} budget={budget} n_cur={n_cur}", flush=True)
+    shape = skv.Shape(1, H, d, dtype)
+    q, kc, vc = (_rand(80 + i, (1, H, n_cur, d), dtype, 1.3).to(DEV) for i in range(3))
+    ks, vs = (_rand(83 + i, (1, H, max(L, n_cur), d), dtype, 1.3).to(DEV) for i in range(2))
+    ws = torch.empty(skv.workspace_bytes(shape, L, n_cur), dtype=torch.uint8, device=DEV)
+    flat = lambda t: t.reshape(H, t.shape[2], d)[:1].cpu()
+    win = list(range(n_cur - 16, n_cur))
+    in_kc, in_vc, in_ks, in_vs = flat(kc), flat(vc), flat(ks)[:, :L], flat(vs)[:, :L]
+    if over == "k_src":
+        out = ks.view(-1)[:q.numel()].view_as(q)
+    else:
+        out = kc if over == "k_cur" else vc
+    kd = torch.empty(1, H, budget + n_cur, d, dtype=dtype, device=DEV); vd = torch.empty_like(kd)
+    idx = torch.empty(1, H, budget, dtype=torch.int32, device=DEV)
+    skv.step(shape, q, kc, vc, win, ks, vs, L, budget, kd, vd, out, idx, ws)
+    torch.cuda.synchronize()
+    ref = oracle.step(flat(q), in_kc, in_vc, win, in_ks, in_vs, budget,
+                      force_idx=idx[0, :1].cpu().numpy())
+    kept = idx[0, 0].long().cpu()
+    assert torch.equal(kd[0, 0].cpu(), torch.cat([in_ks[0][kept], in_kc[0]]))
+    assert torch.equal(vd[0, 0].cpu(), torch.cat([in_vs[0][kept], in_vc[0]]))
+    assert np.abs(out[0, 0].float().cpu().numpy() - ref["out"][0]).max() < 2e-2
+
+
 # keys whose logits are all -inf have weight zero, also where one wave meets nothing else
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("d,n_q", [(64, 20), (128, 33)])
