@@ -33,6 +33,9 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int kBlockKeys = 16;
 constexpr int kMaxSplit = 4;  // waves of a workgroup
+// Running maximum of a wave that has met no key yet: finite, so that a wave whose keys all have logits of -inf
+// adds weights of zero and not NaN (the maximum is subtracted before the logits are scaled).
+constexpr float kNoMaximum = -__FLT_MAX__;
 
 template <int D, int QB>
 __global__ __launch_bounds__(64 * kMaxSplit) void attend_f32_kernel(

@@ -222,9 +222,11 @@ __device__ __forceinline__ float xor32_sum(float x) { float a, b; swap32(x, a, b
 // grow before the running offset is moved and the accumulators are rescaled.
 __device__ __forceinline__ int pi32(int i) { return (i & ~12) | ((i & 4) << 1) | ((i & 8) >> 1); }
 constexpr float kRescaleThreshold = 8.f;
-// Running maximum of a wave that has met no key yet, where the waves of a workgroup split the keys: finite, so
-// that a wave whose keys all have logits of -inf adds weights of zero and not NaN.
-constexpr float kNoMaximum = -__FLT_MAX__;
+// Running maximum of rows that have met no key yet, in kernels that take the weight of a logit s as
+// exp2(s * scale_log2e - maximum * scale_log2e): finite, and finite when it has been scaled, so that keys
+// whose logits are all -inf add weights of zero and not NaN.  (The 2^-20 by which it stays below FLT_MAX
+// covers the rounding of the division and of the product.)
+inline float no_maximum(float scale_log2e) { return -0x1.fffff0p127f / (scale_log2e > 1.f ? scale_log2e : 1.f); }
 
 __device__ __forceinline__ float bf16_bits_to_float(uint32_t bits16) {
   return __uint_as_float(bits16 << 16);

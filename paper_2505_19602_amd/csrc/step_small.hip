@@ -60,6 +60,7 @@ struct SmallArgs {
   int n_copy;           // kGiven: copying workgroups per unit
   int copy_from;        // kGiven: first destination row that is written
   float scale_log2e;
+  float no_maximum;     // where the running maxima start
   // kRank
   WindowRows rows;
   int n_win, cache_len;
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(kThreads) void step_small_kernel(SmallArgs a) {
   float m_run[QB], l_run[QB];
 #pragma unroll
   for (int b = 0; b < QB; ++b) {
-    m_run[b] = kNoMaximum;
+    m_run[b] = a.no_maximum;
     l_run[b] = 0.f;
 #pragma unroll
     for (int c = 0; c < NCB; ++c) o[b][c] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -373,6 +374,7 @@ hipError_t launch_step_small(const SmallStep& s, hipStream_t stream) {
   a.idx = s.idx; a.idx_out = s.idx_out;
   a.n_q = s.n_q; a.len1 = s.len1; a.len2 = s.len2; a.n_head = s.n_head;
   a.scale_log2e = s.sm_scale * 1.4426950408889634f;
+  a.no_maximum = no_maximum(a.scale_log2e);
   a.rows = s.rows; a.n_win = s.n_win; a.cache_len = s.cache_len; a.sm_scale = s.sm_scale;
   // Rows per workgroup: 16 on all eight waves; from 32 on, waves of 32 rows (half the reads of K and V
   // per product), one, two or four such blocks to a workgroup.

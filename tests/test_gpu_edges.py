@@ -230,6 +230,28 @@ def test_attend_over_keys_of_weight_zero(dtype, d, n_q):
     check_output(units(out), ref, dtype, "attend")
 
 
+# the same where the logits are scaled by one and more (queries and keys that are normalised): 16 and 32 query rows
+# per workgroup, a wave that meets nothing but such keys
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("sm_scale", [0.7, 1.0, 8.0])
+@pytest.mark.parametrize("d,H,n_q", [(64, 2, 20), (128, 2, 33), (64, 20, 200), (128, 20, 200)])
+def test_attend_over_keys_of_weight_zero_at_other_scales(dtype, sm_scale, d, H, n_q):
+    kv = 200
+    print(f"weight zero d={d} H={H} n_q={n_q} sm_scale={sm_scale} {dtype}", flush=True)
+    shape = skv.Shape(1, H, d, dtype, sm_scale)
+    q, k, v = (_rand(90 + i, (1, H, n, d), dtype) for i, n in enumerate((n_q, kv, kv)))
+    q = (q.float() / (sm_scale * d ** 0.5)).to(dtype)
+    q[..., 0] = 0.125
+    keep = torch.ones(kv, dtype=torch.bool)
+    keep[16:32] = False; keep[64:96] = False
+    k[:, :, ~keep, 0] = float("-inf")
+    out = torch.empty(1, H, n_q, d, dtype=dtype, device=DEV)
+    skv.attend(shape, q.to(DEV), k.to(DEV), v.to(DEV), kv, out)
+    torch.cuda.synchronize()
+    ref = oracle.attend(units(q), units(k)[:, keep], units(v)[:, keep], sm_scale)
+    check_output(units(out), ref, dtype, "attend")
+
+
 # a key of NaN makes the selectivity NaN, also where a lane holds no other key
 @pytest.mark.parametrize("d", [64, 128])
 def test_asi_of_a_key_of_nan(d):
