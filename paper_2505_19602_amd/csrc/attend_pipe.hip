@@ -202,7 +202,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
                         long long k_head_stride, uint16_t* v, long long v_seq_stride,
                         long long v_head_stride, int len1, const uint16_t* __restrict__ k2,
                         const uint16_t* __restrict__ v2, int len2, int append, int n_head,
-                        int n_qtile, int n_wg, float scale_log2e, uint16_t* __restrict__ out) {
+                        int n_qtile, int n_wg, float scale_log2e, float no_max, uint16_t* __restrict__ out) {
   SCALEKV_STAMP(t_start);
 #if defined(SCALEKV_TIMELINE)
   unsigned long long t_first_tile = 0;
@@ -472,7 +472,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
-    m_run = -INFINITY;
+    m_run = no_max;
     l_run = 0.f;
     issue_tile(0);
     __builtin_amdgcn_s_waitcnt(0);
@@ -619,6 +619,7 @@ hipError_t launch(int n_unit, int n_head, const void* q, int n_q, KvView k, KvVi
   const hipError_t e = allow_dynamic_lds((const void*)attend_pipe_kernel<D>, kLdsBytes<D>, configured);
   if (e != hipSuccess) return e;
   const float scale_log2e = sm_scale * 1.4426950408889634f;
+  const float no_max = no_maximum(scale_log2e);
   const int n_qtile = (n_q + BM - 1) / BM;
   const int n_wg = n_qtile * n_unit;
   if (start || stop)
@@ -626,13 +627,13 @@ hipError_t launch(int n_unit, int n_head, const void* q, int n_q, KvView k, KvVi
                           (const uint16_t*)q, n_q, (uint16_t*)const_cast<void*>(k.ptr), k.seq_stride,
                           k.head_stride, (uint16_t*)const_cast<void*>(v.ptr), v.seq_stride,
                           v.head_stride, len1, (const uint16_t*)k2, (const uint16_t*)v2, len2,
-                          append ? 1 : 0, n_head, n_qtile, n_wg, scale_log2e, (uint16_t*)out);
+                          append ? 1 : 0, n_head, n_qtile, n_wg, scale_log2e, no_max, (uint16_t*)out);
   else
     hipLaunchKernelGGL(attend_pipe_kernel<D>, dim3(n_wg), dim3(256), kLdsBytes<D>, stream,
                        (const uint16_t*)q, n_q, (uint16_t*)const_cast<void*>(k.ptr), k.seq_stride,
                        k.head_stride, (uint16_t*)const_cast<void*>(v.ptr), v.seq_stride,
                        v.head_stride, len1, (const uint16_t*)k2, (const uint16_t*)v2, len2,
-                       append ? 1 : 0, n_head, n_qtile, n_wg, scale_log2e, (uint16_t*)out);
+                       append ? 1 : 0, n_head, n_qtile, n_wg, scale_log2e, no_max, (uint16_t*)out);
   return hipGetLastError();
 }
 

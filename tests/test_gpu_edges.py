@@ -252,6 +252,38 @@ def test_attend_over_keys_of_weight_zero_at_other_scales(dtype, sm_scale, d, H, 
     check_output(units(out), ref, dtype, "attend")
 
 
+# the same in the pipelined kernel (more than 256 units): a first block, a first tile and a second tile of such keys;
+# then as cache and map of a step, where the map's keys are a second segment
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_q", [20, 150])
+@pytest.mark.parametrize("lo,hi", [(0, 32), (0, 64), (0, 100), (64, 128)])
+@pytest.mark.parametrize("sm_scale", [0.0, 1.0])
+def test_pipelined_attention_over_keys_of_weight_zero(d, n_q, lo, hi, sm_scale):
+    S, H, cached, dtype = 4, 75, 110, torch.bfloat16
+    kv = cached + n_q
+    print(f"weight zero, pipelined d={d} n_q={n_q} keys {lo}..{hi} sm_scale={sm_scale}", flush=True)
+    shape = skv.Shape(S, H, d, dtype, sm_scale)
+    scale = sm_scale or d ** -0.5
+    q, k, v = (_rand(94 + i, (S, H, n, d), dtype) for i, n in enumerate((n_q, kv, kv)))
+    q = (q.float() / (scale * d ** 0.5)).to(dtype)
+    q[..., 0] = 0.5
+    keep = torch.ones(kv, dtype=torch.bool)
+    keep[lo:hi] = False
+    k[:, :, ~keep, 0] = float("-inf")
+    pick = [0, S * H - 1]
+    ref = oracle.attend(units(q)[pick], units(k)[pick][:, keep], units(v)[pick][:, keep], scale)
+    dev = [t.contiguous().to(DEV) for t in (q, k, v, k[:, :, cached:], v[:, :, cached:], k[:, :, :cached], v[:, :, :cached])]
+    out = torch.empty(S, H, n_q, d, dtype=dtype, device=DEV)
+    skv.attend(shape, *dev[:3], kv, out)
+    torch.cuda.synchronize()
+    check_output(units(out)[pick], ref, dtype, "attend")
+    kd, vd, out = torch.zeros_like(dev[1]), torch.zeros_like(dev[2]), torch.empty_like(out)
+    skv.step(shape, dev[0], dev[3], dev[4], [0], dev[5], dev[6], cached, cached, kd, vd, out, None, None)
+    torch.cuda.synchronize()
+    check_output(units(out)[pick], ref, dtype, "step")
+    assert torch.equal(kd, dev[1]) and torch.equal(vd, dev[2])
+
+
 # a key of NaN makes the selectivity NaN, also where a lane holds no other key
 @pytest.mark.parametrize("d", [64, 128])
 def test_asi_of_a_key_of_nan(d):
