@@ -7,6 +7,10 @@
 // (another type, a shape that does not match, a non-contiguous tensor): binding.py then takes
 // its own checks, which raise the error that names the argument.  A non-OK status of the library
 // comes back as its negative.  No arithmetic of the method happens here.
+//
+// Torch throws where a tensor has no memory of its own (one that vmap or functionalize has wrapped) or
+// there is no device.  No C++ exception may leave an entry function: it answers None, and binding.py's
+// own way to the same place raises torch's Python exception.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -14,6 +18,8 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Dtype.h>
 #include <torch/csrc/autograd/python_variable.h>
+
+#include <exception>
 
 #include "../../include/scalekv.h"
 
@@ -393,7 +399,7 @@ struct Prepared {
   vectorcallfunc vectorcall;
 };
 
-PyObject* prepared_call(PyObject* self, PyObject* const* a, size_t nf, PyObject*) {
+PyObject* prepared_call(PyObject* self, PyObject* const* a, size_t nf, PyObject*) try {
   const Prepared* p = reinterpret_cast<Prepared*>(self);
   void* stream;
   if (PyVectorcall_NARGS(nf) < 1 || a[0] == Py_None) {
@@ -407,6 +413,9 @@ PyObject* prepared_call(PyObject* self, PyObject* const* a, size_t nf, PyObject*
   const scalekv_status st = p->args.run_append_first(stream, &keep, &moved);
   if (st != SCALEKV_OK) return answer(st, 0);
   return PyLong_FromLong(2L * keep + (moved != 0));
+} catch (const std::exception& e) {
+  PyErr_SetString(PyExc_RuntimeError, e.what());
+  return nullptr;
 }
 
 PyTypeObject g_prepared_type = {PyVarObject_HEAD_INIT(nullptr, 0)};
@@ -445,7 +454,15 @@ PyObject* py_bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
   return none();
 }
 
-#define SCALEKV_METHOD(name) {#name, (PyCFunction)(void (*)(void))py_##name, METH_FASTCALL, nullptr}
+typedef PyObject* (*FastCall)(PyObject*, PyObject* const*, Py_ssize_t);
+template <FastCall CALL>
+PyObject* guarded(PyObject* self, PyObject* const* a, Py_ssize_t n) try {
+  return CALL(self, a, n);
+} catch (const std::exception&) {  // before anything was enqueued: the library does not throw
+  return none();
+}
+
+#define SCALEKV_METHOD(name) {#name, (PyCFunction)(void (*)(void))guarded<py_##name>, METH_FASTCALL, nullptr}
 PyMethodDef g_methods[] = {
     SCALEKV_METHOD(bind), SCALEKV_METHOD(step), SCALEKV_METHOD(step_static), SCALEKV_METHOD(append_first),
     SCALEKV_METHOD(score), SCALEKV_METHOD(select), SCALEKV_METHOD(select_window), SCALEKV_METHOD(select_positional),

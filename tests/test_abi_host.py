@@ -4,6 +4,8 @@ run without a GPU; pointers below are fake but aligned and never dereferenced)."
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 import torch
@@ -294,3 +296,49 @@ def test_step_append_first_rejects_inputs_that_overlap_the_next_cache(L):
     assert step(0x400000 + 512, 0x600000, 0x700000, 0x900000) == 1                                    # q in v_next
     assert step(0x500000, 0x600000, 0x300000, 0x900000) == 1                                          # v_cur in k_next
 
+
+
+# Tensors that claim to be on a device but have no memory there (wrapped by functionalize and by vmap, around
+# fake ones): every call ends in a Python exception.  In a process of its own, which a C++ exception would end.
+WRAPPED = """
+import torch
+from torch._subclasses.fake_tensor import FakeTensorMode
+import paper_2505_19602_amd as skv
+H, n, d = 2, 16, 64
+with FakeTensorMode():
+    fake = [torch.empty(s, dtype=t, device="cuda:0") for s, t in (((1, H, n, d), torch.bfloat16), ((1, H, n), torch.float32),
+            ((1, H, 8), torch.int32), ((1, H, n, 2), torch.float32), ((1 << 20,), torch.uint8))]
+sh, win = skv.Shape(1, H, d, torch.bfloat16), list(range(n))
+def calls(x, f, i, t, ws):
+    step = (sh, x, x, x, win, x, x, n, 8, x, x, x, i)
+    lit = (sh, x, x, x, [1, 3], 1, x, x, 0, 6, x, x, x, i, ws)
+    yield lambda: skv.step(*step, ws)
+    yield lambda: skv.step_static(*step)
+    yield lambda: skv.step_append_first(*lit)
+    yield lambda: skv.score(sh, x, x, n, f, ws)
+    yield lambda: skv.select(sh, f, n, 8, i)
+    yield lambda: skv.select_window(sh, f, n, 6, [1, 3], 3, i)
+    yield lambda: skv.select_positional(sh, n, 2, 6, i)
+    yield lambda: skv.compact(sh, x, x, n, i, 8, None, None, x, x)
+    yield lambda: skv.attend(sh, x, x, x, n, x)
+    yield lambda: skv.asi(sh, x, x, 8, 8, 4, t, None, ws)
+    yield lambda: skv.PreparedStep(*step, ws)()
+    yield lambda: skv.PreparedAppendFirst(*lit)()
+def all_raise(*args):
+    for no, call in enumerate(calls(*args)):
+        try:
+            call()
+        except Exception as e:
+            print(no, type(e).__name__, str(e)[:60], flush=True)
+        else:
+            raise SystemExit(f"call {no} returned")
+    return args[0]
+all_raise(*[torch._to_functional_tensor(x) for x in fake])
+torch.vmap(all_raise)(*[torch._to_functional_tensor(x[None].expand(3, *x.shape)) for x in fake])
+print("all raised")
+"""
+
+
+def test_tensors_without_memory_raise_and_do_not_end_the_process(L):
+    res = subprocess.run([sys.executable, "-c", WRAPPED], cwd=ROOT, capture_output=True, text=True, timeout=600)
+    assert res.returncode == 0 and "all raised" in res.stdout, f"rc {res.returncode}\n{res.stdout}\n{res.stderr[-2000:]}"
