@@ -17,6 +17,7 @@ from __future__ import annotations
 import ctypes
 import os
 from dataclasses import dataclass
+from operator import index
 from typing import Optional, Sequence
 
 import torch
@@ -256,6 +257,23 @@ def attend(shape: Shape, q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, kv_l
                                 int(kv_len), _ptr(out), _stream()))
 
 
+def _step_args(shape: Shape, q, k_cur, v_cur, win_idx, k_src, v_src, cache_len, budget, k_dst, v_dst, out, idx_out, ws):
+    """The checked arguments of scalekv_step up to the stream, the cell that receives the new length, and its value."""
+    n_cur = q.shape[2]
+    _dense(q, shape, n_cur, "q"); _dense(k_cur, shape, n_cur, "k_cur"); _dense(v_cur, shape, n_cur, "v_cur")
+    _dense(out, shape, n_cur, "out")
+    keep = max(0, min(int(budget), int(cache_len)))
+    _idx_tensor(idx_out, shape, keep, "idx_out")
+    win = (ctypes.c_int32 * max(1, len(win_idx)))(*[int(w) for w in win_idx])
+    cs = shape.c()
+    a, b, c, d = _kv(k_src, shape, "k_src"), _kv(v_src, shape, "v_src"), _kv(k_dst, shape, "k_dst"), _kv(v_dst, shape, "v_dst")
+    wp, wb = _ws(ws)
+    new_len = ctypes.c_int32(-1)
+    return (ctypes.byref(cs), _ptr(q), _ptr(k_cur), _ptr(v_cur), int(n_cur), win, int(len(win_idx)), ctypes.byref(a),
+            ctypes.byref(b), int(cache_len), int(budget), ctypes.byref(c), ctypes.byref(d), ctypes.byref(new_len),
+            _ptr(out), _ptr(idx_out), wp, wb), new_len, keep + n_cur
+
+
 def step(shape: Shape, q: torch.Tensor, k_cur: torch.Tensor, v_cur: torch.Tensor,
          win_idx: Sequence[int], k_src: torch.Tensor, v_src: torch.Tensor, cache_len: int, budget: int,
          k_dst: torch.Tensor, v_dst: torch.Tensor, out: torch.Tensor,
@@ -265,24 +283,10 @@ def step(shape: Shape, q: torch.Tensor, k_cur: torch.Tensor, v_cur: torch.Tensor
                            idx_out, ws)
     if r is not None:
         return _checked(r)
-    n_cur = q.shape[2]
-    _dense(q, shape, n_cur, "q"); _dense(k_cur, shape, n_cur, "k_cur"); _dense(v_cur, shape, n_cur, "v_cur")
-    _dense(out, shape, n_cur, "out")
-    keep = max(0, min(int(budget), int(cache_len)))
-    if idx_out is not None:
-        if idx_out.dtype != torch.int32 or not idx_out.is_cuda or not idx_out.is_contiguous() \
-                or tuple(idx_out.shape) != (shape.n_seq, shape.n_head, keep):
-            raise ScaleKVError(1, f"idx_out must be a contiguous int32 device tensor [S,H,{keep}]")
-    win = (ctypes.c_int32 * max(1, len(win_idx)))(*[int(w) for w in win_idx])
-    cs = shape.c()
-    a, b, c, d = _kv(k_src, shape, "k_src"), _kv(v_src, shape, "v_src"), _kv(k_dst, shape, "k_dst"), _kv(v_dst, shape, "v_dst")
-    wp, wb = _ws(ws)
-    new_len = ctypes.c_int32(-1)
-    _check(lib().scalekv_step(ctypes.byref(cs), _ptr(q), _ptr(k_cur), _ptr(v_cur), int(n_cur), win,
-                              int(len(win_idx)), ctypes.byref(a), ctypes.byref(b), int(cache_len), int(budget),
-                              ctypes.byref(c), ctypes.byref(d), ctypes.byref(new_len), _ptr(out), _ptr(idx_out),
-                              wp, wb, _stream()))
-    assert new_len.value == keep + n_cur, "the binding's shape check and the library disagree on keep"
+    args, new_len, expected = _step_args(shape, q, k_cur, v_cur, win_idx, k_src, v_src, cache_len, budget, k_dst, v_dst,
+                                         out, idx_out, ws)
+    _check(lib().scalekv_step(*args, _stream()))
+    assert new_len.value == expected, "the binding's shape check and the library disagree on keep"
     return int(new_len.value)
 
 
@@ -315,6 +319,16 @@ def step_static(shape: Shape, q: torch.Tensor, k_cur: torch.Tensor, v_cur: torch
     return int(new_len.value)
 
 
+def _prepared(fn, args, result):
+    """What _marshal's prepared calls are, for arguments that it does not take: call(stream or None) -> the
+    call's result, or its status as a negative."""
+    def call(stream_ptr: Optional[int]) -> int:
+        stream = torch.cuda.current_stream().cuda_stream if stream_ptr is None else stream_ptr
+        status = fn(*args, ctypes.c_void_p(stream))
+        return -status if status else result()
+    return call
+
+
 class PreparedStep:
     """One scalekv_step call with every argument already marshalled.  Building it does
     all the checks that `step` does; calling it only crosses into C, which matters for
@@ -325,21 +339,14 @@ class PreparedStep:
 
     def __init__(self, shape: Shape, q, k_cur, v_cur, win_idx, k_src, v_src, cache_len, budget,
                  k_dst, v_dst, out, idx_out, ws):
-        win, cache_len, budget = [int(w) for w in win_idx], int(cache_len), int(budget)
+        win, cache_len, budget = [int(w) for w in win_idx], index(cache_len), index(budget)
+        args = (shape, q, k_cur, v_cur, win, k_src, v_src, cache_len, budget, k_dst, v_dst, out, idx_out, ws)
         self._refs = (q, k_cur, v_cur, k_src, v_src, k_dst, v_dst, out, idx_out, ws)
-        self._call = _marshaller().prepare_step(shape, q, k_cur, v_cur, win, k_src, v_src, cache_len, budget, k_dst,
-                                                v_dst, out, idx_out, ws)
-        n_cur, keep = q.shape[2], max(0, min(budget, cache_len))
-        self.new_len = keep + n_cur
+        self.new_len = max(0, min(budget, cache_len)) + q.shape[2]
+        self._call = _marshaller().prepare_step(*args)
         if self._call is None:
-            shape.c()
-            for t, name in ((q, "q"), (k_cur, "k_cur"), (v_cur, "v_cur"), (out, "out")):
-                _dense(t, shape, n_cur, name)
-            _idx_tensor(idx_out, shape, keep, "idx_out")
-            for t, name in ((k_src, "k_src"), (v_src, "v_src"), (k_dst, "k_dst"), (v_dst, "v_dst")):
-                _kv(t, shape, name)
-            _ws(ws)
-            raise ScaleKVError(1, "cache_len and budget must fit 32 bits")
+            c_args, new_len, _ = _step_args(*args)
+            self._call = _prepared(lib().scalekv_step, c_args, lambda: new_len.value)
 
     def __call__(self, stream_ptr: Optional[int] = None) -> int:
         """Enqueue on `stream_ptr` (a hipStream_t as int) or on torch's current stream."""
@@ -358,24 +365,16 @@ class PreparedAppendFirst:
 
     def __init__(self, shape: Shape, q, k_cur, v_cur, win_idx, pool_w, k_cache, v_cache, cache_len, budget,
                  k_next, v_next, out, idx_out, ws):
-        win, pool_w, cache_len, budget = [int(w) for w in win_idx], int(pool_w), int(cache_len), int(budget)
+        win, pool_w, cache_len, budget = [int(w) for w in win_idx], index(pool_w), index(cache_len), index(budget)
+        args = (shape, q, k_cur, v_cur, win, pool_w, k_cache, v_cache, cache_len, budget, k_next, v_next, out, idx_out, ws)
         self._refs = (q, k_cur, v_cur, k_cache, v_cache, k_next, v_next, out, idx_out, ws)
-        self._call = _marshaller().prepare_append_first(shape, q, k_cur, v_cur, win, pool_w, k_cache, v_cache,
-                                                        cache_len, budget, k_next, v_next, out, idx_out, ws)
-        n_cur = q.shape[2]
-        total = cache_len + n_cur
+        total = cache_len + q.shape[2]
         self.keep = len(win) + max(0, min(budget, total - len(win)))
         self.moved = self.keep < total
+        self._call = _marshaller().prepare_append_first(*args)
         if self._call is None:
-            shape.c()
-            for t, name in ((q, "q"), (k_cur, "k_cur"), (v_cur, "v_cur"), (out, "out")):
-                _dense(t, shape, n_cur, name)
-            _idx_tensor(idx_out, shape, self.keep, "idx_out")
-            for t, name in ((k_cache, "k_cache"), (v_cache, "v_cache"), (k_next, "k_next"), (v_next, "v_next")):
-                if t is not None:
-                    _kv(t, shape, name)
-            _ws(ws)
-            raise ScaleKVError(1, "pool_w, cache_len and budget must fit 32 bits")
+            c_args, keep, moved, _ = _append_first_args(*args)
+            self._call = _prepared(lib().scalekv_step_append_first, c_args, lambda: 2 * keep.value + moved.value)
 
     def __call__(self, stream_ptr: Optional[int] = None) -> int:
         r = self._call(stream_ptr)
@@ -431,18 +430,9 @@ def select_window(shape: Shape, log_scores: torch.Tensor, cache_len: int, budget
     return int(out.value)
 
 
-def step_append_first(shape: Shape, q: torch.Tensor, k_cur: torch.Tensor, v_cur: torch.Tensor,
-                      win_idx: Sequence[int], pool_w: int, k_cache: torch.Tensor, v_cache: torch.Tensor,
-                      cache_len: int, budget: int, k_next: Optional[torch.Tensor],
-                      v_next: Optional[torch.Tensor], out: torch.Tensor, idx_out: Optional[torch.Tensor],
-                      ws: Optional[torch.Tensor]):
-    """scalekv_step_append_first; returns (keep, moved): the next cache has `keep` rows and
-    lives in k_next/v_next if `moved`, else still in k_cache/v_cache."""
-    r = _marshaller().append_first(shape, q, k_cur, v_cur, win_idx, pool_w, k_cache, v_cache, cache_len, budget,
-                                   k_next, v_next, out, idx_out, ws)
-    if r is not None:
-        _checked(r)
-        return r >> 1, bool(r & 1)
+def _append_first_args(shape: Shape, q, k_cur, v_cur, win_idx, pool_w, k_cache, v_cache, cache_len, budget, k_next, v_next,
+                       out, idx_out, ws):
+    """The same for scalekv_step_append_first (see _step_args): arguments, cells of keep and moved, keep's value."""
     n_cur = q.shape[2]
     _dense(q, shape, n_cur, "q"); _dense(k_cur, shape, n_cur, "k_cur"); _dense(v_cur, shape, n_cur, "v_cur")
     _dense(out, shape, n_cur, "out")
@@ -456,11 +446,27 @@ def step_append_first(shape: Shape, q: torch.Tensor, k_cur: torch.Tensor, v_cur:
     d = _kv(v_next, shape, "v_next") if v_next is not None else None
     wp, wb = _ws(ws)
     keep_out, moved = ctypes.c_int32(-1), ctypes.c_int32(-1)
-    _check(lib().scalekv_step_append_first(
-        ctypes.byref(cs), _ptr(q), _ptr(k_cur), _ptr(v_cur), int(n_cur), win, int(len(win_idx)), int(pool_w),
-        ctypes.byref(a), ctypes.byref(b), int(cache_len), int(budget),
-        ctypes.byref(c) if c is not None else None, ctypes.byref(d) if d is not None else None,
-        ctypes.byref(keep_out), ctypes.byref(moved), _ptr(out), _ptr(idx_out), wp, wb, _stream()))
+    return (ctypes.byref(cs), _ptr(q), _ptr(k_cur), _ptr(v_cur), int(n_cur), win, int(len(win_idx)), int(pool_w),
+            ctypes.byref(a), ctypes.byref(b), int(cache_len), int(budget),
+            ctypes.byref(c) if c is not None else None, ctypes.byref(d) if d is not None else None,
+            ctypes.byref(keep_out), ctypes.byref(moved), _ptr(out), _ptr(idx_out), wp, wb), keep_out, moved, keep
+
+
+def step_append_first(shape: Shape, q: torch.Tensor, k_cur: torch.Tensor, v_cur: torch.Tensor,
+                      win_idx: Sequence[int], pool_w: int, k_cache: torch.Tensor, v_cache: torch.Tensor,
+                      cache_len: int, budget: int, k_next: Optional[torch.Tensor],
+                      v_next: Optional[torch.Tensor], out: torch.Tensor, idx_out: Optional[torch.Tensor],
+                      ws: Optional[torch.Tensor]):
+    """scalekv_step_append_first; returns (keep, moved): the next cache has `keep` rows and
+    lives in k_next/v_next if `moved`, else still in k_cache/v_cache."""
+    r = _marshaller().append_first(shape, q, k_cur, v_cur, win_idx, pool_w, k_cache, v_cache, cache_len, budget,
+                                   k_next, v_next, out, idx_out, ws)
+    if r is not None:
+        _checked(r)
+        return r >> 1, bool(r & 1)
+    args, keep_out, moved, keep = _append_first_args(shape, q, k_cur, v_cur, win_idx, pool_w, k_cache, v_cache, cache_len,
+                                                     budget, k_next, v_next, out, idx_out, ws)
+    _check(lib().scalekv_step_append_first(*args, _stream()))
     assert keep_out.value == keep, "the binding's shape check and the library disagree on keep"
     return int(keep_out.value), bool(moved.value)
 

@@ -342,3 +342,27 @@ print("all raised")
 def test_tensors_without_memory_raise_and_do_not_end_the_process(L):
     res = subprocess.run([sys.executable, "-c", WRAPPED], cwd=ROOT, capture_output=True, text=True, timeout=600)
     assert res.returncode == 0 and "all raised" in res.stdout, f"rc {res.returncode}\n{res.stdout}\n{res.stderr[-2000:]}"
+
+
+def test_prepared_calls_take_what_the_calls_take(L):
+    # tensor subclasses and a Shape of NumPy integers go to the library (which refuses the fakes' missing memory);
+    # numbers that are not whole are refused as they always were
+    import numpy as np
+    from torch._subclasses.fake_tensor import FakeTensorMode
+    with FakeTensorMode():
+        x = torch.empty(1, 2, 16, 64, dtype=torch.bfloat16, device="cuda:0")
+        idx = torch.empty(1, 2, 8, dtype=torch.int32, device="cuda:0")
+    for t, i in ((x, idx), (torch._to_functional_tensor(x), torch._to_functional_tensor(idx))):
+        shape = skv.Shape(np.int32(1), np.int64(2), np.int64(64), torch.bfloat16)
+        assert (type(t) is torch.Tensor) == (t is not x)
+        step = skv.PreparedStep(shape, t, t, t, [0], t, t, np.int64(16), np.int64(16), t, t, t, None, None)
+        assert step.new_len == 32
+        lit = skv.PreparedAppendFirst(shape, t, t, t, [0, 3], np.int64(1), t, t, 0, np.int64(6), t, t, t, i, None)
+        assert (lit.keep, lit.moved) == (8, True)
+        for call in (step, lit):
+            with pytest.raises(skv.ScaleKVError):
+                call(0)
+        with pytest.raises(TypeError):
+            skv.PreparedStep(shape, t, t, t, [0], t, t, 16.5, 16, t, t, t, None, None)
+        with pytest.raises(skv.ScaleKVError, match="idx_out"):
+            skv.PreparedAppendFirst(shape, t, t, t, [0, 3], 1, t, t, 0, 7, t, t, t, i, None)

@@ -296,3 +296,32 @@ def test_asi_of_a_key_of_nan(d):
     skv.asi(shape, q.to(DEV), k.to(DEV), hist, cur, 64, terms, mean, ws)
     torch.cuda.synchronize()
     assert torch.isnan(terms).all() and torch.isnan(mean).all()
+
+
+# arguments that the native marshalling leaves to the binding (a tensor subclass, NumPy integers in the Shape)
+def test_prepared_steps_of_subclasses_and_numpy_integers():
+    class Tagged(torch.Tensor):
+        pass
+
+    S, H, d, L, budget, n_cur, dtype = 1, 3, 64, 90, 20, 25, torch.bfloat16
+    print("prepared calls with a tensor subclass", flush=True)
+    q, kc, vc = (_rand(110 + i, (S, H, n_cur, d), dtype).to(DEV) for i in range(3))
+    ks, vs = (_rand(113 + i, (S, H, L + n_cur, d), dtype).to(DEV) for i in range(2))
+    win, win2 = list(range(n_cur - 16, n_cur)), [0, 7, 20]
+    results = []
+    for shape, cast in ((skv.Shape(S, H, d, dtype), lambda t: t),
+                        (skv.Shape(np.int32(S), np.int64(H), np.int64(d), dtype), lambda t: t.as_subclass(Tagged))):
+        ws = torch.empty(skv.workspace_bytes(shape, L + n_cur, n_cur), dtype=torch.uint8, device=DEV)
+        kd, vd = (torch.zeros(S, H, budget + n_cur, d, dtype=dtype, device=DEV) for _ in range(2))
+        kn, vn = (torch.zeros(S, H, budget + 3, d, dtype=dtype, device=DEV) for _ in range(2))
+        cache = ks.clone(), vs.clone()
+        out, out2 = torch.zeros_like(q), torch.zeros_like(q)
+        step = skv.PreparedStep(shape, cast(q), kc, vc, win, cast(ks), vs, L, budget, cast(kd), vd, out, None, cast(ws))
+        lit = skv.PreparedAppendFirst(shape, cast(q), kc, vc, win2, 3, cast(cache[0]), cache[1], L, budget, kn, cast(vn), out2,
+                                      None, ws)
+        assert step() == budget + n_cur and lit(torch.cuda.current_stream().cuda_stream) == budget + 3
+        torch.cuda.synchronize()
+        results.append((out, kd, vd, out2, kn, vn, *cache))
+    assert float(results[0][0].abs().max()) > 0 and float(results[0][3].abs().max()) > 0
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
