@@ -113,15 +113,21 @@ __device__ __forceinline__ void radix_kth_largest(KeyAt key_at, int n, uint32_t 
   need_eq = remaining;
 }
 
+constexpr int kCrowdedBits = 28;  // a digit that starts above bit 27 holds at most two bits of mantissa
+
 // The same search for keys whose bits from `bits` up (1 <= bits <= 32) are all those of any_key: the
 // first digit ends at the highest bit that differs, and the search ends as soon as the bin it has
 // narrowed down to is wanted whole.  Then T is one less than the bin's smallest possible key and
 // need_eq is 0: "above T" are exactly the k largest.  hist (kRadixHistWords words) has been cleared
-// and a barrier passed.  Keys of real scores spread over the first digit's bins this way, so the
-// lanes add one by one.
-template <int THREADS, typename KeyAt>
-__device__ __forceinline__ void radix_kth_largest_from(KeyAt key_at, int n, uint32_t k, int bits, uint32_t any_key,
-                                                       uint32_t* hist, uint32_t& T, uint32_t& need_eq) {
+// and a barrier passed.  Keys whose bit c of the thread's `skip` is set (key tid + c THREADS) are not
+// among the n.  A digit that lies in the mantissa spreads the keys over its bins, and the lanes add one
+// by one; one that is little but sign and exponent (scores on both sides of zero, or a few very small
+// ones) does not, and the lanes that share a bin are counted by ballot as above.  BALLOT = false leaves
+// that out: in a step of a few dozen rows the test alone is 0.3 of 11 us.
+template <int THREADS, bool BALLOT, typename KeyAt>
+__device__ __forceinline__ void radix_kth_largest_from(KeyAt key_at, uint32_t skip, int n, uint32_t k, int bits,
+                                                       uint32_t any_key, uint32_t* hist, uint32_t& T,
+                                                       uint32_t& need_eq) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   uint32_t mask = bits < 32 ? ~0u << bits : 0u;
@@ -131,9 +137,25 @@ __device__ __forceinline__ void radix_kth_largest_from(KeyAt key_at, int n, uint
     const int shift = bits - width;
     const uint32_t digit_mask = (1u << width) - 1u;
     uint32_t* h = hist + 256 * pass;
-    for (int i = tid; i < n; i += THREADS) {
+    const bool crowded = BALLOT && bits > kCrowdedBits;
+    uint32_t skipped = skip;
+    for (int i = tid; i < n; i += THREADS, skipped >>= 1) {
       const uint32_t kk = key_at(i);
-      if ((kk & mask) == prefix) atomicAdd(&h[(kk >> shift) & digit_mask], 1u);
+      bool act = (kk & mask) == prefix && !(skipped & 1u);
+      const uint32_t digit = (kk >> shift) & digit_mask;
+      if (crowded) {
+#pragma unroll
+        for (int round = 0; round < 2; ++round) {
+          const unsigned long long am = __builtin_amdgcn_ballot_w64(act);
+          if (am == 0) break;
+          const int first = __builtin_ctzll(am);
+          const uint32_t d0 = __builtin_amdgcn_readlane(digit, first);
+          const unsigned long long same = __builtin_amdgcn_ballot_w64(act && digit == d0);
+          if (lane == first) atomicAdd(&h[d0], (uint32_t)__builtin_popcountll(same));
+          act = act && digit != d0;
+        }
+      }
+      if (act) atomicAdd(&h[digit], 1u);
     }
     __syncthreads();
     // lane L owns bins 4L..4L+3 (see radix_kth_largest)

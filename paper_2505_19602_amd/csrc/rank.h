@@ -28,28 +28,29 @@ struct RankShortLds {
   uint32_t keys[kShortLen];
   int32_t list[kShortLen];                  // the selected rows, ascending
   uint32_t wave_max[16], wave_min[16];
-  uint32_t count[2 * kShortLen / 64];       // per 64 keys: above the threshold, equal to it
+  uint32_t count[kShortLen / 32];           // forced rows, a bit each; later per 64 keys how many are above and at the threshold
 };
 // dynamic LDS for the logits
 inline int rank_short_logit_bytes(int len) { return round_up(len, 32) * kLogitStride * 4; }
 
-// Rows in ascending order: thread tid holds the keys kk[c] of rows tid + c THREADS < len.  Those above T
-// and the first need_eq equal to T go to list[] (LDS) and idx[], each if it is not NULL.  count: one word
-// of LDS per 64 rows.  One barrier; the caller's next one publishes the list.
+// Rows in ascending order: thread tid holds the keys kk[c] of rows tid + c THREADS < len.  Those above T,
+// the first need_eq equal to T and those whose bit c of `forced` is set go to list[] (LDS) and idx[], each
+// if it is not NULL.  count: one word of LDS per 64 rows.  One barrier; the caller's next one publishes the list.
 template <int THREADS, int PER>
-__device__ __forceinline__ void emit_selected(const uint32_t (&kk)[PER], int len, uint32_t T, uint32_t need_eq,
-                                              uint32_t* count, int32_t* list, int32_t* idx) {
+__device__ __forceinline__ void emit_selected(const uint32_t (&kk)[PER], uint32_t forced, int len, uint32_t T,
+                                              uint32_t need_eq, uint32_t* count, int32_t* list, int32_t* idx) {
   constexpr int kWaves = THREADS / 64;
   constexpr int PER_LANE = (PER * kWaves + 63) / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n_slot = (len + 63) / 64;
+  auto above = [&](int c) { return tid + c * THREADS < len && (kk[c] > T || (forced >> c & 1u)); };
+  auto equal = [&](int c) { return tid + c * THREADS < len && kk[c] == T && !(forced >> c & 1u); };
 #pragma unroll
   for (int c = 0; c < PER; ++c) {
     const int slot = c * kWaves + wave;
     if (slot < n_slot) {
-      const bool valid = tid + c * THREADS < len;
-      const uint32_t gt = __builtin_popcountll(__builtin_amdgcn_ballot_w64(valid && kk[c] > T));
-      const uint32_t eq = __builtin_popcountll(__builtin_amdgcn_ballot_w64(valid && kk[c] == T));
+      const uint32_t gt = __builtin_popcountll(__builtin_amdgcn_ballot_w64(above(c)));
+      const uint32_t eq = __builtin_popcountll(__builtin_amdgcn_ballot_w64(equal(c)));
       if (lane == 0) count[slot] = gt | eq << 16;  // (both sums stay below 2^16)
     }
   }
@@ -71,9 +72,8 @@ __device__ __forceinline__ void emit_selected(const uint32_t (&kk)[PER], int len
       for (int x = 0; x < PER_LANE; ++x)
         if (slot / 64 == x) base = __builtin_amdgcn_readlane(before[x], slot % 64);
       const int key = tid + c * THREADS;
-      const bool valid = key < len;
-      const unsigned long long gt = __builtin_amdgcn_ballot_w64(valid && kk[c] > T);
-      const unsigned long long eq = __builtin_amdgcn_ballot_w64(valid && kk[c] == T);
+      const unsigned long long gt = __builtin_amdgcn_ballot_w64(above(c));
+      const unsigned long long eq = __builtin_amdgcn_ballot_w64(equal(c));
       const unsigned long long below = ((unsigned long long)1 << lane) - 1;
       const uint32_t g_before = (base & 0xffffu) + __builtin_popcountll(gt & below);
       const uint32_t e_before = (base >> 16) + __builtin_popcountll(eq & below);
@@ -134,6 +134,17 @@ __device__ __forceinline__ void select_scores(float (&own)[PER], int len, int ke
                                               int32_t* list, int32_t* idx) {
   const int tid = threadIdx.x;
   if constexpr (EXTRAS) {
+    if (ex.n_forced > 0) {  // (a bit per row: the list checked for every row costs 6 us at 12 rows a thread)
+      static_assert(PER * THREADS <= 32 * THREADS, "a thread forms at most one word");
+      if (tid < (len + 31) / 32) {
+        uint32_t word = 0;
+#pragma unroll  // (the list arrives with one scalar load; walked in a loop it costs 16 latencies)
+        for (int j = 0; j < kMaxWindow; ++j)
+          if (j < ex.n_forced && ex.forced[j] >> 5 == tid) word |= 1u << (ex.forced[j] & 31);
+        lds.count[tid] = word;
+      }
+      __syncthreads();
+    }
     if (ex.pool_w > 1) {
       float* raw = reinterpret_cast<float*>(lds.keys);
 #pragma unroll
@@ -147,29 +158,35 @@ __device__ __forceinline__ void select_scores(float (&own)[PER], int len, int ke
       __syncthreads();
     }
   }
+  // Forced rows take no part in the search (a key above all others for them would make the search start
+  // at the sign bit, with all real keys in one bin): `keep` less their number is wanted of the others.
   uint32_t kk[PER];
-  uint32_t hi = 0, lo = 0xffffffffu;
+  uint32_t hi = 0, lo = 0xffffffffu, forced = 0;
+  int wanted = keep;
 #pragma unroll
   for (int c = 0; c < PER; ++c) {
     const int key = tid + c * THREADS;
     kk[c] = 0;
     if (key < len) {
       kk[c] = order_key(own[c]);
-      if constexpr (EXTRAS) {
-        for (int j = 0; j < ex.n_forced; ++j)
-          if (ex.forced[j] == key) kk[c] = 0xffffffffu;
-      }
       lds.keys[key] = kk[c];
-      hi = max(hi, kk[c]);
-      lo = min(lo, kk[c]);
+      if constexpr (EXTRAS) {
+        if (ex.n_forced > 0) forced |= (lds.count[key >> 5] >> (key & 31) & 1u) << c;
+      }
+      if (!(forced >> c & 1u)) {
+        hi = max(hi, kk[c]);
+        lo = min(lo, kk[c]);
+      }
     }
   }
+  if constexpr (EXTRAS) wanted -= ex.n_forced;
   block_extremes<THREADS>(hi, lo, lds.wave_max, lds.wave_min);
   // keys above T are selected, and the first need_eq of those equal to it
-  uint32_t T, need_eq;
-  radix_kth_largest_from<THREADS>([&](int t) { return lds.keys[t]; }, len, (uint32_t)keep,
-                                  32 - __builtin_clz((hi ^ lo) | 1u), hi, lds.hist, T, need_eq);
-  emit_selected<THREADS, PER>(kk, len, T, need_eq, lds.count, list, idx);
+  uint32_t T = 0xffffffffu, need_eq = 0;
+  if (!EXTRAS || wanted > 0)
+    radix_kth_largest_from<THREADS, EXTRAS>([&](int t) { return lds.keys[t]; }, forced, len, (uint32_t)wanted,
+                                            32 - __builtin_clz((hi ^ lo) | 1u), hi, lds.hist, T, need_eq);
+  emit_selected<THREADS, PER>(kk, forced, len, T, need_eq, lds.count, list, idx);
   __syncthreads();
 }
 
@@ -269,7 +286,7 @@ struct RankLongLds {
   float wave_rowmax[16][kMaxWindow], wave_rowsum[16][kMaxWindow];
   uint32_t keys[PER * 1024];
   uint32_t wave_max[16], wave_min[16];
-  uint32_t count[PER * 16];
+  uint32_t count[PER * 32];  // as in RankShortLds
 };
 
 // Returns the index list (LDS, in place of `turn`).  logits_far: [len][kMaxWindow] of the unit.

@@ -204,7 +204,7 @@ struct SelectLds {
   __attribute__((aligned(16))) uint32_t hist[4 * 256];
   uint32_t keys[PER * kThreads];
   uint32_t wave_max[kWaves], wave_min[kWaves];
-  uint32_t count[PER * kWaves];
+  uint32_t count[PER * 2 * kWaves];  // as in RankShortLds
 };
 template <int PER, bool FROM_LOGITS>
 __global__ __launch_bounds__(kThreads) void select_lds_kernel(const float* __restrict__ scores, long long score_unit_stride,
@@ -237,6 +237,7 @@ hipError_t launch_select_lds(int n_unit, const float* scores, long long score_un
   else if (cache_len <= 2 * kThreads) SCALEKV_SELECT(2);
   else if constexpr (!FROM_LOGITS) {
     if (cache_len <= 4 * kThreads) SCALEKV_SELECT(4);
+    else if (cache_len <= 8 * kThreads) SCALEKV_SELECT(8);
     else SCALEKV_SELECT(kLdsKeys / kThreads);
   } else {
     return hipErrorNotSupported;

@@ -162,6 +162,38 @@ def test_rank_edges(d, S, H, L, budget, n_cur, dup):
     _step_against_oracle(S, H, d, L, budget, n_cur, 16, sorted({0, S * H - 1}), 2, dup)
 
 
+# Forced rows beside the search: with the largest and the smallest scores of the unit, next to the threshold, among
+# equal scores, all that is kept; units of 1, 2, 4, 8 and 12 rows a thread, and the route that leaves LDS
+@pytest.mark.parametrize("L", [17, 1024, 1025, 2049, 4097, 8192, 8193, 12288, 12289])
+@pytest.mark.parametrize("kind", ["spread", "close", "equal"])
+@pytest.mark.parametrize("pool_w", [1, 5])
+def test_select_with_forced_rows_edges(L, kind, pool_w):
+    S, H = 1, 3
+    print(f"forced rows L={L} {kind} pool_w={pool_w}", flush=True)
+    shape = skv.Shape(S, H, 64, torch.bfloat16)
+    ls = W.normal_tensor(W.stream_key(4321, 120 + L), (S, H, L)) * {"spread": 4.0, "close": 0.01, "equal": 0.0}[kind] - 5.0
+    order = torch.argsort(ls[0, 0])
+    for budget in sorted({0, 1, min(L // 3, L - 17), L - 17} - {-1}):
+        for forced in ([int(order[0])], [int(order[-1]), int(order[0])], sorted({0, L - 1, *order[-max(1, budget):][:14].tolist()})):
+            if len(forced) + budget >= L:
+                continue
+            keep = len(forced) + budget
+            idx = torch.full((S, H, keep), -1, dtype=torch.int32, device=DEV)
+            assert skv.select_window(shape, ls.to(DEV), L, budget, forced, pool_w, idx) == keep
+            torch.cuda.synchronize()
+            got = idx.cpu().numpy().reshape(S * H, keep)
+            pooled = oracle.pool_log(ls.double().numpy().reshape(S * H, L), pool_w)
+            if pool_w == 1:
+                assert np.array_equal(got, oracle.select_forced(pooled, budget, forced))
+                continue
+            for u in range(S * H):
+                rest = np.setdiff1d(got[u], forced)
+                assert set(forced) <= set(got[u].tolist()) and np.all(np.diff(got[u]) > 0) and len(rest) == budget
+                if budget:   # nothing left out lies above what was taken: both within 4 ulp of 32 (2^-19 each) of the exact
+                    out = np.setdiff1d(np.arange(L), got[u])
+                    assert pooled[u][rest].min() >= pooled[u][out].max() - 8 * 2.0 ** -19
+
+
 # out in the place of q: the workgroups of a unit must not read the window after a neighbour has written
 @pytest.mark.parametrize("d,L,budget,n_cur", [(64, 700, 90, 200), (128, 1536, 300, 128), (128, 90, 20, 16)])
 def test_small_step_writes_over_its_queries(d, L, budget, n_cur):
