@@ -421,8 +421,10 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
   // cache is written by a launch of its own and attended over.
   const bool map_written = dense_overlap(shape, out, k_cur, n_cur) || dense_overlap(shape, out, v_cur, n_cur);
   const bool src_written = keep > 0 && (dense_overlaps(shape, out, n_cur, k_src) || dense_overlaps(shape, out, n_cur, v_src));
-  const bool pipe = !map_written && attend_uses_pipe(shape->dtype, U, n_cur, keep + n_cur);
-  const bool small = !map_written && !src_written && small_tile_rows(shape->dtype, U, n_cur, keep + n_cur) > 0;
+  const SmallWork work = ranks ? SmallWork::kRanked : keep > 0 ? SmallWork::kKeepAll : SmallWork::kAppend;
+  const int small_rows = small_tile_rows(shape->dtype, shape->head_dim, U, n_cur, keep + n_cur, work);
+  const bool pipe = !map_written && shape->dtype == SCALEKV_BF16 && small_rows == 0;
+  const bool small = !map_written && !src_written && small_rows > 0;
   // The small kernel ranks as well.  Each of its workgroups reads the window's queries: with out in the place
   // of q the ranking is a launch of its own.
   const bool one_launch = small && ranks && cache_len <= kShortLen && !dense_overlap(shape, q, out, n_cur);
@@ -498,7 +500,7 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
     // one kernel prunes, appends and attends (and ranks, if the cache is short)
     SmallStep s{};
     s.n_unit = U; s.n_head = shape->n_head; s.d = shape->head_dim;
-    s.q = q; s.n_q = n_cur; s.out = out;
+    s.q = q; s.n_q = n_cur; s.tile_rows = small_rows; s.out = out;
     s.k = view(k_src); s.v = view(v_src); s.k_cur = k_cur; s.v_cur = v_cur;
     s.len1 = keep; s.len2 = n_cur; s.idx = idx;
     s.k_dst = view(k_dst); s.v_dst = view(v_dst); s.copy_kept = true;
@@ -666,8 +668,9 @@ scalekv_status scalekv_step_append_first(const scalekv_shape* shape, const void*
   // 1. the map's K/V join the cache: rows [cache_len, cache_len + n_cur) of every unit (the
   //    bf16 attention kernels do this themselves, unless out lies on top of the map's K/V)
   const bool map_written = dense_overlap(shape, out, k_cur, n_cur) || dense_overlap(shape, out, v_cur, n_cur);
-  const bool fused_append = !map_written && attend_uses_pipe(shape->dtype, U, n_cur, len);
-  const bool small = !map_written && small_tile_rows(shape->dtype, U, n_cur, len) > 0;
+  const int small_rows = small_tile_rows(shape->dtype, d, U, n_cur, len, SmallWork::kAppend);
+  const bool fused_append = !map_written && shape->dtype == SCALEKV_BF16 && small_rows == 0;
+  const bool small = !map_written && small_rows > 0;
   if (!fused_append && !small) {
     const long long tail = (long long)cache_len * d * elem_bytes(shape);
     KvView kt{static_cast<const char*>(k_cache->ptr) + tail, k_cache->seq_stride,
@@ -689,7 +692,7 @@ scalekv_status scalekv_step_append_first(const scalekv_shape* shape, const void*
   } else if (small) {
     SmallStep s{};
     s.n_unit = U; s.n_head = shape->n_head; s.d = d;
-    s.q = q; s.n_q = n_cur; s.out = out;
+    s.q = q; s.n_q = n_cur; s.tile_rows = small_rows; s.out = out;
     s.k = view(k_cache); s.v = view(v_cache); s.k_cur = k_cur; s.v_cur = v_cur;
     s.len1 = cache_len; s.len2 = n_cur;
     s.k_dst = view(k_cache); s.v_dst = view(v_cache); s.copy_kept = false;  // the append alone

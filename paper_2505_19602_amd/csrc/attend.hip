@@ -12,12 +12,13 @@ hipError_t launch_attend(int dtype, int n_seq, int n_head, int d, const void* q,
   if (n_q <= 0 || n_unit <= 0) return hipSuccess;
   if (dtype == 0)
     return launch_attend_f32(n_unit, n_head, d, q, n_q, k, v, kv_len, sm_scale, out, stream);
-  if (attend_uses_pipe(dtype, n_unit, n_q, kv_len))
+  const int rows = small_tile_rows(dtype, d, n_unit, n_q, kv_len, SmallWork::kAttend);
+  if (rows == 0)
     return launch_attend_pipe(n_unit, n_head, d, q, n_q, k, v, kv_len, nullptr, nullptr, 0, false, sm_scale, out,
                               stream);
   SmallStep s{};
   s.n_unit = n_unit; s.n_head = n_head; s.d = d;
-  s.q = q; s.n_q = n_q; s.out = out;
+  s.q = q; s.n_q = n_q; s.tile_rows = rows; s.out = out;
   s.k = k; s.v = v; s.len1 = kv_len;
   s.sm_scale = sm_scale;
   return launch_step_small(s, stream);

@@ -125,6 +125,7 @@ struct SmallStep {
   int n_unit, n_head, d;
   const void* q;            // [U, n_q, d]
   int n_q;
+  int tile_rows;            // query rows per workgroup, from small_tile_rows()
   void* out;                // [U, n_q, d]
   // keys: len1 rows of the source cache (rows idx[t], or row t), then len2 rows of k_cur / v_cur
   KvView k, v;
@@ -142,6 +143,13 @@ struct SmallStep {
   int32_t* idx_out;
 };
 hipError_t launch_step_small(const SmallStep& s, hipStream_t stream);
+// What a call of that kernel does besides the attention.
+enum class SmallWork {
+  kAttend,   // nothing
+  kAppend,   // the map's rows are copied behind the cached ones
+  kKeepAll,  // every cached row is copied as well
+  kRanked    // the kept rows, chosen in this launch or the one before, are copied
+};
 // Query rows per workgroup of that kernel for n_q bf16 queries over kv keys, 0 where the other kernels
 // are the better ones.  A workgroup of it fills a compute unit, and its time grows with the rows it
 // carries, so: the fewest rows with which the chip's 256 compute units take the launch in one round.
@@ -151,14 +159,31 @@ hipError_t launch_step_small(const SmallStep& s, hipStream_t stream);
 //   64 rows:   16 x 1024, 820, 390: 51 / 59         64 x 256, 380, 82: 26.5 / 30.1
 //   128 rows:  256 x 128, 300, 60: 28.3 / 30.2      128 x 256, 380, 82: 33.5 / 33.6
 //              128 x 144, 5000, 5000: 294 / 217     (longer than 320 keys: not worth it)
+// From 64 rows on it is what the launch does besides the attention that pays: the attention alone is then faster in the
+// pipelined kernel (64 x 144 queries, 300 keys: 14.6 / 11.9; 128 x 144, 300 keys, 128 rows: 21.3 / 12.7), but for
+// head_dim 64 over many keys (16 x 1024, 1224 keys: 0.89 of its time).  Without a ranking 64 rows pay while
+// the workgroups leave some compute units to those that copy, which otherwise wait for a round of their
+// own (all kept, 64 x 144 queries, 100 cached, 192 workgroups: 15.2 / 18.8; 64 x 256, 256 workgroups: 23.8 / 21.0;
+// head_dim 64 copies half as much: 0.71-0.99 of the time up to 256), 128 rows do not (128 x 200, 100: 32.3 / 24.5).
+// Appending alone copies least and gains least: head_dim 64, up to 224 workgroups, 0.86-0.95 of the time over 500
+// keys and more; head_dim 128: 1.00-1.24.
 // More units than compute units: two rounds are paid, which only maps of up to 16 queries stand
 // (320 x 4, 65, 65: 10.8 / 20.8;  512 x 16, 69, 14: 22.1 / 22.7;  320 x 36, 85, 21: 26 / 23).
-inline int small_tile_rows(int dtype, int n_unit, int n_q, int kv) {
+inline int small_tile_rows(int dtype, int d, int n_unit, int n_q, int kv, SmallWork work) {
   if (dtype != 1) return 0;
   constexpr int kComputeUnits = 256;
-  for (int rows = 16; rows <= 128; rows *= 2)
-    if ((long long)n_unit * ((n_q + rows - 1) / rows) <= kComputeUnits) return rows < 128 || kv <= 320 ? rows : 0;
-  return n_q <= 16 ? 16 : 0;
+  int rows = 16;
+  long long n_wg = 0;
+  for (; rows <= 128; rows *= 2)
+    if ((n_wg = (long long)n_unit * ((n_q + rows - 1) / rows)) <= kComputeUnits) break;
+  if (rows > 128) return n_q <= 16 ? 16 : 0;
+  if (rows <= 32) return rows;
+  if (rows == 128) return work == SmallWork::kRanked && kv <= 320 ? rows : 0;
+  const bool spare = n_wg <= kComputeUnits * 7 / 8;
+  const bool pays = work == SmallWork::kRanked || (work == SmallWork::kKeepAll && (d == 64 || spare)) ||
+                    (work == SmallWork::kAppend && d == 64 && spare) ||
+                    (work == SmallWork::kAttend && d == 64 && kv >= 512);
+  return pays ? rows : 0;
 }
 
 // bf16: the pipelined kernel used when there is enough work for it.  Keys and values are the
@@ -171,10 +196,6 @@ hipError_t launch_attend_pipe(int n_unit, int n_head, int d, const void* q, int 
                               int len1, const void* k2, const void* v2, int len2, bool append,
                               float sm_scale, void* out, hipStream_t stream,
                               hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
-// whether launch_attend would take the pipelined kernel for this shape
-inline bool attend_uses_pipe(int dtype, int n_unit, int n_q, int kv) {
-  return dtype == 1 && small_tile_rows(dtype, n_unit, n_q, kv) == 0;
-}
 
 // ---- device helpers ----
 // Workgroup coordinates as the kernels read them.  A build with SCALEKV_REVERSE_WG

@@ -378,8 +378,8 @@ hipError_t launch_step_small(const SmallStep& s, hipStream_t stream) {
   a.rows = s.rows; a.n_win = s.n_win; a.cache_len = s.cache_len; a.sm_scale = s.sm_scale;
   // Rows per workgroup: 16 on all eight waves; from 32 on, waves of 32 rows (half the reads of K and V
   // per product), one, two or four such blocks to a workgroup.
-  const int tile_rows = small_tile_rows(1, s.n_unit, s.n_q, s.len1 + s.len2);
-  if (tile_rows == 0) return hipErrorInvalidValue;
+  const int tile_rows = s.tile_rows;
+  if (tile_rows != 16 && tile_rows != 32 && tile_rows != 64 && tile_rows != 128) return hipErrorInvalidValue;
   const int QB = tile_rows == 16 ? 1 : 2;
   a.blocks_log2 = tile_rows == 128 ? 2 : tile_rows == 64 ? 1 : 0;
   a.n_tile = (s.n_q + tile_rows - 1) / tile_rows;

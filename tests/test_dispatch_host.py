@@ -1,0 +1,43 @@
+"""paper_2505_19602_amd.routes against the rules that the library is built from: a host program around
+csrc/common.h prints what they say for a grid of sizes."""
+import os
+import subprocess
+
+import torch
+
+from paper_2505_19602_amd import routes
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2505_19602_amd", "csrc")
+UNITS = (1, 2, 9, 16, 31, 32, 48, 63, 64, 96, 127, 128, 129, 200, 224, 225, 256, 257, 300, 512, 4000)
+QUERIES = (1, 4, 16, 17, 32, 33, 64, 65, 100, 128, 129, 200, 256, 300, 448, 576, 1024, 1025, 2049, 4096)
+KEYS = (1, 60, 320, 321, 511, 512, 1400, 2999, 3000, 4096, 4097, 6500, 12288, 12289, 60000)
+PROGRAM = """
+#include <cstdio>
+#include "common.h"
+using namespace scalekv;
+int main() {
+  const int units[] = {%s}, queries[] = {%s}, keys[] = {%s};
+  for (int u : units) for (int q : queries) for (int k : keys) {
+    for (int dtype = 0; dtype < 2; ++dtype) for (int d = 64; d <= 128; d += 64) for (int w = 0; w < 4; ++w)
+      printf("%%d ", small_tile_rows(dtype, d, u, q, k, (SmallWork)w));
+    printf("%%d\\n", (int)score_select_fits(1, 128, u, k));
+  }
+}
+"""
+
+
+def test_routes_are_the_rules_of_the_library(tmp_path):
+    src, exe = tmp_path / "rules.hip", tmp_path / "rules"
+    src.write_text(PROGRAM % tuple(", ".join(map(str, t)) for t in (UNITS, QUERIES, KEYS)))
+    cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-host-only", "-std=c++17", f"-I{CSRC}", str(src), "-o", str(exe)]
+    res = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stderr[-3000:]
+    lines = iter(subprocess.run([str(exe)], capture_output=True, text=True, check=True, timeout=60).stdout.splitlines())
+    for u in UNITS:
+        for q in QUERIES:
+            for k in KEYS:
+                want = [routes.small_tile_rows(dtype, d, u, q, k, w) for dtype in (torch.float32, torch.bfloat16)
+                        for d in (64, 128) for w in range(4)]
+                want += [int(routes.ranks_in_one_launch(torch.bfloat16, u, k))]
+                assert [int(x) for x in next(lines).split()] == want, (u, q, k)
+    assert next(lines, None) is None
