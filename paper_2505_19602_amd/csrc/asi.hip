@@ -14,7 +14,7 @@
 // butterfly per wave, waves in sequence): results do not depend on scheduling.
 //
 // bf16 with K' up to 256, the use the paper describes, takes a route of its own without that
-// workspace of logits (asi_stream_kernel below).
+// workspace of logits (asi_stream_kernel below) where there is enough of it (asi_stream_pays() in common.h).
 #include "common.h"
 #include "radix_select.h"
 #include "score_mfma.h"
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(kThreads) void asi_terms_kernel(ScoreWorkspace ws, 
   // attention mass on the current map: keys [hist_len, len)
   float part = 0.f;
   for (int i = hist_len + tid; i < len; i += kThreads) part += expf(logit(i) - shift);
-  const float cur = block_sum(part, red);
+  float cur = block_sum(part, red);
 
   // sum of the K' largest history weights
   const int kk = min(top_k, hist_len);
@@ -78,10 +78,12 @@ __global__ __launch_bounds__(kThreads) void asi_terms_kernel(ScoreWorkspace ws, 
     part = 0.f;
     for (int i = tid; i < hist_len; i += kThreads) {
       const uint32_t key = key_at(i);
-      if (kk == hist_len || key > T) part += expf(order_key_value(key) - shift);
+      if (kk == hist_len || key > T || order_key_is_nan(key)) part += expf(order_key_value(key) - shift);
     }
     top = block_sum(part, red);
     if (kk < hist_len) top += (float)need_eq * expf(order_key_value(T) - shift);
+    // a key of NaN makes the row NaN (the normaliser passes over one that is alone among its 64 keys)
+    if (cur != cur || top != top) cur = top = cur + top;
   }
   if (tid == 0) {
     float* out = terms + ((long long)unit * n_samp + row0 + row) * 2;
@@ -426,8 +428,8 @@ hipError_t launch_asi_terms(int n_unit, ScoreWorkspace ws, int n_rows, int hist_
 hipError_t launch_asi_stream(int dtype, int n_seq, int n_head, int d, const void* q, int n_samp, KvView k,
                              int hist_len, int len, int top_k, float sm_scale, void* ws, size_t ws_bytes,
                              float* terms, hipStream_t stream) {
-  if (dtype != 1 || top_k > kStreamTopK) return hipErrorNotSupported;
   const int n_unit = n_seq * n_head;
+  if (dtype != 1 || top_k > kStreamTopK || !asi_stream_pays(n_unit, len, n_samp)) return hipErrorNotSupported;
   // parts of at least two rounds, as many as give every compute unit a workgroup
   int n_part = 1;
   while (n_part < kMaxParts && n_unit * n_part * 2 <= 256 && len >= n_part * 2 * 2 * kRoundKeys) n_part *= 2;

@@ -104,10 +104,23 @@ hipError_t launch_positional(int n_unit, int cache_len, int n_sink, int keep, in
 hipError_t launch_asi_terms(int n_unit, ScoreWorkspace ws, int n_rows, int hist_len, int len,
                             int top_k, float* terms, int n_samp, int row0, hipStream_t stream);
 // Eq. 2 for all n_samp query rows of q ([U, n_samp, d]) without a workspace of logits: bf16 and top_k up to
-// 256, hipErrorNotSupported otherwise (or where ws_bytes does not hold the candidates)
+// 256, hipErrorNotSupported otherwise (or where ws_bytes does not hold the candidates, or where the sizes are
+// such that the route through the logits is the faster one)
 hipError_t launch_asi_stream(int dtype, int n_seq, int n_head, int d, const void* q, int n_samp, KvView k,
                              int hist_len, int len, int top_k, float sm_scale, void* ws, size_t ws_bytes,
                              float* terms, hipStream_t stream);
+// Streaming costs 20-50 us whatever the sizes (lists, merge, one workgroup per part and pass of 32 rows); the route
+// through the logits costs little where there are few keys, but reads and ranks 64 bytes a key and row anew for
+// every row.  Measured, us, logits / streamed (units x keys, query rows; d 128, K' 64):
+//   few rows in all:  4 x 1100, 16: 17 / 29     64 x 2000, 16: 39 / 48     16 x 3500, 64: 95 / 150    256 x 1100, 1: 31 / 34
+//   many:             128 x 400, 8: 29 / 24     64 x 2000, 32: 74 / 77     256 x 1100, 16: 87 / 38
+//   few, long keys:   64 x 3500, 8: 49 / 50     48 x 6300, 16: 64 / 52     16 x 10585, 32: 82 / 80    256 x 3500, 1: 78 / 62
+inline bool asi_stream_pays(int n_unit, int len, int n_samp) {
+  const long long keys = (long long)n_unit * len;
+  const int rows = n_samp < 32 ? n_samp : 32;
+  if ((n_unit < 256 ? n_unit : 256) * rows >= (n_unit >= 128 ? 1024 : 2048)) return true;
+  return rows == 32 ? keys >= 160000 : rows >= 8 ? keys >= 220000 : keys >= 800000 && len >= 3000;
+}
 // out[0], out[1] = means of the two columns of terms [n][2]; out[2] = their product
 hipError_t launch_asi_mean(const float* terms, long long n, float* out, hipStream_t stream);
 hipError_t launch_compact(int dtype, int n_seq, int n_head, int d, KvView k_src, KvView v_src,

@@ -13,6 +13,7 @@ __device__ __forceinline__ uint32_t order_key(float f) {
 __device__ __forceinline__ float order_key_value(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
+__device__ __forceinline__ bool order_key_is_nan(uint32_t k) { return k > 0xff800000u || k < 0x007fffffu; }
 
 // Inclusive prefix sum over the 64 lanes of a wave, all lanes active.  Within a row of 16 lanes
 // four data-parallel-primitive adds (shift right by 1, 2, 4, 8; lanes shifted in from outside the

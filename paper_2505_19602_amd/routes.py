@@ -1,5 +1,5 @@
-"""Which kernels a call takes, by its sizes: the dispatch rules of csrc/common.h and csrc/api.hip
-in Python, for reports (bench.py prices each kernel against its own work) and for tests
+"""Which kernels a call takes, by its sizes: the dispatch rules of csrc/common.h, csrc/asi.hip and
+csrc/api.hip in Python, for reports (bench.py prices each kernel against its own work) and for tests
 that are written for one kernel.  tests/test_dispatch_host.py compares them with the C++ rules.
 Output tensors that overlap inputs take other routes and are not covered."""
 from __future__ import annotations
@@ -47,3 +47,13 @@ def step_kernel(dtype: torch.dtype, d: int, units: int, n_cur: int, cache_len: i
 def ranks_in_one_launch(dtype: torch.dtype, units: int, cache_len: int) -> bool:
     """Scores, selection and pruning of a unit by one workgroup (or inside the kernel for small work)."""
     return dtype == torch.bfloat16 and cache_len <= 12288 and (units >= 64 or cache_len <= 4096)
+
+
+def asi_streams(dtype: torch.dtype, units: int, length: int, n_samp: int, top_k: int) -> bool:
+    """Selectivity without a workspace of logits."""
+    if dtype != torch.bfloat16 or top_k > 256:
+        return False
+    rows, keys = min(n_samp, 32), units * length
+    if min(units, 256) * rows >= (1024 if units >= 128 else 2048):
+        return True
+    return keys >= 160000 if rows == 32 else keys >= 220000 if rows >= 8 else keys >= 800000 and length >= 3000

@@ -20,7 +20,7 @@ int main() {
   for (int u : units) for (int q : queries) for (int k : keys) {
     for (int dtype = 0; dtype < 2; ++dtype) for (int d = 64; d <= 128; d += 64) for (int w = 0; w < 4; ++w)
       printf("%%d ", small_tile_rows(dtype, d, u, q, k, (SmallWork)w));
-    printf("%%d\\n", (int)score_select_fits(1, 128, u, k));
+    printf("%%d %%d\\n", (int)score_select_fits(1, 128, u, k), (int)asi_stream_pays(u, k, q));
   }
 }
 """
@@ -38,6 +38,7 @@ def test_routes_are_the_rules_of_the_library(tmp_path):
             for k in KEYS:
                 want = [routes.small_tile_rows(dtype, d, u, q, k, w) for dtype in (torch.float32, torch.bfloat16)
                         for d in (64, 128) for w in range(4)]
-                want += [int(routes.ranks_in_one_launch(torch.bfloat16, u, k))]
+                want += [int(routes.ranks_in_one_launch(torch.bfloat16, u, k)),
+                         int(routes.asi_streams(torch.bfloat16, u, k, q, 64))]
                 assert [int(x) for x in next(lines).split()] == want, (u, q, k)
     assert next(lines, None) is None

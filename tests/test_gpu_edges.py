@@ -7,6 +7,7 @@ import torch
 import oracle
 import paper_2505_19602_amd as skv
 import workloads as W
+from paper_2505_19602_amd import routes
 from parity_util import check_indices, check_output, units
 
 pytestmark = pytest.mark.gpu
@@ -121,16 +122,22 @@ def test_small_step_edges(d, S, H, L, budget, n_cur, n_win, dup):
     (1, 2, 33, 513, 31, 200, "normal"), (1, 2, 16, 2000, 100, 256, "rising"), (1, 2, 5, 3000, 500, 64, "rising"),
     (1, 2, 20, 1025, 0, 16, "ties"), (2, 2, 16, 1500, 600, 1500, "normal"), (1, 2, 16, 900, 50, 257, "normal"),
     (1, 2, 16, 5000, 30, 255, "ties"), (3, 50, 8, 1100, 70, 0, "normal"), (9, 16, 32, 700, 400, 100, "rising"),
+    # (few units and few keys take the route through the logits: the same edges with enough of them)
+    (16, 16, 4, 1, 1, 1, "normal"), (8, 16, 16, 0, 40, 64, "normal"), (8, 16, 17, 511, 1, 64, "normal"),
+    (8, 16, 33, 513, 31, 200, "normal"), (8, 16, 16, 2000, 100, 256, "rising"), (16, 16, 5, 3000, 500, 64, "rising"),
+    (8, 16, 20, 1025, 0, 16, "ties"), (8, 16, 16, 200, 50, 256, "normal"), (8, 16, 16, 5000, 30, 255, "ties"),
+    (16, 16, 1, 3100, 400, 64, "rising"), (1, 16, 32, 9500, 600, 64, "rising"), (1, 2, 40, 80500, 10, 200, "rising"),
 ])
 def test_asi_edges(d, S, H, n_samp, hist, cur, top_k, kind):
     print(f"asi d={d} S={S} H={H} n_samp={n_samp} hist={hist} cur={cur} top_k={top_k} {kind}", flush=True)
     dtype, n = torch.bfloat16, hist + cur
+    assert routes.asi_streams(dtype, S * H, n, n_samp, top_k) == (S * H > 10 or n > 50000)
     shape = skv.Shape(S, H, d, dtype)
-    q = _rand(7, (S, H, n_samp, d), dtype, 1.5)
-    k = _rand(8, (S, H, n, d), torch.float32)
+    q = _rand(7, (S, H, n_samp, d), dtype, 1.5).to(DEV)
+    k = W.normal_tensor(W.stream_key(4321, 8), (S, H, n, d), DEV)
     if kind == "rising":       # scores of every query grow along the cache
         q = (q.float() * 0.2 + 1.0).to(dtype)
-        k = k * 0.1 + torch.linspace(-0.5, 0.5, n)[None, None, :, None]
+        k = k * 0.1 + torch.linspace(-0.5, 0.5, n).to(DEV)[None, None, :, None]
     elif kind == "ties":
         k = k.repeat_interleave(9, 2)[:, :, :n]
     k = k.to(dtype)
@@ -318,8 +325,11 @@ def test_pipelined_attention_over_keys_of_weight_zero(d, n_q, lo, hi, sm_scale):
 
 # a key of NaN makes the selectivity NaN, also where a lane holds no other key
 @pytest.mark.parametrize("d", [64, 128])
-def test_asi_of_a_key_of_nan(d):
-    S, H, n_samp, hist, cur = 1, 2, 16, 512, 1
+@pytest.mark.parametrize("S,H", [(1, 2), (8, 16)])   # 128 units: the streamed route
+def test_asi_of_a_key_of_nan(d, S, H):
+    n_samp, hist, cur = 16, 512, 1
+    print(f"asi of a key of NaN d={d} units={S * H}", flush=True)
+    assert routes.asi_streams(torch.bfloat16, S * H, hist + cur, n_samp, 64) == (S * H == 128)
     shape = skv.Shape(S, H, d, torch.bfloat16)
     q, k = _rand(80, (S, H, n_samp, d), torch.bfloat16), _rand(81, (S, H, hist + cur, d), torch.bfloat16)
     k[:, :, -1] = float("nan")
