@@ -335,6 +335,10 @@ hipError_t launch_score_select(int dtype, int n_seq, int n_head, int d, const vo
                     : launch_short<128, T, true>(n_unit, cache_len, keep, idx, n_win, ex, si, stream)  \
    : plain ? launch_short<64, T, false>(n_unit, cache_len, keep, idx, n_win, ex, si, stream)           \
            : launch_short<64, T, true>(n_unit, cache_len, keep, idx, n_win, ex, si, stream))
+    // More units than compute units: 512 threads, of which two workgroups share a compute unit up to about 736 rows
+    // (23 KB of LDS and 80 bytes a row of 160 KB), and which wait for fewer waves at each barrier beyond.
+    // 1024 / 512 threads, us, ranking and pruning a fifth, d 128: 512 units x 500 rows 50.3 / 38.1, x 900 67.4 / 64.0,
+    // x 1536 91.1 / 87.0; 320 x 760 56.5 / 52.8; 800 x 1300 141.3 / 134.4.
     return n_unit > kComputeUnits ? SCALEKV_SHORT(512) : SCALEKV_SHORT(1024);
 #undef SCALEKV_SHORT
   }
