@@ -262,32 +262,6 @@ constexpr float kRescaleThreshold = 8.f;
 // covers the rounding of the division and of the product.)
 inline float no_maximum(float scale_log2e) { return -0x1.fffff0p127f / (scale_log2e > 1.f ? scale_log2e : 1.f); }
 
-__device__ __forceinline__ float bf16_bits_to_float(uint32_t bits16) {
-  return __uint_as_float(bits16 << 16);
-}
-
-template <typename T>
-struct Elem;
-template <>
-struct Elem<float> {
-  static constexpr int kPerVec = 4;  // elements per 16-byte vector
-  __device__ static void unpack(const uint4& v, float* f) {
-    f[0] = __uint_as_float(v.x); f[1] = __uint_as_float(v.y);
-    f[2] = __uint_as_float(v.z); f[3] = __uint_as_float(v.w);
-  }
-};
-struct bf16_t { uint16_t bits; };
-template <>
-struct Elem<bf16_t> {
-  static constexpr int kPerVec = 8;
-  __device__ static void unpack(const uint4& v, float* f) {
-    f[0] = __uint_as_float(v.x << 16); f[1] = __uint_as_float(v.x & 0xffff0000u);
-    f[2] = __uint_as_float(v.y << 16); f[3] = __uint_as_float(v.y & 0xffff0000u);
-    f[4] = __uint_as_float(v.z << 16); f[5] = __uint_as_float(v.z & 0xffff0000u);
-    f[6] = __uint_as_float(v.w << 16); f[7] = __uint_as_float(v.w & 0xffff0000u);
-  }
-};
-
 // ---- shared between the score finalisation and the fused select ----
 // Row normalisers max_j + log Z_j of the window rows from the per-chunk (max, sum exp) pairs, into
 // row_shift[kMaxWindow] (LDS; 0 from n_win on), by the whole workgroup (at least 2 kMaxWindow threads).
@@ -347,13 +321,6 @@ __device__ __forceinline__ float score_log_sum(const ScoreWorkspace& ws, int uni
     la[j4] = x.x; la[j4 + 1] = x.y; la[j4 + 2] = x.z; la[j4 + 3] = x.w;
   }
   return log_sum_rows(la, n_win, row_shift);
-}
-
-// round-to-nearest-even float -> bf16 bits (NaN kept quiet)
-__device__ __forceinline__ uint32_t float_to_bf16_bits(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (u >> 16) | 0x40u;
-  return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
 }
 
 }  // namespace scalekv
