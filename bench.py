@@ -64,7 +64,8 @@ ATTEND_PIPE_TRAFFIC = {
 VARIANTS = ("scalekv", "literal", "pyramid", "sliding", "sinks", "calibrated")
 # stages between consecutive events of one call, per variant
 # ("score" holds the whole ranking where the selection kernel streams the keys itself: one launch;
-# "select" is then only what lies between two events)
+# "select" is then only what lies between two events.  Small maps: "attend" holds the pruning as well and,
+# for caches of up to 1536 rows, the ranking: the stages before it are then empty)
 STAGES = {
     "scalekv": ("score", "select", "compact", "attend"),
     "pyramid": ("score", "select", "compact", "attend"),
@@ -453,6 +454,7 @@ def main() -> int:
     import torch
     import paper_2505_19602_amd as skv
     import workloads as W
+    from paper_2505_19602_amd import routes
 
     if not torch.cuda.is_available():
         print("bench.py needs a GPU", file=sys.stderr)
@@ -593,9 +595,16 @@ def main() -> int:
             b_uni = full if k < cfg.first_compressed_scale else max(1, int(uniform_frac * full + 0.5))
             for l, b in enumerate(skv.pyramid_budgets(Lyr, b_uni, b_uni // 4 if k >= cfg.first_compressed_scale else b_uni)):
                 table[l][k - 1] = b
-    def is_big(n_cur):
-        """shapes that take the pipelined attention kernel, which also appends the map's K/V itself"""
-        return n_cur > 128 and dtype == torch.bfloat16 and d == 128
+    def is_big(m):
+        """calls whose attention is the pipelined kernel"""
+        if variant in ("scalekv", "pyramid", "calibrated"):
+            return routes.step_kernel(dtype, d, U, m["n_cur"], m["cache_len"], m["keep"]) == "pipelined"
+        work = routes.APPEND if variant == "literal" else routes.ATTEND
+        return routes.attend_kernel(dtype, d, U, m["n_cur"], m["kv_len"], work) == "pipelined"
+
+    def append_split(m, append_bytes):
+        """bytes of appending the map's K/V: (in the pruning kernel, in the attention kernel)"""
+        return (append_bytes, 0.0) if dtype == torch.float32 else (0.0, append_bytes)
 
     calls, meta = [], []
     lens_before_last = None
@@ -624,11 +633,12 @@ def main() -> int:
                 call = skv.PreparedStep(shape, x.q, x.k_cur, x.v_cur, windows[k], srcs[l][0], srcs[l][1], lens[l],
                                         table[l][k - 1], dst[0], dst[1], outs[k], None, ws)
                 keep = call.new_len - n_cur
-                m.update(keep=keep, kv_len=keep + n_cur, new_len=call.new_len,
-                         move_bytes=2.0 * 2.0 * keep * d * e * U + (4.0 * keep * U if keep < lens[l] else 0)
-                         + (0.0 if is_big(n_cur) else append_bytes),
-                         append_in_attend=append_bytes if is_big(n_cur) else 0.0)
-                if 0 < keep < lens[l]:
+                m.update(keep=keep, kv_len=keep + n_cur, new_len=call.new_len)
+                pruned_too, attended_too = append_split(m, append_bytes)
+                m.update(move_bytes=2.0 * 2.0 * keep * d * e * U + (4.0 * keep * U if keep < lens[l] else 0) + pruned_too,
+                         append_in_attend=attended_too)
+                # (a step whose pruning is part of the attention kernel has no kernel that these bytes belong to)
+                if 0 < keep < lens[l] and routes.step_kernel(dtype, d, U, n_cur, lens[l], keep) != "small":
                     m["score_bytes"] = (lens[l] * d * e + len(windows[k]) * d * e + 4.0 * lens[l]) * U
                 calls.append(LibCall(call))
                 srcs[l], lens[l] = dst, call.new_len
@@ -641,10 +651,10 @@ def main() -> int:
                                                lens[l], budget, dst[0], dst[1], outs[k], None, ws)
                 assert call.moved == (k >= cfg.first_compressed_scale)
                 total = lens[l] + n_cur
-                m.update(keep=call.keep, kv_len=total, new_len=call.keep,
-                         move_bytes=(0.0 if is_big(n_cur) else append_bytes)
-                         + (2.0 * 2.0 * call.keep * d * e * U + 4.0 * call.keep * U if call.moved else 0),
-                         append_in_attend=append_bytes if is_big(n_cur) else 0.0)
+                m.update(keep=call.keep, kv_len=total, new_len=call.keep)
+                pruned_too, attended_too = append_split(m, append_bytes)
+                m.update(move_bytes=pruned_too + (2.0 * 2.0 * call.keep * d * e * U + 4.0 * call.keep * U if call.moved else 0),
+                         append_in_attend=attended_too)
                 calls.append(LibCall(call))
                 lens[l] = call.keep
                 if call.moved:
@@ -679,14 +689,14 @@ def main() -> int:
         log(f"warm-up {w + 1}/{args.warmup} done")
 
     # Timed region: K passes of the sequence.  The only events inside it bracket launches of the
-    # dominant kernel (the pipelined bf16 attention, n_cur > 128); they sit on the launch stream
+    # dominant kernel (the pipelined bf16 attention, all but the small maps); they sit on the launch stream
     # (attached to the kernel's own dispatch) and give that kernel's average duration for the
     # roofline.  Timing every such launch in every pass costs about 1 % of the pass, so each of them
     # is timed in exactly one of the K passes (the j-th such launch of the sequence in pass j mod K).
     n_ev = len(stages) + 1
     big_no = {}
     for i, m in enumerate(meta):
-        if is_big(m["n_cur"]):
+        if is_big(m):
             big_no[i] = len(big_no)
     ev_steps = [[events.block(n_ev, only=(att, att + 1)) if i in big_no and big_no[i] % args.steps == s else None
                  for i in range(len(meta))] for s in range(args.steps)]
@@ -755,12 +765,12 @@ def main() -> int:
             per_scale_ms[k] += sum(t)
             attend_all["ms"] += t[att]; attend_all["flops"] += 4.0 * m["n_cur"] * m["kv_len"] * d * U
             if m["score_bytes"] > 0 and "score" in stages:
-                # a step that ranks: score, select and the gather of the kept rows run in ONE kernel, so the
+                # a step that ranks before its attention: score, select and the gather of the kept rows run in ONE kernel, so the
                 # streaming bytes of all three are priced against the time of the three event slots together
                 # (where the library ranks in one launch -- bf16, and enough units or a short cache -- the
                 # "score" slot brackets exactly that kernel and the other two slots hold nothing but the
                 # next event's own cost)
-                one_launch = dtype == torch.bfloat16 and m["cache_len"] <= 12288 and (U >= 64 or m["cache_len"] <= 4096)
+                one_launch = routes.ranks_in_one_launch(dtype, U, m["cache_len"])
                 t_rank = t[stages.index("score")] if one_launch else \
                     sum(t[stages.index(n)] for n in ("score", "select", "compact"))
                 for st_, on in ((compact_stat, True), (compact_last, k == K)):

@@ -310,6 +310,10 @@ scalekv_status scalekv_pyramid_budgets(int32_t n_layer, int64_t b_uniform, int64
  * anyway).  A NULL entry is left out, so {0,0,0,e3,e4} brackets the attend kernel
  * alone.  scalekv_step_append_first records them too: events[0] before the first
  * kernel, events[1..4] after its append, attend, score+select and compact kernels.
+ * Stages that share a kernel share the time of the last of them: where the ranking is one
+ * kernel (bf16) it lies between events[0] and events[1], the pruning with it; on small bf16
+ * maps one kernel prunes, appends and attends, for caches of up to 1536 rows ranks as
+ * well, and lies between events[3] and events[4], so that the slots before are empty.
  * Where the attention runs in the pipelined bf16 kernel (all but small maps) the
  * two events around it are not recorded as stream operations of their own but attached
  * to that kernel's dispatch and receive its start and end times, so timing that kernel
