@@ -7,7 +7,9 @@ import torch
 import oracle
 import paper_2505_19602_amd as skv
 import workloads as W
+from paper_2505_19602_amd import routes
 from parity_util import TOL, check_indices, check_output, units
+from parity_util import units as all_units
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -159,23 +161,27 @@ def test_attend_matches_oracle(dtype, d, n_q, kv_len):
 
 @pytest.mark.parametrize("where", ["late_in_cache", "in_current_map", "second_tile", "some_rows_only",
                                    "large_but_unchecked", "huge_values"])
-def test_attend_scores_far_above_the_first_tile(where):
+@pytest.mark.parametrize("H,d,n_q", [(2, 128, 300), (9, 128, 2049), (9, 64, 2049)])   # 2049: the pipelined kernel
+def test_attend_scores_far_above_the_first_tile(where, H, d, n_q):
     # Keys whose scores sit far above everything in the first 64 rows: exp2 of their distance to
     # the first tile's maximum leaves the range the kernel adds up unchecked (2^100; for the larger
     # gaps, fp32 altogether), so the workgroup has to fall back to the running-maximum scheme.
     # "large_but_unchecked": a gap of about 34 natural units (2^49), which the kernel adds up as it
     # is; "huge_values": the same gap with value rows of magnitude 2^100, whose weighted sums leave
     # fp32 although the weights do not, so the accumulators' own check has to trigger.
-    S, H, d, n_q, len1, len2 = 1, 2, 128, 300, 400, 300
+    S, len1, len2 = 1, 400, n_q
     dtype = torch.bfloat16
-    _note(f"attend overflow fallback: {where}")
+    _note(f"attend overflow fallback: {where} d={d} n_q={n_q}")
+    assert routes.attend_kernel(dtype, d, S * H, n_q, len1 + len2) == ("pipelined" if n_q == 2049 else "small")
+    pick = list(range(S * H)) if n_q == 300 else [0, S * H - 1]              # units and query rows that are compared
+    rows = list(range(n_q)) if n_q == 300 else sorted({*range(12), *range(12, n_q, 37), n_q - 1})
     shape = skv.Shape(S, H, d, dtype)
     q = _rand(40, (S, H, n_q, d), dtype)
     ks, vs = _rand(41, (S, H, len1 + len2, d), dtype, 0.05), _rand(42, (S, H, len1 + len2, d), dtype)
     row = {"late_in_cache": len1 - 3, "in_current_map": len1 + 170, "second_tile": 70, "some_rows_only": 333,
            "large_but_unchecked": 200, "huge_values": 200}[where]
     gain = {"late_in_cache": 9.0, "in_current_map": 30.0, "second_tile": 10.0, "some_rows_only": 10.0,
-            "large_but_unchecked": 3.0, "huge_values": 3.0}[where]
+            "large_but_unchecked": 3.0, "huge_values": 3.0}[where] * (128 / d) ** 0.5
     post = 1.0
     if where == "huge_values":
         vs = (vs.float() * 2.0 ** 100).to(dtype)
@@ -190,8 +196,8 @@ def test_attend_scores_far_above_the_first_tile(where):
     out = torch.full((S, H, n_q, d), float("nan"), dtype=dtype, device=DEV)
     skv.attend(shape, q.to(DEV), ks.to(DEV), vs.to(DEV), len1 + len2, out)       # one segment
     torch.cuda.synchronize()
-    ref = oracle.attend(units(q), units(ks), units(vs)) * post
-    check_output(out.float() * post, ref, dtype, f"attend {where}")
+    ref = oracle.attend(units(q)[pick][:, rows], units(ks)[pick], units(vs)[pick]) * post
+    check_output(units(out.float() * post)[pick][:, rows], ref, dtype, f"attend {where}")
     # the same keys as cache + current map through the step (budget = len1 keeps every cached row):
     # two key segments, and the kernel appends the map's K/V itself
     kd = torch.zeros(S, H, len1 + len2 + 2, d, dtype=dtype, device=DEV); vd = torch.zeros_like(kd)
@@ -202,7 +208,7 @@ def test_attend_scores_far_above_the_first_tile(where):
     assert new_len == len1 + len2
     assert torch.equal(kd[:, :, :new_len].cpu(), ks) and torch.equal(vd[:, :, :new_len].cpu(), vs)
     assert torch.all(kd[:, :, new_len:] == 0) and torch.all(vd[:, :, new_len:] == 0)
-    check_output(out2.float() * post, ref, dtype, f"step {where}")
+    check_output(units(out2.float() * post)[pick][:, rows], ref, dtype, f"step {where}")
 
 
 def test_attend_closed_forms_on_gpu():
@@ -343,12 +349,14 @@ def test_step_long_cache_and_other_shapes():
         check_output(out, ref["out"], dtype, f"step d={d} L={L}")
 
 
-def test_step_is_reproducible_bit_for_bit_and_stays_inside_its_buffers():
+@pytest.mark.parametrize("S,H,d,n_cur,L,budget,kernel", [
+    (2, 2, 128, 300, 500, 200, "small"), (4, 65, 128, 150, 300, 100, "pipelined"), (4, 65, 64, 150, 300, 100, "pipelined")])
+def test_step_is_reproducible_bit_for_bit_and_stays_inside_its_buffers(S, H, d, n_cur, L, budget, kernel):
     # no atomics on floats and a fixed reduction order everywhere: two runs give the same bits;
     # rows past the new cache length and the spare tail of the output keep their canary
-    S, H, d, n_cur, L, budget = 2, 2, 128, 300, 500, 200
     dtype = torch.bfloat16
-    _note("step reproducibility")
+    _note(f"step reproducibility {S}x{H} units, d={d}")
+    assert routes.step_kernel(dtype, d, S * H, n_cur, L, budget) == kernel
     shape = skv.Shape(S, H, d, dtype)
     q, kc, vc = (_rand(60 + i, (S, H, n_cur, d), dtype).to(DEV) for i in range(3))
     ks, vs = _rand(63, (S, H, L, d), dtype).to(DEV), _rand(64, (S, H, L, d), dtype).to(DEV)
@@ -370,12 +378,13 @@ def test_step_is_reproducible_bit_for_bit_and_stays_inside_its_buffers():
     assert torch.isfinite(out.float()).all()
 
 
-@pytest.mark.parametrize("n_cur", [48, 200])
-def test_step_with_caches_that_are_views_of_larger_buffers(n_cur):
+@pytest.mark.parametrize("n_cur,S,H", [(48, 2, 3), (200, 2, 3), (70, 4, 65)])   # 260 units: the pipelined kernel
+def test_step_with_caches_that_are_views_of_larger_buffers(n_cur, S, H):
     # head stride > capacity * d, for the source and the destination alike
-    S, H, d, L, budget = 2, 3, 128, 260, 100
+    d, L, budget = 128, 260, 100
     dtype = torch.bfloat16
-    _note(f"step on strided cache views n_cur={n_cur}")
+    _note(f"step on strided cache views n_cur={n_cur} units={S * H}")
+    assert routes.step_kernel(dtype, d, S * H, n_cur, L, budget) == ("small" if S * H == 6 else "pipelined")
     shape = skv.Shape(S, H, d, dtype)
     q, kc, vc = (_rand(80 + i, (S, H, n_cur, d), dtype).to(DEV) for i in range(3))
     big_k, big_v = _rand(83, (S, H, L + 77, d), dtype).to(DEV), _rand(84, (S, H, L + 77, d), dtype).to(DEV)
@@ -391,22 +400,26 @@ def test_step_with_caches_that_are_views_of_larger_buffers(n_cur):
     torch.cuda.synchronize()
     assert new_len == cap
     assert torch.all(kd_big[:, :, cap:] == 3.0) and torch.all(vd_big[:, :, cap:] == 3.0)
-    g_idx = idx.cpu().numpy().reshape(S * H, budget)
-    own = oracle.step(units(q), units(kc), units(vc), win, units(ks)[:, :L], units(vs)[:, :L], budget)
-    for u in range(S * H):
+    pick = sorted({0, 1, S * H // 2, S * H - 1})
+    sub = lambda t: units(t)[pick]
+    g_idx = idx.cpu().numpy().reshape(S * H, budget)[pick]
+    own = oracle.step(sub(q), sub(kc), sub(vc), win, sub(ks)[:, :L], sub(vs)[:, :L], budget)
+    for u in range(len(pick)):
         check_indices(g_idx[u], own["log_scores"][u], budget, own["idx"][u])
-    ref = oracle.step(units(q), units(kc), units(vc), win, units(ks)[:, :L], units(vs)[:, :L], budget, force_idx=g_idx)
-    assert np.array_equal(units(kd.contiguous()).double().numpy(), ref["k_dst"])
-    assert np.array_equal(units(vd.contiguous()).double().numpy(), ref["v_dst"])
-    check_output(out, ref["out"], dtype, "strided step")
+    ref = oracle.step(sub(q), sub(kc), sub(vc), win, sub(ks)[:, :L], sub(vs)[:, :L], budget, force_idx=g_idx)
+    assert np.array_equal(sub(kd.contiguous()).double().numpy(), ref["k_dst"])
+    assert np.array_equal(sub(vd.contiguous()).double().numpy(), ref["v_dst"])
+    check_output(sub(out), ref["out"], dtype, "strided step")
 
 
-def test_step_can_be_captured_in_a_graph_and_replayed():
+@pytest.mark.parametrize("S,H,n_cur,kernel", [(1, 4, 200, "small"), (4, 65, 60, "pipelined")])
+def test_step_can_be_captured_in_a_graph_and_replayed(S, H, n_cur, kernel):
     # The library neither allocates nor synchronises, so a step can be recorded into a HIP graph;
     # every replay (with eager work and synchronisations in between) must reproduce the eager bits.
-    S, H, d, n_cur, L, budget = 1, 4, 128, 200, 300, 120
+    d, L, budget = 128, 300, 120
     dtype = torch.bfloat16
-    _note("step under graph capture")
+    _note(f"step under graph capture, {kernel} attention")
+    assert routes.step_kernel(dtype, d, S * H, n_cur, L, budget) == kernel
     shape = skv.Shape(S, H, d, dtype)
     q, kc, vc = (_rand(70 + i, (S, H, n_cur, d), dtype).to(DEV) for i in range(3))
     ks, vs = _rand(73, (S, H, L, d), dtype).to(DEV), _rand(74, (S, H, L, d), dtype).to(DEV)
@@ -438,10 +451,13 @@ def test_step_can_be_captured_in_a_graph_and_replayed():
         assert torch.equal(out, out0) and torch.equal(idx, idx0), f"replay {rep}"
 
 
-@pytest.mark.parametrize("n_cur", [40, 160])   # 160: the pipelined attention kernel with its two key segments
-def test_step_edge_budgets(n_cur):
-    dtype, S, H, d, L = torch.bfloat16, 1, 2, 128, 90
-    _note(f"step edge budgets n_cur={n_cur}")
+@pytest.mark.parametrize("n_cur,S,H", [(40, 1, 2), (160, 1, 2), (160, 4, 65)])   # 260 units: the pipelined attention
+# kernel with its two key segments
+def test_step_edge_budgets(n_cur, S, H):
+    dtype, d, L = torch.bfloat16, 128, 90
+    pick = list(range(S * H)) if S * H == 2 else [0, S * H - 1]
+    units = lambda t: all_units(t)[pick]        # what is compared
+    _note(f"step edge budgets n_cur={n_cur} units={S * H}")
     shape = skv.Shape(S, H, d, dtype)
     q, kc, vc = (_rand(40 + i, (S, H, n_cur, d), dtype) for i in range(3))
     ks, vs = _rand(43, (S, H, L, d), dtype), _rand(44, (S, H, L, d), dtype)
@@ -458,16 +474,17 @@ def test_step_edge_budgets(n_cur):
                            ks.to(DEV), vs.to(DEV), L, budget, kd, vd, out, idx, use_ws)
         torch.cuda.synchronize()
         assert new_len == keep + n_cur
-        ref = oracle.step(units(q), units(kc), units(vc), win, units(ks), units(vs), budget,
-                          force_idx=idx.cpu().numpy().reshape(S * H, keep))
+        assert routes.step_kernel(dtype, d, S * H, n_cur, L, budget) == ("small" if S * H == 2 else "pipelined")
+        g_idx = idx.cpu().numpy().reshape(S * H, keep)[pick]
+        ref = oracle.step(units(q), units(kc), units(vc), win, units(ks), units(vs), budget, force_idx=g_idx)
         if budget >= L:   # exact attention over the whole cache and the current map
             full = oracle.attend(units(q), torch.cat([units(ks), units(kc)], 1), torch.cat([units(vs), units(vc)], 1))
             assert np.abs(full - ref["out"]).max() < 1e-12
-            assert np.array_equal(idx.cpu().numpy().reshape(S * H, keep), np.tile(np.arange(L), (S * H, 1)))
-        check_output(out, ref["out"], dtype, f"budget {budget}")
+            assert np.array_equal(g_idx, np.tile(np.arange(L), (len(pick), 1)))
+        check_output(units(out), ref["out"], dtype, f"budget {budget}")
         own = oracle.step(units(q), units(kc), units(vc), win, units(ks), units(vs), budget)
-        for u in range(S * H):
-            check_indices(idx.cpu().numpy().reshape(S * H, keep)[u], own["log_scores"][u], keep, own["idx"][u])
+        for u in range(len(pick)):
+            check_indices(g_idx[u], own["log_scores"][u], keep, own["idx"][u])
 
 
 def test_step_sweep_of_sizes_around_the_tile_edges():
@@ -555,23 +572,31 @@ def test_step_random_shapes_follow_the_oracle():
 
 
 def test_attend_heavy_tailed_keys_at_random_shapes():
-    """The pipelined attention kernel on Student-t keys scaled by 1 to 10: rows whose later scores
-    sit a little, far, or too far above the first tile's maximum, so that workgroups with and
+    """Attention on Student-t keys scaled by 1 to 10: rows whose later scores sit a little, far, or
+    too far above the first tile's maximum.  The first 24 cases are for the kernel that follows the
+    running maximum; the others are large enough for the pipelined one, where workgroups with and
     without the repeat pass (and both kinds in one launch) are compared with the oracle."""
     rng = np.random.default_rng(20251129)
-    dtype, d = torch.bfloat16, 128
-    for case in range(24):
-        S, H = int(rng.integers(1, 3)), int(rng.integers(1, 4))
-        n_q, kv = int(rng.integers(129, 700)), int(rng.integers(65, 3000))
+    dtype = torch.bfloat16
+    for case in range(36):
+        large = case >= 24
+        d = 64 if large and case % 2 else 128
+        S, H = (int(rng.integers(1, 3)), int(rng.integers(9, 13))) if large else (int(rng.integers(1, 3)), int(rng.integers(1, 4)))
+        n_q, kv = (int(rng.integers(2049, 2400)), int(rng.integers(321, 2000))) if large else \
+            (int(rng.integers(129, 700)), int(rng.integers(65, 3000)))
         scale = float(rng.choice([1.0, 3.0, 6.0, 10.0]))
-        _note(f"heavy-tailed attend case={case} S={S} H={H} n_q={n_q} kv={kv} scale={scale}")
+        _note(f"heavy-tailed attend case={case} S={S} H={H} n_q={n_q} kv={kv} d={d} scale={scale}")
+        assert routes.attend_kernel(dtype, d, S * H, n_q, kv) == ("pipelined" if large else "small")
         q = _rand(7000 + 3 * case, (S, H, n_q, d), dtype)
         k = (W.student_t_tensor(W.stream_key(7001, case), W.stream_key(7002, case), (S, H, kv, d)) * scale).to(dtype)
         v = _rand(7000 + 3 * case + 2, (S, H, kv, d), dtype)
         out = torch.full((S, H, n_q, d), float("nan"), dtype=dtype, device=DEV)
         skv.attend(skv.Shape(S, H, d, dtype), q.to(DEV), k.to(DEV), v.to(DEV), kv, out)
         torch.cuda.synchronize()
-        check_output(out, oracle.attend(units(q), units(k), units(v)), dtype, f"heavy-tailed attend case {case}")
+        pick = [0, S * H - 1] if large else list(range(S * H))
+        rows = sorted({*range(int(rng.integers(0, 29)), n_q, 29), n_q - 1}) if large else list(range(n_q))
+        ref = oracle.attend(units(q)[pick][:, rows], units(k)[pick], units(v)[pick])
+        check_output(units(out)[pick][:, rows], ref, dtype, f"heavy-tailed attend case {case}")
 
 
 def test_step_one_hot_pattern_selects_its_argmax():
