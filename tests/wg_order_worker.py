@@ -15,26 +15,36 @@ DEV = "cuda"
 def run_all():
     import paper_2505_19602_amd as skv
     import workloads as W
+    from paper_2505_19602_amd import routes
 
     out = {"library": np.array(os.path.basename(skv.lib_path()))}
 
     def rand(key, shape, dtype):
-        return W.normal_tensor(W.stream_key(4321, key), shape).to(dtype).to(DEV)
+        return W.normal_tensor(W.stream_key(4321, key), shape, DEV).to(dtype)
 
     def keep_np(name, t):
         t = t.detach().cpu()
         out[name] = (t.view(torch.int16) if t.dtype == torch.bfloat16 else t).numpy().copy()
 
-    # (tag, S, H, d, n_cur, cache_len, budget, dtype): pipelined attention with a fused ranking
-    # kernel, the small-map attention kernel, a head size of 64, fp32, and a cache longer than the
-    # ranking kernel's LDS (the two-launch route)
-    cases = [("pipe", 3, 5, 128, 300, 900, 333, torch.bfloat16),
-             ("pipe_ragged", 2, 4, 128, 400, 1500, 210, torch.bfloat16),
-             ("small", 2, 3, 128, 36, 140, 50, torch.bfloat16),
-             ("d64", 2, 2, 64, 70, 260, 90, torch.bfloat16),
-             ("fp32", 1, 2, 64, 33, 150, 60, torch.float32),
-             ("long", 1, 2, 128, 130, 12600, 1000, torch.bfloat16)]
-    for c, (tag, S, H, d, n_cur, L, budget, dtype) in enumerate(cases):
+    # (tag, S, H, d, n_cur, cache_len, budget, dtype, attention kernel): whole steps in one launch (several
+    # workgroups to a unit), fp32, a ranking in several launches in front of the small kernel; then the
+    # pipelined attention, which appends, behind each form of the ranking kernel: in LDS, in registers, and
+    # with the rows beyond them in the workspace
+    cases = [("one_launch", 3, 5, 128, 300, 900, 333, torch.bfloat16, "small"),
+             ("one_launch_ragged", 2, 4, 128, 400, 1500, 210, torch.bfloat16, "small"),
+             ("small", 2, 3, 128, 36, 140, 50, torch.bfloat16, "small"),
+             ("d64", 2, 2, 64, 70, 260, 90, torch.bfloat16, "small"),
+             ("fp32", 1, 2, 64, 33, 150, 60, torch.float32, "f32"),
+             ("long", 1, 2, 128, 130, 12600, 1000, torch.bfloat16, "small"),
+             ("registers_small", 1, 6, 128, 40, 1700, 300, torch.bfloat16, "small"),
+             ("pipe_short", 5, 52, 128, 150, 300, 77, torch.bfloat16, "pipelined"),
+             ("pipe_short_d64", 5, 52, 64, 40, 300, 77, torch.bfloat16, "pipelined"),
+             ("pipe_registers", 1, 65, 128, 530, 1700, 300, torch.bfloat16, "pipelined"),
+             ("pipe_registers_d64", 1, 65, 64, 530, 1700, 300, torch.bfloat16, "pipelined"),
+             ("pipe_far", 1, 65, 128, 530, 4300, 300, torch.bfloat16, "pipelined"),
+             ("pipe_far_d64", 1, 65, 64, 530, 4300, 300, torch.bfloat16, "pipelined")]
+    for c, (tag, S, H, d, n_cur, L, budget, dtype, kernel) in enumerate(cases):
+        assert routes.step_kernel(dtype, d, S * H, n_cur, L, budget) == kernel, tag
         print(f"workgroup order: step {tag}: {S}x{H} units, {n_cur} queries, {L} cached rows", flush=True)
         shape = skv.Shape(S, H, d, dtype)
         q, kc, vc = (rand(10 * c + i, (S, H, n_cur, d), dtype) for i in range(3))
@@ -63,38 +73,44 @@ def run_all():
         for name, t in (("scores", scores), ("idx", idx2), ("k_dst", kd2), ("v_dst", vd2), ("out", o2)):
             keep_np(f"stages_{tag}_{name}", t)
 
-    # the literal order of Sec. 3.3 (append, attend, rank with pooling and forced window rows)
-    print("workgroup order: step_append_first", flush=True)
-    S, H, d, n_cur, L, budget, dtype = 2, 3, 128, 144, 500, 120, torch.bfloat16
-    shape = skv.Shape(S, H, d, dtype)
-    q, kc, vc = (rand(900 + i, (S, H, n_cur, d), dtype) for i in range(3))
-    cap = L + n_cur
-    kcache, vcache = rand(903, (S, H, cap, d), dtype), rand(904, (S, H, cap, d), dtype)
-    win = skv.window_centroids(12, 12)
-    keep = len(win) + min(budget, L + n_cur - len(win))
-    kn = torch.zeros((S, H, keep, d), dtype=dtype, device=DEV); vn = torch.zeros_like(kn)
-    o = torch.zeros((S, H, n_cur, d), dtype=dtype, device=DEV)
-    idx = torch.full((S, H, keep), -1, dtype=torch.int32, device=DEV)
-    ws = torch.zeros(skv.workspace_bytes(shape, cap, n_cur), dtype=torch.uint8, device=DEV)
-    skv.step_append_first(shape, q, kc, vc, win, 7, kcache, vcache, L, budget, kn, vn, o, idx, ws)
-    torch.cuda.synchronize()
-    for name, t in (("k_next", kn), ("v_next", vn), ("out", o), ("idx", idx)):
-        keep_np(f"literal_{name}", t)
+    # the literal order of Sec. 3.3 (append, attend, rank with pooling and forced window rows), with both
+    # attention kernels; 1700 rows: the ranking kernel that holds the logits in registers
+    for tag, H, L in (("", 3, 500), ("_pipe", 130, 200), ("_registers", 130, 1556)):
+        S, d, n_cur, budget, dtype = 2, 128, 144, 120, torch.bfloat16
+        print(f"workgroup order: step_append_first {S}x{H} units, {L} cached rows", flush=True)
+        assert routes.attend_kernel(dtype, d, S * H, n_cur, L + n_cur, routes.APPEND) == ("small" if H == 3 else "pipelined")
+        shape = skv.Shape(S, H, d, dtype)
+        q, kc, vc = (rand(900 + i, (S, H, n_cur, d), dtype) for i in range(3))
+        cap = L + n_cur
+        kcache, vcache = rand(903, (S, H, cap, d), dtype), rand(904, (S, H, cap, d), dtype)
+        win = skv.window_centroids(12, 12)
+        keep = len(win) + min(budget, L + n_cur - len(win))
+        kn = torch.zeros((S, H, keep, d), dtype=dtype, device=DEV); vn = torch.zeros_like(kn)
+        o = torch.zeros((S, H, n_cur, d), dtype=dtype, device=DEV)
+        idx = torch.full((S, H, keep), -1, dtype=torch.int32, device=DEV)
+        ws = torch.zeros(skv.workspace_bytes(shape, cap, n_cur), dtype=torch.uint8, device=DEV)
+        skv.step_append_first(shape, q, kc, vc, win, 7, kcache, vcache, L, budget, kn, vn, o, idx, ws)
+        torch.cuda.synchronize()
+        for name, t in (("k_cache", kcache), ("k_next", kn), ("v_next", vn), ("out", o), ("idx", idx)):
+            keep_np(f"literal{tag}_{name}", t)
 
     # Eq. 2 terms and position-only retention
     print("workgroup order: asi, select_positional", flush=True)
-    S, H, d, dtype = 2, 2, 128, torch.bfloat16
+    hist, cur, d, dtype = 700, 256, 128, torch.bfloat16
+    for tag, S, H in (("", 2, 2), ("_streamed", 8, 16)):
+        assert routes.asi_streams(dtype, S * H, hist + cur, 16, 64) == bool(tag)
+        shape = skv.Shape(S, H, d, dtype)
+        k = rand(950, (S, H, hist + cur, d), dtype)
+        qs = rand(951, (S, H, 16, d), dtype)
+        ws = torch.zeros(skv.workspace_bytes(shape, hist + cur, 16), dtype=torch.uint8, device=DEV)
+        terms = torch.zeros((S, H, 16, 2), dtype=torch.float32, device=DEV)
+        asi_out = torch.zeros(3, dtype=torch.float32, device=DEV)
+        skv.asi(shape, qs, k, hist, cur, 64, terms, asi_out, ws)
+        torch.cuda.synchronize()
+        keep_np(f"asi{tag}_terms", terms)
+        keep_np(f"asi{tag}_out", asi_out)
+    S, H = 2, 2
     shape = skv.Shape(S, H, d, dtype)
-    hist, cur = 700, 256
-    k = rand(950, (S, H, hist + cur, d), dtype)
-    qs = rand(951, (S, H, 16, d), dtype)
-    ws = torch.zeros(skv.workspace_bytes(shape, hist + cur, 16), dtype=torch.uint8, device=DEV)
-    terms = torch.zeros((S, H, 16, 2), dtype=torch.float32, device=DEV)
-    asi_out = torch.zeros(3, dtype=torch.float32, device=DEV)
-    skv.asi(shape, qs, k, hist, cur, 64, terms, asi_out, ws)
-    torch.cuda.synchronize()
-    keep_np("asi_terms", terms)
-    keep_np("asi_out", asi_out)
     idxp = torch.full((S, H, 80), -1, dtype=torch.int32, device=DEV)
     skv.select_positional(shape, 500, 16, 64, idxp)
     torch.cuda.synchronize()
