@@ -55,8 +55,9 @@ def test_score_f32_edges(d, L, n_win):
     assert np.abs(ls.cpu().numpy().reshape(S * H, L).astype(np.float64) - ref).max() < 2e-4
 
 
-def _step_against_oracle(S, H, d, L, budget, n_cur, n_win, pick, seed, dup=1, with_idx=True):
-    """One step; units `pick` followed by the oracle.  dup > 1: cached rows repeat in runs of that length (ties)."""
+def _step_against_oracle(S, H, d, L, budget, n_cur, n_win, pick, seed, dup=1, idx_of=None):
+    """One step; units `pick` followed by the oracle.  dup > 1: cached rows repeat in runs of that length (ties).
+    idx_of: the indices of the same step; it is then called without an index list.  Returns its outputs and indices."""
     dtype = torch.bfloat16
     shape = skv.Shape(S, H, d, dtype)
     keep = min(budget, L)
@@ -68,7 +69,7 @@ def _step_against_oracle(S, H, d, L, budget, n_cur, n_win, pick, seed, dup=1, wi
     cap = keep + n_cur + 2
     kd = torch.full((S, H, cap, d), 7.0, dtype=dtype, device=DEV); vd = torch.full_like(kd, 7.0)
     out = torch.full((S, H, n_cur, d), float("nan"), dtype=dtype, device=DEV)
-    idx = torch.full((S, H, keep), -1, dtype=torch.int32, device=DEV) if with_idx else None
+    idx = torch.full((S, H, keep), -1, dtype=torch.int32, device=DEV) if idx_of is None else None
     ws = torch.empty(skv.workspace_bytes(shape, max(L, 1), n_cur), dtype=torch.uint8, device=DEV)
     assert skv.step(shape, q.to(DEV), kc.to(DEV), vc.to(DEV), win, ks.to(DEV), vs.to(DEV), L, budget, kd, vd, out, idx,
                     ws) == keep + n_cur
@@ -82,19 +83,18 @@ def _step_against_oracle(S, H, d, L, budget, n_cur, n_win, pick, seed, dup=1, wi
         own = oracle.select(ls, budget)
     else:
         ls, own = np.zeros((len(pick), L)), np.tile(np.arange(keep), (len(pick), 1))
-    if with_idx:
-        got = idx.cpu().numpy().reshape(S * H, keep)[pick]
-        for u in range(len(pick)):
-            if dup == 1:
-                check_indices(got[u], ls[u], keep, own[u])
-            else:      # equal rows have equal scores: of a run that is cut, the lower rows are kept
-                assert np.array_equal(got[u], own[u])
-    else:
-        got = own
+    idx = idx if idx_of is None else idx_of
+    got = idx.cpu().numpy().reshape(S * H, keep)[pick]
+    for u in range(len(pick)):
+        if dup == 1:
+            check_indices(got[u], ls[u], keep, own[u])
+        else:      # equal rows have equal scores: of a run that is cut, the lower rows are kept
+            assert np.array_equal(got[u], own[u])
     ref = oracle.step(sub(q), sub(kc), sub(vc), win, kpart, vpart, budget, force_idx=got)
     assert np.array_equal(sub(kd)[:, : keep + n_cur].double().numpy(), ref["k_dst"])
     assert np.array_equal(sub(vd)[:, : keep + n_cur].double().numpy(), ref["v_dst"])
     check_output(sub(out), ref["out"], dtype, "step")
+    return kd, vd, out, idx
 
 
 # One-launch steps: groups of 32 keys, rounds of 512 keys, the longest cache ranked in LDS and the
@@ -110,7 +110,10 @@ def _step_against_oracle(S, H, d, L, budget, n_cur, n_win, pick, seed, dup=1, wi
 def test_small_step_edges(d, S, H, L, budget, n_cur, n_win, dup):
     print(f"small step d={d} S={S} H={H} L={L} budget={budget} n_cur={n_cur} n_win={n_win} dup={dup}", flush=True)
     pick = sorted({0, S * H // 2, S * H - 1})
-    _step_against_oracle(S, H, d, L, budget, n_cur, n_win, pick, 1, dup)
+    kept = _step_against_oracle(S, H, d, L, budget, n_cur, n_win, pick, 1, dup)
+    # the same step without an index list to write: what is kept, and everything else, must not change
+    for a, b in zip(kept, _step_against_oracle(S, H, d, L, budget, n_cur, n_win, pick, 1, dup, idx_of=kept[3])):
+        assert torch.equal(a, b)
 
 
 # Streamed selectivity: rounds of 512 keys, lists that overflow and are cut (keys in ascending order of
@@ -223,7 +226,7 @@ def test_small_step_writes_over_its_queries(d, L, budget, n_cur):
 # out on top of the map's keys or values, or of the source cache: all of them are read before it is stored
 @pytest.mark.parametrize("d,H,L,budget,n_cur", [(64, 12, 700, 90, 200), (128, 12, 90, 20, 16), (128, 12, 40, 40, 100),
                                                 (128, 6, 1600, 200, 120), (64, 40, 300, 60, 1100)])
-@pytest.mark.parametrize("over", ["k_cur", "v_cur", "k_src"])
+@pytest.mark.parametrize("over", ["k_cur", "v_cur", "k_src", "v_src"])
 def test_step_writes_over_its_inputs(over, d, H, L, budget, n_cur):
     dtype = torch.bfloat16
     print(f"out over {over} d={d} H={H} L={L} budget={budget} n_cur={n_cur}", flush=True)
@@ -231,23 +234,30 @@ def test_step_writes_over_its_inputs(over, d, H, L, budget, n_cur):
     q, kc, vc = (_rand(80 + i, (1, H, n_cur, d), dtype, 1.3).to(DEV) for i in range(3))
     ks, vs = (_rand(83 + i, (1, H, max(L, n_cur), d), dtype, 1.3).to(DEV) for i in range(2))
     ws = torch.empty(skv.workspace_bytes(shape, L, n_cur), dtype=torch.uint8, device=DEV)
-    flat = lambda t: t.reshape(H, t.shape[2], d)[:1].cpu()
     win = list(range(n_cur - 16, n_cur))
-    in_kc, in_vc, in_ks, in_vs = flat(kc), flat(vc), flat(ks)[:, :L], flat(vs)[:, :L]
-    if over == "k_src":
-        out = ks.view(-1)[:q.numel()].view_as(q)
+    in_q, in_kc, in_vc, in_ks, in_vs = (units(t).clone() for t in (q, kc, vc, ks[:, :, :L], vs[:, :, :L]))
+    if over in ("k_src", "v_src"):
+        out = (ks if over == "k_src" else vs).view(-1)[:q.numel()].view_as(q)
     else:
         out = kc if over == "k_cur" else vc
     kd = torch.empty(1, H, budget + n_cur, d, dtype=dtype, device=DEV); vd = torch.empty_like(kd)
     idx = torch.empty(1, H, budget, dtype=torch.int32, device=DEV)
     skv.step(shape, q, kc, vc, win, ks, vs, L, budget, kd, vd, out, idx, ws)
     torch.cuda.synchronize()
-    ref = oracle.step(flat(q), in_kc, in_vc, win, in_ks, in_vs, budget,
-                      force_idx=idx[0, :1].cpu().numpy())
-    kept = idx[0, 0].long().cpu()
-    assert torch.equal(kd[0, 0].cpu(), torch.cat([in_ks[0][kept], in_kc[0]]))
-    assert torch.equal(vd[0, 0].cpu(), torch.cat([in_vs[0][kept], in_vc[0]]))
-    assert np.abs(out[0, 0].float().cpu().numpy() - ref["out"][0]).max() < 2e-2
+    kept = idx.cpu()[0]
+    for u in range(H):      # every unit's rows; whose selection and output are right: the first, a middle and the last
+        rows = kept[u].long()
+        assert torch.equal(kd[0, u].cpu(), torch.cat([in_ks[u][rows], in_kc[u]]))
+        assert torch.equal(vd[0, u].cpu(), torch.cat([in_vs[u][rows], in_vc[u]]))
+    pick = [0, H // 2, H - 1]
+    if budget < L:
+        _, ls = oracle.score(in_q[pick][:, win], in_ks[pick])
+        own = oracle.select(ls, budget)
+        for i, u in enumerate(pick):
+            check_indices(kept[u].numpy(), ls[i], budget, own[i])
+    ref = oracle.step(in_q[pick], in_kc[pick], in_vc[pick], win, in_ks[pick], in_vs[pick], budget,
+                      force_idx=kept[pick].numpy())
+    check_output(units(out)[pick], ref["out"], dtype, "step")
 
 
 # keys whose logits are all -inf have weight zero, also where one wave meets nothing else
