@@ -846,6 +846,8 @@ def main() -> int:
                                "frac": v["flops"] / (v["ms"] * 1e-3) / 1e12 / PEAK_BF16_TFLOPS if v["ms"] > 0 else 0.0}
                       for k, v in sorted(attend_by_scale.items())},
     }
+    if not dom["launches"]:
+        roofline["note"] = "no call of this workload takes the kernel: small maps and fp32 have kernels of their own"
     gbs = lambda st: st["bytes"] / (st["ms"] * 1e-3) / 1e9 if st["ms"] > 0 else 0.0
     compact_gbs, score_gbs = gbs(compact_stat), gbs(score_stat)
 

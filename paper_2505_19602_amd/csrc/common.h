@@ -177,7 +177,9 @@ enum class SmallWork {
 // head_dim 64 over many keys (16 x 1024, 1224 keys: 0.89 of its time).  Without a ranking 64 rows pay while
 // the workgroups leave some compute units to those that copy, which otherwise wait for a round of their
 // own (all kept, 64 x 144 queries, 100 cached, 192 workgroups: 15.2 / 18.8; 64 x 256, 256 workgroups: 23.8 / 21.0;
-// head_dim 64 copies half as much: 0.71-0.99 of the time up to 256), 128 rows do not (128 x 200, 100: 32.3 / 24.5).
+// head_dim 64 copies half as much: 0.71-0.99 of the time up to 256; one workgroup per unit is as fast or faster but
+// around 100 cached rows: 256 x 36 queries, 19, 70, 100, 500: 13.3 / 13.8, 17.0 / 19.2, 22.8 / 20.7, 42.8 / 47.7),
+// 128 rows do not (128 x 200, 100: 32.3 / 24.5).
 // Appending alone copies least and gains least: head_dim 64, up to 224 workgroups, 0.86-0.95 of the time over 500
 // keys and more; head_dim 128: 1.00-1.24.
 // More units than compute units: two rounds are paid, which only maps of up to 16 queries stand
@@ -193,7 +195,7 @@ inline int small_tile_rows(int dtype, int d, int n_unit, int n_q, int kv, SmallW
   if (rows <= 32) return rows;
   if (rows == 128) return work == SmallWork::kRanked && kv <= 320 ? rows : 0;
   const bool spare = n_wg <= kComputeUnits * 7 / 8;
-  const bool pays = work == SmallWork::kRanked || (work == SmallWork::kKeepAll && (d == 64 || spare)) ||
+  const bool pays = work == SmallWork::kRanked || (work == SmallWork::kKeepAll && (d == 64 || spare || n_q <= 64)) ||
                     (work == SmallWork::kAppend && d == 64 && spare) ||
                     (work == SmallWork::kAttend && d == 64 && kv >= 512);
   return pays ? rows : 0;

@@ -25,8 +25,8 @@ def small_tile_rows(dtype: torch.dtype, d: int, units: int, n_q: int, kv: int, w
     if rows == 128:
         return rows if work == RANKED and kv <= 320 else 0
     spare = n_wg <= COMPUTE_UNITS * 7 // 8
-    pays = work == RANKED or (work == KEEP_ALL and (d == 64 or spare)) or (work == APPEND and d == 64 and spare) or \
-        (work == ATTEND and d == 64 and kv >= 512)
+    pays = work == RANKED or (work == KEEP_ALL and (d == 64 or spare or n_q <= 64)) or \
+        (work == APPEND and d == 64 and spare) or (work == ATTEND and d == 64 and kv >= 512)
     return rows if pays else 0
 
 
