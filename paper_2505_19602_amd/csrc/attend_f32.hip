@@ -22,8 +22,9 @@
 // 32 units are 416 waves of 32 rows for 1024 SIMDs), so the waves of a workgroup share their query
 // rows and split the keys; their partial results are joined in LDS at the end.
 // 400 queries x 517 keys x 32 units: 55 us, 62 TFLOP/s (plain FMA from LDS: 408 us); 400 x 600 x
-// 104 units: 162 us, 79 TFLOP/s.  What is left: 2.6 rounds of workgroups where 3 are paid, 5 us of
-// first loads and joining in each, and the softmax between the products.
+// 104 units: 162 us, 79 TFLOP/s.  What is left there: 2.6 rounds of workgroups where 3 are paid (two to a compute
+// unit), 5 us of first loads and joining in each, and the softmax between the products; of the 400 x 517 x 32
+// launch, 416 workgroups, fewer than two to a compute unit, so that first loads and joins are hardly hidden.
 #include "common.h"
 
 namespace scalekv {
