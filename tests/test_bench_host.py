@@ -9,7 +9,10 @@ import sys
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
 
+import torch  # noqa: E402
+
 import workloads as W  # noqa: E402
+from paper_2505_19602_amd import routes  # noqa: E402
 
 
 def _bench_module():
@@ -37,7 +40,7 @@ def test_traffic_table_covers_every_pipelined_shape_of_the_headline_workload():
         n_cur = cfg.n_tokens(k)
         for l in range(cfg.n_layer):
             keep = min(table[l][k - 1], lens[l])
-            if n_cur > 128:
+            if routes.step_kernel(torch.bfloat16, cfg.head_dim, cfg.n_seq * cfg.n_head, n_cur, lens[l], keep) == "pipelined":
                 seen.add((n_cur, keep))
             lens[l] = keep + n_cur
     assert seen, "the workload should have shapes that take the pipelined kernel"
