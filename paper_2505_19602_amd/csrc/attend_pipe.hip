@@ -8,47 +8,52 @@
 //                                    registers the first product left it in.
 // so one lane owns one query column: the softmax statistics are per-lane scalars.
 //
-// MFMA 32x32x16 operand layout (lane = 32h + j):
-//   A (32 x 16): lane holds row j, k-indices 8h..8h+7
-//   B (16 x 32): lane holds column j, k-indices 8h..8h+7
-//   C (32 x 32): lane holds column j, rows 8(r/4) + 4h + r%4 for r = 0..15
-// MFMA row i of the first product is fed key row pi(i) (pi swaps bits 2 and 3),
-// so registers r = 8m..8m+7 of an S^T block are keys 16m + 8h + (0..7) of the
-// block: already the B operand of the second product.
+// MFMA 16x16x32 operand layout (lane = 16g + i):
+//   A (16 x 32): lane holds row i, k-indices 8g..8g+7
+//   B (32 x 16): lane holds column i, k-indices 8g..8g+7
+//   C (16 x 16): lane holds column i, rows 4g..4g+3
+// A wave's block is 32 keys x 32 queries: two key tiles times two query tiles of S^T.  MFMA row 4a + v of
+// key tile t is fed key row 16(a & 1) + 8(a >> 1) + 4t + v of the block, so the registers of both key tiles of a
+// query tile are, in lane group g, the eight keys from 16(g & 1) + 8(g >> 1) on: taken as k-indices 8g..8g+7 they
+// are the B operand of the second product.  (This order of the keys lets the LDS swizzle below
+// separate the rows that neighbouring lanes read.)
 //
-// Occupancy.  Vector instructions that follow a run of a wave's own MFMAs wait for the
-// run (the wave issues in order and stalls at each MFMA until the pipe takes it), so
-// the softmax of a block hides behind the matrix pipe only if a second wave shares
-// the SIMD, or if it is cut up and spread between the MFMAs of another product.  The
-// second form was built as well (blocks skewed by one, PV(b-1) interleaved with the
-// softmax of block b) and measured 2-3 % slower than this one.  The kernel is written
-// for two workgroups of 4 waves per CU: every wave owns 32 query rows, stays under
-// 256 registers, and runs plain in-order code (S, softmax, PV per block of 32 keys);
-// the two workgroups drift apart and fill each other's gaps.  LDS operand traffic is
-// 16 KB per wave and block, half of what the LDS delivers at full MFMA rate.
+// Why 16x16x32 and not 32x32x16: the chip is power-limited under this kernel, and the smaller instruction does the
+// same products for less energy (issue loop on registers, normal operands: 2.05 PFLOP/s, 1.76 with
+// 32x32x16 on the same card).
+//
+// Schedule.  The unit of work is a block of 32 keys, 32 queries of a wave: kSlots MFMAs for S^T, as many for O^T, and
+// 48 vector instructions of softmax between them.  A wave works on three blocks at once: beside the softmax of block b
+// it issues the scores of block b + 1 and the weighted values of block b - 1, an MFMA, a request to the LDS and a
+// step of the softmax in turn (`slots`), so that within a wave the vector and the matrix pipe run side by side; a
+// second wave per SIMD (third, head_dim 64), from another workgroup, covers what is left of the latencies.  LDS
+// operands are requested a product ahead of the MFMAs that take them, into registers which the product before has
+// left.  Every slot is fenced: the compiler otherwise gathers the vector instructions behind the MFMAs (1-3 % slower,
+// head_dim 64).  The loop runs two tiles a turn and leaves at one place: with a second exit in its middle the
+// compiler spilled 45 registers.
+// 4096 queries x 5718 keys x 256 units, d 128: 2800 us with 32x32x16 and the three phases of a block in sequence;
+// 2655 so with 16x16x32; 2625 in this order (1.17 PFLOP/s).  1024 x 1180 x 64: 46.0 -> 42.5 us.
 //
 // Data movement.  K and V tiles (64 keys x 256 B) go from HBM/L2 straight into LDS
 // (global_load_lds, 16 B per lane, no registers), row-major, with the 16-byte
-// chunks of each row XOR-swizzled so that operand reads are bank-conflict free.
+// chunks of each row XOR-swizzled so that operand reads are free of bank conflicts.
 // The V^T operand is read with the transposing LDS load (ds_read_b64_tr_b16):
 // inside a group of 16 lanes, lane i supplies the address of 4 elements and
 // receives element (i & 3) of the data addressed by lanes (i >> 2) + 4r, r = 0..3.
-// Two stages per workgroup; tile t+2 is requested right after the barrier in the
-// middle of tile t's second block, which is also the point from which tile t+1 may
-// be read.  LDS operands are requested one phase ahead of the MFMAs that use them.
+// Two stages per workgroup and tensor.  One barrier per tile (`turn`), in the middle of the second product of its
+// first half: a wave has then read all of K tile t and of V tile t - 1, and has waited for its share of K tile t + 1
+// and V tile t, which may be read from there on, while K tile t + 2 and V tile t + 1 are requested.
 //
-// Softmax.  The exponent offset m_run of a query row is taken from the row's maximum
-// over the first tile and then left alone: every later probability is exp2 of
-// (score - m_run), whatever its size, and the row sum adds the bf16-rounded
+// Softmax.  The exponent offset of a query row is taken from the row's maximum
+// over the first block and then left alone: every later probability is exp2 of
+// (score - offset), whatever its size, and the row sum adds the bf16-rounded
 // probabilities, the very numbers the MFMA multiplies by.  No running maximum is
 // formed (it costs a sixth of the vector instructions of a block).  This is exact as
-// long as nothing overflows, and fp32 / bf16 carry 2^127: a lane only checks that its
-// share of a block's row sum stays below 2^100 (scores up to 69 natural units above the
-// first tile's maximum: heavy-tailed keys reach 35) and records a failure in a scalar
-// mask; row sums then stay below 2^114.  The accumulators could still overflow if the
-// values themselves are huge (2^100 times 2^14 keys leaves room for |v| up to 2^13), so
-// at the end of the pass every lane also checks that its accumulators are finite.
-// If any wave of the workgroup recorded a failure (forced by the tests), the workgroup
+// long as nothing overflows, and fp32 / bf16 carry 2^127: at the end of the pass a lane
+// checks that its share of the row sum is below 2^100 (scores up to 69 natural units above the
+// first block's maximum: heavy-tailed keys reach 35; an infinite weight or a NaN is still in the
+// sum then) and, since huge values could overflow them even so, that its accumulators are finite.
+// If any lane of the workgroup finds a failure (forced by the tests), the workgroup
 // discards its result and repeats the whole pass with the classical scheme: running
 // maximum per block, offsets moved (and O, l rescaled) when some row maximum grew by
 // more than kRescaleThreshold in log2 units.
@@ -65,8 +70,6 @@
 // kernel would be bound by the HBM and leave the matrix pipe idle.
 #include <hip/hip_ext.h>
 
-#include <type_traits>
-
 #include "common.h"
 
 namespace scalekv {
@@ -75,10 +78,8 @@ namespace {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) const void glb_void;
 
 constexpr int BM = 128;              // query rows per workgroup: 4 waves x 32
 constexpr int TN = 64;               // keys per staged tile (two blocks of 32)
@@ -87,25 +88,31 @@ constexpr int kStages = 2;
 // What depends on head_dim.  head_dim 64 halves the tiles and the accumulators, so that three
 // workgroups share a compute unit instead of two; per block of 32 keys its 8 MFMA (256 clocks) and
 // its softmax (16 fma, 16 exp2, 16 others: 260 clocks) are about equal, and the third wave per SIMD
-// lets the two pipes overlap.  (Two waves: 3-10 % slower; four: 18 registers spilled, 0.7 % faster
-// on the largest launches and 5-8 % slower on the others.)  4096 queries x 4420 keys x 256 units:
-// 1824 us, 651 TFLOP/s with the register-staged kernel this one replaced, 1264 us, 938 TFLOP/s now;
-// 1215 x 1648 x 60: 74 -> 51 us.
+// lets the two pipes overlap.  4096 queries x 4420 keys x 256 units: 1240 us with 32x32x16, 1160 now (1.02 PFLOP/s);
+// 1215 x 1648 x 60: 47.0 -> 43.5 us.
 // LDS rows are swizzled in 16-byte chunks so that operand reads are free of bank conflicts: chunk c of
-// row r sits in slot c ^ k_flip(r) of a K (or query) row and c ^ v_flip(r) of a V row.  Sixteen rows
-// of 256 bytes start in the same bank, of rows of 128 bytes every second.
+// row r sits in slot c ^ k_flip(r) of a K row, c ^ v_flip(r) of a V row and c ^ q_flip(r) of a query row.  Rows
+// of 256 bytes all start in the same bank, of rows of 128 bytes every second.  The sixteen lanes that read
+// one chunk of sixteen K rows differ in row bits 0, 1, 3 and 4, the eight groups of lanes that read 32 bytes
+// each of eight V rows in bits 0, 1 and 4.
 template <int D>
 struct Shape {
   static constexpr int kRowBytes = D * 2;
   static constexpr int kTileBytes = TN * kRowBytes;       // 16 KB (d 128), 8 KB
-  static constexpr int kSlabs = D / 16;                   // k-slabs of the first product
-  static constexpr int kBlocks = D / 32;                  // 32-channel blocks of the output
+  static constexpr int kSlabs = D / 32;                   // k-slabs of the first product
+  static constexpr int kBlocks = D / 16;                  // 16-channel blocks of the output
   static constexpr int kChunks = D / 8;                   // 16-byte chunks per row
   static constexpr int kRowsPerOp = 64 / kChunks;         // rows that one transfer of a wave covers
   static constexpr int kOps = 16 / kRowsPerOp;            // transfers for a wave's 16 rows of a tile
   static constexpr int kWavesPerSimd = D == 128 ? 2 : 3;
-  __device__ static constexpr int k_flip(int r) { return D == 128 ? r & 15 : r >> 1 & 7; }
-  __device__ static constexpr int v_flip(int r) { return D == 128 ? (r & 3) << 2 : (r >> 1 & 1) << 2; }
+  __device__ static constexpr int k_flip(int r) {
+    const int high = (r >> 4 & 1) | (r >> 3 & 1) << 1;
+    return D == 128 ? (r & 3) | high << 2 : (r >> 1 & 1) | high << 1;
+  }
+  __device__ static constexpr int v_flip(int r) {
+    return D == 128 ? (r & 3) << 1 | (r >> 4 & 1) << 3 : (r >> 1 & 1) << 1 | (r >> 4 & 1) << 2;
+  }
+  __device__ static constexpr int q_flip(int r) { return D == 128 ? r & 15 : r >> 1 & 7; }
 };
 // Measurement-only builds (python -m paper_2505_19602_amd.build --variant ...; never the library
 // the tests or the bench's headline load): each takes one ingredient out of the kernel so that
@@ -133,29 +140,7 @@ __device__ unsigned long long g_timeline[kTimelineMaxWg * kTimelineWords];
 #else
 #define SCALEKV_STAMP(name)
 #endif
-constexpr float kBlockSumLimit = 0x1p100f;  // largest row-sum share a block may add unchecked
-
-// Three-input max as one instruction and without the NaN-quieting pre-pass the
-// compiler puts in front of fmaxf on values it has not produced itself.
-__device__ __forceinline__ float max3(float a, float b, float c) {
-  float r;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-
-// Lanes l and l^32 hold the two halves of one query row's statistics.  The swap
-// hands every lane {own value, partner's value} in some order; max and sum do not
-// care which is which.
-__device__ __forceinline__ float both_halves_max(float x) {
-  const uint32_t u = __float_as_uint(x);
-  auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float both_halves_sum(float x) {
-  const uint32_t u = __float_as_uint(x);
-  auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
+constexpr float kRowSumLimit = 0x1p100f;  // largest share of a row sum that a pass without maxima may end with
 
 // One 16-byte-per-lane transfer from global memory straight into LDS: lane l's vector comes
 // from base + voff + IMM and lands at LDS byte lds_addr + IMM + 16 l (the instruction's
@@ -209,7 +194,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   const unsigned long long c_start = __builtin_readcyclecounter();
 #endif
   using G = Shape<D>;
-  constexpr int kRowBytes = G::kRowBytes, kTileBytes = G::kTileBytes, NSL = G::kSlabs, NDB = G::kBlocks;
+  constexpr int kRowBytes = G::kRowBytes, kTileBytes = G::kTileBytes, NSL = G::kSlabs, NCB = G::kBlocks;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   unsigned char* const k_lds = smem;
   unsigned char* const v_lds = smem + kStages * kTileBytes;
@@ -218,7 +203,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   const int unit = wg / n_qtile, qtile = wg - unit * n_qtile;
   const int seq = unit / n_head, head = unit - seq * n_head;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int j = lane & 31, h = lane >> 5;
+  const int i = lane & 15, g = lane >> 4;
   const int q_base = qtile * BM + wave * 32;
   const uint16_t* qu = q + (long long)unit * n_q * D;
   const unsigned char* ku = (const unsigned char*)(k + seq * k_seq_stride + head * k_head_stride);
@@ -231,69 +216,92 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   // ---- tile loader: per thread kOps K vectors and kOps V vectors of 16 bytes (4 each, d 64: 2).
   // Instruction p of wave w fills LDS rows 16w + kRowsPerOp p .. (64 lanes x 16 B = 4 rows, d 64: 8);
   // the lane that lands in chunk slot s of row r fetches global chunk s ^ flip(r).  For this lane
-  // r = r0 + kRowsPerOp p, and both flips are linear: its K chunk is c0 ^ 4p with c0 the one for
-  // p = 0, and its V chunk does not depend on p.  One register pair serves all instructions, the
-  // rest (1024 p bytes) rides in the instruction's immediate offset.
+  // r = r0 + kRowsPerOp p, and both flips are linear: its K chunk is c0 ^ k_step(p) with c0 the one for
+  // p = 0 (bit 3 of r alone depends on p), and its V chunk does not depend on p.  One register pair serves all
+  // instructions, the rest (1024 p bytes) rides in the instruction's immediate offset.
   const int ld_row = lane / G::kChunks;                                  // row inside an instruction
   const int ld_row0 = 16 * wave + ld_row;
   const unsigned ld_krow = ld_row0 * kRowBytes;                          // K: row part
-  const unsigned ld_kchunk = 16 * ((lane % G::kChunks) ^ G::k_flip(ld_row));  // K: chunk part for p = 0
-  const unsigned ld_vofs = ld_row0 * kRowBytes + 16 * ((lane % G::kChunks) ^ G::v_flip(ld_row));
+  const unsigned ld_kchunk = 16 * ((lane % G::kChunks) ^ G::k_flip(ld_row0));  // K: chunk part for p = 0
+  const unsigned ld_vofs = ld_row0 * kRowBytes + 16 * ((lane % G::kChunks) ^ G::v_flip(ld_row0));
+  constexpr auto k_step = [](int p) -> unsigned { return 16 * G::k_flip(G::kRowsPerOp * p); };  // bytes
   auto lds_addr = [](const unsigned char* p) -> unsigned {
     return (unsigned)(size_t)(const __attribute__((address_space(3))) unsigned char*)p;
   };
   // LDS byte addresses of this wave's 16 rows in stage 0 (wave-uniform, kept in scalar registers)
   const unsigned k_lds_wave = __builtin_amdgcn_readfirstlane(lds_addr(k_lds + (16 * wave) * kRowBytes));
   const unsigned v_lds_wave = __builtin_amdgcn_readfirstlane(lds_addr(v_lds + (16 * wave) * kRowBytes));
-  auto issue_tile = [&](int tile) __attribute__((always_inline)) {
-    const unsigned ks = k_lds_wave + (tile % kStages) * kTileBytes;
-    const unsigned vs = v_lds_wave + (tile % kStages) * kTileBytes;
-    // wave-uniform tile base and number of valid rows, in whichever segment the tile lies
-    const bool second = tile >= n_tile1;
-    const int lt = second ? tile - n_tile1 : tile;
-    const unsigned char* kt = (second ? k2u : ku) + (long long)lt * kTileBytes;
-    const unsigned char* vt = (second ? v2u : vu) + (long long)lt * kTileBytes;
-    const int valid = (second ? len2 : len1) - lt * TN;
+  // wave-uniform base of a tile and its number of valid rows, in whichever segment it lies
+  auto rows_of = [&](int tile) { return tile < n_tile1 ? len1 - tile * TN : len2 - (tile - n_tile1) * TN; };
+  auto issue_k = [&](int tile) __attribute__((always_inline)) {
+    const unsigned dst = k_lds_wave + (tile % kStages) * kTileBytes;
+    const unsigned char* src = tile < n_tile1 ? ku + (long long)tile * kTileBytes
+                                              : k2u + (long long)(tile - n_tile1) * kTileBytes;
+    const int valid = rows_of(tile);
     if (valid >= TN) {
       // the immediate offset moves the LDS destination along with the global source, which
       // is exactly the kRowsPerOp rows between a lane's consecutive transfers
-      dma16_xor<0>(kt, ld_krow, ld_kchunk, 0u, ks);
-      dma16<0>(vt, ld_vofs, vs);
-      dma16_xor<1024>(kt, ld_krow, ld_kchunk, 64u, ks);
-      dma16<1024>(vt, ld_vofs, vs);
+      dma16_xor<0>(src, ld_krow, ld_kchunk, 0u, dst);
+      dma16_xor<1024>(src, ld_krow, ld_kchunk, k_step(1), dst);
       if constexpr (G::kOps == 4) {
-        dma16_xor<2048>(kt, ld_krow, ld_kchunk, 128u, ks);
-        dma16<2048>(vt, ld_vofs, vs);
-        dma16_xor<3072>(kt, ld_krow, ld_kchunk, 192u, ks);
-        dma16<3072>(vt, ld_vofs, vs);
+        dma16_xor<2048>(src, ld_krow, ld_kchunk, k_step(2), dst);
+        dma16_xor<3072>(src, ld_krow, ld_kchunk, k_step(3), dst);
       }
     } else {
       // ragged last tile: rows past the end re-read the last valid row (finite data that
-      // the mask turns into zero weight)
-      const int last_row = valid - 1;
+      // the mask turns into zero weight).  (An opaque row number keeps what is formed from it in this branch.)
+      int row0 = ld_row0;
+      asm volatile("" : "+v"(row0));
 #pragma unroll
       for (int p = 0; p < G::kOps; ++p) {
-        const int back = max(ld_row0 + G::kRowsPerOp * p - last_row, 0) * kRowBytes;
-        dma16<0>(kt, ld_krow + (ld_kchunk ^ (64 * p)) + 1024 * p - back, ks + 1024 * p);
-        dma16<0>(vt, ld_vofs + 1024 * p - back, vs + 1024 * p);
+        const int back = max(row0 + G::kRowsPerOp * p - (valid - 1), 0) * kRowBytes;
+        dma16<0>(src, row0 * kRowBytes + (ld_kchunk ^ k_step(p)) + 1024 * p - back, dst + 1024 * p);
+      }
+    }
+  };
+  auto issue_v = [&](int tile) __attribute__((always_inline)) {
+    const unsigned dst = v_lds_wave + (tile % kStages) * kTileBytes;
+    const unsigned char* src = tile < n_tile1 ? vu + (long long)tile * kTileBytes
+                                              : v2u + (long long)(tile - n_tile1) * kTileBytes;
+    const int valid = rows_of(tile);
+    if (valid >= TN) {
+      dma16<0>(src, ld_vofs, dst);
+      dma16<1024>(src, ld_vofs, dst);
+      if constexpr (G::kOps == 4) {
+        dma16<2048>(src, ld_vofs, dst);
+        dma16<3072>(src, ld_vofs, dst);
+      }
+    } else {
+      int row0 = ld_row0;
+      asm volatile("" : "+v"(row0));
+#pragma unroll
+      for (int p = 0; p < G::kOps; ++p) {
+        const int back = max(row0 + G::kRowsPerOp * p - (valid - 1), 0) * kRowBytes;
+        dma16<0>(src, ld_vofs + 1024 * p - back, dst + 1024 * p);
       }
     }
   };
 
-  // ---- per-lane operand offsets inside a 32-key block (bytes)
-  int k_ofs[NSL];  // K operand, slab sl: row pi(j), chunk (2sl + h) ^ flip
+  // ---- per-lane operand addresses (LDS, bytes) in the first 32-key block; key tile t is 4 rows further on
+  unsigned k_adr[NSL];  // K operand, slab sl: chunk 4sl + g of the row that MFMA row i is fed
   {
-    const int row = pi32(j);
+    const int row = 16 * (i >> 2 & 1) + 8 * (i >> 3) + (i & 3);
 #pragma unroll
-    for (int sl = 0; sl < NSL; ++sl) k_ofs[sl] = row * kRowBytes + 16 * ((2 * sl + h) ^ G::k_flip(row));
+    for (int sl = 0; sl < NSL; ++sl)
+      k_adr[sl] = lds_addr(k_lds) + row * kRowBytes + 16 * ((4 * sl + g) ^ G::k_flip(row));
   }
-  int v_ofs[NDB];  // V^T operand, channel block db: this lane's address role in the transposing load
+  unsigned v_adr[NCB];  // V^T operand, channel block c: this lane's address role in the transposing load
   {
-    const int i = j & 15, g = i >> 2;
+    const int row = 16 * (g & 1) + 8 * (g >> 1) + (i >> 2);
 #pragma unroll
-    for (int db = 0; db < NDB; ++db)
-      v_ofs[db] = (8 * h + g) * kRowBytes + 64 * (db ^ (G::v_flip(g) >> 2)) + 32 * (j >> 4) + 8 * (i & 3);
+    for (int c = 0; c < NCB; ++c)
+      v_adr[c] = lds_addr(v_lds) + row * kRowBytes + 16 * (2 * c ^ G::v_flip(row)) + 8 * (i & 3);
   }
+  // (opaque, so that every load is one of these registers plus an immediate offset)
+#pragma unroll
+  for (int sl = 0; sl < NSL; ++sl) asm volatile("" : "+v"(k_adr[sl]));
+#pragma unroll
+  for (int c = 0; c < NCB; ++c) asm volatile("" : "+v"(v_adr[c]));
 
   // ---- Q fragments: B operand of the first product, resident for the whole kernel.  A lane's
   // fragments are eight 16-byte pieces of its query row, 32 bytes apart: fetched as such, every
@@ -303,9 +311,9 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   // barrier, each wave's rows exactly where the same wave will later put its share of the second
   // tile (16 K rows and 16 V rows): nobody else writes there, so no barrier is needed
   // before that tile is requested, only the wave's own reads must have returned.  Chunk c of row
-  // r sits in slot c ^ k_flip(r), so that the fragment reads are free of bank conflicts.  Rows
+  // r sits in slot c ^ q_flip(r), so that the fragment reads are free of bank conflicts.  Rows
   // past the end of the map repeat its last row; nothing is stored for them.
-  bf16x8 qf[NSL];
+  bf16x8 qf[2][NSL];
   unsigned char* const q_stage_k = k_lds + kTileBytes + (16 * wave) * kRowBytes;  // query rows 0-15 of the wave
   unsigned char* const q_stage_v = v_lds + kTileBytes + (16 * wave) * kRowBytes;  // query rows 16-31
   {
@@ -315,197 +323,280 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     for (int p = 0; p < 2 * G::kOps; ++p) {
       const int r = G::kRowsPerOp * p + ld_row;
       const unsigned row = (unsigned)min(q_base + r, n_q - 1);
-      dma16<0>((const unsigned char*)qu, row * kRowBytes + 16 * ((lane % G::kChunks) ^ G::k_flip(r)),
+      dma16<0>((const unsigned char*)qu, row * kRowBytes + 16 * ((lane % G::kChunks) ^ G::q_flip(r)),
                (p < G::kOps ? qk : qv) + 1024 * (p % G::kOps));
     }
   }
   auto read_q = [&]() __attribute__((always_inline)) {
-    const unsigned char* row = (j < 16 ? q_stage_k : q_stage_v) + (j & 15) * kRowBytes;
 #pragma unroll
-    for (int s = 0; s < NSL; ++s) qf[s] = *(const bf16x8*)(row + 16 * ((2 * s + h) ^ G::k_flip(j & 15)));
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int sl = 0; sl < NSL; ++sl)
+        qf[b][sl] = *(const bf16x8*)((b ? q_stage_v : q_stage_k) + i * kRowBytes + 16 * ((4 * sl + g) ^ G::q_flip(i)));
   };
 
-  f32x16 o[NDB];
-  float m_run;  // exponent offset
-  float l_run;  // this lane's share of the row sum
-  unsigned long long overflowed = 0;  // lanes whose block sum left the unchecked range
+  f32x4 o[2][NCB];   // [query tile][channel block]
+  float neg_off[2];  // less the exponent offsets
+  float l_run[2];    // this lane's share of the row sums
 
-  auto load_k = [&](int ofs, int sl) -> bf16x8 { return *(const bf16x8*)(k_lds + ofs + k_ofs[sl]); };
-  auto load_vt = [&](int ofs, int sl, int db) -> bf16x8 {
-    const unsigned char* p = v_lds + ofs + sl * 16 * kRowBytes + v_ofs[db];
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (__attribute__((address_space(3))) s16x4*)(p + 4 * kRowBytes));
-    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-  };
-  auto exps = [&](const f32x16& s, float off, bf16x8 (&p)[2]) -> float {
-    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-    float rs = 0.f;
-#pragma unroll
-    for (int r = 0; r < 16; r += 2) {
-#if defined(SCALEKV_ABLATE_SOFTMAX)
-      const float p0 = s[r], p1 = s[r + 1];
-#else
-      const float p0 = __builtin_amdgcn_exp2f(fmaf(s[r], scale_log2e, -off));
-      const float p1 = __builtin_amdgcn_exp2f(fmaf(s[r + 1], scale_log2e, -off));
-#endif
-      const bf16x2 pr = {(__bf16)p0, (__bf16)p1};
-      p[r / 8][r % 8] = pr[0];
-      p[r / 8][r % 8 + 1] = pr[1];
-#if !defined(SCALEKV_ABLATE_SOFTMAX)
-      rs = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, rs, false);
-#endif
-    }
-#if defined(SCALEKV_ABLATE_SOFTMAX)
-    rs = 1.f;
-#endif
-    return rs;
-  };
-
-  // ---- the phases of one block of 32 keys
-  auto fetch_k = [&](bf16x8 (&kf)[NSL], int ofs) {
-#pragma unroll
-    for (int sl = 0; sl < NSL; ++sl) kf[sl] = load_k(ofs, sl);
-  };
-  auto fetch_vt = [&](bf16x8 (&vf)[2][NDB], int ofs) {
-#pragma unroll
-    for (int sl = 0; sl < 2; ++sl)
-#pragma unroll
-      for (int db = 0; db < NDB; ++db) vf[sl][db] = load_vt(ofs, sl, db);
-  };
-  auto scores = [&](const bf16x8 (&kf)[NSL]) -> f32x16 {
-    f32x16 s;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = 0.f;
-#pragma unroll
-    for (int sl = 0; sl < NSL; ++sl) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[sl], qf[sl], s, 0, 0, 0);
-    return s;
-  };
-  // softmax of the block's scores (register r = key 16(r/8) + 8h + r%8 of the block, which
-  // starts at row first_key of its tile; `mask` hides rows at or beyond `valid`) followed by
-  // O^T += V^T P^T
-  // `tracked` (a std::bool_constant): follow the running maximum; otherwise keep m_run and
-  // only watch for overflow.
-  auto softmax_pv = [&](auto tracked, f32x16& s, const bf16x8 (&vf)[2][NDB], bool mask, int first_key,
-                        int valid) __attribute__((always_inline)) {
-    if (mask) {
-      // (the lane half is taken from the lane number on the spot, so that the sixteen key
-      // indices of this rarely taken branch are not kept in registers through the main loop)
-      const int half = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) >> 5;
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (first_key + 16 * (r / 8) + 8 * half + (r % 8) >= valid) s[r] = -INFINITY;
-    }
-    if constexpr (decltype(tracked)::value) {
-      float mx = max3(s[0], s[1], s[2]);
-#pragma unroll
-      for (int r = 3; r < 15; r += 2) mx = max3(mx, s[r], s[r + 1]);
-      mx = both_halves_max(fmaxf(mx, s[15]));
-      if (__builtin_amdgcn_ballot_w64((mx - m_run) * scale_log2e > kRescaleThreshold) != 0) {
-        const float m_new = fmaxf(m_run, mx);
-        const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2e);
-        m_run = m_new;
-        l_run *= alpha;
-#pragma unroll
-        for (int db = 0; db < NDB; ++db)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
-      }
-    }
-    bf16x8 pf[2];
-    const float rs = exps(s, m_run * scale_log2e, pf);
-    if constexpr (!decltype(tracked)::value)
-      overflowed |= __builtin_amdgcn_ballot_w64(!(rs <= kBlockSumLimit));  // catches NaN too
-    l_run += rs;
-#pragma unroll
-    for (int sl = 0; sl < 2; ++sl)
-#pragma unroll
-      for (int db = 0; db < NDB; ++db)
-        o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[sl][db], pf[sl], o[db], 0, 0, 0);
-  };
-
-  // Schedule.  LDS operands are always requested one phase before the MFMAs that use
-  // them: V^T of a block ahead of its S MFMAs, K of the next block ahead of the softmax.
-  // One barrier per tile, in the middle of the tile's second block: by then a wave has
-  // finished every LDS read of the tile (so its stage may be refilled) and has waited for
-  // its share of the next tile (so that tile may be read).  The fences stop the compiler
-  // from sinking the requests back next to their uses.
+  typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
   constexpr int kHalf = 32 * kRowBytes;
-  bf16x8 kf[NSL], vf[2][NDB];
-  // One tile (two blocks).  `ofs` / `next_ofs` are the byte offsets of this tile's and the
-  // next tile's stage; in the main loop they are constants and fold into the LDS
-  // instructions' offset fields.
-  auto tile = [&](auto tracked, int t, int ofs, int next_ofs) __attribute__((always_inline)) {
-    const int valid = t < n_tile1 ? len1 - t * TN : len2 - (t - n_tile1) * TN;
-    const bool mask = valid < TN;
-    // ---- first block of the tile
-    fetch_vt(vf, ofs);
-    __builtin_amdgcn_sched_barrier(0);
-    f32x16 s = scores(kf);
-    __builtin_amdgcn_sched_barrier(0);
-    fetch_k(kf, ofs + kHalf);
-    __builtin_amdgcn_sched_barrier(0);
-    softmax_pv(tracked, s, vf, mask, 0, valid);
-    // ---- second block
-    __builtin_amdgcn_sched_barrier(0);
-    fetch_vt(vf, ofs + kHalf);
-    __builtin_amdgcn_sched_barrier(0);
-    s = scores(kf);
-    __builtin_amdgcn_sched_barrier(0);
-    if (t + 1 < n_tile) {
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-#if !defined(SCALEKV_ABLATE_TRANSFER)
-      if (t + 2 < n_tile) issue_tile(t + 2);
-#endif
-      fetch_k(kf, next_ofs);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    softmax_pv(tracked, s, vf, mask, 32, valid);
+  constexpr int kSlots = 4 * NSL;          // MFMAs of one product over a block (the two have the same number)
+  constexpr int kSteps = 16 / kSlots;      // softmax steps behind each
+  static_assert(kSlots == 2 * NCB && 2 * NSL <= kSlots - kSlots / 2, "the requests fit in the slots");
+  constexpr int kBarrierSlot = kSlots / 2 - 1;  // of the second product of a tile's first half
+  bf16x8 kf[2][NSL];       // K operand, [key tile][slab]
+  s16x4 vf[NCB][2];        // V^T operand, [channel block][key tile]
+  f32x4 sa[2][2], sb[2][2];  // scores of an even and an odd block, [query tile][key tile]
+  u32x4 pa[2], pb[2];      // their weights, bf16
+
+  auto read_k = [&](int ofs, int e) {
+    kf[e & 1][e >> 1] = *(lds_bf16x8*)(k_adr[e >> 1] + ofs + 4 * (e & 1) * kRowBytes);
   };
-  // One pass over all tiles.  The first tile always follows its maxima: that is where
-  // m_run comes from.
-  // `first` (a std::bool_constant): the query rows are waiting in LDS and are taken into registers
-  // before the second tile may overwrite them.
-  auto pass = [&](auto tracked, auto first) __attribute__((always_inline)) {
+  auto read_v = [&](int ofs, int e) {
+    const unsigned adr = v_adr[e >> 1] + ofs + 4 * (e & 1) * kRowBytes;
+    vf[e >> 1][e & 1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)adr);
+  };
+  // MFMA m of the two products over a block
+  auto score_mfma = [&](f32x4 (&s)[2][2], int m) {
+    const int sl = m >> 2, t = m >> 1 & 1, b = m & 1;
+    const f32x4 sum = sl ? s[b][t] : f32x4{0.f, 0.f, 0.f, 0.f};
+    s[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[t][sl], qf[b][sl], sum, 0, 0, 0);
+  };
+  auto value_mfma = [&](const u32x4 (&p)[2], int m) {
+    const int c = m >> 1, b = m & 1;
+    const bf16x8 vt = __builtin_bit_cast(bf16x8, __builtin_shufflevector(vf[c][0], vf[c][1], 0, 1, 2, 3, 4, 5, 6, 7));
+    o[b][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vt, __builtin_bit_cast(bf16x8, p[b]), o[b][c], 0, 0, 0);
+  };
+  // Step k of 32 of a block's softmax: four for each pair of weights.  (The empty statements keep each step in
+  // its slot: without them the compiler moves the arithmetic to where its result is used.)
+  auto softmax_step = [&](f32x4 (&s)[2][2], u32x4 (&p)[2], int k) {
+    const int b = k >> 4, x = 2 * (k >> 2 & 3), t = x >> 2, v = x & 3;
+    float w0 = s[b][t][v], w1 = s[b][t][v + 1];
+#if defined(SCALEKV_ABLATE_SOFTMAX)
+    if ((k & 3) == 3) p[b][x / 2] = __builtin_bit_cast(uint32_t, bf16x2{(__bf16)w0, (__bf16)w1});
+#else
+    if ((k & 3) == 0) {
+      w0 = fmaf(w0, scale_log2e, neg_off[b]);
+      w1 = fmaf(w1, scale_log2e, neg_off[b]);
+      asm volatile("" : "+v"(w0), "+v"(w1));
+    } else if ((k & 3) == 1) {
+      w0 = __builtin_amdgcn_exp2f(w0);
+      asm volatile("" : "+v"(w0));
+    } else if ((k & 3) == 2) {
+      w1 = __builtin_amdgcn_exp2f(w1);
+      asm volatile("" : "+v"(w1));
+    } else {
+      const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f}, pr = {(__bf16)w0, (__bf16)w1};
+      uint32_t word = __builtin_bit_cast(uint32_t, pr);
+      // the row sum adds the rounded weights, the very numbers the MFMA multiplies by
+      l_run[b] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, l_run[b], false);
+      asm volatile("" : "+v"(word), "+v"(l_run[b]));
+      p[b][x / 2] = word;
+    }
+    s[b][t][v] = w0;
+    s[b][t][v + 1] = w1;
+#endif
+  };
+  // hides the keys of a block (register v of key tile t = key 16(g & 1) + 8(g >> 1) + 4t + v) from `valid` on
+  auto hide = [&](f32x4 (&s)[2][2], int valid) __attribute__((always_inline)) {
+    if (valid < 32) {
+      // (the lane group is taken from the lane number on the spot, so that the eight key
+      // indices of this rarely taken branch are not kept in registers through the main loop)
+      const int group = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)) >> 4;
+      const int left = valid - 16 * (group & 1) - 8 * (group >> 1);
 #pragma unroll
-    for (int db = 0; db < NDB; ++db)
+      for (int x = 0; x < 8; ++x)
+        if (x >= left) s[0][x / 4][x % 4] = s[1][x / 4][x % 4] = -INFINITY;
+    }
+  };
+  // largest score of each query of a block
+  auto block_max = [&](const f32x4 (&s)[2][2], float (&mx)[2]) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
-    m_run = no_max;
-    l_run = 0.f;
-    issue_tile(0);
+    for (int b = 0; b < 2; ++b) {
+      float m = s[b][0][0];
+#pragma unroll
+      for (int x = 1; x < 8; ++x) m = fmaxf(m, s[b][x / 4][x % 4]);
+      mx[b] = xor32_max(xor16_max(m));
+    }
+  };
+
+  // One product over a block, with the other work of the wave between its MFMAs: slot m is an MFMA, what
+  // `beside` puts there, and kSteps steps of the softmax of another block.  The fences keep the order.
+  auto slots = [&](auto mfma, auto beside, f32x4 (&s)[2][2], u32x4 (&p)[2],
+                   int first_step) __attribute__((always_inline)) {
+#pragma unroll
+    for (int m = 0; m < kSlots; ++m) {
+      mfma(m);
+      beside(m);
+#pragma unroll
+      for (int r = 0; r < kSteps; ++r) softmax_step(s, p, first_step + m * kSteps + r);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // Publishes tile t + 1 of K and tile t of V, and requests the tiles after them, in the place of those that all
+  // waves have left.
+  auto turn = [&](int t) __attribute__((always_inline)) {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if constexpr (decltype(first)::value) {
-#if defined(SCALEKV_TIMELINE)
-      t_first_tile = __builtin_amdgcn_s_memrealtime();
+#if !defined(SCALEKV_ABLATE_TRANSFER)
+    if (t + 2 < n_tile) issue_k(t + 2);
+    if (t + 1 < n_tile) issue_v(t + 1);
 #endif
-      read_q();
-      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the fragments are in registers, their space may be refilled
-    }
-    if (n_tile > 1) issue_tile(1);
-    fetch_k(kf, 0);
-    tile(std::true_type{}, 0, 0, kTileBytes);
-    int t = 1;
-    for (; t + 1 < n_tile; t += 2) {  // t odd: stage 1 then stage 0
-      tile(tracked, t, kTileBytes, 0);
-      tile(tracked, t + 1, 0, kTileBytes);
-    }
-    if (t < n_tile) tile(tracked, t, kTileBytes, 0);
-    if constexpr (!decltype(tracked)::value) {
-      // inf or NaN in an accumulator (huge values times large unchecked weights): repeat tracked
-      bool bad = false;
-#pragma unroll
-      for (int db = 0; db < NDB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) bad |= !(fabsf(o[db][r]) < INFINITY);
-      overflowed |= __builtin_amdgcn_ballot_w64(bad);
-    }
+    __builtin_amdgcn_sched_barrier(0);
   };
-  pass(std::false_type{}, std::true_type{});
-  // every wave has left its last tile when the votes are in, so the stages may be refilled
-  if (__syncthreads_or(overflowed != 0)) pass(std::true_type{}, std::false_type{});
+  auto nothing = [](int) {};
+  // First half of tile t: softmax of its first block beside the scores of its second and the weighted values
+  // of the block before.  par = t mod 2.
+  auto first_half = [&](int t, int par) __attribute__((always_inline)) {
+    hide(sa, rows_of(t));
+    __builtin_amdgcn_sched_barrier(0);
+    slots([&](int m) { score_mfma(sb, m); }, [&](int m) { read_v((1 - par) * kTileBytes + kHalf, m); }, sa, pa, 0);
+    slots([&](int m) { value_mfma(pb, m); },
+          [&](int m) {
+            if (m == kBarrierSlot) turn(t);
+            const int e = m - kBarrierSlot - 1;
+            if (e >= 0 && e < 2 * NSL) read_k((1 - par) * kTileBytes, e);
+          },
+          sa, pa, 16);
+  };
+  // Second half: softmax of its second block beside the scores of the next tile's first and the weighted values
+  // of its own first.
+  auto second_half = [&](int t, int par) __attribute__((always_inline)) {
+    hide(sb, rows_of(t) - 32);
+    __builtin_amdgcn_sched_barrier(0);
+    slots([&](int m) { score_mfma(sa, m); }, [&](int m) { read_v(par * kTileBytes, m); }, sb, pb, 0);
+    slots([&](int m) { value_mfma(pa, m); },
+          [&](int m) { if (m < 2 * NSL) read_k((1 - par) * kTileBytes + kHalf, m); }, sb, pb, 16);
+  };
+
+  // ---- the pass without maxima
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+#pragma unroll
+    for (int c = 0; c < NCB; ++c) o[b][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    l_run[b] = 0.f;
+  }
+  issue_k(0);
+  issue_v(0);
+  __builtin_amdgcn_s_waitcnt(0x0f70 | G::kOps);  // vmcnt(kOps): all but the V tile
+  __syncthreads();
+#if defined(SCALEKV_TIMELINE)
+  t_first_tile = __builtin_amdgcn_s_memrealtime();
+#endif
+  read_q();
+#pragma unroll
+  for (int e = 0; e < 2 * NSL; ++e) read_k(0, e);
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the query fragments are in registers, their space may be refilled
+  if (n_tile > 1) issue_k(1);
+#pragma unroll
+  for (int m = 0; m < kSlots; ++m) score_mfma(sa, m);
+#pragma unroll
+  for (int e = 0; e < 2 * NSL; ++e) read_k(kHalf, e);
+  hide(sa, rows_of(0));
+  {
+    float mx[2];
+    block_max(sa, mx);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) neg_off[b] = -(fmaxf(no_max, mx[b]) * scale_log2e);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  slots([&](int m) { score_mfma(sb, m); }, nothing, sa, pa, 0);
+  turn(0);
+  slots(nothing, [&](int m) { if (m < 2 * NSL) read_k(kTileBytes, m); }, sa, pa, 16);
+  int t = 0;
+  for (; t + 2 < n_tile; t += 2) {
+    second_half(t, 0);
+    first_half(t + 1, 1);
+    second_half(t + 1, 1);
+    first_half(t + 2, 0);
+  }
+  if (t + 1 < n_tile) {
+    second_half(t, 0);
+    first_half(t + 1, 1);
+    ++t;
+  }
+  {
+    const int ofs = (t & 1) * kTileBytes;
+    hide(sb, rows_of(t) - 32);
+    slots(nothing, [&](int m) { read_v(ofs, m); }, sb, pb, 0);
+    slots([&](int m) { value_mfma(pa, m); }, nothing, sb, pb, 16);
+#pragma unroll
+    for (int m = 0; m < kSlots; ++m) read_v(ofs + kHalf, m);
+#pragma unroll
+    for (int m = 0; m < kSlots; ++m) value_mfma(pb, m);
+  }
+  // A weight or a sum beyond the range, or inf or NaN in an accumulator (huge values times large weights)?
+  // Weights are not negative, so what went wrong with one is still in its row's sum.
+  bool overflowed = false;
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    overflowed |= !(l_run[b] <= kRowSumLimit);  // catches NaN too
+#pragma unroll
+    for (int c = 0; c < NCB; ++c)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) overflowed |= !(fabsf(o[b][c][v]) < INFINITY);
+  }
+  // ---- the pass that follows the maxima (every wave has left its last tile when the votes are in)
+#if defined(SCALEKV_ABLATE_SOFTMAX)
+  overflowed = false;
+#endif
+  if (__syncthreads_or(overflowed)) {
+    float m_run[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+#pragma unroll
+      for (int c = 0; c < NCB; ++c) o[b][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+      m_run[b] = no_max;
+      l_run[b] = 0.f;
+    }
+    issue_k(0);
+    issue_v(0);
+    for (int t = 0; t < n_tile; ++t) {
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+      if (t + 1 < n_tile) {
+        issue_k(t + 1);
+        issue_v(t + 1);
+      }
+      for (int half = 0; half < 2; ++half) {
+        const int ofs = (t & 1) * kTileBytes + half * kHalf;
+#pragma unroll
+        for (int e = 0; e < 2 * NSL; ++e) read_k(ofs, e);
+#pragma unroll
+        for (int e = 0; e < kSlots; ++e) read_v(ofs, e);
+#pragma unroll
+        for (int m = 0; m < kSlots; ++m) score_mfma(sa, m);
+        hide(sa, rows_of(t) - 32 * half);
+        float mx[2];
+        block_max(sa, mx);
+        bool grow = false;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) grow |= (mx[b] - m_run[b]) * scale_log2e > kRescaleThreshold;
+        if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            const float m_new = fmaxf(m_run[b], mx[b]);
+            const float alpha = __builtin_amdgcn_exp2f((m_run[b] - m_new) * scale_log2e);
+            m_run[b] = m_new;
+            l_run[b] *= alpha;
+#pragma unroll
+            for (int c = 0; c < NCB; ++c)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) o[b][c][v] *= alpha;
+          }
+        }
+#pragma unroll
+        for (int b = 0; b < 2; ++b) neg_off[b] = -(m_run[b] * scale_log2e);
+#pragma unroll
+        for (int k = 0; k < 32; ++k) softmax_step(sa, pa, k);
+#pragma unroll
+        for (int m = 0; m < kSlots; ++m) value_mfma(pa, m);
+      }
+    }
+    __syncthreads();
+  }
   SCALEKV_STAMP(t_loop_end);
 
   // ---- append, first half: this workgroup's share of the second segment goes behind the first,
@@ -518,51 +609,55 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   const u32x4* ap_ks = (const u32x4*)(k2u + (long long)ap_row0 * kRowBytes);
   const u32x4* ap_vs = (const u32x4*)(v2u + (long long)ap_row0 * kRowBytes);
   u32x4 ap_a[8], ap_b[8];
-  int ap_tid = tid;
-  asm volatile("" : "+v"(ap_tid));  // keeps the requests below the tile loop: they must not be hoisted into it
+  // (a thread number of its own keeps the requests below the tile loop, and the row numbers of the store from
+  // being held through it: they are those that the query rows were fetched with)
+  int end_tid = tid;
+  asm volatile("" : "+v"(end_tid));
   if (ap_vec > 0) {
     // (lanes past the end of the share re-read its last vector and store nothing)
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int i = min(u * 256 + ap_tid, ap_vec - 1);
-      ap_a[u] = ap_ks[i];
-      ap_b[u] = ap_vs[i];
+      const int e = min(u * 256 + end_tid, ap_vec - 1);
+      ap_a[u] = ap_ks[e];
+      ap_b[u] = ap_vs[e];
     }
   }
   __builtin_amdgcn_sched_barrier(0);
 
-  // ---- normalise and write.  A lane owns query column j, channels 32db + 8(r/4) + 4h + r%4:
-  // sixteen 8-byte pieces of its output row.  Stored from there, every instruction of the wave
-  // would touch 32 rows with 16 bytes each; instead the wave turns its 32 x 128 block round in
+  // ---- normalise and write.  A lane owns query columns i and 16 + i, channels 16c + 4g + v:
+  // eight 8-byte pieces of each output row.  Stored from there, every instruction of the wave
+  // would touch 16 rows with 32 bytes each; instead the wave turns its 32 x 128 block round in
   // LDS (the tile stages are free: every wave has left its last tile; each wave uses a region of
   // its own, rows padded to 272 bytes against bank conflicts) and writes whole 256-byte rows,
   // 16 bytes per lane.
   {
     constexpr int kOutRowStride = kRowBytes + 16;
-    unsigned char* const ostage = smem + wave * (32 * kOutRowStride);
-    const float l_tot = both_halves_sum(l_run);
-    const float inv = 1.f / l_tot;
+    const int end_lane = end_tid & 63, end_wave = end_tid >> 6;
+    unsigned char* const ostage = smem + end_wave * (32 * kOutRowStride);
 #pragma unroll
-    for (int db = 0; db < NDB; ++db)
+    for (int b = 0; b < 2; ++b) {
+      const float inv = 1.f / xor32_sum(xor16_sum(l_run[b]));
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const bf16x2 lo = {(__bf16)(o[db][4 * g] * inv), (__bf16)(o[db][4 * g + 1] * inv)};
-        const bf16x2 hi = {(__bf16)(o[db][4 * g + 2] * inv), (__bf16)(o[db][4 * g + 3] * inv)};
+      for (int c = 0; c < NCB; ++c) {
+        const bf16x2 lo = {(__bf16)(o[b][c][0] * inv), (__bf16)(o[b][c][1] * inv)};
+        const bf16x2 hi = {(__bf16)(o[b][c][2] * inv), (__bf16)(o[b][c][3] * inv)};
         uint2 pk;
         pk.x = __builtin_bit_cast(uint32_t, lo);
         pk.y = __builtin_bit_cast(uint32_t, hi);
-        *(uint2*)(ostage + j * kOutRowStride + 64 * db + 16 * g + 8 * h) = pk;
+        *(uint2*)(ostage + (16 * b + (end_lane & 15)) * kOutRowStride + 32 * c + 8 * (end_lane >> 4)) = pk;
       }
+    }
     // the wave's own LDS writes have landed before it reads them back (same wave: no barrier)
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    unsigned char* const obase = (unsigned char*)(out + ((long long)unit * n_q + q_base) * D);
+    const int row0 = qtile * BM + end_wave * 32;
+    unsigned char* const obase = (unsigned char*)(out + ((long long)unit * n_q + row0) * D);
 #pragma unroll
     for (int p = 0; p < 2 * G::kOps; ++p) {
-      const int r = G::kRowsPerOp * p + ld_row, c = 16 * (lane % G::kChunks);
+      const int r = G::kRowsPerOp * p + end_lane / G::kChunks, c = 16 * (end_lane % G::kChunks);
       const u32x4 val = *(const u32x4*)(ostage + r * kOutRowStride + c);
-      if (q_base + r < n_q) *(u32x4*)(obase + (long long)r * kRowBytes + c) = val;
+      if (row0 + r < n_q) *(u32x4*)(obase + (long long)r * kRowBytes + c) = val;
     }
   }
   __builtin_amdgcn_sched_barrier(0);
@@ -574,24 +669,24 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     u32x4* vd = (u32x4*)(const_cast<unsigned char*>(vu) + (long long)(len1 + ap_row0) * kRowBytes);
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int i = u * 256 + tid;
-      if (i < ap_vec) {
-        __builtin_nontemporal_store(ap_a[u], kd + i);
-        __builtin_nontemporal_store(ap_b[u], vd + i);
+      const int e = u * 256 + end_tid;
+      if (e < ap_vec) {
+        __builtin_nontemporal_store(ap_a[u], kd + e);
+        __builtin_nontemporal_store(ap_b[u], vd + e);
       }
     }
-    for (int i0 = 8 * 256; i0 < ap_vec; i0 += 8 * 256) {
+    for (int e0 = 8 * 256; e0 < ap_vec; e0 += 8 * 256) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const int i = i0 + u * 256 + tid;
-        if (i < ap_vec) { ap_a[u] = ap_ks[i]; ap_b[u] = ap_vs[i]; }
+        const int e = e0 + u * 256 + end_tid;
+        if (e < ap_vec) { ap_a[u] = ap_ks[e]; ap_b[u] = ap_vs[e]; }
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const int i = i0 + u * 256 + tid;
-        if (i < ap_vec) {
-          __builtin_nontemporal_store(ap_a[u], kd + i);
-          __builtin_nontemporal_store(ap_b[u], vd + i);
+        const int e = e0 + u * 256 + end_tid;
+        if (e < ap_vec) {
+          __builtin_nontemporal_store(ap_a[u], kd + e);
+          __builtin_nontemporal_store(ap_b[u], vd + e);
         }
       }
     }

@@ -252,11 +252,8 @@ __device__ __forceinline__ float xor32_max(float x) { float a, b; swap32(x, a, b
 __device__ __forceinline__ float xor16_sum(float x) { float a, b; swap16(x, a, b); return a + b; }
 __device__ __forceinline__ float xor32_sum(float x) { float a, b; swap32(x, a, b); return a + b; }
 
-// In the 32x32 MFMA attention kernel the key row fed to MFMA row i of the first product
-// is row pi32(i) of the 32-key block (bits 2 and 3 swapped), which makes the registers of an
-// S^T block the B operand of the second product; and the number of log2 units a row maximum may
-// grow before the running offset is moved and the accumulators are rescaled.
-__device__ __forceinline__ int pi32(int i) { return (i & ~12) | ((i & 4) << 1) | ((i & 8) >> 1); }
+// The number of log2 units a row maximum may grow before the running offset is moved and the accumulators are
+// rescaled.
 constexpr float kRescaleThreshold = 8.f;
 // Running maximum of rows that have met no key yet, in kernels that take the weight of a logit s as
 // exp2(s * scale_log2e - maximum * scale_log2e): finite, and finite when it has been scaled, so that keys
