@@ -256,6 +256,7 @@ def attend_alone(args, torch, skv) -> int:
     the measurement-only builds of `python -m paper_2505_19602_amd.build --variant ...`, whose
     results are wrong on purpose: timing only.  One JSON line."""
     import workloads as W
+    from paper_2505_19602_amd import routes
     dev, dt = "cuda", torch.bfloat16
     S, H, d = args.case_seqs, args.case_heads, 128
     n_q, kv = (int(x) for x in args.attend_alone.split(","))
@@ -280,7 +281,7 @@ def attend_alone(args, torch, skv) -> int:
             "units": S * H, "n_q": n_q, "kv_len": kv, "reps": args.reps, "ms": ms,
             "tflops": flops / (ms * 1e-3) / 1e12, "frac_of_bf16_peak": flops / (ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS}
     if args.timeline:
-        line["timeline"] = timeline_summary(skv, (n_q + 127) // 128 * S * H)
+        line["timeline"] = timeline_summary(skv, -(-n_q // routes.pipe_rows(routes.pipe_form(d, S * H, n_q, kv))) * S * H)
     print(json.dumps(line), flush=True)
     return 0
 

@@ -75,7 +75,6 @@ def build(force: bool = True, verbose: bool = False) -> str:
 VARIANTS = {
     "no_softmax": ["-DSCALEKV_ABLATE_SOFTMAX"],
     "no_transfer": ["-DSCALEKV_ABLATE_TRANSFER"],
-    "one_wg_per_cu": ["-DSCALEKV_ONE_WG_PER_CU"],
     "timeline": ["-DSCALEKV_TIMELINE"],
     # every grid walked backwards; results must be bit-identical (tests/test_gpu_wg_order.py)
     "reversed_order": ["-DSCALEKV_REVERSE_WG"],

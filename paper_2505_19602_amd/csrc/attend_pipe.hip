@@ -40,9 +40,17 @@
 // The V^T operand is read with the transposing LDS load (ds_read_b64_tr_b16):
 // inside a group of 16 lanes, lane i supplies the address of 4 elements and
 // receives element (i & 3) of the data addressed by lanes (i >> 2) + 4r, r = 0..3.
-// Two stages per workgroup and tensor.  One barrier per tile (`turn`), in the middle of the second product of its
-// first half: a wave has then read all of K tile t and of V tile t - 1, and has waited for its share of K tile t + 1
-// and V tile t, which may be read from there on, while K tile t + 2 and V tile t + 1 are requested.
+// Two stages per workgroup and tensor (wide form: four).  One barrier per tile (`turn`), in the middle of the second
+// product of its first half: a wave has then read all of K tile t and of V tile t - 1, and has waited for its share of
+// K tile t + 1 and V tile t, which may be read from there on, while K tile t + 2 and V tile t + 1 (t + 4 and t + 3)
+// are requested.
+//
+// Three forms, chosen by pipe_form() in common.h, which holds their times.  Plain: four waves, 128 query rows, two
+// workgroups per compute unit (head_dim 64: three).  Wide (d 128): eight waves, 256 rows, one workgroup per compute
+// unit.  Its waves share the tiles, so the transfers into the LDS, which cost energy and issue slots (without any the
+// plain form is 20 % faster), are halved, and they are requested three tiles ahead.  Split: where there is at most one
+// plain workgroup per compute unit, two (three) groups of four waves take the tiles of the same 128 rows in turn, each
+// with stages of its own, and join their accumulators through the LDS at the end.
 //
 // Softmax.  The exponent offset of a query row is taken from the row's maximum
 // over the first block and then left alone: every later probability is exp2 of
@@ -81,9 +89,7 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
-constexpr int BM = 128;              // query rows per workgroup: 4 waves x 32
 constexpr int TN = 64;               // keys per staged tile (two blocks of 32)
-constexpr int kStages = 2;
 
 // What depends on head_dim.  head_dim 64 halves the tiles and the accumulators, so that three
 // workgroups share a compute unit instead of two; per block of 32 keys its 8 MFMA (256 clocks) and
@@ -95,15 +101,20 @@ constexpr int kStages = 2;
 // of 256 bytes all start in the same bank, of rows of 128 bytes every second.  The sixteen lanes that read
 // one chunk of sixteen K rows differ in row bits 0, 1, 3 and 4, the eight groups of lanes that read 32 bytes
 // each of eight V rows in bits 0, 1 and 4.
-template <int D>
+template <int D, int WAVES, int SPLIT>
 struct Shape {
+  static constexpr int kThreads = 64 * WAVES * SPLIT;
+  static constexpr int kRows = 32 * WAVES;                // query rows per workgroup
+  static constexpr int kStages = WAVES == 8 ? 4 : 2;
   static constexpr int kRowBytes = D * 2;
   static constexpr int kTileBytes = TN * kRowBytes;       // 16 KB (d 128), 8 KB
   static constexpr int kSlabs = D / 32;                   // k-slabs of the first product
   static constexpr int kBlocks = D / 16;                  // 16-channel blocks of the output
   static constexpr int kChunks = D / 8;                   // 16-byte chunks per row
   static constexpr int kRowsPerOp = 64 / kChunks;         // rows that one transfer of a wave covers
-  static constexpr int kOps = 16 / kRowsPerOp;            // transfers for a wave's 16 rows of a tile
+  static constexpr int kWaveRows = TN / WAVES;            // rows of a tile that one wave transfers
+  static constexpr int kOps = kWaveRows / kRowsPerOp;     // transfers for them
+  static constexpr int kQOps = 32 / kRowsPerOp;           // transfers for a wave's query rows
   static constexpr int kWavesPerSimd = D == 128 ? 2 : 3;
   __device__ static constexpr int k_flip(int r) {
     const int high = (r >> 4 & 1) | (r >> 3 & 1) << 1;
@@ -120,21 +131,15 @@ struct Shape {
 //   SCALEKV_ABLATE_SOFTMAX    probabilities are the raw scores converted to bf16: no exp2, no
 //                             row sums, no overflow watch
 //   SCALEKV_ABLATE_TRANSFER   only the first two key tiles are fetched; later tiles re-use them
-//   SCALEKV_ONE_WG_PER_CU     the workgroup claims more than half of the LDS, so that one
-//                             workgroup runs per compute unit (results stay correct)
 //   SCALEKV_TIMELINE          every workgroup records when it started, when its first tile had
 //                             arrived, when it left the tile loop and when it ended (results stay
 //                             correct); scalekv_timeline_read() hands the records to the host
-#if defined(SCALEKV_ONE_WG_PER_CU)
-template <int D>
-constexpr int kLdsBytes = 96 * 1024;
-#else
-template <int D>
-constexpr int kLdsBytes = 2 * kStages * Shape<D>::kTileBytes;  // K stages then V stages: 64 KB (d 128), 32 KB
-#endif
+template <int D, int WAVES, int SPLIT>  // K stages then V stages, of every group
+constexpr int kLdsBytes = 2 * SPLIT * Shape<D, WAVES, SPLIT>::kStages * Shape<D, WAVES, SPLIT>::kTileBytes;
 #if defined(SCALEKV_TIMELINE)
 constexpr int kTimelineMaxWg = 8192;
-constexpr int kTimelineWords = 7;  // four readings of the 100 MHz counter, the hardware id register, the shader clock counter at start and end
+// four readings of the 100 MHz counter, the hardware id register, the shader clock counter at start and end
+constexpr int kTimelineWords = 7;
 __device__ unsigned long long g_timeline[kTimelineMaxWg * kTimelineWords];
 #define SCALEKV_STAMP(name) const unsigned long long name = __builtin_amdgcn_s_memrealtime()
 #else
@@ -180,9 +185,9 @@ __device__ __forceinline__ void dma16_xor(const unsigned char* base_uniform, uns
       : "m0", "memory");
 }
 
-template <int D>
-__global__ __launch_bounds__(256)
-__attribute__((amdgpu_waves_per_eu(Shape<D>::kWavesPerSimd, Shape<D>::kWavesPerSimd)))
+template <int D, int WAVES, int SPLIT>
+__global__ __launch_bounds__(64 * WAVES * SPLIT)
+__attribute__((amdgpu_waves_per_eu(Shape<D, WAVES, SPLIT>::kWavesPerSimd, Shape<D, WAVES, SPLIT>::kWavesPerSimd)))
 void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, long long k_seq_stride,
                         long long k_head_stride, uint16_t* v, long long v_seq_stride,
                         long long v_head_stride, int len1, const uint16_t* __restrict__ k2,
@@ -193,34 +198,40 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   unsigned long long t_first_tile = 0;
   const unsigned long long c_start = __builtin_readcyclecounter();
 #endif
-  using G = Shape<D>;
-  constexpr int kRowBytes = G::kRowBytes, kTileBytes = G::kTileBytes, NSL = G::kSlabs, NCB = G::kBlocks;
+  using G = Shape<D, WAVES, SPLIT>;
+  constexpr int kStages = G::kStages, kRowBytes = G::kRowBytes, kTileBytes = G::kTileBytes;
+  constexpr int NSL = G::kSlabs, NCB = G::kBlocks;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  unsigned char* const k_lds = smem;
-  unsigned char* const v_lds = smem + kStages * kTileBytes;
 
   const int wg = xcd_order(SCALEKV_WG_X, n_wg);  // all query tiles of a unit share one L2
   const int unit = wg / n_qtile, qtile = wg - unit * n_qtile;
   const int seq = unit / n_head, head = unit - seq * n_head;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  // wave `wave` of the `group`-th group: the groups share the query rows and take the key tiles in turn
+  const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int group = SPLIT > 1 ? wave_id / WAVES : 0, wave = SPLIT > 1 ? wave_id - group * WAVES : wave_id;
+  unsigned char* const k_lds = smem + group * (2 * kStages * kTileBytes);
+  unsigned char* const v_lds = k_lds + kStages * kTileBytes;
   const int i = lane & 15, g = lane >> 4;
-  const int q_base = qtile * BM + wave * 32;
+  const int q_base = qtile * G::kRows + wave * 32;
   const uint16_t* qu = q + (long long)unit * n_q * D;
   const unsigned char* ku = (const unsigned char*)(k + seq * k_seq_stride + head * k_head_stride);
   const unsigned char* vu = (const unsigned char*)(v + seq * v_seq_stride + head * v_head_stride);
   const unsigned char* k2u = (const unsigned char*)(k2 + (long long)unit * len2 * D);
   const unsigned char* v2u = (const unsigned char*)(v2 + (long long)unit * len2 * D);
   const int n_tile1 = (len1 + TN - 1) / TN;
-  const int n_tile = n_tile1 + (len2 + TN - 1) / TN;
+  const int n_all = n_tile1 + (len2 + TN - 1) / TN;
+  const int n_tile = (n_all - group + SPLIT - 1) / SPLIT;  // of this group
+  const int n_turn = (n_all + SPLIT - 1) / SPLIT;          // of the first, which has the most
 
-  // ---- tile loader: per thread kOps K vectors and kOps V vectors of 16 bytes (4 each, d 64: 2).
-  // Instruction p of wave w fills LDS rows 16w + kRowsPerOp p .. (64 lanes x 16 B = 4 rows, d 64: 8);
+  // ---- tile loader: per thread kOps K vectors and kOps V vectors of 16 bytes (4 each; wide form and d 64: 2).
+  // Instruction p of wave w fills LDS rows kWaveRows w + kRowsPerOp p .. (64 lanes x 16 B = 4 rows, d 64: 8);
   // the lane that lands in chunk slot s of row r fetches global chunk s ^ flip(r).  For this lane
   // r = r0 + kRowsPerOp p, and both flips are linear: its K chunk is c0 ^ k_step(p) with c0 the one for
   // p = 0 (bit 3 of r alone depends on p), and its V chunk does not depend on p.  One register pair serves all
   // instructions, the rest (1024 p bytes) rides in the instruction's immediate offset.
   const int ld_row = lane / G::kChunks;                                  // row inside an instruction
-  const int ld_row0 = 16 * wave + ld_row;
+  const int ld_row0 = G::kWaveRows * wave + ld_row;
   const unsigned ld_krow = ld_row0 * kRowBytes;                          // K: row part
   const unsigned ld_kchunk = 16 * ((lane % G::kChunks) ^ G::k_flip(ld_row0));  // K: chunk part for p = 0
   const unsigned ld_vofs = ld_row0 * kRowBytes + 16 * ((lane % G::kChunks) ^ G::v_flip(ld_row0));
@@ -229,20 +240,24 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     return (unsigned)(size_t)(const __attribute__((address_space(3))) unsigned char*)p;
   };
   // LDS byte addresses of this wave's 16 rows in stage 0 (wave-uniform, kept in scalar registers)
-  const unsigned k_lds_wave = __builtin_amdgcn_readfirstlane(lds_addr(k_lds + (16 * wave) * kRowBytes));
-  const unsigned v_lds_wave = __builtin_amdgcn_readfirstlane(lds_addr(v_lds + (16 * wave) * kRowBytes));
-  // wave-uniform base of a tile and its number of valid rows, in whichever segment it lies
-  auto rows_of = [&](int tile) { return tile < n_tile1 ? len1 - tile * TN : len2 - (tile - n_tile1) * TN; };
-  auto issue_k = [&](int tile) __attribute__((always_inline)) {
-    const unsigned dst = k_lds_wave + (tile % kStages) * kTileBytes;
+  const unsigned k_lds_wave = __builtin_amdgcn_readfirstlane(lds_addr(k_lds + G::kWaveRows * wave * kRowBytes));
+  const unsigned v_lds_wave = __builtin_amdgcn_readfirstlane(lds_addr(v_lds + G::kWaveRows * wave * kRowBytes));
+  // Tile t of the group: its number of valid rows, in whichever segment it lies.
+  auto rows_of = [&](int t) {
+    const int tile = t * SPLIT + group;
+    return tile < n_tile1 ? len1 - tile * TN : len2 - (tile - n_tile1) * TN;
+  };
+  auto issue_k = [&](int t) __attribute__((always_inline)) {
+    const unsigned dst = k_lds_wave + (t % kStages) * kTileBytes;
+    const int tile = t * SPLIT + group;
     const unsigned char* src = tile < n_tile1 ? ku + (long long)tile * kTileBytes
                                               : k2u + (long long)(tile - n_tile1) * kTileBytes;
-    const int valid = rows_of(tile);
+    const int valid = rows_of(t);
     if (valid >= TN) {
       // the immediate offset moves the LDS destination along with the global source, which
       // is exactly the kRowsPerOp rows between a lane's consecutive transfers
       dma16_xor<0>(src, ld_krow, ld_kchunk, 0u, dst);
-      dma16_xor<1024>(src, ld_krow, ld_kchunk, k_step(1), dst);
+      if constexpr (G::kOps >= 2) dma16_xor<1024>(src, ld_krow, ld_kchunk, k_step(1), dst);
       if constexpr (G::kOps == 4) {
         dma16_xor<2048>(src, ld_krow, ld_kchunk, k_step(2), dst);
         dma16_xor<3072>(src, ld_krow, ld_kchunk, k_step(3), dst);
@@ -259,14 +274,15 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
       }
     }
   };
-  auto issue_v = [&](int tile) __attribute__((always_inline)) {
-    const unsigned dst = v_lds_wave + (tile % kStages) * kTileBytes;
+  auto issue_v = [&](int t) __attribute__((always_inline)) {
+    const unsigned dst = v_lds_wave + (t % kStages) * kTileBytes;
+    const int tile = t * SPLIT + group;
     const unsigned char* src = tile < n_tile1 ? vu + (long long)tile * kTileBytes
                                               : v2u + (long long)(tile - n_tile1) * kTileBytes;
-    const int valid = rows_of(tile);
+    const int valid = rows_of(t);
     if (valid >= TN) {
       dma16<0>(src, ld_vofs, dst);
-      dma16<1024>(src, ld_vofs, dst);
+      if constexpr (G::kOps >= 2) dma16<1024>(src, ld_vofs, dst);
       if constexpr (G::kOps == 4) {
         dma16<2048>(src, ld_vofs, dst);
         dma16<3072>(src, ld_vofs, dst);
@@ -304,27 +320,28 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   for (int c = 0; c < NCB; ++c) asm volatile("" : "+v"(v_adr[c]));
 
   // ---- Q fragments: B operand of the first product, resident for the whole kernel.  A lane's
-  // fragments are eight 16-byte pieces of its query row, 32 bytes apart: fetched as such, every
-  // instruction of the wave would touch 32 rows with 32 bytes each.  Instead the wave's 32 rows
+  // fragments are 16-byte pieces of two query rows, 64 bytes apart: fetched as such, every
+  // instruction of the wave would touch 16 rows with 64 bytes each.  Instead the wave's 32 rows
   // go, whole and 16 bytes per lane, straight into LDS and are read from there once the first
-  // tile has arrived.  They wait in the second stage, which is not in use before the first
-  // barrier, each wave's rows exactly where the same wave will later put its share of the second
-  // tile (16 K rows and 16 V rows): nobody else writes there, so no barrier is needed
-  // before that tile is requested, only the wave's own reads must have returned.  Chunk c of row
+  // tile has arrived.  They wait in the last stages, which are not in use yet, each wave's rows exactly
+  // where the same wave will later put its share of those tiles (kWaveRows K rows, then as many V rows,
+  // kQParts such parts): nobody else writes there, so no barrier is needed before those
+  // tiles are requested, only the wave's own reads must have returned.  Chunk c of row
   // r sits in slot c ^ q_flip(r), so that the fragment reads are free of bank conflicts.  Rows
   // past the end of the map repeat its last row; nothing is stored for them.
   bf16x8 qf[2][NSL];
-  unsigned char* const q_stage_k = k_lds + kTileBytes + (16 * wave) * kRowBytes;  // query rows 0-15 of the wave
-  unsigned char* const q_stage_v = v_lds + kTileBytes + (16 * wave) * kRowBytes;  // query rows 16-31
+  constexpr int kPartRows = G::kWaveRows, kQParts = 32 / kPartRows;
+  auto q_part = [&](int part) -> unsigned char* {
+    const int stage = kStages - kQParts / 2 + part / 2;
+    return (part & 1 ? v_lds : k_lds) + stage * kTileBytes + kPartRows * wave * kRowBytes;
+  };
   {
-    const unsigned qk = __builtin_amdgcn_readfirstlane(lds_addr(q_stage_k));
-    const unsigned qv = __builtin_amdgcn_readfirstlane(lds_addr(q_stage_v));
 #pragma unroll
-    for (int p = 0; p < 2 * G::kOps; ++p) {
+    for (int p = 0; p < G::kQOps; ++p) {
       const int r = G::kRowsPerOp * p + ld_row;
       const unsigned row = (unsigned)min(q_base + r, n_q - 1);
-      dma16<0>((const unsigned char*)qu, row * kRowBytes + 16 * ((lane % G::kChunks) ^ G::q_flip(r)),
-               (p < G::kOps ? qk : qv) + 1024 * (p % G::kOps));
+      const unsigned dst = __builtin_amdgcn_readfirstlane(lds_addr(q_part(p / G::kOps))) + 1024 * (p % G::kOps);
+      dma16<0>((const unsigned char*)qu, row * kRowBytes + 16 * ((lane % G::kChunks) ^ G::q_flip(r)), dst);
     }
   }
   auto read_q = [&]() __attribute__((always_inline)) {
@@ -332,7 +349,8 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     for (int b = 0; b < 2; ++b)
 #pragma unroll
       for (int sl = 0; sl < NSL; ++sl)
-        qf[b][sl] = *(const bf16x8*)((b ? q_stage_v : q_stage_k) + i * kRowBytes + 16 * ((4 * sl + g) ^ G::q_flip(i)));
+        qf[b][sl] = *(const bf16x8*)((kPartRows == 16 ? q_part(b) : i < 8 ? q_part(2 * b) : q_part(2 * b + 1)) +
+                                     (i % kPartRows) * kRowBytes + 16 * ((4 * sl + g) ^ G::q_flip(i)));
   };
 
   f32x4 o[2][NCB];   // [query tile][channel block]
@@ -345,7 +363,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   constexpr int kSlots = 4 * NSL;          // MFMAs of one product over a block (the two have the same number)
   constexpr int kSteps = 16 / kSlots;      // softmax steps behind each
   static_assert(kSlots == 2 * NCB && 2 * NSL <= kSlots - kSlots / 2, "the requests fit in the slots");
-  constexpr int kBarrierSlot = kSlots / 2 - 1;  // of the second product of a tile's first half
+  constexpr int kBarrierSlot = kSlots / 2 - 1;
   bf16x8 kf[2][NSL];       // K operand, [key tile][slab]
   s16x4 vf[NCB][2];        // V^T operand, [channel block][key tile]
   f32x4 sa[2][2], sb[2][2];  // scores of an even and an odd block, [query tile][key tile]
@@ -435,40 +453,47 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  // Publishes tile t + 1 of K and tile t of V, and requests the tiles after them, in the place of those that all
-  // waves have left.
+  // Publishes tile t + 1 of K and tile t of V, and requests the tiles kStages further on, in the place of those that
+  // all waves have left.  Requests are made in the order V(x), K(x + 1): what may still be under way is those of x > t.
   auto turn = [&](int t) __attribute__((always_inline)) {
-    __builtin_amdgcn_s_waitcnt(0);
+    if (kStages > 2 && t + kStages - 1 < n_tile)
+      __builtin_amdgcn_s_waitcnt(0x0070 | 2 * (kStages - 2) * G::kOps);  // vmcnt; lgkmcnt(0)
+    else
+      __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
 #if !defined(SCALEKV_ABLATE_TRANSFER)
-    if (t + 2 < n_tile) issue_k(t + 2);
-    if (t + 1 < n_tile) issue_v(t + 1);
+    if (t + kStages - 1 < n_tile) issue_v(t + kStages - 1);
+    if (t + kStages < n_tile) issue_k(t + kStages);
 #endif
     __builtin_amdgcn_sched_barrier(0);
   };
   auto nothing = [](int) {};
   // First half of tile t: softmax of its first block beside the scores of its second and the weighted values
-  // of the block before.  par = t mod 2.
-  auto first_half = [&](int t, int par) __attribute__((always_inline)) {
+  // of the block before.  st = t mod kStages.
+  auto first_half = [&](int t, int st) __attribute__((always_inline)) {
     hide(sa, rows_of(t));
     __builtin_amdgcn_sched_barrier(0);
-    slots([&](int m) { score_mfma(sb, m); }, [&](int m) { read_v((1 - par) * kTileBytes + kHalf, m); }, sa, pa, 0);
+    slots([&](int m) { score_mfma(sb, m); },
+          [&](int m) { read_v((st + kStages - 1) % kStages * kTileBytes + kHalf, m); },
+          sa, pa, 0);
     slots([&](int m) { value_mfma(pb, m); },
           [&](int m) {
             if (m == kBarrierSlot) turn(t);
             const int e = m - kBarrierSlot - 1;
-            if (e >= 0 && e < 2 * NSL) read_k((1 - par) * kTileBytes, e);
+            if (e >= 0 && e < 2 * NSL) read_k((st + 1) % kStages * kTileBytes, e);
           },
           sa, pa, 16);
   };
   // Second half: softmax of its second block beside the scores of the next tile's first and the weighted values
   // of its own first.
-  auto second_half = [&](int t, int par) __attribute__((always_inline)) {
+  auto second_half = [&](int t, int st) __attribute__((always_inline)) {
     hide(sb, rows_of(t) - 32);
     __builtin_amdgcn_sched_barrier(0);
-    slots([&](int m) { score_mfma(sa, m); }, [&](int m) { read_v(par * kTileBytes, m); }, sb, pb, 0);
+    slots([&](int m) { score_mfma(sa, m); }, [&](int m) { read_v(st * kTileBytes, m); },
+          sb, pb, 0);
     slots([&](int m) { value_mfma(pa, m); },
-          [&](int m) { if (m < 2 * NSL) read_k((1 - par) * kTileBytes + kHalf, m); }, sb, pb, 16);
+          [&](int m) { if (m < 2 * NSL) read_k((st + 1) % kStages * kTileBytes + kHalf, m); },
+          sb, pb, 16);
   };
 
   // ---- the pass without maxima
@@ -477,10 +502,24 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
 #pragma unroll
     for (int c = 0; c < NCB; ++c) o[b][c] = f32x4{0.f, 0.f, 0.f, 0.f};
     l_run[b] = 0.f;
+    neg_off[b] = -(no_max * scale_log2e);
   }
-  issue_k(0);
-  issue_v(0);
-  __builtin_amdgcn_s_waitcnt(0x0f70 | G::kOps);  // vmcnt(kOps): all but the V tile
+  if (SPLIT == 1 || n_tile > 0) {
+    issue_k(0);
+    issue_v(0);
+  }
+  if constexpr (kStages == 2) {
+    if (SPLIT == 1 || n_tile > 0)
+      __builtin_amdgcn_s_waitcnt(0x0f70 | G::kOps);  // vmcnt(kOps): all but the V tile
+    else
+      __builtin_amdgcn_s_waitcnt(0);
+  } else if (n_tile > 1) {
+    issue_k(1);
+    issue_v(1);
+    __builtin_amdgcn_s_waitcnt(0x0f70 | 3 * G::kOps);
+  } else {
+    __builtin_amdgcn_s_waitcnt(0);
+  }
   __syncthreads();
 #if defined(SCALEKV_TIMELINE)
   t_first_tile = __builtin_amdgcn_s_memrealtime();
@@ -489,44 +528,60 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
 #pragma unroll
   for (int e = 0; e < 2 * NSL; ++e) read_k(0, e);
   __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the query fragments are in registers, their space may be refilled
-  if (n_tile > 1) issue_k(1);
-#pragma unroll
-  for (int m = 0; m < kSlots; ++m) score_mfma(sa, m);
-#pragma unroll
-  for (int e = 0; e < 2 * NSL; ++e) read_k(kHalf, e);
-  hide(sa, rows_of(0));
-  {
-    float mx[2];
-    block_max(sa, mx);
-#pragma unroll
-    for (int b = 0; b < 2; ++b) neg_off[b] = -(fmaxf(no_max, mx[b]) * scale_log2e);
+  if constexpr (kStages == 2) {
+    if (n_tile > 1) issue_k(1);
+  } else {
+    if (n_tile > 2) issue_k(2), issue_v(2);
+    if (n_tile > 3) issue_k(3);
   }
-  __builtin_amdgcn_sched_barrier(0);
-  slots([&](int m) { score_mfma(sb, m); }, nothing, sa, pa, 0);
-  turn(0);
-  slots(nothing, [&](int m) { if (m < 2 * NSL) read_k(kTileBytes, m); }, sa, pa, 16);
-  int t = 0;
-  for (; t + 2 < n_tile; t += 2) {
-    second_half(t, 0);
-    first_half(t + 1, 1);
-    second_half(t + 1, 1);
-    first_half(t + 2, 0);
-  }
-  if (t + 1 < n_tile) {
-    second_half(t, 0);
-    first_half(t + 1, 1);
-    ++t;
-  }
-  {
-    const int ofs = (t & 1) * kTileBytes;
-    hide(sb, rows_of(t) - 32);
-    slots(nothing, [&](int m) { read_v(ofs, m); }, sb, pb, 0);
-    slots([&](int m) { value_mfma(pa, m); }, nothing, sb, pb, 16);
+  // (a wave whose query rows all lie behind the last one only carries its share of the tiles)
+  const bool idle = q_base >= n_q || (SPLIT > 1 && n_tile == 0);
+  int turns = 0;  // barriers of the tile loop behind this wave: all waves make n_turn
+  if (!idle) {
 #pragma unroll
-    for (int m = 0; m < kSlots; ++m) read_v(ofs + kHalf, m);
+    for (int m = 0; m < kSlots; ++m) score_mfma(sa, m);
 #pragma unroll
-    for (int m = 0; m < kSlots; ++m) value_mfma(pb, m);
+    for (int e = 0; e < 2 * NSL; ++e) read_k(kHalf, e);
+    hide(sa, rows_of(0));
+    {
+      float mx[2];
+      block_max(sa, mx);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) neg_off[b] = -(fmaxf(no_max, mx[b]) * scale_log2e);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    slots([&](int m) { score_mfma(sb, m); }, nothing, sa, pa, 0);
+    turn(0);
+    slots(nothing, [&](int m) { if (m < 2 * NSL) read_k(kTileBytes, m); }, sa, pa, 16);
+    int t = 0;
+    for (; t + kStages < n_tile; t += kStages) {
+#pragma unroll
+      for (int x = 0; x < kStages; ++x) {
+        second_half(t + x, x);
+        first_half(t + x + 1, (x + 1) % kStages);
+      }
+    }
+#pragma unroll
+    for (int x = 0; x < kStages - 1; ++x)
+      if (t + 1 < n_tile) {
+        second_half(t, x);
+        first_half(t + 1, x + 1);
+        ++t;
+      }
+    {
+      const int ofs = t % kStages * kTileBytes;
+      hide(sb, rows_of(t) - 32);
+      slots(nothing, [&](int m) { read_v(ofs, m); }, sb, pb, 0);
+      slots([&](int m) { value_mfma(pa, m); }, nothing, sb, pb, 16);
+#pragma unroll
+      for (int m = 0; m < kSlots; ++m) read_v(ofs + kHalf, m);
+#pragma unroll
+      for (int m = 0; m < kSlots; ++m) value_mfma(pb, m);
+    }
+    turns = n_tile;
   }
+  if (SPLIT > 1 || idle)
+    for (; turns < n_turn; ++turns) turn(turns);
   // A weight or a sum beyond the range, or inf or NaN in an accumulator (huge values times large weights)?
   // Weights are not negative, so what went wrong with one is still in its row's sum.
   bool overflowed = false;
@@ -536,7 +591,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
 #pragma unroll
     for (int c = 0; c < NCB; ++c)
 #pragma unroll
-      for (int v = 0; v < 4; ++v) overflowed |= !(fabsf(o[b][c][v]) < INFINITY);
+      for (int v = 0; v < 4; ++v) overflowed |= !(fabsf(o[b][c][v]) < (SPLIT > 1 ? 0x1p125f : INFINITY));
   }
   // ---- the pass that follows the maxima (every wave has left its last tile when the votes are in)
 #if defined(SCALEKV_ABLATE_SOFTMAX)
@@ -551,17 +606,19 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
       m_run[b] = no_max;
       l_run[b] = 0.f;
     }
-    issue_k(0);
-    issue_v(0);
-    for (int t = 0; t < n_tile; ++t) {
+    if (SPLIT == 1 || n_tile > 0) {
+      issue_k(0);
+      issue_v(0);
+    }
+    for (int t = 0; t < n_turn; ++t) {
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
       if (t + 1 < n_tile) {
         issue_k(t + 1);
         issue_v(t + 1);
       }
-      for (int half = 0; half < 2; ++half) {
-        const int ofs = (t & 1) * kTileBytes + half * kHalf;
+      for (int half = idle || (SPLIT > 1 && t >= n_tile) ? 2 : 0; half < 2; ++half) {
+        const int ofs = t % kStages * kTileBytes + half * kHalf;
 #pragma unroll
         for (int e = 0; e < 2 * NSL; ++e) read_k(ofs, e);
 #pragma unroll
@@ -617,12 +674,48 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     // (lanes past the end of the share re-read its last vector and store nothing)
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int e = min(u * 256 + end_tid, ap_vec - 1);
+      const int e = min(u * G::kThreads + end_tid, ap_vec - 1);
       ap_a[u] = ap_ks[e];
       ap_b[u] = ap_vs[e];
     }
   }
   __builtin_amdgcn_sched_barrier(0);
+
+  // ---- join the groups: a common offset, then the sums.  Wave w of the first group takes the parts that waves w of
+  // the others leave in LDS (the tile stages are free).
+  constexpr int kPartBytes = 64 * 2 * NCB * 16;       // a wave's accumulators, fp32
+  if constexpr (SPLIT > 1) {
+    auto part = [&](int grp) { return (f32x4*)(smem + (grp - 1) * (WAVES * kPartBytes) + wave * kPartBytes) + lane; };
+    __shared__ float part_off[SPLIT][WAVES][2][64], part_sum[SPLIT][WAVES][2][64];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      part_off[group][wave][b][lane] = -neg_off[b];
+      part_sum[group][wave][b][lane] = l_run[b];
+      if (group > 0)
+#pragma unroll
+        for (int c = 0; c < NCB; ++c) part(group)[(b * NCB + c) * 64] = o[b][c];
+    }
+    __syncthreads();
+    if (group == 0) {
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        float top = -neg_off[b];
+#pragma unroll
+        for (int x = 1; x < SPLIT; ++x) top = fmaxf(top, part_off[x][wave][b][lane]);
+        const float f0 = __builtin_amdgcn_exp2f(-neg_off[b] - top);
+        l_run[b] *= f0;
+#pragma unroll
+        for (int c = 0; c < NCB; ++c) o[b][c] *= f0;
+#pragma unroll
+        for (int x = 1; x < SPLIT; ++x) {
+          const float f = __builtin_amdgcn_exp2f(part_off[x][wave][b][lane] - top);
+          l_run[b] += f * part_sum[x][wave][b][lane];
+#pragma unroll
+          for (int c = 0; c < NCB; ++c) o[b][c] += f * part(x)[(b * NCB + c) * 64];
+        }
+      }
+    }
+  }
 
   // ---- normalise and write.  A lane owns query columns i and 16 + i, channels 16c + 4g + v:
   // eight 8-byte pieces of each output row.  Stored from there, every instruction of the wave
@@ -630,10 +723,10 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   // LDS (the tile stages are free: every wave has left its last tile; each wave uses a region of
   // its own, rows padded to 272 bytes against bank conflicts) and writes whole 256-byte rows,
   // 16 bytes per lane.
-  {
+  if (SPLIT == 1 || group == 0) {
     constexpr int kOutRowStride = kRowBytes + 16;
-    const int end_lane = end_tid & 63, end_wave = end_tid >> 6;
-    unsigned char* const ostage = smem + end_wave * (32 * kOutRowStride);
+    const int end_lane = end_tid & 63;
+    unsigned char* const ostage = smem + wave * (SPLIT > 1 ? kPartBytes : 32 * kOutRowStride);
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
       const float inv = 1.f / xor32_sum(xor16_sum(l_run[b]));
@@ -651,10 +744,10 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int row0 = qtile * BM + end_wave * 32;
+    const int row0 = q_base;
     unsigned char* const obase = (unsigned char*)(out + ((long long)unit * n_q + row0) * D);
 #pragma unroll
-    for (int p = 0; p < 2 * G::kOps; ++p) {
+    for (int p = 0; p < G::kQOps; ++p) {
       const int r = G::kRowsPerOp * p + end_lane / G::kChunks, c = 16 * (end_lane % G::kChunks);
       const u32x4 val = *(const u32x4*)(ostage + r * kOutRowStride + c);
       if (row0 + r < n_q) *(u32x4*)(obase + (long long)r * kRowBytes + c) = val;
@@ -669,21 +762,21 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     u32x4* vd = (u32x4*)(const_cast<unsigned char*>(vu) + (long long)(len1 + ap_row0) * kRowBytes);
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const int e = u * 256 + end_tid;
+      const int e = u * G::kThreads + end_tid;
       if (e < ap_vec) {
         __builtin_nontemporal_store(ap_a[u], kd + e);
         __builtin_nontemporal_store(ap_b[u], vd + e);
       }
     }
-    for (int e0 = 8 * 256; e0 < ap_vec; e0 += 8 * 256) {
+    for (int e0 = 8 * G::kThreads; e0 < ap_vec; e0 += 8 * G::kThreads) {
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const int e = e0 + u * 256 + end_tid;
+        const int e = e0 + u * G::kThreads + end_tid;
         if (e < ap_vec) { ap_a[u] = ap_ks[e]; ap_b[u] = ap_vs[e]; }
       }
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
-        const int e = e0 + u * 256 + end_tid;
+        const int e = e0 + u * G::kThreads + end_tid;
         if (e < ap_vec) {
           __builtin_nontemporal_store(ap_a[u], kd + e);
           __builtin_nontemporal_store(ap_b[u], vd + e);
@@ -706,29 +799,32 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
 #endif
 }
 
-template <int D>
+template <int D, int WAVES, int SPLIT>
 hipError_t launch(int n_unit, int n_head, const void* q, int n_q, KvView k, KvView v, int len1, const void* k2,
                   const void* v2, int len2, bool append, float sm_scale, void* out, hipStream_t stream,
                   hipEvent_t start, hipEvent_t stop) {
+  using G = Shape<D, WAVES, SPLIT>;
+  constexpr int kLds = kLdsBytes<D, WAVES, SPLIT>;
+  const auto kernel = attend_pipe_kernel<D, WAVES, SPLIT>;
   static std::atomic<uint64_t> configured{0};
-  const hipError_t e = allow_dynamic_lds((const void*)attend_pipe_kernel<D>, kLdsBytes<D>, configured);
+  const hipError_t e = allow_dynamic_lds((const void*)kernel, kLds, configured);
   if (e != hipSuccess) return e;
   const float scale_log2e = sm_scale * 1.4426950408889634f;
   const float no_max = no_maximum(scale_log2e);
-  const int n_qtile = (n_q + BM - 1) / BM;
+  const int n_qtile = (n_q + G::kRows - 1) / G::kRows;
   const int n_wg = n_qtile * n_unit;
   if (start || stop)
-    hipExtLaunchKernelGGL(attend_pipe_kernel<D>, dim3(n_wg), dim3(256), kLdsBytes<D>, stream, start, stop, 0,
-                          (const uint16_t*)q, n_q, (uint16_t*)const_cast<void*>(k.ptr), k.seq_stride,
-                          k.head_stride, (uint16_t*)const_cast<void*>(v.ptr), v.seq_stride,
-                          v.head_stride, len1, (const uint16_t*)k2, (const uint16_t*)v2, len2,
-                          append ? 1 : 0, n_head, n_qtile, n_wg, scale_log2e, no_max, (uint16_t*)out);
+    hipExtLaunchKernelGGL(kernel, dim3(n_wg), dim3(G::kThreads), kLds, stream, start, stop, 0, (const uint16_t*)q, n_q,
+                          (uint16_t*)const_cast<void*>(k.ptr), k.seq_stride, k.head_stride,
+                          (uint16_t*)const_cast<void*>(v.ptr), v.seq_stride, v.head_stride, len1, (const uint16_t*)k2,
+                          (const uint16_t*)v2, len2, append ? 1 : 0, n_head, n_qtile, n_wg, scale_log2e, no_max,
+                          (uint16_t*)out);
   else
-    hipLaunchKernelGGL(attend_pipe_kernel<D>, dim3(n_wg), dim3(256), kLdsBytes<D>, stream,
-                       (const uint16_t*)q, n_q, (uint16_t*)const_cast<void*>(k.ptr), k.seq_stride,
-                       k.head_stride, (uint16_t*)const_cast<void*>(v.ptr), v.seq_stride,
-                       v.head_stride, len1, (const uint16_t*)k2, (const uint16_t*)v2, len2,
-                       append ? 1 : 0, n_head, n_qtile, n_wg, scale_log2e, no_max, (uint16_t*)out);
+    hipLaunchKernelGGL(kernel, dim3(n_wg), dim3(G::kThreads), kLds, stream, (const uint16_t*)q, n_q,
+                       (uint16_t*)const_cast<void*>(k.ptr), k.seq_stride, k.head_stride,
+                       (uint16_t*)const_cast<void*>(v.ptr), v.seq_stride, v.head_stride, len1, (const uint16_t*)k2,
+                       (const uint16_t*)v2, len2, append ? 1 : 0, n_head, n_qtile, n_wg, scale_log2e, no_max,
+                       (uint16_t*)out);
   return hipGetLastError();
 }
 
@@ -738,10 +834,14 @@ hipError_t launch_attend_pipe(int n_unit, int n_head, int d, const void* q, int 
                               int len1, const void* k2, const void* v2, int len2, bool append,
                               float sm_scale, void* out, hipStream_t stream, hipEvent_t start,
                               hipEvent_t stop) {
-  return d == 128 ? launch<128>(n_unit, n_head, q, n_q, k, v, len1, k2, v2, len2, append, sm_scale, out, stream,
-                                start, stop)
-                  : launch<64>(n_unit, n_head, q, n_q, k, v, len1, k2, v2, len2, append, sm_scale, out, stream,
-                               start, stop);
+#define SCALEKV_PIPE(D, W, S) \
+  launch<D, W, S>(n_unit, n_head, q, n_q, k, v, len1, k2, v2, len2, append, sm_scale, out, stream, start, stop)
+  switch (pipe_form(d, n_unit, n_q, len1 + len2)) {
+    case PipeForm::kWide: return SCALEKV_PIPE(128, 8, 1);
+    case PipeForm::kSplit: return d == 128 ? SCALEKV_PIPE(128, 4, 2) : SCALEKV_PIPE(64, 4, 3);
+    default: return d == 128 ? SCALEKV_PIPE(128, 4, 1) : SCALEKV_PIPE(64, 4, 1);
+  }
+#undef SCALEKV_PIPE
 }
 
 }  // namespace scalekv

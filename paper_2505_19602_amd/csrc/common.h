@@ -161,7 +161,8 @@ enum class SmallWork {
   kAttend,   // nothing
   kAppend,   // the map's rows are copied behind the cached ones
   kKeepAll,  // every cached row is copied as well
-  kRanked    // the kept rows, chosen in this launch or the one before, are copied
+  kRanked,   // the kept rows, chosen in this launch, are copied
+  kRankedBefore  // the kept rows, chosen in the launch before, are copied
 };
 // Query rows per workgroup of that kernel for n_q bf16 queries over kv keys, 0 where the other kernels
 // are the better ones.  A workgroup of it fills a compute unit, and its time grows with the rows it
@@ -173,10 +174,13 @@ enum class SmallWork {
 //   128 rows:  256 x 128, 300, 60: 28.3 / 30.2      128 x 256, 380, 82: 33.5 / 33.6
 //              128 x 144, 5000, 5000: 294 / 217     (longer than 320 keys: not worth it)
 // From 64 rows on it is what the launch does besides the attention that pays: the attention alone is then faster in the
-// pipelined kernel (64 x 144 queries, 300 keys: 14.6 / 11.9; 128 x 144, 300 keys, 128 rows: 21.3 / 12.7), but for
-// head_dim 64 over many keys (16 x 1024, 1224 keys: 0.89 of its time).  Without a ranking 64 rows pay while
+// pipelined kernel (64 x 144 queries, 300 keys: 14.6 / 11.9; 128 x 144, 300 keys, 128 rows: 21.3 / 12.7), and with few
+// keys from 32 rows on (8 x 700, 64 keys: 7.5 / 5.6; 130: 8.5 / 8.2; 400: 11.7 / 12.1).  A ranking in the same launch
+// is repeated by every workgroup of a unit: 64 rows pay up to 16 of those, 32 only with head_dim 64 (8 x 2048, 380, 82:
+// 57.9 / 49.8, head_dim 64 33.6 / 36.5).  Without one 64 rows pay while
 // the workgroups leave some compute units to those that copy, which otherwise wait for a round of their
-// own (all kept, 64 x 144 queries, 100 cached, 192 workgroups: 15.2 / 18.8; 64 x 256, 256 workgroups: 23.8 / 21.0;
+// own (all kept, 64 x 144 queries, 100 cached, 192 workgroups: 13.1 / 17.2; 64 x 256, 256 workgroups: 23.8 / 19.2;
+// ranked before, 2500 cached, 300 kept: 64 x 144 54.3 / 57.4; 64 x 256 62.7 / 59.4; 16 x 1024 73.6 / 66.4;
 // head_dim 64 copies half as much: 0.71-0.99 of the time up to 256; one workgroup per unit is as fast or faster but
 // around 100 cached rows: 256 x 36 queries, 19, 70, 100, 500: 13.3 / 13.8, 17.0 / 19.2, 22.8 / 20.7, 42.8 / 47.7),
 // 128 rows do not (128 x 200, 100: 32.3 / 24.5).
@@ -192,14 +196,46 @@ inline int small_tile_rows(int dtype, int d, int n_unit, int n_q, int kv, SmallW
   for (; rows <= 128; rows *= 2)
     if ((n_wg = (long long)n_unit * ((n_q + rows - 1) / rows)) <= kComputeUnits) break;
   if (rows > 128) return n_q <= 16 ? 16 : 0;
+  if (rows == 32 && work == SmallWork::kAttend && kv <= 128) return 0;
   if (rows <= 32) return rows;
   if (rows == 128) return work == SmallWork::kRanked && kv <= 320 ? rows : 0;
   const bool spare = n_wg <= kComputeUnits * 7 / 8;
-  const bool pays = work == SmallWork::kRanked || (work == SmallWork::kKeepAll && (d == 64 || spare || n_q <= 64)) ||
-                    (work == SmallWork::kAppend && d == 64 && spare) ||
-                    (work == SmallWork::kAttend && d == 64 && kv >= 512);
+  const bool pays = (work == SmallWork::kRanked && (d == 64 || n_q <= 1024)) ||
+                    (work == SmallWork::kRankedBefore && spare) || (work == SmallWork::kKeepAll && (d == 64 || spare || n_q <= 64)) ||
+                    (work == SmallWork::kAppend && d == 64 && spare);
   return pays ? rows : 0;
 }
+
+// Forms of the pipelined attention kernel.
+enum class PipeForm {
+  kPlain,  // 128 query rows and four waves per workgroup, two (head_dim 64: three) workgroups per compute unit
+  kWide,   // 256 query rows and eight waves, one workgroup per compute unit: half the tile transfers
+  kSplit   // 128 query rows, two (three) groups of four waves that share them and split the keys
+};
+// Measured (us; units x queries, keys; d 128 unless stated):
+//   split / plain, up to a workgroup per compute unit (a plain one leaves half of it idle):
+//     16 x 1024, 400: 12.5 / 13.3   1200: 22.3 / 27.4   4000: 59 / 79      64 x 400, 1200: 23.5 / 28.2
+//     few keys do not pay for the join: 16 x 1024, 130: 9.1 / 8.8   64 keys: 7.4 / 6.1
+//     more workgroups than compute units: 48 x 700, 1200: 45 / 35
+//     d 64: 64 x 400, 400: 9.7 / 10.1   1200: 16.1 / 20.4   4000: 38.6 / 58.4   130: 7.5 / 6.7
+//   wide / plain, from a workgroup per compute unit on: 256 x 4096, 3000: 1425 / 1469     256 x 129, 3000: 92 / 98
+//     few keys do not pay (start and end of a workgroup have no neighbour to hide behind): 256 x 4096, 1200: 646 / 647
+//     300: 261 / 234
+//     a last round that is nearly empty, or rows of padding, cost twice as much:
+//     256 x 320, 3000: 169 / 161    512 x 576, 3000: 520 / 475     64 x 2304, 3000: 241 / 223
+//     less than a round: 96 x 320, 3000: 77 / 75
+inline PipeForm pipe_form(int d, int n_unit, int n_q, int kv) {
+  constexpr int kComputeUnits = 256;
+  const long long wide = (long long)n_unit * ((n_q + 255) / 256), plain = (long long)n_unit * ((n_q + 127) / 128);
+  if (plain <= kComputeUnits) return kv >= 320 ? PipeForm::kSplit : PipeForm::kPlain;
+  if (d != 128 || wide < kComputeUnits || kv < 2048) return PipeForm::kPlain;
+  // rounds over the chip, in hundredths; a plain round that is at most half full takes 70
+  const long long rest = plain % (2 * kComputeUnits);
+  const long long wide_rounds = (wide + kComputeUnits - 1) / kComputeUnits * 100;
+  const long long plain_rounds = plain / (2 * kComputeUnits) * 100 + (rest == 0 ? 0 : rest <= kComputeUnits ? 70 : 100);
+  return wide_rounds * 96 <= plain_rounds * 100 ? PipeForm::kWide : PipeForm::kPlain;
+}
+inline int pipe_rows(PipeForm form) { return form == PipeForm::kWide ? 256 : 128; }  // query rows per workgroup
 
 // bf16: the pipelined kernel used when there is enough work for it.  Keys and values are the
 // first len1 rows of the caches k, v followed by the len2 rows of the dense tensors k2, v2

@@ -7,7 +7,8 @@ from __future__ import annotations
 import torch
 
 COMPUTE_UNITS = 256
-ATTEND, APPEND, KEEP_ALL, RANKED = range(4)   # enum class SmallWork
+ATTEND, APPEND, KEEP_ALL, RANKED, RANKED_BEFORE = range(5)   # enum class SmallWork
+SHORT_LEN = 1536   # longest cache that is ranked in the launch that attends
 
 
 def small_tile_rows(dtype: torch.dtype, d: int, units: int, n_q: int, kv: int, work: int) -> int:
@@ -20,13 +21,15 @@ def small_tile_rows(dtype: torch.dtype, d: int, units: int, n_q: int, kv: int, w
             break
     else:
         return 16 if n_q <= 16 else 0
+    if rows == 32 and work == ATTEND and kv <= 128:
+        return 0
     if rows <= 32:
         return rows
     if rows == 128:
         return rows if work == RANKED and kv <= 320 else 0
     spare = n_wg <= COMPUTE_UNITS * 7 // 8
-    pays = work == RANKED or (work == KEEP_ALL and (d == 64 or spare or n_q <= 64)) or \
-        (work == APPEND and d == 64 and spare) or (work == ATTEND and d == 64 and kv >= 512)
+    pays = (work == RANKED and (d == 64 or n_q <= 1024)) or (work == RANKED_BEFORE and spare) or \
+        (work == KEEP_ALL and (d == 64 or spare or n_q <= 64)) or (work == APPEND and d == 64 and spare)
     return rows if pays else 0
 
 
@@ -37,10 +40,28 @@ def attend_kernel(dtype: torch.dtype, d: int, units: int, n_q: int, kv: int, wor
     return "small" if small_tile_rows(dtype, d, units, n_q, kv, work) else "pipelined"
 
 
+def pipe_form(d: int, units: int, n_q: int, kv: int) -> str:
+    """The form of the pipelined kernel: "plain", "wide" or "split"."""
+    wide, plain = units * -(-n_q // 256), units * -(-n_q // 128)
+    if plain <= COMPUTE_UNITS:
+        return "split" if kv >= 320 else "plain"
+    if d != 128 or wide < COMPUTE_UNITS or kv < 2048:
+        return "plain"
+    rest = plain % (2 * COMPUTE_UNITS)
+    plain_rounds = plain // (2 * COMPUTE_UNITS) * 100 + (0 if rest == 0 else 70 if rest <= COMPUTE_UNITS else 100)
+    return "wide" if -(-wide // COMPUTE_UNITS) * 9600 <= plain_rounds * 100 else "plain"
+
+
+def pipe_rows(form: str) -> int:
+    """Query rows per workgroup."""
+    return 256 if form == "wide" else 128
+
+
 def step_kernel(dtype: torch.dtype, d: int, units: int, n_cur: int, cache_len: int, budget: int) -> str:
     """The same for the attention of scalekv_step; "small" prunes and appends in the same launch."""
     keep = min(budget, cache_len)
-    work = RANKED if 0 < keep < cache_len else KEEP_ALL if keep else APPEND
+    ranked = RANKED if cache_len <= SHORT_LEN else RANKED_BEFORE
+    work = ranked if 0 < keep < cache_len else KEEP_ALL if keep else APPEND
     return attend_kernel(dtype, d, units, n_cur, keep + n_cur, work)
 
 

@@ -42,3 +42,40 @@ def test_routes_are_the_rules_of_the_library(tmp_path):
                          int(routes.asi_streams(torch.bfloat16, u, k, q, 64))]
                 assert [int(x) for x in next(lines).split()] == want, (u, q, k)
     assert next(lines, None) is None
+
+
+FORMS_PROGRAM = """
+#include <cstdio>
+#include "common.h"
+using namespace scalekv;
+int main() {
+  const int units[] = {%s}, queries[] = {%s}, keys[] = {%s};
+  for (int u : units) for (int q : queries) for (int k : keys)
+    for (int d = 64; d <= 128; d += 64) {
+      const PipeForm f = pipe_form(d, u, q, k);
+      printf("%%s %%d %%d\\n", f == PipeForm::kPlain ? "plain" : f == PipeForm::kWide ? "wide" : "split", pipe_rows(f),
+             small_tile_rows(1, d, u, q, k, SmallWork::kRankedBefore));
+    }
+}
+"""
+
+
+def test_forms_of_the_pipelined_kernel_are_the_rules_of_the_library(tmp_path):
+    src, exe = tmp_path / "forms.hip", tmp_path / "forms"
+    keys = KEYS + (319, 2047, 2048)
+    src.write_text(FORMS_PROGRAM % tuple(", ".join(map(str, t)) for t in (UNITS, QUERIES, keys)))
+    cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-host-only", "-std=c++17", f"-I{CSRC}", str(src), "-o", str(exe)]
+    res = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stderr[-3000:]
+    lines = iter(subprocess.run([str(exe)], capture_output=True, text=True, check=True, timeout=60).stdout.splitlines())
+    seen = set()
+    for u in UNITS:
+        for q in QUERIES:
+            for k in keys:
+                for d in (64, 128):
+                    form = routes.pipe_form(d, u, q, k)
+                    seen.add((d, form))
+                    rows = routes.small_tile_rows(torch.bfloat16, d, u, q, k, routes.RANKED_BEFORE)
+                    assert next(lines) == f"{form} {routes.pipe_rows(form)} {rows}", (u, q, k, d)
+    assert next(lines, None) is None
+    assert seen == {(64, "plain"), (64, "split"), (128, "plain"), (128, "wide"), (128, "split")}

@@ -1,0 +1,79 @@
+"""The three forms of the pipelined bf16 attention kernel (four waves, eight waves on 256 rows, groups of waves that
+split the keys) at the edges of their tiles, groups and stages, against the oracle; rows whose scores rise so far above the
+first block's that the pass is repeated; the two-segment form with the append."""
+import pytest
+import torch
+
+import oracle
+import paper_2505_19602_amd as skv
+import workloads as W
+from paper_2505_19602_amd import routes
+from parity_util import check_output, units
+
+pytestmark = pytest.mark.gpu
+DEV, BF16 = "cuda", torch.bfloat16
+
+
+def _rand(key, shape):
+    return W.normal_tensor(W.stream_key(777, key), shape, DEV).to(BF16)
+
+
+def _check(form, d, S, H, n_q, kv, key, rise=0.0, rise_from=0, cached=None):
+    """One attention of S x H units; with `cached` as a step that keeps that many rows and appends the others."""
+    assert routes.attend_kernel(BF16, d, S * H, n_q, kv) == "pipelined"
+    assert routes.pipe_form(d, S * H, n_q, kv) == form
+    print(f"{form} d={d} {S}x{H} units {n_q} queries {kv} keys rise={rise} from {rise_from} cached={cached}", flush=True)
+    shape = skv.Shape(S, H, d, BF16)
+    q, k, v = (_rand(10 * key + i, (S, H, n, d)) for i, n in enumerate((n_q, kv, kv)))
+    if rise:
+        q[..., 0] = 8.0
+        k[..., 0] = 0.0
+        k[:, :, rise_from:, 0] = rise * d ** 0.5 / 8.0
+    out = torch.empty_like(q)
+    if cached is None:
+        skv.attend(shape, q, k, v, kv, out)
+    else:
+        parts = [t.contiguous() for t in (k[:, :, cached:], v[:, :, cached:], k[:, :, :cached], v[:, :, :cached])]
+        kd, vd = torch.zeros_like(k), torch.zeros_like(v)
+        skv.step(shape, q, parts[0], parts[1], [0], parts[2], parts[3], cached, cached, kd, vd, out, None, None)
+        assert torch.equal(kd, k) and torch.equal(vd, v)
+    torch.cuda.synchronize()
+    pick = sorted({0, S * H // 2, S * H - 1})
+    rows = sorted({0, 31, 32, 127, 128, n_q // 2, n_q - 33, n_q - 1} & set(range(n_q)))
+    take = lambda t: units(t.reshape(S * H, 1, *t.shape[2:])[pick])
+    ref = oracle.attend(take(q)[:, rows], take(k), take(v), d ** -0.5)
+    check_output(take(out)[:, rows], ref, BF16, form)
+    assert torch.isfinite(out).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("kv", [320, 321, 383, 384, 385, 449, 577, 640, 1023])
+def test_split_form_at_tile_and_group_edges(d, kv):
+    _check("split", d, 4, 5, 430, kv, kv)
+
+
+@pytest.mark.parametrize("n_q,kv", [(129, 2048), (200, 2049), (256, 2111), (256, 2112), (161, 2177), (224, 2304)])
+def test_wide_form_at_tile_and_stage_edges(n_q, kv):
+    _check("wide", 128, 16, 16, n_q, kv, kv)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n_q,kv", [(20, 1), (129, 31), (100, 33), (128, 64), (33, 65), (200, 127), (129, 129), (64, 193)])
+def test_plain_form_of_few_keys(d, n_q, kv):
+    _check("plain", d, 15, 20, n_q, kv, kv)
+
+
+# 78 natural units are 112 binary ones: weights beyond the checked 2^100 but finite; 110 are 159: infinite weights
+@pytest.mark.parametrize("rise", [78.0, 110.0])
+@pytest.mark.parametrize("form,d,S,H,n_q,kv", [("split", 64, 4, 5, 430, 500), ("split", 128, 4, 5, 430, 500),
+                                               ("wide", 128, 16, 16, 130, 2100), ("plain", 128, 15, 20, 40, 200)])
+@pytest.mark.parametrize("last", [False, True])
+def test_scores_far_above_the_first_block_in_each_form(form, d, S, H, n_q, kv, rise, last):
+    _check(form, d, S, H, n_q, kv, 3, rise, kv - 1 if last else 100)
+
+
+@pytest.mark.parametrize("form,d,S,H,n_q,cached", [("split", 64, 4, 10, 430, 101), ("split", 128, 4, 10, 430, 64),
+                                                   ("split", 128, 4, 10, 430, 129), ("wide", 128, 16, 16, 200, 1999)])
+def test_step_of_two_segments_in_each_form(form, d, S, H, n_q, cached):
+    assert routes.step_kernel(BF16, d, S * H, n_q, cached, cached) == "pipelined"
+    _check(form, d, S, H, n_q, cached + n_q, 4, cached=cached)
