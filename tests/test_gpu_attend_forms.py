@@ -1,6 +1,6 @@
 """The three forms of the pipelined bf16 attention kernel (four waves, eight waves on 256 rows, groups of waves that
-split the keys) at the edges of their tiles, groups and stages, against the oracle; rows whose scores rise so far above the
-first block's that the pass is repeated; the two-segment form with the append."""
+split the keys) at the edges of their tiles, groups and stages, against the oracle; rows whose scores rise so far above
+the first block's that the pass is repeated; the two-segment form with the append."""
 import pytest
 import torch
 
@@ -18,13 +18,14 @@ def _rand(key, shape):
     return W.normal_tensor(W.stream_key(777, key), shape, DEV).to(BF16)
 
 
-def _check(form, d, S, H, n_q, kv, key, rise=0.0, rise_from=0, cached=None):
+def _check(form, d, S, H, n_q, kv, key, rise=0.0, rise_from=0, cached=None, value_scale=1.0):
     """One attention of S x H units; with `cached` as a step that keeps that many rows and appends the others."""
     assert routes.attend_kernel(BF16, d, S * H, n_q, kv) == "pipelined"
     assert routes.pipe_form(d, S * H, n_q, kv) == form
     print(f"{form} d={d} {S}x{H} units {n_q} queries {kv} keys rise={rise} from {rise_from} cached={cached}", flush=True)
     shape = skv.Shape(S, H, d, BF16)
     q, k, v = (_rand(10 * key + i, (S, H, n, d)) for i, n in enumerate((n_q, kv, kv)))
+    v = v * value_scale
     if rise:
         q[..., 0] = 8.0
         k[..., 0] = 0.0
@@ -42,7 +43,7 @@ def _check(form, d, S, H, n_q, kv, key, rise=0.0, rise_from=0, cached=None):
     rows = sorted({0, 31, 32, 127, 128, n_q // 2, n_q - 33, n_q - 1} & set(range(n_q)))
     take = lambda t: units(t.reshape(S * H, 1, *t.shape[2:])[pick])
     ref = oracle.attend(take(q)[:, rows], take(k), take(v), d ** -0.5)
-    check_output(take(out)[:, rows], ref, BF16, form)
+    check_output(take(out)[:, rows].double() / value_scale, ref / value_scale, BF16, form)
     assert torch.isfinite(out).all()
 
 
@@ -63,8 +64,9 @@ def test_plain_form_of_few_keys(d, n_q, kv):
     _check("plain", d, 15, 20, n_q, kv, kv)
 
 
-# 78 natural units are 112 binary ones: weights beyond the checked 2^100 but finite; 110 are 159: infinite weights
-@pytest.mark.parametrize("rise", [78.0, 110.0])
+# The first block's largest weight is 2^-60.  100 natural units above it, 144 binary ones, the pass stays as it is; at
+# 126.5 weights are 2^122.5, above the checked 2^120; at 150 they are infinite.
+@pytest.mark.parametrize("rise", [100.0, 126.5, 150.0])
 @pytest.mark.parametrize("form,d,S,H,n_q,kv", [("split", 64, 4, 5, 430, 500), ("split", 128, 4, 5, 430, 500),
                                                ("wide", 128, 16, 16, 130, 2100), ("plain", 128, 15, 20, 40, 200)])
 @pytest.mark.parametrize("last", [False, True])
@@ -77,3 +79,19 @@ def test_scores_far_above_the_first_block_in_each_form(form, d, S, H, n_q, kv, r
 def test_step_of_two_segments_in_each_form(form, d, S, H, n_q, cached):
     assert routes.step_kernel(BF16, d, S * H, n_q, cached, cached) == "pipelined"
     _check(form, d, S, H, n_q, cached + n_q, 4, cached=cached)
+
+
+# values whose products with weights around 2^-60 and below would be lost (2^-80, 2^-110), or nearly (2^-36); and none
+@pytest.mark.parametrize("value_scale", [2.0 ** -36, 2.0 ** -80, 2.0 ** -110])
+@pytest.mark.parametrize("form,d,S,H,n_q,kv", [("split", 64, 4, 5, 430, 500), ("split", 128, 4, 5, 430, 500),
+                                               ("wide", 128, 16, 16, 130, 2100), ("plain", 128, 15, 20, 40, 200)])
+def test_small_values_in_each_form(form, d, S, H, n_q, kv, value_scale):
+    _check(form, d, S, H, n_q, kv, 5, value_scale=value_scale)
+
+
+def test_values_of_zero():
+    shape = skv.Shape(15, 20, 128, BF16)
+    q, k = _rand(1, (15, 20, 40, 128)), _rand(2, (15, 20, 200, 128))
+    v, out = torch.zeros_like(k), torch.ones_like(q)
+    skv.attend(shape, q, k, v, 200, out)
+    assert torch.equal(out, torch.zeros_like(out))
