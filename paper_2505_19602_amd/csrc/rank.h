@@ -105,8 +105,8 @@ __device__ __forceinline__ void block_extremes(uint32_t& hi, uint32_t& lo, uint3
 }
 
 // Row normalisers max_j + log Z_j of all sixteen window rows, by one wave: lane (g, i) brings maximum and
-// sum of virtual waves 4g .. 4g+3 of row i and, in mm, the largest of those maxima.
-__device__ __forceinline__ void row_shifts(const float (&vm)[4], const float (&ve)[4], float mm,
+// sum of virtual waves 4g .. 4g+3 of row i and, in mm, the largest of those maxima.  Those of g >= turns are empty.
+__device__ __forceinline__ void row_shifts(const float (&vm)[4], const float (&ve)[4], float mm, int turns,
                                            float (&shift)[kMaxWindow]) {
   const int i = threadIdx.x & 15;
   mm = xor32_max(xor16_max(mm));
@@ -114,6 +114,7 @@ __device__ __forceinline__ void row_shifts(const float (&vm)[4], const float (&v
   float z = 0.f;
 #pragma unroll
   for (int turn = 0; turn < 4; ++turn) {
+    if (turn >= turns) break;
     float part = z;
 #pragma unroll
     for (int x = 0; x < 4; ++x)
@@ -191,6 +192,48 @@ __device__ __forceinline__ void select_scores(float (&own)[PER], int len, int ke
   __syncthreads();
 }
 
+// The same for a few rows (len PARTS <= THREADS; own: log-score of row tid) by counting, for every row, those with a
+// larger score: PARTS lanes share a row, and each compares its key with a part of the others.  The radix search takes
+// three or four barriers and as many round trips through LDS counters; this takes two.  False, with nothing
+// emitted, if equal scores straddle the border: then it takes the search to choose among them.
+// Whole steps, us, search / counting: 16 units, 16 queries, 69 rows 11.0 / 9.9; 128 rows 12.1 / 10.8; 200 rows (two parts)
+// 12.7 / 12.3; head_dim 64, 69 rows 9.2 / 8.0; 256 units, 69 rows 12.9 / 11.4; 64 queries, 250 rows 21.7 / 21.5.
+constexpr int kCountedRows = 256;  // longest for two parts: 128 comparisons a lane
+template <int THREADS, int PARTS, typename Lds>
+__device__ __forceinline__ bool select_by_rank(float own, int len, int keep, Lds& lds, int32_t* list, int32_t* idx) {
+  constexpr int kWaves = THREADS / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int share = (len + 4 * PARTS - 1) / (4 * PARTS) * 4;  // keys per lane; a key of 0 beyond len is larger than none
+  if (tid < share * PARTS) lds.keys[tid] = tid < len ? order_key(own) : 0u;
+  __syncthreads();
+  const int row = tid / PARTS;
+  const uint32_t mine = lds.keys[min(row, len - 1)];
+  const uint4* part = reinterpret_cast<const uint4*>(lds.keys + tid % PARTS * share);
+  int above = 0;
+#pragma unroll 4
+  for (int j = 0; j < share / 4; ++j) {
+    const uint4 x = part[j];
+    above += (x.x > mine) + (x.y > mine) + (x.z > mine) + (x.w > mine);
+  }
+  above += __builtin_amdgcn_update_dpp(0, above, 0xb1, 0xf, 0xf, true);             // lane ^ 1
+  if (PARTS == 4) above += __builtin_amdgcn_update_dpp(0, above, 0x4e, 0xf, 0xf, true);  // lane ^ 2
+  const bool take = row < len && above < keep;
+  const unsigned long long taken = __builtin_amdgcn_ballot_w64(take && tid % PARTS == 0);
+  if (lane == 0) lds.count[wave] = __builtin_popcountll(taken);
+  __syncthreads();
+  const uint32_t counted = lane < kWaves ? lds.count[lane] : 0u;
+  const uint32_t upto = wave_prefix_sum(counted, lane);
+  if (__builtin_amdgcn_readlane(upto, 63) != (uint32_t)keep) return false;
+  const uint32_t before = wave > 0 ? __builtin_amdgcn_readlane(upto, wave - 1) : 0u;
+  if (taken >> lane & 1) {
+    const uint32_t pos = before + __builtin_popcountll(taken & (((unsigned long long)1 << lane) - 1));
+    list[pos] = row;
+    if (idx) idx[pos] = row;
+  }
+  __syncthreads();
+  return true;
+}
+
 // Leaves the `keep` selected rows in lds.list (0 < keep < len <= kShortLen) and, if idx is not
 // NULL, in idx.  All THREADS threads of the workgroup call it; `logits` may be overwritten
 // afterwards without a barrier.
@@ -246,7 +289,7 @@ __device__ __forceinline__ void rank_short(const uint16_t* qu, const WindowRows&
       ve[x] = e_run;
       mm = fmaxf(mm, m_run);
     }
-    row_shifts(vm, ve, mm, shift);
+    row_shifts(vm, ve, mm, (min(n_group, kVirtualWaves) + 3) / 4, shift);
   }
 
   // ---- log-scores, as keys whose order is theirs
@@ -263,6 +306,13 @@ __device__ __forceinline__ void rank_short(const uint16_t* qu, const WindowRows&
         la[j4] = x.x; la[j4 + 1] = x.y; la[j4 + 2] = x.z; la[j4 + 3] = x.w;
       }
       own[c] = log_sum_rows(la, n_win, shift);
+    }
+  }
+  if constexpr (!EXTRAS) {
+    if (len <= THREADS / 4) {
+      if (select_by_rank<THREADS, 4>(own[0], len, keep, lds, lds.list, idx)) return;
+    } else if (len <= kCountedRows && len <= THREADS / 2) {
+      if (select_by_rank<THREADS, 2>(own[0], len, keep, lds, lds.list, idx)) return;
     }
   }
   select_scores<THREADS, kPer, EXTRAS>(own, len, keep, ex, lds, lds.list, idx);
@@ -354,7 +404,7 @@ __device__ __forceinline__ const int32_t* rank_long(const uint16_t* qu, const Wi
       ve[x] = lds.wave_rowsum[4 * g + x][i];
       mm = fmaxf(mm, vm[x]);
     }
-    row_shifts(vm, ve, mm, shift);
+    row_shifts(vm, ve, mm, 4, shift);
   }
   auto log_score = [&](const float* lg) -> float {
     float la[kMaxWindow];

@@ -116,6 +116,18 @@ def test_small_step_edges(d, S, H, L, budget, n_cur, n_win, dup):
         assert torch.equal(a, b)
 
 
+# Short caches are selected by counting, four lanes or two to a row (512 threads: up to 128 and 256 rows; the ranking
+# kernel with 1024: 256): shares of four keys and their remainders, the first length beyond; runs of equal rows that
+# the border cuts or not, and rows that are all equal, which the search decides.
+@pytest.mark.parametrize("S,H,n_cur", [(1, 3, 20), (4, 50, 300)])
+@pytest.mark.parametrize("L,budget", [(5, 2), (16, 15), (17, 8), (127, 60), (128, 1), (129, 128), (255, 90), (256, 255),
+                                      (257, 30)])
+@pytest.mark.parametrize("dup", [1, 3, 1000])
+def test_selection_of_short_caches(S, H, n_cur, L, budget, dup):
+    print(f"short selection {S}x{H} L={L} budget={budget} n_cur={n_cur} dup={dup}", flush=True)
+    _step_against_oracle(S, H, 64, L, budget, n_cur, 16, sorted({0, S * H - 1}), 11, dup)
+
+
 # Streamed selectivity: rounds of 512 keys, lists that overflow and are cut (keys in ascending order of
 # their scores), ties at the threshold, several parts per unit, one and two blocks of 16 rows, history
 # within a round, K' at its limits and beyond (the route through the logits)
