@@ -21,10 +21,10 @@
 // ahead of use.  A map of a few hundred queries alone leaves most of the chip idle (400 queries x
 // 32 units are 416 waves of 32 rows for 1024 SIMDs), so the waves of a workgroup share their query
 // rows and split the keys; their partial results are joined in LDS at the end.
-// 400 queries x 517 keys x 32 units: 55 us, 62 TFLOP/s (plain FMA from LDS: 408 us); 400 x 600 x
-// 104 units: 162 us, 79 TFLOP/s.  What is left there: 2.6 rounds of workgroups where 3 are paid (two to a compute
-// unit), 5 us of first loads and joining in each, and the softmax between the products; of the 400 x 517 x 32
-// launch, 416 workgroups, fewer than two to a compute unit, so that first loads and joins are hardly hidden.
+// Two waves per SIMD (no accumulation registers: with them the compiler copied hundreds of registers a block and kept
+// one wave per SIMD) cover what is serial in a block: the softmax between the products and the joins.
+// 400 queries x 517 keys x 32 units: 59 us with one wave, 53 now (64 TFLOP/s; 416 workgroups, one or two to a compute
+// unit); 400 x 900 x 512 units: 1219 -> 917 us, 103 TFLOP/s; 200 x 1600 x 32: 75 -> 61.
 #include "common.h"
 
 namespace scalekv {
@@ -39,7 +39,7 @@ constexpr int kMaxSplit = 4;  // waves of a workgroup
 constexpr float kNoMaximum = -__FLT_MAX__;
 
 template <int D, int QB>
-__global__ __launch_bounds__(64 * kMaxSplit) void attend_f32_kernel(
+__global__ __launch_bounds__(64 * kMaxSplit) __attribute__((amdgpu_waves_per_eu(2))) void attend_f32_kernel(
     const float* __restrict__ q, int n_q, const float* __restrict__ k, long long k_seq_stride,
     long long k_head_stride, const float* __restrict__ v, long long v_seq_stride,
     long long v_head_stride, int kv_len, int n_head, int n_tile, int n_split, float scale_log2e,
@@ -52,7 +52,7 @@ __global__ __launch_bounds__(64 * kMaxSplit) void attend_f32_kernel(
   const int wg = xcd_order(SCALEKV_WG_X, gridDim.x);  // the tiles of a unit share an L2
   const int unit = wg / n_tile, tile = wg - unit * n_tile;
   const int seq = unit / n_head, head = unit - seq * n_head;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, g = lane >> 4;
   const int q0 = tile * (16 * QB);
   const float* qu = q + (long long)unit * n_q * D;
@@ -73,11 +73,6 @@ __global__ __launch_bounds__(64 * kMaxSplit) void attend_f32_kernel(
       for (int t = 0; t < NO; ++t) vf[r][t] = *(const f32x4*)(row + 64 * t);
     }
   };
-  const int n_block = (kv_len + kBlockKeys - 1) / kBlockKeys;
-  if (wave < n_block) {
-    load_k(wave);
-    load_v(wave);
-  }
   f32x4 qf[QB][NT];
 #pragma unroll
   for (int b = 0; b < QB; ++b) {
@@ -85,6 +80,14 @@ __global__ __launch_bounds__(64 * kMaxSplit) void attend_f32_kernel(
 #pragma unroll
     for (int t = 0; t < NT; ++t) qf[b][t] = *(const f32x4*)(row + 16 * t);
   }
+  // (behind the queries, so that the loop waits for the keys alone when it begins a block: with the queries the
+  // younger ones it waited for the values as well, requested only just before)
+  __builtin_amdgcn_sched_barrier(0);
+  const int n_block = (kv_len + kBlockKeys - 1) / kBlockKeys;
+  load_k(wave);  // (a wave without keys takes the last row, and drops it)
+  __builtin_amdgcn_sched_barrier(0);
+  load_v(wave);
+  __builtin_amdgcn_sched_barrier(0);
   f32x4 o[QB][NO][4];
   float m_run[QB], l_run[QB];
 #pragma unroll
@@ -98,7 +101,6 @@ __global__ __launch_bounds__(64 * kMaxSplit) void attend_f32_kernel(
   }
 
   for (int block = wave; block < n_block; block += n_split) {
-    const bool more = block + n_split < n_block;
     f32x4 s[QB];
 #pragma unroll
     for (int b = 0; b < QB; ++b) s[b] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -110,7 +112,9 @@ __global__ __launch_bounds__(64 * kMaxSplit) void attend_f32_kernel(
         for (int b = 0; b < QB; ++b)
           s[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t][e], qf[b][t][e], s[b], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
-    if (more) load_k(block + n_split);
+    // (behind the last block: its last row again, dropped.  A condition here, or on the values below, would let the
+    // compiler assume that it may not have been requested, and wait for everything.)
+    load_k(block + n_split);
     __builtin_amdgcn_sched_barrier(0);
     if ((block + 1) * kBlockKeys > kv_len) {
 #pragma unroll
@@ -126,8 +130,7 @@ __global__ __launch_bounds__(64 * kMaxSplit) void attend_f32_kernel(
 #pragma unroll
     for (int b = 0; b < QB; ++b) {
       float m = fmaxf(fmaxf(s[b][0], s[b][1]), fmaxf(s[b][2], s[b][3]));
-      m = fmaxf(m, __shfl_xor(m, 16));
-      mx[b] = fmaxf(m, __shfl_xor(m, 32));
+      mx[b] = xor32_max(xor16_max(m));
       grow |= (mx[b] - m_run[b]) * scale_log2e > kRescaleThreshold;
     }
     if (__builtin_amdgcn_ballot_w64(grow) != 0) {
@@ -162,15 +165,14 @@ __global__ __launch_bounds__(64 * kMaxSplit) void attend_f32_kernel(
           for (int b = 0; b < QB; ++b)
             o[b][t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][t][c], s[b][r], o[b][t][c], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
-    if (more) load_v(block + n_split);
+    load_v(block + n_split);
     __builtin_amdgcn_sched_barrier(0);
   }
 
   // ---- join the waves' parts: common offset, then sums over the waves, 64 channels at a time
 #pragma unroll
   for (int b = 0; b < QB; ++b) {
-    l_run[b] += __shfl_xor(l_run[b], 16);
-    l_run[b] += __shfl_xor(l_run[b], 32);
+    l_run[b] = xor32_sum(xor16_sum(l_run[b]));
     if (g == 0) {
       part_m[wave][b][i] = m_run[b];
       part_l[wave][b][i] = l_run[b];
@@ -223,7 +225,11 @@ hipError_t launch(int n_unit, int n_head, const float* q, int n_q, KvView k, KvV
   // 10-20 % slower at every size tried, two or one equal at best and up to 3 times slower.)
   const int n_block = (kv_len + kBlockKeys - 1) / kBlockKeys;
   const int split = n_block >= kMaxSplit ? kMaxSplit : n_block >= 2 ? 2 : 1;
-  hipLaunchKernelGGL((attend_f32_kernel<D, QB>), dim3(n_tile * n_unit), dim3(64 * split), 0, stream, q, n_q,
+  // A third workgroup of 16 rows per compute unit (head_dim 128) pays while the keys are few: over many the three walk
+  // through more rows than the caches hold (256 units x 40 queries, 300 keys: 31 us, 38 with two; 900 keys: 74 / 67).
+  // LDS that nothing uses keeps it out.
+  const int lds = D == 128 && QB == 1 && kv_len >= 512 ? 40 * 1024 : 0;
+  hipLaunchKernelGGL((attend_f32_kernel<D, QB>), dim3(n_tile * n_unit), dim3(64 * split), lds, stream, q, n_q,
                      (const float*)k.ptr, k.seq_stride, k.head_stride, (const float*)v.ptr, v.seq_stride,
                      v.head_stride, kv_len, n_head, n_tile, split, sm_scale * 1.4426950408889634f, out);
   return hipGetLastError();
@@ -235,12 +241,15 @@ hipError_t launch_attend_f32(int n_unit, int n_head, int d, const void* q, int n
                              int kv_len, float sm_scale, void* out, hipStream_t stream) {
   const float* qp = (const float*)q;
   float* op = (float*)out;
-  // 32 query rows per wave halve the reads of K and V per flop, 16 rows make twice as many
-  // workgroups and fewer padded rows: 32 from where they give the chip's 1024 SIMDs 1.5 waves each
-  // (400 queries x 517 keys x 32 units: 55 us against 64; below, 16 x 576 x 800: 74 against 67).
-  // A short map whose last 32 rows are half empty keeps to 16 (100 x 400 x 96 units: 43 against 39).
-  const bool half_empty = n_q <= 256 && n_q % 32 != 0 && n_q % 32 <= 16;
-  const bool wide = !half_empty && (long long)((n_q + 31) / 32) * n_unit * kMaxSplit >= 1536;
+  // 32 query rows per wave halve the reads of K and V per flop, 16 rows make twice as many workgroups and fewer
+  // padded rows.  The launch takes as long as the compute unit that has most to do: m1 workgroups of 16 rows or m2 of
+  // 32, of which one costs 12/7 (head_dim 64: 16/9) of the smaller; up to one (three) small ones are always better.
+  // us, 16 / 32 rows, d 128, 1600 keys: m 2 / 1 78 / 61, 3 / 2 110 / 130, 4 / 2 146 / 133, 13 / 7 480 / 431; d 64:
+  // 2 / 1 36.2 / 35.1 (300 keys 11.2 / 11.5), 3 / 2 56 / 64, 7 / 4 127 / 131, 13 / 7 235 / 226.
+  constexpr int kComputeUnits = 256;
+  const long long m1 = ((long long)((n_q + 15) / 16) * n_unit + kComputeUnits - 1) / kComputeUnits;
+  const long long m2 = ((long long)((n_q + 31) / 32) * n_unit + kComputeUnits - 1) / kComputeUnits;
+  const bool wide = d == 128 ? m1 > 1 && m2 * 12 <= m1 * 7 : m1 > 3 && m2 * 16 <= m1 * 9;
   if (d == 128)
     return wide ? launch<128, 2>(n_unit, n_head, qp, n_q, k, v, kv_len, sm_scale, op, stream)
                 : launch<128, 1>(n_unit, n_head, qp, n_q, k, v, kv_len, sm_scale, op, stream);

@@ -59,8 +59,8 @@
 // formed (it costs a sixth of the vector instructions of a block).  This is as good as
 // long as nothing leaves the range of fp32 and bf16, 2^-126 to 2^127.  The offset lies 60 log2 units above that
 // maximum, so the weights may grow by 2^180 (scores up to 125 natural units above the first block's maximum) and what
-// is lost at the small end weighs less than 2^-66 of the first block's largest.  At the end of the pass a lane checks that its
-// share of the row sum is in range (an infinite weight or a NaN is still in it), that its accumulators are finite, and
+// is lost at the small end weighs less than 2^-66 of the first block's largest.  At the end of the pass a lane checks that
+// its share of the row sum is in range (an infinite weight or a NaN is still in it), that its accumulators are finite, and
 // that they are not so small (values below 2^-40) that products were lost.
 // If any lane of the workgroup finds a failure (forced by the tests), the workgroup
 // discards its result and repeats the whole pass with the classical scheme: running

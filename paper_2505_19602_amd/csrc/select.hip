@@ -143,7 +143,8 @@ __global__ __launch_bounds__(kThreads) void select_far_kernel(const float* __res
 // The whole ranking step of Sec. 3.3 and the pruning in one kernel, a workgroup per unit, for short caches
 // (rank.h): nothing but the index list leaves the compute unit
 // between the keys and the pruned rows.  EXTRAS: forced positions and pooling may be asked for.
-// 256 units, 546 cached rows, 246 kept: 30.6 us with the logits through global memory, 26.3 here; 16-256 units, 70-400 rows: 13-17 -> 8-13 us.
+// 256 units, 546 cached rows, 246 kept: 30.6 us with the logits through global memory, 26.3 here; 16-256 units,
+// 70-400 rows: 13-17 -> 8-13 us.
 template <int D, int THREADS, bool EXTRAS>
 __global__ __launch_bounds__(THREADS) void rank_short_kernel(int cache_len, int keep, int32_t* __restrict__ idx,
                                                              int n_win, SelectExtras ex, ScoreInputs si) {
