@@ -740,7 +740,9 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   // would touch 16 rows with 32 bytes each; instead the wave turns its 32 x 128 block round in
   // LDS (the tile stages are free: every wave has left its last tile; each wave uses a region of
   // its own, rows padded to 272 bytes against bank conflicts) and writes whole 256-byte rows,
-  // 16 bytes per lane.
+  // 16 bytes per lane, past the caches, which hold keys and values that other workgroups still want
+  // (1024 queries x 1180 keys x 64 units after their pruning: 62.9 -> 61.0 us; with plain stores of the kept rows, steps
+  // of 256 to 1024 queries are 2-8 % faster).
   if (SPLIT == 1 || group == 0) {
     constexpr int kOutRowStride = kRowBytes + 16;
     const int end_lane = end_tid & 63;
@@ -768,7 +770,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     for (int p = 0; p < G::kQOps; ++p) {
       const int r = G::kRowsPerOp * p + end_lane / G::kChunks, c = 16 * (end_lane % G::kChunks);
       const u32x4 val = *(const u32x4*)(ostage + r * kOutRowStride + c);
-      if (row0 + r < n_q) *(u32x4*)(obase + (long long)r * kRowBytes + c) = val;
+      if (row0 + r < n_q) __builtin_nontemporal_store(val, (u32x4*)(obase + (long long)r * kRowBytes + c));
     }
   }
   __builtin_amdgcn_sched_barrier(0);

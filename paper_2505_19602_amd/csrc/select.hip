@@ -63,6 +63,8 @@ __device__ __forceinline__ void prune_unit(const ScoreInputs& si, int unit, int 
   const vec4* kcur = (const vec4*)(si.k_cur + (long long)unit * si.n_app * D);
   const vec4* vcur = (const vec4*)(si.v_cur + (long long)unit * si.n_app * D);
   const int total = (keep + si.n_app) * VPR;
+  // (the attention reads the kept rows next: plain stores, which may leave them in the caches.  256 units, 246 of 546
+  // rows, 576 queries, the whole step: 110.8 us with streaming stores, 107.2 so)
 #pragma unroll 1
   for (int f0 = tid; f0 < total; f0 += THREADS * kFly) {
     vec4 a[kFly], b[kFly];
@@ -81,8 +83,8 @@ __device__ __forceinline__ void prune_unit(const ScoreInputs& si, int unit, int 
     for (int u = 0; u < kFly; ++u) {
       const int f = f0 + u * THREADS;
       if (f < total) {
-        __builtin_nontemporal_store(a[u], kdst + f);
-        __builtin_nontemporal_store(b[u], vdst + f);
+        kdst[f] = a[u];
+        vdst[f] = b[u];
       }
     }
   }
