@@ -59,9 +59,9 @@
 // formed (it costs a sixth of the vector instructions of a block).  This is as good as
 // long as nothing leaves the range of fp32 and bf16, 2^-126 to 2^127.  The offset lies 60 log2 units above that
 // maximum, so the weights may grow by 2^180 (scores up to 125 natural units above the first block's maximum) and what
-// is lost at the small end weighs less than 2^-66 of the first block's largest.  At the end of the pass a lane checks that
-// its share of the row sum is in range (an infinite weight or a NaN is still in it), that its accumulators are finite, and
-// that they are not so small (values below 2^-40) that products were lost.
+// is lost at the small end weighs less than 2^-66 of the first block's largest.  At the end of the pass a lane checks
+// that its share of the row sum is in range (an infinite weight or a NaN is still in it), that its accumulators are
+// finite, and that they are not so small (values below 2^-40) that products were lost.
 // If any lane of the workgroup finds a failure (forced by the tests), the workgroup
 // discards its result and repeats the whole pass with the classical scheme: running
 // maximum per block, offsets moved (and O, l rescaled) when some row maximum grew by
@@ -190,7 +190,21 @@ __device__ __forceinline__ void dma16_xor(const unsigned char* base_uniform, uns
       : "m0", "memory");
 }
 
+// LOOP: when the append is done, with the tiles that fall to the workgroup as they pass through the loop, or with its
+// share of the rows after it.  The loop wins where workgroups follow each other on a compute unit, and the rows at the
+// end would keep the next one waiting: steps, end / loop, us: d 128, 256 units x 576 queries 107 / 101, 480 x 576
+// 188 / 183, 256 x 300 37.9 / 36.7; d 64, 256 x 576 67.4 / 62.  Where all are resident at once it loses (80 x 576,
+// d 128, 49.9 / 51.3; d 64, 32 x 1500 over 6000 kept rows 151 / 155), but not in the split form of head_dim 64 (64 x 400
+// 27.6 / 26.7, 80 x 256 22.9 / 21.9; d 128 within 2 % either way), and it does in the wide form, whose barriers hold
+// eight waves to the slowest store (4096 queries, 256 units, 2772 / 2796).  A form of its own: code that is not used
+// costs 1-3 %.
 template <int D, int WAVES, int SPLIT>
+constexpr bool appends_in_loop(long long n_wg) {
+  constexpr int kResident = 256 * Shape<D, WAVES, SPLIT>::kWavesPerSimd;  // plain form: workgroups on all compute units
+  return WAVES == 4 && (SPLIT > 1 ? D == 64 : n_wg > kResident);
+}
+
+template <int D, int WAVES, int SPLIT, bool LOOP>
 __global__ __launch_bounds__(64 * WAVES * SPLIT)
 __attribute__((amdgpu_waves_per_eu(Shape<D, WAVES, SPLIT>::kWavesPerSimd, Shape<D, WAVES, SPLIT>::kWavesPerSimd)))
 void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, long long k_seq_stride,
@@ -458,6 +472,32 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
       __builtin_amdgcn_sched_barrier(0);
     }
   };
+  // ---- append in the loop: the second segment goes behind the first in the cache from the LDS, as its
+  // tiles pass.  A wave copies the rows that it has brought in itself; turn x of the second segment falls to query tile
+  // x mod n_qtile, so that the workgroups of a unit write at different times.
+  [[maybe_unused]] int copy_turn = append ? n_tile1 / SPLIT + qtile : -1;  // the next of this workgroup
+  auto copy_tile = [&](int t, const unsigned char* stages, const unsigned char* cache, auto ofs)
+                       __attribute__((always_inline)) {
+    const int tile = t * SPLIT + group - n_tile1;
+    if (t >= n_tile || tile < 0) return;
+    // (formed on the spot, and a vector at a time: nothing of it stays in registers through the tile loop)
+    const int mine = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    const unsigned char* const src = stages + t % kStages * kTileBytes + G::kWaveRows * wave * kRowBytes + 16 * mine;
+    unsigned char* const dst = const_cast<unsigned char*>(cache) + (long long)(len1 + tile * TN) * kRowBytes;
+    const int left = len2 - tile * TN - G::kWaveRows * wave - mine / G::kChunks;
+#pragma unroll
+    for (int p = 0; p < G::kOps; ++p) {
+      const u32x4 val = *(const u32x4*)(src + 1024 * p);
+      if (G::kRowsPerOp * p < left) __builtin_nontemporal_store(val, (u32x4*)(dst + ofs(p)));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  [[maybe_unused]] auto copy_k = [&](int t) __attribute__((always_inline)) {
+    copy_tile(t, k_lds, ku, [&](int p) { return ld_krow + (ld_kchunk ^ k_step(p)) + 1024 * p; });
+  };
+  [[maybe_unused]] auto copy_v = [&](int t) __attribute__((always_inline)) {
+    copy_tile(t, v_lds, vu, [&](int p) { return ld_vofs + 1024 * p; });
+  };
   // Publishes tile t + 1 of K and tile t of V, and requests the tiles kStages further on, in the place of those that
   // all waves have left.  Requests are made in the order V(x), K(x + 1): what may still be under way is those of x > t.
   auto turn = [&](int t) __attribute__((always_inline)) {
@@ -470,6 +510,13 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     if (t + kStages - 1 < n_tile) issue_v(t + kStages - 1);
     if (t + kStages < n_tile) issue_k(t + kStages);
 #endif
+    if constexpr (LOOP) {
+      if (t == copy_turn) {
+        copy_v(t);
+        copy_turn += n_qtile;
+      }
+      if (t + 1 == copy_turn) copy_k(t + 1);
+    }
     __builtin_amdgcn_sched_barrier(0);
   };
   auto nothing = [](int) {};
@@ -539,6 +586,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     if (n_tile > 2) issue_k(2), issue_v(2);
     if (n_tile > 3) issue_k(3);
   }
+  if (LOOP && copy_turn == 0) copy_k(0);
   // (a wave whose query rows all lie behind the last one only carries its share of the tiles)
   const bool idle = q_base >= n_q || (SPLIT > 1 && n_tile == 0);
   int turns = 0;  // barriers of the tile loop behind this wave: all waves make n_turn
@@ -668,11 +716,11 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   }
   SCALEKV_STAMP(t_loop_end);
 
-  // ---- append, first half: this workgroup's share of the second segment goes behind the first,
-  // as 16-byte vectors.  The vectors of the first round (the whole share when it is at most 128
+  // ---- append at the end, first half: this workgroup's share of the second segment goes behind the first,
+  // as 16-byte vectors.  The vectors of the first round (the whole share when it is at most 256
   // rows) are requested here, before the output is normalised and stored, so that their latency
   // hides behind that work; the registers of the operand fragments are free by now.
-  const int ap_per = append ? (len2 + n_qtile - 1) / n_qtile : 0;
+  const int ap_per = !LOOP && append ? (len2 + n_qtile - 1) / n_qtile : 0;
   const int ap_row0 = min(qtile * ap_per, len2);
   const int ap_vec = min(ap_per, len2 - ap_row0) * (kRowBytes / 16);  // per tensor
   const u32x4* ap_ks = (const u32x4*)(k2u + (long long)ap_row0 * kRowBytes);
@@ -741,8 +789,8 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   // LDS (the tile stages are free: every wave has left its last tile; each wave uses a region of
   // its own, rows padded to 272 bytes against bank conflicts) and writes whole 256-byte rows,
   // 16 bytes per lane, past the caches, which hold keys and values that other workgroups still want
-  // (1024 queries x 1180 keys x 64 units after their pruning: 62.9 -> 61.0 us; with plain stores of the kept rows, steps
-  // of 256 to 1024 queries are 2-8 % faster).
+  // (1024 queries x 1180 keys x 64 units after their pruning: 62.9 -> 61.0 us; with plain stores of the kept rows,
+  // steps of 256 to 1024 queries are 2-8 % faster).
   if (SPLIT == 1 || group == 0) {
     constexpr int kOutRowStride = kRowBytes + 16;
     const int end_lane = end_tid & 63;
@@ -819,13 +867,13 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
 #endif
 }
 
-template <int D, int WAVES, int SPLIT>
-hipError_t launch(int n_unit, int n_head, const void* q, int n_q, KvView k, KvView v, int len1, const void* k2,
+template <int D, int WAVES, int SPLIT, bool LOOP>
+hipError_t launch_form(int n_unit, int n_head, const void* q, int n_q, KvView k, KvView v, int len1, const void* k2,
                   const void* v2, int len2, bool append, float sm_scale, void* out, hipStream_t stream,
                   hipEvent_t start, hipEvent_t stop) {
   using G = Shape<D, WAVES, SPLIT>;
   constexpr int kLds = kLdsBytes<D, WAVES, SPLIT>;
-  const auto kernel = attend_pipe_kernel<D, WAVES, SPLIT>;
+  const auto kernel = attend_pipe_kernel<D, WAVES, SPLIT, LOOP>;
   static std::atomic<uint64_t> configured{0};
   const hipError_t e = allow_dynamic_lds((const void*)kernel, kLds, configured);
   if (e != hipSuccess) return e;
@@ -846,6 +894,19 @@ hipError_t launch(int n_unit, int n_head, const void* q, int n_q, KvView k, KvVi
                        (const uint16_t*)v2, len2, append ? 1 : 0, n_head, n_qtile, n_wg, scale_log2e, no_max,
                        (uint16_t*)out);
   return hipGetLastError();
+}
+
+template <int D, int WAVES, int SPLIT>
+hipError_t launch(int n_unit, int n_head, const void* q, int n_q, KvView k, KvView v, int len1, const void* k2,
+                  const void* v2, int len2, bool append, float sm_scale, void* out, hipStream_t stream,
+                  hipEvent_t start, hipEvent_t stop) {
+  constexpr int kRows = Shape<D, WAVES, SPLIT>::kRows;
+  if constexpr (appends_in_loop<D, WAVES, SPLIT>(1LL << 40))  // (not at all, whatever the number of workgroups)
+    if (append && appends_in_loop<D, WAVES, SPLIT>((long long)n_unit * ((n_q + kRows - 1) / kRows)))
+      return launch_form<D, WAVES, SPLIT, true>(n_unit, n_head, q, n_q, k, v, len1, k2, v2, len2, true, sm_scale, out,
+                                                stream, start, stop);
+  return launch_form<D, WAVES, SPLIT, false>(n_unit, n_head, q, n_q, k, v, len1, k2, v2, len2, append, sm_scale, out,
+                                             stream, start, stop);
 }
 
 }  // namespace

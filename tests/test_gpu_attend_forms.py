@@ -34,7 +34,8 @@ def _check(form, d, S, H, n_q, kv, key, rise=0.0, rise_from=0, cached=None, valu
     if cached is None:
         skv.attend(shape, q, k, v, kv, out)
     else:
-        parts = [t.contiguous() for t in (k[:, :, cached:], v[:, :, cached:], k[:, :, :cached], v[:, :, :cached])]
+        rows = max(cached, 1)
+        parts = [t.contiguous() for t in (k[:, :, cached:], v[:, :, cached:], k[:, :, :rows], v[:, :, :rows])]
         kd, vd = torch.zeros_like(k), torch.zeros_like(v)
         skv.step(shape, q, parts[0], parts[1], [0], parts[2], parts[3], cached, cached, kd, vd, out, None, None)
         assert torch.equal(kd, k) and torch.equal(vd, v)
@@ -79,6 +80,20 @@ def test_scores_far_above_the_first_block_in_each_form(form, d, S, H, n_q, kv, r
 def test_step_of_two_segments_in_each_form(form, d, S, H, n_q, cached):
     assert routes.step_kernel(BF16, d, S * H, n_q, cached, cached) == "pipelined"
     _check(form, d, S, H, n_q, cached + n_q, 4, cached=cached)
+
+
+# more workgroups than the compute units hold at once, and the split form of head_dim 64: tiles are appended as they
+# pass through the loop; one query tile and several, no kept rows, ragged tiles of both segments
+@pytest.mark.parametrize("form,d,S,H,n_q,cached", [
+    ("plain", 128, 20, 30, 96, 0), ("plain", 128, 20, 30, 97, 1), ("plain", 128, 20, 30, 128, 64),
+    ("plain", 128, 20, 20, 190, 63), ("plain", 128, 20, 20, 193, 65), ("plain", 128, 15, 20, 385, 130),
+    ("plain", 64, 20, 41, 65, 0), ("plain", 64, 20, 41, 127, 3), ("plain", 64, 20, 20, 191, 128),
+    ("plain", 64, 20, 30, 258, 61),
+    ("split", 64, 4, 10, 449, 0), ("split", 64, 4, 10, 385, 191), ("split", 64, 4, 10, 500, 1),
+])
+def test_append_of_passing_tiles(form, d, S, H, n_q, cached):
+    assert routes.step_kernel(BF16, d, S * H, n_q, cached, cached) == "pipelined"
+    _check(form, d, S, H, n_q, cached + n_q, 6, cached=cached)
 
 
 # values whose products with weights around 2^-60 and below would be lost (2^-80, 2^-110), or nearly (2^-36); and none
