@@ -281,7 +281,8 @@ def attend_alone(args, torch, skv) -> int:
             "units": S * H, "n_q": n_q, "kv_len": kv, "reps": args.reps, "ms": ms,
             "tflops": flops / (ms * 1e-3) / 1e12, "frac_of_bf16_peak": flops / (ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS}
     if args.timeline:
-        line["timeline"] = timeline_summary(skv, -(-n_q // routes.pipe_rows(routes.pipe_form(d, S * H, n_q, kv))) * S * H)
+        form = routes.pipe_form(d, S * H, n_q, kv)
+        line["timeline"] = timeline_summary(skv, -(-n_q // routes.pipe_rows(form)) * S * H, 2 if form == "plain" else 1)
     print(json.dumps(line), flush=True)
     return 0
 
@@ -312,9 +313,9 @@ def attend_clock_leg():
         return {"error": f"{type(exc).__name__}: {exc}"[:300]}
 
 
-def timeline_summary(skv, n_wg: int) -> dict:
-    """Per-workgroup records of the last attention launch, from a library built with
-    `--variant timeline` (four readings of the 100 MHz counter, the hardware id register and two readings of
+def timeline_summary(skv, n_wg: int, slots: int = 2) -> dict:
+    """Per-workgroup records of the last attention launch (`slots` workgroups share a compute unit), from a library built
+    with `--variant timeline` (four readings of the 100 MHz counter, the hardware id register and two readings of
     the shader clock counter per workgroup), summed up per XCD: hardware hands workgroup i to XCD i mod 8."""
     import ctypes
 
@@ -345,8 +346,8 @@ def timeline_summary(skv, n_wg: int) -> dict:
             "start_to_first_tile_us": round(float((t[:, 1] - t[:, 0]).mean()), 2),
             "tile_loop_us": round(float((t[:, 2] - t[:, 1]).mean()), 1),
             "loop_end_to_end_us": round(float((t[:, 3] - t[:, 2]).mean()), 2),
-            "slot_occupancy": round(float(dur.sum() / (2 * n_cu * span)), 3),
-            "tile_loop_share_of_slot_time": round(float((t[:, 2] - t[:, 1]).sum() / (2 * n_cu * span)), 3),
+            "slot_occupancy": round(float(dur.sum() / (slots * n_cu * span)), 3),
+            "tile_loop_share_of_slot_time": round(float((t[:, 2] - t[:, 1]).sum() / (slots * n_cu * span)), 3),
             "per_xcd": per_xcd,
             "idle_at_the_end": round(float(1.0 - np.mean(ends) / span), 4)}
 
