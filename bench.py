@@ -50,14 +50,14 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # 2.0: what the same counter reads for a plain copy of known size) plus --pmc WRITE_SIZE (KiB,
 # scale 1.0), three launches each, inside scalekv_step.  The commands and the full per-kernel table are in profiles/step_hbm_traffic.md.
 ATTEND_PIPE_TRAFFIC = {
-    (144, 46): 63.0e6, (144, 9): 58.2e6,
-    (256, 82): 125.9e6, (256, 16): 119.6e6,
-    (400, 146): 191.2e6, (400, 29): 177.0e6,
-    (576, 246): 283.4e6, (576, 49): 262.3e6,
-    (1024, 390): 488.1e6, (1024, 78): 459.5e6,
-    (1600, 646): 841.4e6, (1600, 129): 759.3e6,
-    (2304, 1046): 1304.6e6, (2304, 209): 1152.4e6,
-    (4096, 1622): 1943.3e6, (4096, 324): 1855.5e6,
+    (144, 46): 63.1e6, (144, 9): 58.2e6,
+    (256, 82): 120.2e6, (256, 16): 108.5e6,
+    (400, 146): 176.8e6, (400, 29): 161.5e6,
+    (576, 246): 264.4e6, (576, 49): 236.2e6,
+    (1024, 390): 454.1e6, (1024, 78): 413.3e6,
+    (1600, 646): 764.7e6, (1600, 129): 678.8e6,
+    (2304, 1046): 1277.9e6, (2304, 209): 1125.4e6,
+    (4096, 1622): 1947.1e6, (4096, 324): 1777.3e6,
 }
 
 
