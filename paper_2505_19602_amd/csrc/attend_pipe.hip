@@ -56,18 +56,17 @@
 // over the first block and then left alone: every later probability is exp2 of
 // (score - offset), whatever its size, and the row sum adds the bf16-rounded
 // probabilities, the very numbers the MFMA multiplies by.  No running maximum is
-// formed (it costs a sixth of the vector instructions of a block).  This is as good as
-// long as nothing leaves the range of fp32 and bf16, 2^-126 to 2^127.  The offset lies 60 log2 units above that
-// maximum, so the weights may grow by 2^180 (scores up to 125 natural units above the first block's maximum) and what
-// is lost at the small end weighs less than 2^-66 of the first block's largest.  At the end of the pass a lane checks
-// that its share of the row sum is in range (an infinite weight or a NaN is still in it), that its accumulators are
-// finite, and that they are not so small (values below 2^-40) that products were lost.
+// formed (it costs a sixth of the vector instructions of a block).  This is exact as
+// long as nothing overflows, and fp32 / bf16 carry 2^127: at the end of the pass a lane
+// checks that its share of the row sum is below 2^120 (scores up to 83 natural units above the
+// first block's maximum; an infinite weight or a NaN is still in the sum then) and, since huge values could overflow
+// them even so, that its accumulators are finite.  The split form, whose groups are joined relative to the largest
+// of their offsets, has lower limits, 2^100 (69 units) and 2^125: the join scales a sum by no less than 2^-126 or drops
+// what is then below 2^-24 of the row.
 // If any lane of the workgroup finds a failure (forced by the tests), the workgroup
 // discards its result and repeats the whole pass with the classical scheme: running
 // maximum per block, offsets moved (and O, l rescaled) when some row maximum grew by
-// more than kRescaleThreshold in log2 units.  With Student-t keys (three degrees of freedom, 4096 x 4424) one unit in
-// sixteen holds a key that lifts some row of most workgroups by more than 69 natural units, the range without
-// those 60: 512 units, 4619 -> 4511 us.
+// more than kRescaleThreshold in log2 units.
 //
 // Workgroups of one (sequence, head) unit are numbered so that they land on the
 // same XCD and share its L2 while they stream the same K/V.
@@ -148,9 +147,11 @@ __device__ unsigned long long g_timeline[kTimelineMaxWg * kTimelineWords];
 #else
 #define SCALEKV_STAMP(name)
 #endif
-// Of a pass without maxima: what is added to the first block's maximum (log2 units), the largest share of a row sum it
-// may end with, and the smallest quotient of a lane's largest output and its row's sum.
-constexpr float kOffsetMargin = 60.f, kRowSumLimit = 0x1p120f, kSmallestOutput = 0x1p-40f;
+// A pass without maxima: the largest share of a row sum that it may end with and, where groups are added up, the largest
+// accumulator.
+template <int SPLIT>
+constexpr float kRowSumLimit = SPLIT > 1 ? 0x1p100f : 0x1p120f;
+constexpr float kSplitOutputLimit = 0x1p125f;
 
 // One 16-byte-per-lane transfer from global memory straight into LDS: lane l's vector comes
 // from base + voff + IMM and lands at LDS byte lds_addr + IMM + 16 l (the instruction's
@@ -600,7 +601,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
       float mx[2];
       block_max(sa, mx);
 #pragma unroll
-      for (int b = 0; b < 2; ++b) neg_off[b] = -(fmaxf(no_max, mx[b]) * scale_log2e + kOffsetMargin);
+      for (int b = 0; b < 2; ++b) neg_off[b] = -(fmaxf(no_max, mx[b]) * scale_log2e);
     }
     __builtin_amdgcn_sched_barrier(0);
     slots([&](int m) { score_mfma(sb, m); }, nothing, sa, pa, 0);
@@ -635,13 +636,12 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   }
   if (SPLIT > 1 || idle)
     for (; turns < n_turn; ++turns) turn(turns);
-  // A weight or a sum beyond the range, inf or NaN in an accumulator (huge values times large weights), or values so
-  // small that their products with small weights were lost?  Weights are not negative, so what went wrong with one
-  // is still in its row's sum; a sum of accumulators is finite only if they all are.
-  bool repeat = false;
+  // A weight or a sum beyond the range, or inf or NaN in an accumulator (huge values times large weights)?  Weights are
+  // not negative, so what went wrong with one is still in its row's sum; a sum of accumulators is finite only if they
+  // all are (and may not be although they are: then the repeat is for nothing).
+  bool overflowed = false;
 #pragma unroll
   for (int b = 0; b < 2; ++b) {
-    const float row_sum = xor32_sum(xor16_sum(l_run[b]));
     float largest = 0.f;
     f32x4 all = o[b][0];
 #pragma unroll
@@ -650,14 +650,14 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
 #pragma unroll
       for (int v = 0; v < 4; ++v) largest = fmaxf(largest, fabsf(o[b][c][v]));
     }
-    repeat |= !(l_run[b] <= kRowSumLimit) || !(fabsf(all[0] + all[1] + all[2] + all[3]) < INFINITY) ||
-              largest < kSmallestOutput * row_sum || (SPLIT > 1 && largest > 0x1p125f);
+    overflowed |= !(l_run[b] <= kRowSumLimit<SPLIT>) || !(fabsf(all[0] + all[1] + all[2] + all[3]) < INFINITY) ||
+                  (SPLIT > 1 && largest > kSplitOutputLimit);
   }
   // ---- the pass that follows the maxima (every wave has left its last tile when the votes are in)
 #if defined(SCALEKV_ABLATE_SOFTMAX)
-  repeat = false;
+  overflowed = false;
 #endif
-  if (__syncthreads_or(repeat)) {
+  if (__syncthreads_or(overflowed)) {
     float m_run[2];
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
@@ -741,16 +741,15 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   }
   __builtin_amdgcn_sched_barrier(0);
 
-  // ---- join the groups: row sums and accumulators relative to the largest row sum (not to the largest offset: with
-  // rising scores a group's sum may lie 2^180 above its first weight).  Wave w of the first group takes the parts that
-  // waves w of the others leave in LDS (the tile stages are free).
+  // ---- join the groups: a common offset, the largest, then the sums.  The group it comes from has a weight of about 1,
+  // so that a part whose factor underflows (below 2^-126, of a sum below 2^102) is less than 2^-24 of the row.  Wave w of
+  // the first group takes the parts that waves w of the others leave in LDS (the tile stages are free).
   constexpr int kPartBytes = 64 * 2 * NCB * 16;       // a wave's accumulators, fp32
   if constexpr (SPLIT > 1) {
     auto part = [&](int grp) { return (f32x4*)(smem + (grp - 1) * (WAVES * kPartBytes) + wave * kPartBytes) + lane; };
     __shared__ float part_off[SPLIT][WAVES][2][64], part_sum[SPLIT][WAVES][2][64];
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      l_run[b] = xor32_sum(xor16_sum(l_run[b]));
       part_off[group][wave][b][lane] = -neg_off[b];
       part_sum[group][wave][b][lane] = l_run[b];
       if (group > 0)
@@ -761,26 +760,22 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     if (group == 0) {
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
-        float top = -INFINITY, f[SPLIT];
+        float top = -neg_off[b];
 #pragma unroll
-        for (int x = 0; x < SPLIT; ++x)
-          top = fmaxf(top, part_off[x][wave][b][lane] + __builtin_amdgcn_logf(part_sum[x][wave][b][lane]));
+        for (int x = 1; x < SPLIT; ++x) top = fmaxf(top, part_off[x][wave][b][lane]);
+        const float f0 = __builtin_amdgcn_exp2f(-neg_off[b] - top);
+        l_run[b] *= f0;
 #pragma unroll
-        for (int x = 0; x < SPLIT; ++x) f[x] = __builtin_amdgcn_exp2f(part_off[x][wave][b][lane] - top);
-        l_run[b] *= f[0];
-#pragma unroll
-        for (int c = 0; c < NCB; ++c) o[b][c] *= f[0];
+        for (int c = 0; c < NCB; ++c) o[b][c] *= f0;
 #pragma unroll
         for (int x = 1; x < SPLIT; ++x) {
-          l_run[b] += f[x] * part_sum[x][wave][b][lane];
+          const float f = __builtin_amdgcn_exp2f(part_off[x][wave][b][lane] - top);
+          l_run[b] += f * part_sum[x][wave][b][lane];
 #pragma unroll
-          for (int c = 0; c < NCB; ++c) o[b][c] += f[x] * part(x)[(b * NCB + c) * 64];
+          for (int c = 0; c < NCB; ++c) o[b][c] += f * part(x)[(b * NCB + c) * 64];
         }
       }
     }
-  } else {
-#pragma unroll
-    for (int b = 0; b < 2; ++b) l_run[b] = xor32_sum(xor16_sum(l_run[b]));
   }
 
   // ---- normalise and write.  A lane owns query columns i and 16 + i, channels 16c + 4g + v:
@@ -797,7 +792,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     unsigned char* const ostage = smem + wave * (SPLIT > 1 ? kPartBytes : 32 * kOutRowStride);
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      const float inv = 1.f / l_run[b];
+      const float inv = 1.f / xor32_sum(xor16_sum(l_run[b]));
 #pragma unroll
       for (int c = 0; c < NCB; ++c) {
         const bf16x2 lo = {(__bf16)(o[b][c][0] * inv), (__bf16)(o[b][c][1] * inv)};

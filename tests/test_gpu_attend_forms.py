@@ -65,9 +65,10 @@ def test_plain_form_of_few_keys(d, n_q, kv):
     _check("plain", d, 15, 20, n_q, kv, kv)
 
 
-# The first block's largest weight is 2^-60.  100 natural units above it, 144 binary ones, the pass stays as it is; at
-# 126.5 weights are 2^122.5, above the checked 2^120; at 150 they are infinite.
-@pytest.mark.parametrize("rise", [100.0, 126.5, 150.0])
+# The first block's largest weight is about 1 (2^4 at most, since the other channels differ).  60 natural units above it,
+# 86.6 binary ones, the pass stays as it is; 78 are 112.5: above the split form's 2^100, below the 2^120 of the others;
+# at 86, 124 binary units, those repeat too, and from 100 on, 144, weights are infinite.
+@pytest.mark.parametrize("rise", [60.0, 78.0, 86.0, 100.0, 126.5, 150.0])
 @pytest.mark.parametrize("form,d,S,H,n_q,kv", [("split", 64, 4, 5, 430, 500), ("split", 128, 4, 5, 430, 500),
                                                ("wide", 128, 16, 16, 130, 2100), ("plain", 128, 15, 20, 40, 200)])
 @pytest.mark.parametrize("last", [False, True])
@@ -96,7 +97,7 @@ def test_append_of_passing_tiles(form, d, S, H, n_q, cached):
     _check(form, d, S, H, n_q, cached + n_q, 6, cached=cached)
 
 
-# values whose products with weights around 2^-60 and below would be lost (2^-80, 2^-110), or nearly (2^-36); and none
+# values whose products with weights far below 1 would be lost; and none
 @pytest.mark.parametrize("value_scale", [2.0 ** -36, 2.0 ** -80, 2.0 ** -110])
 @pytest.mark.parametrize("form,d,S,H,n_q,kv", [("split", 64, 4, 5, 430, 500), ("split", 128, 4, 5, 430, 500),
                                                ("wide", 128, 16, 16, 130, 2100), ("plain", 128, 15, 20, 40, 200)])
@@ -110,3 +111,55 @@ def test_values_of_zero():
     v, out = torch.zeros_like(k), torch.ones_like(q)
     skv.attend(shape, q, k, v, 200, out)
     assert torch.equal(out, torch.zeros_like(out))
+
+
+# A channel of tiny values beside ordinary ones, compared on its own scale.
+@pytest.mark.parametrize("form,d,S,H,n_q,kv", [("split", 64, 4, 5, 430, 500), ("split", 128, 4, 5, 430, 500),
+                                               ("wide", 128, 16, 16, 130, 2100), ("plain", 128, 15, 20, 40, 200)])
+def test_channels_of_small_values_in_each_form(form, d, S, H, n_q, kv):
+    assert routes.pipe_form(d, S * H, n_q, kv) == form
+    print(f"{form} d={d} channels of small values", flush=True)
+    shape = skv.Shape(S, H, d, BF16)
+    q, k, v = (_rand(70 + i, (S, H, n, d)) for i, n in enumerate((n_q, kv, kv)))
+    scale = torch.ones(d, device=DEV)
+    scale[5::8] = 2.0 ** -100
+    out = torch.empty_like(q)
+    skv.attend(shape, q, k, v * scale.to(BF16), kv, out)
+    torch.cuda.synchronize()
+    ref = oracle.attend(units(q)[[0, S * H - 1]], units(k)[[0, S * H - 1]], units(v)[[0, S * H - 1]], d ** -0.5)
+    got = units((out.double() / scale.double()).float())[[0, S * H - 1]]
+    check_output(got, ref, BF16, form)
+
+
+# Weighted values beyond fp32 although the weights, 2^49, are not: the accumulators' own check has to trigger.  And
+# accumulators of 2^125 to 2^127, which the groups of the split form must not add up.
+@pytest.mark.parametrize("rise,value_scale", [(34.0, 2.0 ** 100), (32.0, 2.0 ** 79)])
+@pytest.mark.parametrize("form,d,S,H,n_q,kv", [("split", 64, 4, 5, 430, 500), ("split", 128, 4, 5, 430, 500),
+                                               ("wide", 128, 16, 16, 130, 2100), ("plain", 128, 15, 20, 40, 200)])
+@pytest.mark.parametrize("last", [False, True])
+def test_large_values_in_each_form(form, d, S, H, n_q, kv, rise, value_scale, last):
+    _check(form, d, S, H, n_q, kv, 8, rise, kv - 1 if last else 100, value_scale=value_scale)
+
+
+# Split form: one group meets a score in its first tile (key 64) to which four keys of another group, far above that
+# group's first tile, add 3 %.  Its factor in the join underflows if it is formed from the groups' offsets alone.
+# The same with the four within the range of the pass: what the join drops is then less than 2^-24.
+@pytest.mark.parametrize("d,unit,first,high,top", [(64, 1.0, 192, 124.5, 129.0), (128, 2.0 ** 0.5, 128, 88.0, 91.5),
+                                                   (64, 1.0, 192, 66.0, 69.5), (128, 2.0 ** 0.5, 128, 47.0, 49.5)])
+def test_join_of_groups_with_distant_offsets(d, unit, first, high, top):
+    S, H, n_q, kv = 4, 5, 430, 500
+    assert routes.pipe_form(d, S * H, n_q, kv) == "split"
+    print(f"join d={d} {high * unit:.1f} below {top * unit:.1f}", flush=True)
+    q, k, v = torch.zeros(S, H, n_q, d), torch.zeros(S, H, kv, d), _rand(90, (S, H, kv, d)).cpu().float()
+    q[..., 0] = unit * d ** 0.5 if d == 64 else 16.0   # a score is unit times the key's first channel
+    k[:, :, 64, 0] = top
+    high_rows = [first, first + 8, first + 16, first + 24]
+    k[:, :, high_rows, 0] = high
+    v[:, :, 64], v[:, :, high_rows] = -2.0, 2.0
+    q, k, v = (t.to(BF16).to(DEV) for t in (q, k, v))
+    out = torch.empty_like(q)
+    skv.attend(skv.Shape(S, H, d, BF16), q, k, v, kv, out)
+    torch.cuda.synchronize()
+    ref = oracle.attend(units(q)[[0]], units(k)[[0]], units(v)[[0]], d ** -0.5)
+    assert (ref[0, 0] + 2.0).max() > 0.04   # what the four keys add is seen
+    check_output(units(out)[[0]], ref, BF16, "join")
