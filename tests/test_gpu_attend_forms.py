@@ -1,6 +1,6 @@
 """The three forms of the pipelined bf16 attention kernel (four waves, eight waves on 256 rows, groups of waves that
 split the keys) at the edges of their tiles, groups and stages, against the oracle; rows whose scores rise so far above
-the first block's that the pass is repeated; the two-segment form with the append."""
+the first tile's that the pass is repeated; the two-segment form with the append."""
 import pytest
 import torch
 
@@ -65,7 +65,7 @@ def test_plain_form_of_few_keys(d, n_q, kv):
     _check("plain", d, 15, 20, n_q, kv, kv)
 
 
-# The first block's largest weight is about 1 (2^4 at most, since the other channels differ).  60 natural units above it,
+# The first tile's largest weight is about 1 (2^4 at most, since the other channels differ).  60 natural units above it,
 # 86.6 binary ones, the pass stays as it is; 78 are 112.5: above the split form's 2^100, below the 2^120 of the others;
 # at 86, 124 binary units, those repeat too, and from 100 on, 144, weights are infinite.
 @pytest.mark.parametrize("rise", [60.0, 78.0, 86.0, 100.0, 126.5, 150.0])
@@ -163,3 +163,27 @@ def test_join_of_groups_with_distant_offsets(d, unit, first, high, top):
     ref = oracle.attend(units(q)[[0]], units(k)[[0]], units(v)[[0]], d ** -0.5)
     assert (ref[0, 0] + 2.0).max() > 0.04   # what the four keys add is seen
     check_output(units(out)[[0]], ref, BF16, "join")
+
+
+# A score of the first tile, 64 keys, that lies far above the others is the exponent offset: its weight is 1 without
+# rounding.  Keys a and b, both in its second half, outweigh all others by 2^45 and more, b with 0.7503 of a's weight, which bf16 rounds to
+# 0.75: with values 0.75 and -1 they cancel exactly.  With any other offset, such as the maximum over the first block,
+# both weights are rounded, and 1e-4 to 1e-3 is left in most rows.
+@pytest.mark.parametrize("form,d,S,H,n_q,kv,a,b", [
+    ("split", 64, 4, 5, 430, 500, 40, 63), ("split", 128, 4, 5, 430, 500, 32, 41), ("wide", 128, 16, 16, 130, 2100, 63, 47),
+    ("plain", 128, 15, 20, 40, 200, 33, 60), ("plain", 64, 15, 20, 40, 64, 50, 34), ("plain", 128, 15, 20, 40, 37, 36, 35)])
+def test_largest_weight_of_the_first_tile_is_one(form, d, S, H, n_q, kv, a, b):
+    assert routes.pipe_form(d, S * H, n_q, kv) == form
+    print(f"{form} d={d} {kv} keys, largest weights at {a} and {b}", flush=True)
+    q, k, v = torch.zeros(S, H, n_q, d), torch.zeros(S, H, kv, d), torch.zeros(S, H, kv, d)
+    q[..., 0], q[..., 1] = 44.0 + 0.25 * (torch.arange(n_q) % 32), 1.0
+    k[:, :, [a, b], 0] = 8.0
+    k[:, :, b, 1] = -2.296875 if d == 64 else -3.25   # ln 0.7503 = -0.2873
+    v[:, :, a], v[:, :, b] = 0.75, -1.0
+    q, k, v = (t.to(BF16).to(DEV) for t in (q, k, v))
+    out = torch.empty_like(q)
+    skv.attend(skv.Shape(S, H, d, BF16), q, k, v, kv, out)
+    torch.cuda.synchronize()
+    ref = oracle.attend(units(q)[[0]], units(k)[[0]], units(v)[[0]], d ** -0.5)
+    check_output(units(out)[[0]], ref, BF16, form)
+    assert out.abs().max() < 1e-6

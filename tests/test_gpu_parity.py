@@ -164,7 +164,7 @@ def test_attend_matches_oracle(dtype, d, n_q, kv_len):
 @pytest.mark.parametrize("H,d,n_q", [(2, 128, 300), (9, 128, 2049), (9, 64, 2049)])   # 2049: the pipelined kernel
 def test_attend_scores_far_above_the_first_tile(where, H, d, n_q):
     # Keys whose scores sit far above everything in the first 64 rows: exp2 of their distance to
-    # the first block's maximum leaves the range the kernel adds up unchecked (2^100 in the form that 2049
+    # the first tile's maximum leaves the range the kernel adds up unchecked (2^100 in the form that 2049
     # queries take; for the larger gaps, fp32 altogether), so the workgroup has to fall back to the running-maximum
     # scheme.  "large_but_unchecked": a gap of about 34 natural units (2^49), which the kernel adds up as it
     # is; "huge_values": the same gap with value rows of magnitude 2^100, whose weighted sums leave
