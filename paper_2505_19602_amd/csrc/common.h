@@ -123,6 +123,23 @@ inline bool asi_stream_pays(int n_unit, int len, int n_samp) {
 }
 // out[0], out[1] = means of the two columns of terms [n][2]; out[2] = their product
 hipError_t launch_asi_mean(const float* terms, long long n, float* out, hipStream_t stream);
+// Rows of a cache that the pruning writes (of all units, K and V) are what the attention reads next: they are stored so
+// that they may stay in the caches, unless that is more than the last-level cache (256 MB) holds; then they go past it.
+// compact_kernel, which reads every source row once, still gains from what little stays at 1.5 times that size, the
+// ranking kernels, which read the keys a second time when they copy, do not.
+// Pruning and the attention of a step behind it, us, through / past the caches (256 units; written, queries):
+//   compact_kernel    213 MB, 64: 120 / 124, 256: 154 / 166    288 MB, 64: 164 / 164, 256: 198 / 204, 1024: 533 / 543
+//     384 MB, 64: 217 / 206, 256: 252 / 256, 1024: 645 / 648    425 MB, 64: 251 / 230, 256: 275 / 269, 1024: 669 / 666
+//     603 MB, 64: 359 / 317, 256: 382 / 365, 1024: 868 / 861
+//     (alone, with nothing that reads its rows, past the caches from 70 MB on: 213 MB 83.5 / 77.0, 749 MB 277 / 250)
+//   ranking kernels   213 MB, 64: 155 / 152, 256: 188 / 191, 1024: 462 / 463    288 MB, 64: 203 / 201, 256: 232 / 227,
+//     1024: 539 / 530    341 MB, 64: 247 / 227, 256: 270 / 259, 1024: 593 / 593    425 MB, 64: 318 / 274, 256: 342 / 307
+//     (3244 of 6489 rows, 425 MB, 256: 399 / 384, 1024: 743 / 753)
+enum class CacheWriter { kCompact, kRanking };
+inline bool rows_go_past_caches(CacheWriter by, int n_unit, long long rows, int row_bytes) {
+  const long long limit = by == CacheWriter::kCompact ? 400000000 : 256000000;
+  return 2 * rows * n_unit * row_bytes > limit;
+}
 hipError_t launch_compact(int dtype, int n_seq, int n_head, int d, KvView k_src, KvView v_src,
                           const int32_t* idx, int keep, const void* k_cur, const void* v_cur,
                           int n_cur, KvView k_dst, KvView v_dst, hipStream_t stream);

@@ -12,10 +12,9 @@ constexpr int kThreads = 256;
 constexpr int kUnroll = 4;  // 16-byte vectors in flight per thread per tensor pass
 
 // 16-byte vector in the compiler's native form, so that the streaming (non-temporal)
-// load builtin accepts it.  Every byte is read once per call, so the reads should not displace
+// load and store builtins accept it.  Every byte is read once per call, so the reads should not displace
 // cache lines that other kernels still want.  What is written is what the attention reads next:
-// it may stay (64 units, 156 + 1024 rows of 256 bytes and the attention over them: 62.9 us
-// with streaming stores, 62.0 with plain ones).
+// it may stay unless it is more than fits (PAST, from rows_go_past_caches()).
 typedef unsigned int vec4 __attribute__((ext_vector_type(4)));
 
 // One workgroup copies a contiguous range of destination vectors of one unit,
@@ -28,6 +27,7 @@ struct Side {
   long long src_seq_stride, src_head_stride, dst_seq_stride, dst_head_stride;
 };
 
+template <bool PAST>
 __global__ __launch_bounds__(kThreads) void compact_kernel(Side k_side, Side v_side,
                                                            const int32_t* __restrict__ idx,
                                                            int keep, int n_cur, int n_head,
@@ -63,7 +63,9 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(Side k_side, Side v_s
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
     const int f = f0 + u * kThreads;
-    if (ok[u]) dst[f] = val[u];
+    if (!ok[u]) continue;
+    if constexpr (PAST) __builtin_nontemporal_store(val[u], dst + f);
+    else dst[f] = val[u];
   }
 }
 
@@ -85,8 +87,10 @@ hipError_t launch_compact(int dtype, int n_seq, int n_head, int d, KvView k_src,
           k_src.head_stride / epv, k_dst.seq_stride / epv, k_dst.head_stride / epv};
   Side vs{(const vec4*)v_src.ptr, (const vec4*)v_cur, (vec4*)v_dst.ptr, v_src.seq_stride / epv,
           v_src.head_stride / epv, v_dst.seq_stride / epv, v_dst.head_stride / epv};
-  hipLaunchKernelGGL(compact_kernel, grid, dim3(kThreads), 0, stream, ks, vs, idx, keep, n_cur,
-                     n_head, vlog);
+  if (rows_go_past_caches(CacheWriter::kCompact, n_seq * n_head, keep + n_cur, d * elem))
+    hipLaunchKernelGGL(compact_kernel<true>, grid, dim3(kThreads), 0, stream, ks, vs, idx, keep, n_cur, n_head, vlog);
+  else
+    hipLaunchKernelGGL(compact_kernel<false>, grid, dim3(kThreads), 0, stream, ks, vs, idx, keep, n_cur, n_head, vlog);
   return hipGetLastError();
 }
 

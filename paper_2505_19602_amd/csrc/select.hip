@@ -11,6 +11,8 @@
 // ends; done on log-scores as a log-sum-exp, which ranks the same), and positions
 // that are preserved whatever their score (the observation window): those get the
 // largest key, and `keep` counts them.
+#include <type_traits>
+
 #include "common.h"
 #include "radix_select.h"
 #include "rank.h"
@@ -45,6 +47,7 @@ struct ScoreInputs {
   const uint16_t* k_cur;
   const uint16_t* v_cur;
   int n_app;
+  bool past_caches;         // rows_go_past_caches()
 };
 
 // Pruning of one unit by one workgroup: the kept rows (and, if asked, the map's rows behind them)
@@ -63,31 +66,40 @@ __device__ __forceinline__ void prune_unit(const ScoreInputs& si, int unit, int 
   const vec4* kcur = (const vec4*)(si.k_cur + (long long)unit * si.n_app * D);
   const vec4* vcur = (const vec4*)(si.v_cur + (long long)unit * si.n_app * D);
   const int total = (keep + si.n_app) * VPR;
-  // (the attention reads the kept rows next: plain stores, which may leave them in the caches.  256 units, 246 of 546
-  // rows, 576 queries, the whole step: 110.8 us with streaming stores, 107.2 so)
+  // (the attention reads the kept rows next: plain stores, which may leave them in the caches, unless they are too many.
+  // 256 units, 246 of 546 rows, 576 queries, the whole step: 110.8 us with streaming stores, 107.2 so.  Two loops: of
+  // two kinds of store in one the compiler makes plain ones.)
+  auto copy = [&](auto past) __attribute__((always_inline)) {
 #pragma unroll 1
-  for (int f0 = tid; f0 < total; f0 += THREADS * kFly) {
-    vec4 a[kFly], b[kFly];
+    for (int f0 = tid; f0 < total; f0 += THREADS * kFly) {
+      vec4 a[kFly], b[kFly];
 #pragma unroll
-    for (int u = 0; u < kFly; ++u) {
-      // (lanes past the end re-read the last vector and store nothing: a branch around the loads
-      // costs the kernel 30 registers)
-      const int f = min(f0 + u * THREADS, total - 1);
-      const int row = f / VPR, c = f % VPR;
-      const bool kept = row < keep;
-      const long long o = (long long)(kept ? list[row] : row - keep) * VPR + c;
-      a[u] = __builtin_nontemporal_load((kept ? ksrc : kcur) + o);
-      b[u] = __builtin_nontemporal_load((kept ? vsrc : vcur) + o);
-    }
+      for (int u = 0; u < kFly; ++u) {
+        // (lanes past the end re-read the last vector and store nothing: a branch around the loads
+        // costs the kernel 30 registers)
+        const int f = min(f0 + u * THREADS, total - 1);
+        const int row = f / VPR, c = f % VPR;
+        const bool kept = row < keep;
+        const long long o = (long long)(kept ? list[row] : row - keep) * VPR + c;
+        a[u] = __builtin_nontemporal_load((kept ? ksrc : kcur) + o);
+        b[u] = __builtin_nontemporal_load((kept ? vsrc : vcur) + o);
+      }
 #pragma unroll
-    for (int u = 0; u < kFly; ++u) {
-      const int f = f0 + u * THREADS;
-      if (f < total) {
-        kdst[f] = a[u];
-        vdst[f] = b[u];
+      for (int u = 0; u < kFly; ++u) {
+        const int f = f0 + u * THREADS;
+        if (f >= total) continue;
+        if constexpr (decltype(past)::value) {
+          __builtin_nontemporal_store(a[u], kdst + f);
+          __builtin_nontemporal_store(b[u], vdst + f);
+        } else {
+          kdst[f] = a[u];
+          vdst[f] = b[u];
+        }
       }
     }
-  }
+  };
+  if (si.past_caches) copy(std::true_type{});
+  else copy(std::false_type{});
 }
 
 // Units too long for their keys to stay in LDS: scores given, keys formed anew in each pass.
@@ -329,6 +341,7 @@ hipError_t launch_score_select(int dtype, int n_seq, int n_head, int d, const vo
     si.vd_seq_stride = prune->v_dst.seq_stride; si.vd_head_stride = prune->v_dst.head_stride;
     si.k_cur = (const uint16_t*)prune->k_cur; si.v_cur = (const uint16_t*)prune->v_cur;
     si.n_app = prune->k_cur ? prune->n_app : 0;
+    si.past_caches = rows_go_past_caches(CacheWriter::kRanking, n_unit, keep + si.n_app, d * 2);
   }
   constexpr int kComputeUnits = 256;  // MI355X
   const bool plain = ex.n_forced == 0 && ex.pool_w == 1;

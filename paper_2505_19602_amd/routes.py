@@ -78,3 +78,8 @@ def asi_streams(dtype: torch.dtype, units: int, length: int, n_samp: int, top_k:
     if min(units, 256) * rows >= (1024 if units >= 128 else 2048):
         return True
     return keys >= 160000 if rows == 32 else keys >= 220000 if rows >= 8 else keys >= 800000 and length >= 3000
+
+
+def rows_go_past_caches(ranking: bool, units: int, rows: int, row_bytes: int) -> bool:
+    """Whether the pruning stores its rows past the caches: by a ranking kernel or by compact_kernel."""
+    return 2 * rows * units * row_bytes > (256_000_000 if ranking else 400_000_000)

@@ -53,8 +53,9 @@ int main() {
   for (int u : units) for (int q : queries) for (int k : keys)
     for (int d = 64; d <= 128; d += 64) {
       const PipeForm f = pipe_form(d, u, q, k);
-      printf("%%s %%d %%d\\n", f == PipeForm::kPlain ? "plain" : f == PipeForm::kWide ? "wide" : "split", pipe_rows(f),
-             small_tile_rows(1, d, u, q, k, SmallWork::kRankedBefore));
+      printf("%%s %%d %%d %%d %%d\\n", f == PipeForm::kPlain ? "plain" : f == PipeForm::kWide ? "wide" : "split", pipe_rows(f),
+             small_tile_rows(1, d, u, q, k, SmallWork::kRankedBefore), rows_go_past_caches(CacheWriter::kRanking, u, k, 2 * d),
+             rows_go_past_caches(CacheWriter::kCompact, u, k, 2 * d));
     }
 }
 """
@@ -76,6 +77,7 @@ def test_forms_of_the_pipelined_kernel_are_the_rules_of_the_library(tmp_path):
                     form = routes.pipe_form(d, u, q, k)
                     seen.add((d, form))
                     rows = routes.small_tile_rows(torch.bfloat16, d, u, q, k, routes.RANKED_BEFORE)
-                    assert next(lines) == f"{form} {routes.pipe_rows(form)} {rows}", (u, q, k, d)
+                    past = [int(routes.rows_go_past_caches(ranking, u, k, 2 * d)) for ranking in (True, False)]
+                    assert next(lines) == f"{form} {routes.pipe_rows(form)} {rows} {past[0]} {past[1]}", (u, q, k, d)
     assert next(lines, None) is None
     assert seen == {(64, "plain"), (64, "split"), (128, "plain"), (128, "wide"), (128, "split")}

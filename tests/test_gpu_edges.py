@@ -391,3 +391,47 @@ def test_prepared_steps_of_subclasses_and_numpy_integers():
     assert float(results[0][0].abs().max()) > 0 and float(results[0][3].abs().max()) > 0
     for a, b in zip(*results):
         assert torch.equal(a, b)
+
+
+# Kept rows are stored through the caches up to a size and past them beyond, by compact_kernel and by the ranking
+# kernels: on either side of the limits, with a ragged end, every row of every unit.
+@pytest.mark.parametrize("rows", [3051, 3053])
+def test_large_compactions_on_both_sides_of_the_limit(rows):
+    S, H, d, n_cur = 16, 16, 128, 7
+    keep, L = rows - n_cur, rows + 200
+    assert routes.rows_go_past_caches(False, S * H, rows, 2 * d) == (rows == 3053)
+    print(f"compaction of {keep} + {n_cur} rows, {S * H} units", flush=True)
+    shape = skv.Shape(S, H, d, torch.bfloat16)
+    k, v = (torch.arange(S * H * L * d, device=DEV, dtype=torch.int32).mul_(m).to(torch.int16).view(torch.bfloat16).view(S, H, L, d)
+            for m in (3, 5))
+    kc, vc = (t[:, :, :n_cur].contiguous() for t in (v, k))
+    idx = torch.randperm(L, generator=torch.Generator().manual_seed(rows))[:keep].sort().values.int().to(DEV)
+    kd = torch.zeros(S, H, rows, d, dtype=torch.bfloat16, device=DEV)
+    vd = torch.zeros_like(kd)
+    skv.compact(shape, k, v, L, idx.expand(S, H, keep).contiguous(), keep, kc, vc, kd, vd)
+    torch.cuda.synchronize()
+    for got, cache, cur in ((kd, k, kc), (vd, v, vc)):   # (bits are compared: some are NaN)
+        assert torch.equal(got[:, :, :keep].view(torch.int16), cache.view(torch.int16)[:, :, idx.long()])
+        assert torch.equal(got[:, :, keep:].view(torch.int16), cur.view(torch.int16))
+
+
+@pytest.mark.parametrize("keep", [1953, 1954])
+def test_large_rankings_on_both_sides_of_the_limit(keep):
+    S, H, d, L, n_cur = 16, 16, 128, 2100, 300
+    assert routes.rows_go_past_caches(True, S * H, keep, 2 * d) == (keep == 1954)
+    assert routes.step_kernel(torch.bfloat16, d, S * H, n_cur, L, keep) == "pipelined"
+    print(f"ranking that keeps {keep} of {L} rows, {S * H} units", flush=True)
+    shape = skv.Shape(S, H, d, torch.bfloat16)
+    rand = lambda key, n: W.normal_tensor(W.stream_key(4321, key), (S, H, n, d), DEV).to(torch.bfloat16)
+    q, kc, vc = (rand(60 + i, n_cur) for i in range(3))
+    k, v = (rand(63 + i, L) for i in range(2))
+    kd = torch.zeros(S, H, keep + n_cur, d, dtype=torch.bfloat16, device=DEV)
+    vd, out = torch.zeros_like(kd), torch.empty_like(q)
+    idx = torch.empty(S, H, keep, dtype=torch.int32, device=DEV)
+    ws = torch.empty(skv.workspace_bytes(shape, L, n_cur), dtype=torch.uint8, device=DEV)
+    skv.step(shape, q, kc, vc, list(range(n_cur - 16, n_cur)), k, v, L, keep, kd, vd, out, idx, ws)
+    torch.cuda.synchronize()
+    assert bool((idx[..., 1:] > idx[..., :-1]).all()) and int(idx.min()) >= 0 and int(idx.max()) < L
+    rows = idx.long()[..., None].expand(S, H, keep, d)
+    for got, cache, cur in ((kd, k, kc), (vd, v, vc)):
+        assert torch.equal(got[:, :, :keep], cache.gather(2, rows)) and torch.equal(got[:, :, keep:], cur)
