@@ -137,7 +137,8 @@ struct Shape {
 // its share of the running time can be read off a timing.  Their results are wrong on purpose.
 //   SCALEKV_ABLATE_SOFTMAX    probabilities are the raw scores converted to bf16: no exp2, no
 //                             row sums, no overflow watch
-//   SCALEKV_ABLATE_TRANSFER   only the first two key tiles are fetched; later tiles re-use them
+//   SCALEKV_ABLATE_TRANSFER   only the tiles that fill the stages once are fetched (two of each group, wide form:
+//                             four); later tiles re-use them
 //   SCALEKV_TIMELINE          every workgroup records when it started, when its first tile had
 //                             arrived, when it left the tile loop and when it ended (results stay
 //                             correct); scalekv_timeline_read() hands the records to the host
@@ -512,7 +513,9 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     else
       __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-#if !defined(SCALEKV_ABLATE_TRANSFER)
+#if defined(SCALEKV_ABLATE_TRANSFER)
+    if (t == 0 && kStages <= n_tile) issue_v(kStages - 1);  // (fills the last stage, where query rows have been)
+#else
     if (t + kStages - 1 < n_tile) issue_v(t + kStages - 1);
     if (t + kStages < n_tile) issue_k(t + kStages);
 #endif

@@ -1,6 +1,10 @@
 """The three forms of the pipelined bf16 attention kernel (four waves, eight waves on 256 rows, groups of waves that
 split the keys) at the edges of their tiles, groups and stages, against the oracle; rows whose scores rise so far above
 the first tile's that the pass is repeated; the two-segment form with the append."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -187,3 +191,35 @@ def test_largest_weight_of_the_first_tile_is_one(form, d, S, H, n_q, kv, a, b):
     ref = oracle.attend(units(q)[[0]], units(k)[[0]], units(v)[[0]], d ** -0.5)
     check_output(units(out)[[0]], ref, BF16, form)
     assert out.abs().max() < 1e-6
+
+
+# The measurement-only build without tile transfers fetches the tiles that fill its stages once: with no more keys than
+# that it computes what the library does.
+NO_TRANSFER = os.path.join(os.path.dirname(skv.__file__), "libscalekv_no_transfer.so")
+NO_TRANSFER_CHILD = """
+import sys, torch
+import paper_2505_19602_amd as skv
+q, k, v = torch.load(sys.argv[1], weights_only=True)
+q, k, v = q.cuda(), k.cuda(), v.cuda()
+out = torch.empty_like(q)
+skv.attend(skv.Shape(15, 20, q.shape[3], torch.bfloat16), q, k, v, k.shape[2], out)
+torch.save(out.cpu(), sys.argv[2])
+"""
+
+
+@pytest.mark.skipif(not os.path.exists(NO_TRANSFER),
+                    reason="build it with: python -m paper_2505_19602_amd.build --variant no_transfer")
+@pytest.mark.parametrize("d", [64, 128])
+def test_build_without_transfers_fills_its_stages(d, tmp_path):
+    assert routes.pipe_form(d, 300, 40, 128) == "plain"
+    print(f"no_transfer build d={d}", flush=True)
+    q, k, v = (_rand(80 + i, (15, 20, n, d)) for i, n in enumerate((40, 128, 128)))
+    out = torch.empty_like(q)
+    skv.attend(skv.Shape(15, 20, d, BF16), q, k, v, 128, out)
+    torch.save([t.cpu() for t in (q, k, v)], tmp_path / "in.pt")
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    env = dict(os.environ, SCALEKV_LIBRARY=NO_TRANSFER, PYTHONPATH=root + os.pathsep + os.environ.get("PYTHONPATH", ""))
+    res = subprocess.run([sys.executable, "-c", NO_TRANSFER_CHILD, str(tmp_path / "in.pt"), str(tmp_path / "out.pt")], env=env,
+                         capture_output=True, text=True, timeout=100)
+    assert res.returncode == 0, res.stderr[-2000:]
+    assert torch.equal(out.cpu(), torch.load(tmp_path / "out.pt", weights_only=True))
