@@ -421,9 +421,7 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
   // cache is written by a launch of its own and attended over.
   const bool map_written = dense_overlap(shape, out, k_cur, n_cur) || dense_overlap(shape, out, v_cur, n_cur);
   const bool src_written = keep > 0 && (dense_overlaps(shape, out, n_cur, k_src) || dense_overlaps(shape, out, n_cur, v_src));
-  const SmallWork work = ranks ? (cache_len <= kShortLen ? SmallWork::kRanked : SmallWork::kRankedBefore)
-                               : keep > 0 ? SmallWork::kKeepAll : SmallWork::kAppend;
-  const int small_rows = small_tile_rows(shape->dtype, shape->head_dim, U, n_cur, keep + n_cur, work);
+  const int small_rows = small_tile_rows(shape->dtype, shape->head_dim, U, n_cur, keep + n_cur, step_work(keep, cache_len));
   const bool pipe = !map_written && shape->dtype == SCALEKV_BF16 && small_rows == 0;
   const bool small = !map_written && !src_written && small_rows > 0;
   // The small kernel ranks as well.  Each of its workgroups reads the window's queries: with out in the place

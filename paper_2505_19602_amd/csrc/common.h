@@ -181,6 +181,11 @@ enum class SmallWork {
   kRanked,   // the kept rows, chosen in this launch, are copied
   kRankedBefore  // the kept rows, chosen in the launch before, are copied
 };
+// The same of a step that keeps `keep` of cache_len rows.
+inline SmallWork step_work(int keep, int cache_len) {
+  if (keep > 0 && keep < cache_len) return cache_len <= kShortLen ? SmallWork::kRanked : SmallWork::kRankedBefore;
+  return keep > 0 ? SmallWork::kKeepAll : SmallWork::kAppend;
+}
 // Query rows per workgroup of that kernel for n_q bf16 queries over kv keys, 0 where the other kernels
 // are the better ones.  A workgroup of it fills a compute unit, and its time grows with the rows it
 // carries, so: the fewest rows with which the chip's 256 compute units take the launch in one round.

@@ -57,12 +57,17 @@ def pipe_rows(form: str) -> int:
     return 256 if form == "wide" else 128
 
 
+def step_work(keep: int, cache_len: int) -> int:
+    """What a step does besides the attention."""
+    if 0 < keep < cache_len:
+        return RANKED if cache_len <= SHORT_LEN else RANKED_BEFORE
+    return KEEP_ALL if keep else APPEND
+
+
 def step_kernel(dtype: torch.dtype, d: int, units: int, n_cur: int, cache_len: int, budget: int) -> str:
     """The same for the attention of scalekv_step; "small" prunes and appends in the same launch."""
     keep = min(budget, cache_len)
-    ranked = RANKED if cache_len <= SHORT_LEN else RANKED_BEFORE
-    work = ranked if 0 < keep < cache_len else KEEP_ALL if keep else APPEND
-    return attend_kernel(dtype, d, units, n_cur, keep + n_cur, work)
+    return attend_kernel(dtype, d, units, n_cur, keep + n_cur, step_work(keep, cache_len))
 
 
 def ranks_in_one_launch(dtype: torch.dtype, units: int, cache_len: int) -> bool:

@@ -11,6 +11,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 UNITS = (1, 2, 9, 16, 31, 32, 48, 63, 64, 96, 127, 128, 129, 200, 224, 225, 256, 257, 300, 512, 4000)
 QUERIES = (1, 4, 16, 17, 32, 33, 64, 65, 100, 128, 129, 200, 256, 300, 448, 576, 1024, 1025, 2049, 4096)
 KEYS = (1, 60, 320, 321, 511, 512, 1400, 2999, 3000, 4096, 4097, 6500, 12288, 12289, 60000)
+LENGTHS = (1, 2, 1535, 1536, 1537, 4096)   # cached rows: ranked in the launch that attends up to 1536
 PROGRAM = """
 #include <cstdio>
 #include "common.h"
@@ -57,6 +58,8 @@ int main() {
              small_tile_rows(1, d, u, q, k, SmallWork::kRankedBefore), rows_go_past_caches(CacheWriter::kRanking, u, k, 2 * d),
              rows_go_past_caches(CacheWriter::kCompact, u, k, 2 * d));
     }
+  const int lengths[] = {%s};
+  for (int n : lengths) for (int keep : {0, 1, n - 1, n}) printf("%%d\\n", (int)step_work(keep, n));
 }
 """
 
@@ -64,7 +67,7 @@ int main() {
 def test_forms_of_the_pipelined_kernel_are_the_rules_of_the_library(tmp_path):
     src, exe = tmp_path / "forms.hip", tmp_path / "forms"
     keys = KEYS + (319, 2047, 2048)
-    src.write_text(FORMS_PROGRAM % tuple(", ".join(map(str, t)) for t in (UNITS, QUERIES, keys)))
+    src.write_text(FORMS_PROGRAM % tuple(", ".join(map(str, t)) for t in (UNITS, QUERIES, keys, LENGTHS)))
     cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-host-only", "-std=c++17", f"-I{CSRC}", str(src), "-o", str(exe)]
     res = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
     assert res.returncode == 0, res.stderr[-3000:]
@@ -79,5 +82,8 @@ def test_forms_of_the_pipelined_kernel_are_the_rules_of_the_library(tmp_path):
                     rows = routes.small_tile_rows(torch.bfloat16, d, u, q, k, routes.RANKED_BEFORE)
                     past = [int(routes.rows_go_past_caches(ranking, u, k, 2 * d)) for ranking in (True, False)]
                     assert next(lines) == f"{form} {routes.pipe_rows(form)} {rows} {past[0]} {past[1]}", (u, q, k, d)
+    for n in LENGTHS:
+        for keep in (0, 1, n - 1, n):
+            assert int(next(lines)) == routes.step_work(keep, n), (keep, n)
     assert next(lines, None) is None
     assert seen == {(64, "plain"), (64, "split"), (128, "plain"), (128, "wide"), (128, "split")}
