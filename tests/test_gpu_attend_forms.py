@@ -193,6 +193,29 @@ def test_largest_weight_of_the_first_tile_is_one(form, d, S, H, n_q, kv, a, b):
     assert out.abs().max() < 1e-6
 
 
+# Keys whose logits are all -inf have weight zero: a first block, a first tile, tiles further on, and every tile of one
+# group (split form: tiles 1, 3, 5, 7, head_dim 64: 1, 4, 7), which then has nothing to join.
+@pytest.mark.parametrize("form,d,S,H,n_q,kv", [("split", 64, 4, 5, 430, 500), ("split", 128, 4, 5, 430, 500),
+                                               ("wide", 128, 16, 16, 130, 2100)])
+@pytest.mark.parametrize("where", ["first_block", "first_tile", "two_tiles", "group", "rest"])
+def test_keys_of_weight_zero_in_each_form(form, d, S, H, n_q, kv, where):
+    assert routes.pipe_form(d, S * H, n_q, kv) == form
+    print(f"weight zero, {form} d={d} {where}", flush=True)
+    tile, groups = torch.arange(kv) // 64, 3 if d == 64 else 2
+    gone = {"first_block": torch.arange(kv) < 32, "first_tile": tile == 0, "two_tiles": (tile == 1) | (tile == 2),
+            "group": tile % groups == 1, "rest": tile > 0}[where]
+    q, k, v = (_rand(120 + i, (S, H, n, d)) for i, n in enumerate((n_q, kv, kv)))
+    q[..., 0] = 0.5
+    k[:, :, gone.to(DEV), 0] = float("-inf")
+    out = torch.empty_like(q)
+    skv.attend(skv.Shape(S, H, d, BF16), q, k, v, kv, out)
+    torch.cuda.synchronize()
+    pick = [0, S * H - 1]
+    ref = oracle.attend(units(q)[pick], units(k)[pick][:, ~gone], units(v)[pick][:, ~gone], d ** -0.5)
+    check_output(units(out)[pick], ref, BF16, form)
+    assert torch.isfinite(out).all()
+
+
 # The measurement-only build without tile transfers fetches the tiles that fill its stages once: with no more keys than
 # that it computes what the library does.
 NO_TRANSFER = os.path.join(os.path.dirname(skv.__file__), "libscalekv_no_transfer.so")

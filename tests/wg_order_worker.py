@@ -3,6 +3,7 @@
 tests/test_gpu_wg_order.py runs it twice: in the test process with the library in the tree, and in
 a child process whose SCALEKV_LIBRARY names the build that walks every grid backwards
 (python -m paper_2505_19602_amd.build --variant reversed_order).  Not collected by pytest."""
+import hashlib
 import os
 import sys
 
@@ -24,12 +25,13 @@ def run_all():
 
     def keep_np(name, t):
         t = t.detach().cpu()
-        out[name] = (t.view(torch.int16) if t.dtype == torch.bfloat16 else t).numpy().copy()
+        a = (t.view(torch.int16) if t.dtype == torch.bfloat16 else t).numpy().copy()
+        out[name] = a if a.size < 1 << 23 else np.array(hashlib.sha256(a.tobytes()).hexdigest())
 
     # (tag, S, H, d, n_cur, cache_len, budget, dtype, attention kernel): whole steps in one launch (several
     # workgroups to a unit), fp32, a ranking in several launches in front of the small kernel; then the
     # pipelined attention, which appends, behind each form of the ranking kernel: in LDS, in registers, and
-    # with the rows beyond them in the workspace
+    # with the rows beyond them in the workspace; its three forms, and both kinds of append in the plain and split ones
     cases = [("one_launch", 3, 5, 128, 300, 900, 333, torch.bfloat16, "small"),
              ("one_launch_ragged", 2, 4, 128, 400, 1500, 210, torch.bfloat16, "small"),
              ("small", 2, 3, 128, 36, 140, 50, torch.bfloat16, "small"),
@@ -42,9 +44,15 @@ def run_all():
              ("pipe_registers", 1, 65, 128, 530, 1700, 300, torch.bfloat16, "pipelined"),
              ("pipe_registers_d64", 1, 65, 64, 530, 1700, 300, torch.bfloat16, "pipelined"),
              ("pipe_far", 1, 65, 128, 530, 4300, 300, torch.bfloat16, "pipelined"),
-             ("pipe_far_d64", 1, 65, 64, 530, 4300, 300, torch.bfloat16, "pipelined")]
+             ("pipe_far_d64", 1, 65, 64, 530, 4300, 300, torch.bfloat16, "pipelined"),
+             ("pipe_loop_d64", 5, 52, 64, 330, 300, 77, torch.bfloat16, "pipelined"),
+             ("pipe_split", 4, 10, 128, 430, 500, 120, torch.bfloat16, "pipelined"),
+             ("pipe_split_d64", 4, 10, 64, 430, 500, 120, torch.bfloat16, "pipelined"),
+             ("pipe_wide", 16, 16, 128, 200, 2100, 1860, torch.bfloat16, "pipelined")]
+    forms = {"pipe_short": "plain", "pipe_loop_d64": "plain", "pipe_split": "split", "pipe_split_d64": "split", "pipe_wide": "wide"}
     for c, (tag, S, H, d, n_cur, L, budget, dtype, kernel) in enumerate(cases):
         assert routes.step_kernel(dtype, d, S * H, n_cur, L, budget) == kernel, tag
+        assert tag not in forms or routes.pipe_form(d, S * H, n_cur, min(budget, L) + n_cur) == forms[tag], tag
         print(f"workgroup order: step {tag}: {S}x{H} units, {n_cur} queries, {L} cached rows", flush=True)
         shape = skv.Shape(S, H, d, dtype)
         q, kc, vc = (rand(10 * c + i, (S, H, n_cur, d), dtype) for i in range(3))
