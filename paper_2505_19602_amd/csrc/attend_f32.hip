@@ -24,7 +24,9 @@
 // Two waves per SIMD (no accumulation registers: with them the compiler copied hundreds of registers a block and kept
 // one wave per SIMD) cover what is serial in a block: the softmax between the products and the joins.
 // 400 queries x 517 keys x 32 units: 59 us with one wave, 53 now (64 TFLOP/s; 416 workgroups, one or two to a compute
-// unit); 400 x 900 x 512 units: 1219 -> 917 us, 103 TFLOP/s; 200 x 1600 x 32: 75 -> 61.
+// unit); 400 x 900 x 512 units: 1214 -> 904 us, 104 TFLOP/s; 200 x 1600 x 32: 74 -> 60.
+#include <type_traits>
+
 #include "common.h"
 
 namespace scalekv {
@@ -84,7 +86,7 @@ __global__ __launch_bounds__(64 * kMaxSplit) __attribute__((amdgpu_waves_per_eu(
   // younger ones it waited for the values as well, requested only just before)
   __builtin_amdgcn_sched_barrier(0);
   const int n_block = (kv_len + kBlockKeys - 1) / kBlockKeys;
-  load_k(wave);  // (a wave without keys takes the last row, and drops it)
+  load_k(wave);
   __builtin_amdgcn_sched_barrier(0);
   load_v(wave);
   __builtin_amdgcn_sched_barrier(0);
@@ -100,7 +102,15 @@ __global__ __launch_bounds__(64 * kMaxSplit) __attribute__((amdgpu_waves_per_eu(
       for (int c = 0; c < 4; ++c) o[b][t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
-  for (int block = wave; block < n_block; block += n_split) {
+  // `more`: whether a block follows, whose keys and values are requested as soon as the products have left their
+  // registers.  The last block is a copy of its own: a condition at the requests would let the compiler assume that
+  // they may not have been made, and wait for everything, and requests that nobody needs keep the join waiting (128
+  // units x 33 queries x 60 keys, a block per wave: 9.4 us with them, 8.1 without; 32 x 400 x 300, 16 rows: 38.0, 34.8;
+  // head_dim 64, many rounds: 6-10 %).  With 32 rows of head_dim 128, which are taken where there is much to do, one
+  // body is the faster (256 x 1024 x 600 768 us, 822 with two; 512 x 400 x 600 630 / 670): there the last request takes
+  // the last row again, and is dropped.
+  constexpr bool kSameBody = D == 128 && QB == 2;
+  auto walk = [&](int block, auto more) __attribute__((always_inline)) {
     f32x4 s[QB];
 #pragma unroll
     for (int b = 0; b < QB; ++b) s[b] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -112,11 +122,9 @@ __global__ __launch_bounds__(64 * kMaxSplit) __attribute__((amdgpu_waves_per_eu(
         for (int b = 0; b < QB; ++b)
           s[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t][e], qf[b][t][e], s[b], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
-    // (behind the last block: its last row again, dropped.  A condition here, or on the values below, would let the
-    // compiler assume that it may not have been requested, and wait for everything.)
-    load_k(block + n_split);
+    if constexpr (decltype(more)::value) load_k(block + n_split);
     __builtin_amdgcn_sched_barrier(0);
-    if ((block + 1) * kBlockKeys > kv_len) {
+    if ((!decltype(more)::value || kSameBody) && (block + 1) * kBlockKeys > kv_len) {  // (only the last block may be)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
         if (block * kBlockKeys + 4 * g + r >= kv_len)
@@ -165,8 +173,15 @@ __global__ __launch_bounds__(64 * kMaxSplit) __attribute__((amdgpu_waves_per_eu(
           for (int b = 0; b < QB; ++b)
             o[b][t][c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[r][t][c], s[b][r], o[b][t][c], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
-    load_v(block + n_split);
+    if constexpr (decltype(more)::value) load_v(block + n_split);
     __builtin_amdgcn_sched_barrier(0);
+  };
+  if constexpr (kSameBody) {
+    for (int block = wave; block < n_block; block += n_split) walk(block, std::true_type{});
+  } else {
+    int block = wave;  // (every wave has one)
+    for (; block + n_split < n_block; block += n_split) walk(block, std::true_type{});
+    walk(block, std::false_type{});
   }
 
   // ---- join the waves' parts: common offset, then sums over the waves, 64 channels at a time
@@ -226,9 +241,10 @@ hipError_t launch(int n_unit, int n_head, const float* q, int n_q, KvView k, KvV
   const int n_block = (kv_len + kBlockKeys - 1) / kBlockKeys;
   const int split = n_block >= kMaxSplit ? kMaxSplit : n_block >= 2 ? 2 : 1;
   // A third workgroup of 16 rows per compute unit (head_dim 128) pays while the keys are few: over many the three walk
-  // through more rows than the caches hold (256 units x 40 queries, 300 keys: 31 us, 38 with two; 900 keys: 74 / 67).
-  // LDS that nothing uses keeps it out.
-  const int lds = D == 128 && QB == 1 && kv_len >= 512 ? 40 * 1024 : 0;
+  // through more rows than the caches hold (with three / two, us: 100 units x 200 queries, 300 keys 49.5 / 52.4, 450
+  // 70.7 / 71.2, 511 78.1 / 75.5, 800 117 / 105; 256 x 200, 300 108 / 120, 511 174 / 164).  LDS that nothing uses keeps
+  // it out.
+  const int lds = D == 128 && QB == 1 && kv_len >= 480 ? 40 * 1024 : 0;
   hipLaunchKernelGGL((attend_f32_kernel<D, QB>), dim3(n_tile * n_unit), dim3(64 * split), lds, stream, q, n_q,
                      (const float*)k.ptr, k.seq_stride, k.head_stride, (const float*)v.ptr, v.seq_stride,
                      v.head_stride, kv_len, n_head, n_tile, split, sm_scale * 1.4426950408889634f, out);
@@ -241,15 +257,22 @@ hipError_t launch_attend_f32(int n_unit, int n_head, int d, const void* q, int n
                              int kv_len, float sm_scale, void* out, hipStream_t stream) {
   const float* qp = (const float*)q;
   float* op = (float*)out;
-  // 32 query rows per wave halve the reads of K and V per flop, 16 rows make twice as many workgroups and fewer
-  // padded rows.  The launch takes as long as the compute unit that has most to do: m1 workgroups of 16 rows or m2 of
-  // 32, of which one costs 12/7 (head_dim 64: 16/9) of the smaller; up to one (three) small ones are always better.
-  // us, 16 / 32 rows, d 128, 1600 keys: m 2 / 1 78 / 61, 3 / 2 110 / 130, 4 / 2 146 / 133, 13 / 7 480 / 431; d 64:
-  // 2 / 1 36.2 / 35.1 (300 keys 11.2 / 11.5), 3 / 2 56 / 64, 7 / 4 127 / 131, 13 / 7 235 / 226.
+  // 32 query rows per wave halve the reads of K and V per flop; 16 rows make twice as many workgroups and fewer padded
+  // rows, and their joins take half as long.  The launch takes as long as the compute unit that has most to do, m1
+  // workgroups of 16 rows or m2 of 32.  Two of 32 rows share a compute unit, and one that is left alone in the last of a
+  // few rounds costs as much as two: then 32 rows are taken where m2 is even (or 1) and m1 twice that.
+  // 16 / 32 rows, us, d 128: m 2 / 1  120 keys 10.9 / 12.2, 160 13.2 / 14.3, 300 19.4 / 18.4, 1200 57.9 / 47.3
+  //   4 / 2  120 keys 20.1 / 21.3, 300 35.4 / 34.9   6 / 3  300 keys 49.7 / 61.3, 1600 207 / 185   9 / 5  400 keys 90 / 104
+  //   12 / 6  120 keys 53.0 / 56.4, 300 99.4 / 95.9   36 / 18  200 keys 208 / 221, 300 284 / 279, 600 477 / 451
+  // d 64 (half the reads to save): 4 / 2  160 keys 11.8 / 13.2, 300 18.1 / 18.0, 1200 54.6 / 49.4   7 / 4  120 keys 16.1 /
+  //   17.4, 800 64.9 / 65.4   8 / 4  300 keys 32.9 / 30.7   18 / 9  100 keys 0.98 of the time, 40 1.05   36 / 18  40 0.99
   constexpr int kComputeUnits = 256;
   const long long m1 = ((long long)((n_q + 15) / 16) * n_unit + kComputeUnits - 1) / kComputeUnits;
   const long long m2 = ((long long)((n_q + 31) / 32) * n_unit + kComputeUnits - 1) / kComputeUnits;
-  const bool wide = d == 128 ? m1 > 1 && m2 * 12 <= m1 * 7 : m1 > 3 && m2 * 16 <= m1 * 9;
+  const bool even = m1 == 2 * m2 && (m2 == 1 || m2 % 2 == 0);
+  const bool wide = d == 128 ? m1 > 1 && m2 * 12 <= m1 * 7 && kv_len >= (m1 >= 18 || even ? 240 : 1000)
+                             : m1 > 3 && m2 * 11 <= m1 * 6 &&
+                                   kv_len >= (m1 >= 32 ? 0 : m1 >= 16 ? 100 : m1 > 4 ? 160 : 300);
   if (d == 128)
     return wide ? launch<128, 2>(n_unit, n_head, qp, n_q, k, v, kv_len, sm_scale, op, stream)
                 : launch<128, 1>(n_unit, n_head, qp, n_q, k, v, kv_len, sm_scale, op, stream);

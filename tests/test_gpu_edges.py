@@ -18,14 +18,16 @@ def _rand(key, shape, dtype, scale=1.0):
     return (W.normal_tensor(W.stream_key(4321, key), shape) * scale).to(dtype)
 
 
-# 16 and 32 query rows per wave (many units: from 2 workgroups of 16 rows per compute unit for head_dim 128, from 4 for
-# 64), 1, 2 and 4 waves sharing the keys, a wave without keys, ragged blocks of 16 keys and of query rows, 16 rows with
-# and without the LDS that keeps a third workgroup away (512 keys)
+# 16 and 32 query rows per wave (by the workgroups of the fullest compute unit and the keys: (1, 40, 190, 241) and those
+# behind it take 32 rows with head_dim 128, the last two with 64 too), 1, 2 and 4 waves sharing the keys, blocks that
+# only some waves have, ragged blocks of 16 keys and of query rows, 16 rows with and without the LDS that keeps a third
+# workgroup away (480 keys)
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("S,H,n_q,kv_len", [
     (1, 2, 1, 1), (1, 2, 16, 15), (1, 3, 17, 16), (2, 2, 15, 17), (1, 2, 33, 48), (1, 2, 40, 63), (1, 2, 5, 65),
     (1, 1, 31, 129), (4, 48, 64, 33), (4, 48, 50, 80), (1, 100, 120, 20),
-    (1, 40, 16, 511), (1, 40, 17, 512), (4, 80, 33, 513), (2, 64, 40, 527), (2, 64, 32, 97), (4, 64, 64, 529),
+    (1, 40, 16, 511), (1, 40, 17, 512), (4, 80, 33, 513), (2, 64, 40, 527), (2, 64, 32, 97), (1, 40, 17, 479), (1, 40, 17, 480),
+    (1, 40, 190, 241), (4, 64, 50, 263), (4, 64, 113, 240), (4, 64, 64, 529),
 ])
 def test_attend_f32_edges(d, S, H, n_q, kv_len):
     print(f"attend f32 d={d} S={S} H={H} n_q={n_q} kv_len={kv_len}", flush=True)
