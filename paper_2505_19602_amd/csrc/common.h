@@ -76,9 +76,16 @@ hipError_t launch_select_from_logits(int n_unit, int n_win, ScoreWorkspace ws, i
                                      hipStream_t stream);
 // The whole ranking step in one launch (bf16 only): one workgroup per unit forms the logits of
 // the window rows against the unit's cached keys, the row normalisers and the log-scores
-// (Eq. 5) and selects.  Worth it when there are enough units to fill the chip or the caches are
-// short; returns hipErrorNotSupported otherwise (and for fp32 or very long caches), and the
-// caller takes the two launches.  The logits part of `ws` is used, the chunk statistics are not.
+// (Eq. 5) and selects.  Returns hipErrorNotSupported where score_select_fits() says no (and for fp32 or
+// very long caches), and the caller takes the launches of the single stages, which fill the chip whatever the units.
+// The logits part of `ws` is used, the chunk statistics are not.
+// Ranked steps of 300 queries that keep a quarter, us, one launch / several (d 128; units x rows):
+//   16 x 600: 24.3 / 24.2   16 x 1600: 39.7 / 31.9   16 x 4096: 68.5 / 41.7   16 x 6400: 103 / 54
+//   64 x 600: 34.8 / 36.1   64 x 1600: 52.9 / 47.3   64 x 4096: 97 / 76   64 x 6400: 153 / 106   64 x 12000: 270 / 173
+//   128 x 1600: 64.8 / 70.0   128 x 4096: 126 / 124   128 x 6400: 190 / 173     256 x 600: 65 / 75   256 x 4096: 188 / 222
+//   256 x 12000: 527 / 574    d 64: 60 x 1600: 36.6 / 37.2   60 x 4096: 62 / 53   128 x 4096: 79 / 83   256 x 12000: 292 / 338
+// The line is an old one and does not lie where the two cross: up to about 128 units the several launches are as fast
+// from about 1600 rows on, and with few units much faster.
 inline bool score_select_fits(int dtype, int d, int n_unit, int cache_len) {
   return dtype == 1 && (d == 64 || d == 128) && cache_len <= 12288 && (n_unit >= 64 || cache_len <= 4096);
 }
@@ -189,27 +196,29 @@ inline SmallWork step_work(int keep, int cache_len) {
 // Query rows per workgroup of that kernel for n_q bf16 queries over kv keys, 0 where the other kernels
 // are the better ones.  A workgroup of it fills a compute unit, and its time grows with the rows it
 // carries, so: the fewest rows with which the chip's 256 compute units take the launch in one round.
-// Measured against ranking + pruning + pipelined attention (us, d 128; units, queries, cached, kept):
-//   16 rows:   16 x 144, 340, 80: 16.5 / 26.2       16 x 144, 5000, 5000: 60 / 117
-//   32 rows:   32 x 256, 380, 82: 21.5 / 28.9       16 x 400, 1500, 1500: 29 / 48
-//   64 rows:   16 x 1024, 820, 390: 51 / 59         64 x 256, 380, 82: 26.5 / 30.1
-//   128 rows:  256 x 128, 300, 60: 28.3 / 30.2      128 x 256, 380, 82: 33.5 / 33.6
-//              128 x 144, 5000, 5000: 294 / 217     (longer than 320 keys: not worth it)
+// Measured against ranking + pruning + pipelined attention (us, d 128; units, queries, cached, kept; this kernel's
+// time stands first, also where the rule takes the other side):
+//   16 rows:   16 x 144, 340, 80: 16.4 / 25.0       16 x 144, 5000, 5000: 60.8 / 88.6     16 x 256, 1200, 300: 28.1 / 42.5
+//   32 rows:   32 x 256, 380, 82: 21.8 / 28.0       16 x 400, 1500, 1500: 27.0 / 39.5     8 x 1024, 1500, 700: 45.5 / 65.1
+//   64 rows:   16 x 1024, 820, 390: 49.7 / 52.4     64 x 256, 380, 82: 26.3 / 28.6        16 x 576, 1200, 300: 43.2 / 46.6
+//              16 x 1024, 400, 80: 40.7 / 39.3      (the narrowest; head_dim 64, 16 x 1024, 820, 390: 31.3 / 37.3)
+//   128 rows:  256 x 128, 300, 60: 28.5 / 28.4      (equal by now; up to 320 keys)
+//              128 x 256, 380, 82: 33.9 / 32.2      128 x 144, 5000, 5000: 295 / 202     (longer: not worth it)
 // From 64 rows on it is what the launch does besides the attention that pays: the attention alone is then faster in the
-// pipelined kernel (64 x 144 queries, 300 keys: 14.6 / 11.9; 128 x 144, 300 keys, 128 rows: 21.3 / 12.7), and with few
-// keys from 32 rows on (8 x 700, 64 keys: 7.5 / 5.6; 130: 8.5 / 8.2; 400: 11.7 / 12.1).  A ranking in the same launch
+// pipelined kernel (64 x 144 queries, 300 keys: 13.6 / 10.6; 128 x 144, 300 keys, 128 rows: 19.8 / 11.5), and with few
+// keys from 32 rows on (8 x 700, 64 keys: 7.3 / 5.2; 130: 8.3 / 8.0; 400: 11.4 / 11.9).  A ranking in the same launch
 // is repeated by every workgroup of a unit: 64 rows pay up to 16 of those, 32 only with head_dim 64 (8 x 2048, 380, 82:
-// 57.9 / 49.8, head_dim 64 33.6 / 36.5).  Without one 64 rows pay while
+// 58.7 / 51.5, head_dim 64 33.3 / 36.0).  Without one 64 rows pay while
 // the workgroups leave some compute units to those that copy, which otherwise wait for a round of their
-// own (all kept, 64 x 144 queries, 100 cached, 192 workgroups: 13.1 / 17.2; 64 x 256, 256 workgroups: 23.8 / 19.2;
-// ranked before, 2500 cached, 300 kept: 64 x 144 54.3 / 57.4; 64 x 256 62.7 / 59.4; 16 x 1024 73.6 / 66.4;
+// own (all kept, 64 x 144 queries, 100 cached, 192 workgroups: 12.9 / 16.8; 64 x 256, 256 workgroups: 19.3 / 18.7;
+// ranked before, 2500 cached, 300 kept: 64 x 144 51.8 / 54.7; 64 x 256 58.8 / 56.1; 16 x 1024 69.2 / 63.9;
 // head_dim 64 copies half as much: 0.71-0.99 of the time up to 256; one workgroup per unit is as fast or faster but
-// around 100 cached rows: 256 x 36 queries, 19, 70, 100, 500: 13.3 / 13.8, 17.0 / 19.2, 22.8 / 20.7, 42.8 / 47.7),
-// 128 rows do not (128 x 200, 100: 32.3 / 24.5).
+// around 100 cached rows: 256 x 36 queries, 19, 70, 100, 500: 12.4 / 11.9, 13.5 / 16.8, 18.0 / 17.3, 39.6 / 42.2),
+// 128 rows do not (128 x 200, 100: 26.2 / 21.1).
 // Appending alone copies least and gains least: head_dim 64, up to 224 workgroups, 0.86-0.95 of the time over 500
 // keys and more; head_dim 128: 1.00-1.24.
 // More units than compute units: two rounds are paid, which only maps of up to 16 queries stand
-// (320 x 4, 65, 65: 10.8 / 20.8;  512 x 16, 69, 14: 22.1 / 22.7;  320 x 36, 85, 21: 26 / 23).
+// (320 x 4, 65, 65: 11.7 / 18.2;  512 x 16, 69, 14: 19.9 / 18.7;  320 x 36, 85, 21, 128 rows: 20.5 / 20.1).
 inline int small_tile_rows(int dtype, int d, int n_unit, int n_q, int kv, SmallWork work) {
   if (dtype != 1) return 0;
   constexpr int kComputeUnits = 256;
