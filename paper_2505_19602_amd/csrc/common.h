@@ -314,6 +314,15 @@ __device__ __forceinline__ void swap32(float x, float& a, float& b) {
   a = __uint_as_float(r[0]);
   b = __uint_as_float(r[1]);
 }
+// x of lane 16 ROW + l % 16, in every lane.
+template <int ROW>
+__device__ __forceinline__ float from_row(float x) {
+  float lo, hi;
+  swap32(x, lo, hi);  // the lower half in both halves, the upper half in both
+  const float half = ROW / 2 ? hi : lo;
+  swap16(half, lo, hi);
+  return ROW % 2 ? hi : lo;
+}
 __device__ __forceinline__ float xor16_max(float x) { float a, b; swap16(x, a, b); return fmaxf(a, b); }
 __device__ __forceinline__ float xor32_max(float x) { float a, b; swap32(x, a, b); return fmaxf(a, b); }
 __device__ __forceinline__ float xor16_sum(float x) { float a, b; swap16(x, a, b); return a + b; }

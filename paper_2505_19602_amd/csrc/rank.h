@@ -90,11 +90,20 @@ __device__ __forceinline__ void emit_selected(const uint32_t (&kk)[PER], uint32_
 // Largest and smallest of a value per thread, over the workgroup.  wave_max, wave_min: a word per wave.
 template <int THREADS>
 __device__ __forceinline__ void block_extremes(uint32_t& hi, uint32_t& lo, uint32_t* wave_max, uint32_t* wave_min) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    hi = max(hi, (uint32_t)__shfl_xor((int)hi, off));
-    lo = min(lo, (uint32_t)__shfl_xor((int)lo, off));
-  }
+#define SCALEKV_ROW_ROR(v, n) (uint32_t) __builtin_amdgcn_update_dpp(0, (int)(v), 0x120 + (n), 0xf, 0xf, true)
+  hi = max(hi, SCALEKV_ROW_ROR(hi, 8)), lo = min(lo, SCALEKV_ROW_ROR(lo, 8));
+  hi = max(hi, SCALEKV_ROW_ROR(hi, 4)), lo = min(lo, SCALEKV_ROW_ROR(lo, 4));
+  hi = max(hi, SCALEKV_ROW_ROR(hi, 2)), lo = min(lo, SCALEKV_ROW_ROR(lo, 2));
+  hi = max(hi, SCALEKV_ROW_ROR(hi, 1)), lo = min(lo, SCALEKV_ROW_ROR(lo, 1));
+#undef SCALEKV_ROW_ROR
+  auto across = [](uint32_t x, auto join) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    const uint32_t y = join(r[0], r[1]);
+    const auto s = __builtin_amdgcn_permlane32_swap(y, y, false, false);
+    return join(s[0], s[1]);
+  };
+  hi = across(hi, [](uint32_t a, uint32_t b) { return max(a, b); });
+  lo = across(lo, [](uint32_t a, uint32_t b) { return min(a, b); });
   if ((threadIdx.x & 63) == 0) { wave_max[threadIdx.x >> 6] = hi; wave_min[threadIdx.x >> 6] = lo; }
   __syncthreads();
 #pragma unroll
@@ -104,28 +113,84 @@ __device__ __forceinline__ void block_extremes(uint32_t& hi, uint32_t& lo, uint3
   }
 }
 
-// Row normalisers max_j + log Z_j of all sixteen window rows, by one wave: lane (g, i) brings maximum and
-// sum of virtual waves 4g .. 4g+3 of row i and, in mm, the largest of those maxima.  Those of g >= turns are empty.
-__device__ __forceinline__ void row_shifts(const float (&vm)[4], const float (&ve)[4], float mm, int turns,
-                                           float (&shift)[kMaxWindow]) {
-  const int i = threadIdx.x & 15;
-  mm = xor32_max(xor16_max(mm));
+// Row normaliser max + log Z of window row i in every lane (g, i), by one wave: the lane brings maximum (-inf: no
+// key) and sum of virtual waves 4g .. 4g+3 of that row.  Those of g >= turns are empty.  FUSED: the products of all
+// turns are added unrounded, otherwise those of the first (the border of a selection may lie between scores that differ
+// in the last bit: which rows are kept depends on every rounding here).
+template <bool FUSED>
+__device__ __forceinline__ float row_shift(const float (&vm)[4], const float (&ve)[4], int turns) {
+#pragma clang fp contract(off)
+  float mm = xor32_max(xor16_max(fmaxf(fmaxf(vm[0], vm[1]), fmaxf(vm[2], vm[3]))));
+  float f[4];
+#pragma unroll
+  for (int x = 0; x < 4; ++x) f[x] = expf(vm[x] - mm);
   // the sum runs over the virtual waves in order: g = 0 hands its part to g = 1 and so on
-  float z = 0.f;
+  auto add = [&](float z, bool fused) __attribute__((always_inline)) {
+#pragma clang fp contract(off)
 #pragma unroll
-  for (int turn = 0; turn < 4; ++turn) {
-    if (turn >= turns) break;
-    float part = z;
-#pragma unroll
-    for (int x = 0; x < 4; ++x)
-      if (vm[x] > -INFINITY) part += ve[x] * expf(vm[x] - mm);
-    // after turn t the lanes of g = t hold the sum so far; everybody takes it from there
-    z = __shfl(part, 16 * turn + i);
-  }
-  const float s = mm + logf(z);
+    for (int x = 0; x < 4; ++x) z = !(vm[x] > -INFINITY) ? z : fused ? fmaf(ve[x], f[x], z) : z + ve[x] * f[x];
+    return z;
+  };
+  float z = from_row<0>(add(0.f, true));
+  if (turns > 1) z = from_row<1>(add(z, FUSED));
+  if (turns > 2) z = from_row<2>(add(z, FUSED));
+  if (turns > 3) z = from_row<3>(add(z, FUSED));
+  return mm + logf(z);
+}
+// The same of all sixteen rows, as scalars.
+__device__ __forceinline__ void row_shifts(float own, float (&shift)[kMaxWindow]) {
 #pragma unroll
   for (int j = 0; j < kMaxWindow; ++j)
-    shift[j] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(s), j));
+    shift[j] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(own), j));
+}
+
+// log_sum_rows (common.h) of one key by PARTS neighbouring lanes, each with 16 / PARTS of its window rows: `logits` are
+// those of the key, `shift` is row_shift() of lane (g, i).  The terms are added in the order of the rows, the lanes in
+// turn, so that every PARTS gives the same result.  A chain of 16 exponentials by a few of the waves is what a lane to a
+// key costs; with it and the normalisers' chains shortened (row_shift, block_extremes in registers, logits stored
+// without conditions) a step of 16 queries over 69 rows, 16 units, went from 9.8 to 9.2 us, 6 x 6 queries over 56 rows,
+// 80 units, 9.3 to 8.9, ten maps of one image, 16 units, 172.6 to 168.1.
+template <int PARTS>
+__device__ __forceinline__ float log_sum_parts(const float* logits, int n_win, float shift) {
+  static_assert(PARTS == 2 || PARTS == 4, "lanes of a row of four");
+  constexpr int kOwn = kMaxWindow / PARTS;
+  const int j0 = threadIdx.x % PARTS * kOwn;
+  float la[kOwn], top = -INFINITY;
+#pragma unroll
+  for (int j = 0; j < kOwn; j += 4) {
+    const float4 x = *(const float4*)(logits + j0 + j);
+    la[j] = x.x; la[j + 1] = x.y; la[j + 2] = x.z; la[j + 3] = x.w;
+  }
+#pragma unroll
+  for (int j = 0; j < kOwn; ++j) {
+    const float row = __shfl(shift, j0 + j);
+    la[j] = j0 + j < n_win ? la[j] - row : -INFINITY;
+    top = fmaxf(top, la[j]);
+  }
+#define SCALEKV_QUAD(v, ctrl) \
+  __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true))
+  top = fmaxf(top, SCALEKV_QUAD(top, 0xb1));                  // lane ^ 1
+  if (PARTS == 4) top = fmaxf(top, SCALEKV_QUAD(top, 0x4e));  // lane ^ 2
+#pragma unroll
+  for (int j = 0; j < kOwn; ++j) la[j] = j0 + j < n_win ? expf(la[j] - top) : 0.f;
+  auto add = [&](float z) {
+#pragma unroll
+    for (int j = 0; j < kOwn; ++j) z += la[j];
+    return z;
+  };
+  // after turn t lane t of the key holds the sum so far; the others take it from there
+  float z = add(0.f);
+  if constexpr (PARTS == 4) {
+    z = add(SCALEKV_QUAD(z, 0x00));
+    z = add(SCALEKV_QUAD(z, 0x55));
+    z = add(SCALEKV_QUAD(z, 0xaa));
+    z = SCALEKV_QUAD(z, 0xff);
+  } else {
+    z = add(SCALEKV_QUAD(z, 0xa0));  // lanes 0 and 2
+    z = SCALEKV_QUAD(z, 0xf5);       // lanes 1 and 3
+  }
+#undef SCALEKV_QUAD
+  return top + logf(z);
 }
 
 // From the log-scores to the selection.  own[c]: log-score of row tid + c THREADS.  `keys` (LDS, len words)
@@ -192,7 +257,7 @@ __device__ __forceinline__ void select_scores(float (&own)[PER], int len, int ke
   __syncthreads();
 }
 
-// The same for a few rows (len PARTS <= THREADS; own: log-score of row tid) by counting, for every row, those with a
+// The same for a few rows (len PARTS <= THREADS; own: log-score of row tid / PARTS) by counting, for every row, those with a
 // larger score: PARTS lanes share a row, and each compares its key with a part of the others.  The radix search takes
 // three or four barriers and as many round trips through LDS counters; this takes two.  False, with nothing
 // emitted, if equal scores straddle the border: then it takes the search to choose among them.
@@ -204,10 +269,10 @@ __device__ __forceinline__ bool select_by_rank(float own, int len, int keep, Lds
   constexpr int kWaves = THREADS / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int share = (len + 4 * PARTS - 1) / (4 * PARTS) * 4;  // keys per lane; a key of 0 beyond len is larger than none
-  if (tid < share * PARTS) lds.keys[tid] = tid < len ? order_key(own) : 0u;
-  __syncthreads();
   const int row = tid / PARTS;
-  const uint32_t mine = lds.keys[min(row, len - 1)];
+  const uint32_t mine = row < len ? order_key(own) : 0u;
+  if (tid % PARTS == 0 && row < share * PARTS) lds.keys[row] = mine;
+  __syncthreads();
   const uint4* part = reinterpret_cast<const uint4*>(lds.keys + tid % PARTS * share);
   int above = 0;
 #pragma unroll 4
@@ -261,7 +326,7 @@ __device__ __forceinline__ void rank_short(const uint16_t* qu, const WindowRows&
       score_products<D, 2>(kf, qf, c);
       if (group + kWaves < n_group) score_load_keys<D, 2>(ku, 32 * (group + kWaves), len, kf);
       score_statistics<2>(c, 32 * group, len, sm_scale, m, e);
-      score_store_logits<2>(c, 32 * group, len, logits, kLogitStride);
+      score_store_logits<2, true>(c, 32 * group, len, logits, kLogitStride);
       if (lane < kMaxWindow) {
         lds.group_max[group][lane] = m;
         lds.group_sum[group][lane] = e;
@@ -272,27 +337,46 @@ __device__ __forceinline__ void rank_short(const uint16_t* qu, const WindowRows&
   __syncthreads();
 
   // ---- row normalisers, by every wave: lane (g, i) merges virtual waves 4g .. 4g+3 of row i
-  float shift[kMaxWindow];
+  float own_shift;
   {
     float vm[4], ve[4];
-    float mm = -INFINITY;
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
-      float m_run = -INFINITY, e_run = 0.f;
-      for (int group = 4 * g + x; group < n_group; group += kVirtualWaves) {
-        const float m = lds.group_max[group][i], e = lds.group_sum[group][i];
-        const float m_new = fmaxf(m_run, m);
-        e_run = e_run * expf(m_run - m_new) + e * expf(m - m_new);
-        m_run = m_new;
-      }
-      vm[x] = m_run;
-      ve[x] = e_run;
-      mm = fmaxf(mm, m_run);
+      const int group = 4 * g + x;
+      const float m = lds.group_max[min(group, n_group - 1)][i], e = lds.group_sum[min(group, n_group - 1)][i];
+      vm[x] = group < n_group ? m : -INFINITY;
+      ve[x] = group < n_group ? e : 0.f;
     }
-    row_shifts(vm, ve, mm, (min(n_group, kVirtualWaves) + 3) / 4, shift);
+#pragma unroll
+    for (int first = kVirtualWaves; first < kShortGroups; first += kVirtualWaves)
+      if (first < n_group) {  // (the same for all lanes)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          const int group = first + 4 * g + x;
+          const float m = lds.group_max[min(group, n_group - 1)][i], e = lds.group_sum[min(group, n_group - 1)][i];
+          const float m_new = fmaxf(vm[x], m);
+          const float e_new = ve[x] * expf(vm[x] - m_new) + e * expf(m - m_new);
+          vm[x] = group < n_group ? m_new : vm[x];
+          ve[x] = group < n_group ? e_new : ve[x];
+        }
+      }
+    own_shift = row_shift<false>(vm, ve, (min(n_group, kVirtualWaves) + 3) / 4);
+  }
+
+  if constexpr (!EXTRAS) {  // few rows: several lanes to a row
+    const int part4 = min(tid / 4, len - 1), part2 = min(tid / 2, len - 1);
+    if (len <= THREADS / 4) {
+      const float own = log_sum_parts<4>(logits + part4 * kLogitStride, n_win, own_shift);
+      if (select_by_rank<THREADS, 4>(own, len, keep, lds, lds.list, idx)) return;
+    } else if (len <= kCountedRows && len <= THREADS / 2) {
+      const float own = log_sum_parts<2>(logits + part2 * kLogitStride, n_win, own_shift);
+      if (select_by_rank<THREADS, 2>(own, len, keep, lds, lds.list, idx)) return;
+    }
   }
 
   // ---- log-scores, as keys whose order is theirs
+  float shift[kMaxWindow];
+  row_shifts(own_shift, shift);
   float own[kPer];
 #pragma unroll
   for (int c = 0; c < kPer; ++c) {
@@ -306,13 +390,6 @@ __device__ __forceinline__ void rank_short(const uint16_t* qu, const WindowRows&
         la[j4] = x.x; la[j4 + 1] = x.y; la[j4 + 2] = x.z; la[j4 + 3] = x.w;
       }
       own[c] = log_sum_rows(la, n_win, shift);
-    }
-  }
-  if constexpr (!EXTRAS) {
-    if (len <= THREADS / 4) {
-      if (select_by_rank<THREADS, 4>(own[0], len, keep, lds, lds.list, idx)) return;
-    } else if (len <= kCountedRows && len <= THREADS / 2) {
-      if (select_by_rank<THREADS, 2>(own[0], len, keep, lds, lds.list, idx)) return;
     }
   }
   select_scores<THREADS, kPer, EXTRAS>(own, len, keep, ex, lds, lds.list, idx);
@@ -384,7 +461,7 @@ __device__ __forceinline__ const int32_t* rank_long(const uint16_t* qu, const Wi
         __builtin_amdgcn_sched_barrier(0);
         float m, e;
         score_statistics<2>(far, key0, len, sm_scale, m, e);
-        score_store_logits<2>(far, key0, len, logits_far, kMaxWindow);
+        score_store_logits<2, true>(far, key0, len, logits_far, kMaxWindow);
         join(m, e);
       }
     }
@@ -397,14 +474,13 @@ __device__ __forceinline__ const int32_t* rank_long(const uint16_t* qu, const Wi
   __syncthreads();  // also makes the far logits visible to the whole workgroup
   float shift[kMaxWindow];
   {
-    float vm[4], ve[4], mm = -INFINITY;
+    float vm[4], ve[4];
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
       vm[x] = lds.wave_rowmax[4 * g + x][i];
       ve[x] = lds.wave_rowsum[4 * g + x][i];
-      mm = fmaxf(mm, vm[x]);
     }
-    row_shifts(vm, ve, mm, 4, shift);
+    row_shifts(row_shift<true>(vm, ve, 4), shift);
   }
   auto log_score = [&](const float* lg) -> float {
     float la[kMaxWindow];

@@ -87,8 +87,9 @@ __device__ __forceinline__ void score_statistics(score_f32x4 (&c)[NT], int key0,
   e = xor32_sum(xor16_sum(e));
 }
 
-// The scaled logits of valid keys, key-major: logits[key * stride + row] (global memory or LDS).
-template <int NT>
+// The scaled logits of valid keys, key-major: logits[key * stride + row] (global memory or LDS).  PADDED: there is room
+// for all 16 NT keys, and those at or beyond cache_len are stored as well (eight stores without a branch around each).
+template <int NT, bool PADDED>
 __device__ __forceinline__ void score_store_logits(const score_f32x4 (&c)[NT], int key0, int cache_len, float* logits,
                                                    int stride) {
   const int lane = threadIdx.x & 63, i = lane & 15, g = lane >> 4;
@@ -97,7 +98,7 @@ __device__ __forceinline__ void score_store_logits(const score_f32x4 (&c)[NT], i
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int key = key0 + 16 * t + 4 * g + v;
-      if (key < cache_len) logits[key * stride + i] = c[t][v];
+      if (PADDED || key < cache_len) logits[key * stride + i] = c[t][v];
     }
 }
 
@@ -111,7 +112,7 @@ __device__ __forceinline__ void score_wave_logits(const uint16_t* ku, const scor
   score_load_keys<D, NT>(ku, key0, cache_len, kf);
   score_products<D, NT>(kf, qf, c);
   score_statistics<NT>(c, key0, cache_len, sm_scale, m, e);
-  score_store_logits<NT>(c, key0, cache_len, logits_unit, stride);
+  score_store_logits<NT, false>(c, key0, cache_len, logits_unit, stride);
 }
 
 }  // namespace scalekv

@@ -135,6 +135,17 @@ def test_selection_of_short_caches(S, H, n_cur, L, budget, dup):
 # Streamed selectivity: rounds of 512 keys, lists that overflow and are cut (keys in ascending order of
 # their scores), ties at the threshold, several parts per unit, one and two blocks of 16 rows, history
 # within a round, K' at its limits and beyond (the route through the logits)
+# four lanes to a row up to 128 rows, two up to 256 (1024 threads, as with the 150 units x 300 queries: 256 and 256),
+# then one; windows that leave some of those lanes without a row of their own
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("S,H,n_cur", [(1, 3, 20), (3, 50, 300)])
+@pytest.mark.parametrize("L,budget", [(2, 1), (33, 9), (128, 50), (129, 50), (256, 90), (257, 90), (520, 100)])
+@pytest.mark.parametrize("n_win", [1, 4, 7, 9, 15])
+def test_window_sizes_of_short_rankings(d, S, H, n_cur, L, budget, n_win):
+    print(f"window of a short ranking d={d} S={S} H={H} n_cur={n_cur} L={L} budget={budget} n_win={n_win}", flush=True)
+    _step_against_oracle(S, H, d, L, budget, n_cur, n_win, sorted({0, S * H - 1}), 71 + L + n_win)
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("S,H,n_samp,hist,cur,top_k,kind", [
     (1, 2, 1, 1, 1, 1, "normal"), (1, 2, 16, 0, 40, 64, "normal"), (1, 2, 17, 511, 1, 64, "normal"),
