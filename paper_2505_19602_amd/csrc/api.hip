@@ -165,6 +165,8 @@ ScoreWorkspace score_ws(const WsLayout& w, void* ws) {
   sw.partial = reinterpret_cast<float*>(static_cast<char*>(ws) + w.partial_off);
   sw.len_pad = w.len_pad;
   sw.n_chunk = w.n_chunk;
+  sw.scores = reinterpret_cast<float*>(static_cast<char*>(ws) + w.scores_off);
+  sw.groups = reinterpret_cast<float*>(static_cast<char*>(ws) + w.idx_off);
   return sw;
 }
 
@@ -421,12 +423,19 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
   // cache is written by a launch of its own and attended over.
   const bool map_written = dense_overlap(shape, out, k_cur, n_cur) || dense_overlap(shape, out, v_cur, n_cur);
   const bool src_written = keep > 0 && (dense_overlaps(shape, out, n_cur, k_src) || dense_overlaps(shape, out, n_cur, v_src));
-  const int small_rows = small_tile_rows(shape->dtype, shape->head_dim, U, n_cur, keep + n_cur, step_work(keep, cache_len));
+  const SmallWork work = step_work(keep, cache_len);
+  int small_rows = small_tile_rows(shape->dtype, shape->head_dim, U, n_cur, keep + n_cur, work);
+  const bool spread = ranks && score_select_fits(shape->dtype, shape->head_dim, U, cache_len) &&
+                      rank_spreads(shape->head_dim, U, cache_len, small_rows > 0);
+  if (spread && small_rows > 0)
+    small_rows = small_tile_rows(shape->dtype, shape->head_dim, U, n_cur, keep + n_cur, SmallWork::kRankedBefore);
   const bool pipe = !map_written && shape->dtype == SCALEKV_BF16 && small_rows == 0;
   const bool small = !map_written && !src_written && small_rows > 0;
   // The small kernel ranks as well.  Each of its workgroups reads the window's queries: with out in the place
   // of q the ranking is a launch of its own.
-  const bool one_launch = small && ranks && cache_len <= kShortLen && !dense_overlap(shape, q, out, n_cur);
+  const bool one_launch = small && ranks && !spread && cache_len <= kShortLen && !dense_overlap(shape, q, out, n_cur);
+  const bool one_wg = !spread && score_select_fits(shape->dtype, shape->head_dim, U, cache_len);  // ranks a whole unit
+  const bool prune_first = !small || (!one_wg && small_pruned_before((long long)U * ((n_cur + small_rows - 1) / small_rows)));
   bool pruned = false;           // the ranking kernel has already written the destination caches
   WindowRows rows;
   for (int j = 0; j < kMaxWindow; ++j) rows.row[j] = ranks && j < n_win ? win_idx[j] : 0;
@@ -436,7 +445,6 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
   } else if (ranks) {
     const WsLayout w = ws_layout(shape, cache_len);
     const ScoreWorkspace sw = score_ws(w, ws);
-    float* scores = reinterpret_cast<float*>(static_cast<char*>(ws) + w.scores_off);
     int32_t* idx_ws = idx_out ? idx_out
                               : reinterpret_cast<int32_t*>(static_cast<char*>(ws) + w.idx_off);
     // One launch for the whole ranking where it pays (enough units to fill the chip, or short
@@ -448,28 +456,29 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
     hipError_t one = launch_score_select(shape->dtype, shape->n_seq, shape->n_head, shape->head_dim, q,
                                          (long long)n_cur * shape->head_dim, rows, n_win,
                                          view(k_src), cache_len, resolve_scale(shape), sw, keep,
-                                         idx_ws, nullptr, small ? nullptr : &prune, st);
+                                         idx_ws, nullptr, prune_first ? &prune : nullptr, small, st);
     if (one == hipErrorNotSupported) {
       SCALEKV_HIP(launch_score_logits(shape->dtype, shape->n_seq, shape->n_head, shape->head_dim, q,
                                       (long long)n_cur * shape->head_dim, rows, n_win, view(k_src),
                                       cache_len, resolve_scale(shape), sw, st),
                   "score logits launch");
       SCALEKV_HIP(mark(1), "event record");
-      // the finalisation of the score is fused into the select; long caches take the three-kernel
-      // route through the scores buffer
-      hipError_t fused = launch_select_from_logits(U, n_win, sw, cache_len, keep, idx_ws, nullptr, st);
-      if (fused == hipErrorNotSupported) {
-        SCALEKV_HIP(launch_score_finalize(U, n_win, cache_len, sw, scores, w.len_pad, st),
+      const bool prunes = prune_first && select_prunes(U);
+      hipError_t rest = launch_select_prune(shape->dtype, shape->n_seq, shape->n_head, shape->head_dim, n_win, sw,
+                                            view(k_src), cache_len, keep, idx_ws, nullptr, prunes ? &prune : nullptr, st);
+      if (rest == hipErrorNotSupported) {
+        SCALEKV_HIP(launch_score_finalize(U, n_win, cache_len, sw, sw.scores, w.len_pad, st),
                     "score finalize launch");
-        SCALEKV_HIP(launch_select(U, scores, w.len_pad, cache_len, keep, idx_ws, nullptr, st),
+        SCALEKV_HIP(launch_select(U, sw.scores, w.len_pad, cache_len, keep, idx_ws, nullptr, st),
                     "select launch");
       } else {
-        SCALEKV_HIP(fused, "fused select launch");
+        SCALEKV_HIP(rest, "select + prune launch");
+        pruned = prunes;
       }
     } else {
       SCALEKV_HIP(one, "score + select + prune launch");
       SCALEKV_HIP(mark(1), "event record");   // after the launch: the stages up to the pruning share it
-      pruned = !small;
+      pruned = prune_first;
     }
     idx = idx_ws;
   } else {
@@ -502,7 +511,11 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
     s.q = q; s.n_q = n_cur; s.tile_rows = small_rows; s.out = out;
     s.k = view(k_src); s.v = view(v_src); s.k_cur = k_cur; s.v_cur = v_cur;
     s.len1 = keep; s.len2 = n_cur; s.idx = idx;
-    s.k_dst = view(k_dst); s.v_dst = view(v_dst); s.copy_kept = true;
+    if (pruned) {  // (with the map's rows behind the kept ones)
+      s.k = view(k_dst); s.v = view(v_dst); s.idx = nullptr;
+    } else {
+      s.k_dst = view(k_dst); s.v_dst = view(v_dst); s.copy_kept = true;
+    }
     s.sm_scale = resolve_scale(shape);
     if (one_launch) {
       s.cache_len = cache_len; s.rows = rows; s.n_win = n_win; s.idx_out = idx_out;
@@ -723,26 +736,27 @@ scalekv_status scalekv_step_append_first(const scalekv_shape* shape, const void*
   if (ranks) {
     const WsLayout w = ws_layout(shape, len);
     const ScoreWorkspace sw = score_ws(w, ws);
-    float* scores = reinterpret_cast<float*>(static_cast<char*>(ws) + w.scores_off);
     WindowRows rows;
     for (int j = 0; j < kMaxWindow; ++j) rows.row[j] = j < n_win ? win_idx[j] : 0;
     // (the ranking workgroup also moves its unit's kept rows into the next cache)
     const PruneTarget prune{view(v_cache), view(k_next), view(v_next), nullptr, nullptr, 0};
     hipError_t one = launch_score_select(shape->dtype, shape->n_seq, shape->n_head, d, q, (long long)n_cur * d, rows,
                                          n_win, view(k_cache), len, resolve_scale(shape), sw, keep,
-                                         idx_ws, &ex, &prune, st);
+                                         idx_ws, &ex, &prune, false, st);
     if (one == hipErrorNotSupported) {
       SCALEKV_HIP(launch_score_logits(shape->dtype, shape->n_seq, shape->n_head, d, q,
                                       (long long)n_cur * d, rows, n_win, view(k_cache), len,
                                       resolve_scale(shape), sw, st),
                   "score logits launch");
-      hipError_t fused = launch_select_from_logits(U, n_win, sw, len, keep, idx_ws, &ex, st);
-      if (fused == hipErrorNotSupported) {
-        SCALEKV_HIP(launch_score_finalize(U, n_win, len, sw, scores, w.len_pad, st),
+      hipError_t rest = launch_select_prune(shape->dtype, shape->n_seq, shape->n_head, d, n_win, sw, view(k_cache), len,
+                                            keep, idx_ws, &ex, select_prunes(U) ? &prune : nullptr, st);
+      if (rest == hipErrorNotSupported) {
+        SCALEKV_HIP(launch_score_finalize(U, n_win, len, sw, sw.scores, w.len_pad, st),
                     "score finalize launch");
-        SCALEKV_HIP(launch_select(U, scores, w.len_pad, len, keep, idx_ws, &ex, st), "select launch");
+        SCALEKV_HIP(launch_select(U, sw.scores, w.len_pad, len, keep, idx_ws, &ex, st), "select launch");
       } else {
-        SCALEKV_HIP(fused, "fused select launch");
+        SCALEKV_HIP(rest, "select + prune launch");
+        pruned = select_prunes(U);
       }
     } else {
       SCALEKV_HIP(one, "score + select + prune launch");

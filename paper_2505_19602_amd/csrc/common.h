@@ -28,6 +28,8 @@ struct ScoreWorkspace {
   float* partial;   // [U][n_chunk][2][kMaxWindow]  (row max, row sum of exp(logit - max))
   int len_pad;
   int n_chunk;
+  float* scores;    // [U][len_pad]  log-scores
+  float* groups;    // [U][len_pad / 32][2][kMaxWindow]  as `partial`, of 32 keys; where the index list is written later
 };
 
 // Optional parts of the selection (Sec. 3.3): positions preserved whatever their score
@@ -68,12 +70,6 @@ hipError_t launch_score_finalize(int n_unit, int n_win, int cache_len, ScoreWork
 hipError_t launch_select(int n_unit, const float* scores, long long score_unit_stride,
                          int cache_len, int keep, int32_t* idx, const SelectExtras* extras,
                          hipStream_t stream);
-// select straight from the logits workspace (score finalisation fused in); returns
-// hipErrorNotSupported for units of more than 2048 rows: one workgroup takes 4 us per 1024 rows for the
-// finalisation, as long as a launch of its own that spreads it over the chip
-hipError_t launch_select_from_logits(int n_unit, int n_win, ScoreWorkspace ws, int cache_len,
-                                     int keep, int32_t* idx, const SelectExtras* extras,
-                                     hipStream_t stream);
 // The whole ranking step in one launch (bf16 only): one workgroup per unit forms the logits of
 // the window rows against the unit's cached keys, the row normalisers and the log-scores
 // (Eq. 5) and selects.  Returns hipErrorNotSupported where score_select_fits() says no (and for fp32 or
@@ -84,12 +80,48 @@ hipError_t launch_select_from_logits(int n_unit, int n_win, ScoreWorkspace ws, i
 //   64 x 600: 34.8 / 36.1   64 x 1600: 52.9 / 47.3   64 x 4096: 97 / 76   64 x 6400: 153 / 106   64 x 12000: 270 / 173
 //   128 x 1600: 64.8 / 70.0   128 x 4096: 126 / 124   128 x 6400: 190 / 173     256 x 600: 65 / 75   256 x 4096: 188 / 222
 //   256 x 12000: 527 / 574    d 64: 60 x 1600: 36.6 / 37.2   60 x 4096: 62 / 53   128 x 4096: 79 / 83   256 x 12000: 292 / 338
-// The line is an old one and does not lie where the two cross: up to about 128 units the several launches are as fast
-// from about 1600 rows on, and with few units much faster.
+// Inside this line rank_spreads() says how the one ranking is launched; the several launches outside of it round the row
+// normalisers by chunks of 256 keys, so that rows at the border of a selection may differ in the last bit of their score.
 inline bool score_select_fits(int dtype, int d, int n_unit, int cache_len) {
   return dtype == 1 && (d == 64 || d == 128) && cache_len <= 12288 && (n_unit >= 64 || cache_len <= 4096);
 }
-// With `prune` the same workgroup then also prunes its unit (Sec. 3.3): source row idx[t] of k
+// Whether the ranking of a unit is spread over workgroups (three launches instead of one, the same rows bit for bit),
+// where score_select_fits().  `small`: the attention goes to the kernel for small work, which ranks up to kShortLen rows in
+// its own launch, and prunes.  Whole steps that keep a quarter, us, a workgroup per unit / spread:
+//   300 queries, d 128: 8 units x 600: 21.4 / 21.5   8 x 800: 24.8 / 22.9   8 x 1600: 36.5 / 26.7   8 x 4096: 65.6 / 35.9
+//     32 x 800: 33.9 / 32.4   32 x 1600: 47.3 / 40.3   64 x 800: 39.8 / 36.1   64 x 1600: 53.9 / 45.9   64 x 10000: 235 / 151
+//     96 x 1000: 48.5 / 47.0   96 x 1600: 61.9 / 58.7   96 x 4096: 115.5 / 102.8   128 x 1600: 64.8 / 66.2   128 x 4096: 118.4 / 119.9
+//     128 x 6000: 180 / 166   192 x 6000: 240 / 255
+//   d 64: 8 x 1000: 18.9 / 19.3   32 x 1000: 24.7 / 25.2   32 x 1600: 32.7 / 29.4   64 x 1600: 39.2 / 36.2   96 x 1600: 44.5 / 44.7
+//     96 x 4096: 77.4 / 76.8   96 x 6000: 112.8 / 102.6
+//   small, units, queries, rows, d 128: 16, 8, 600: 17.8 / 18.3   16, 8, 800: 21.4 / 19.1   16, 256, 900: 26.2 / 25.4
+//     32, 100, 900: 25.1 / 25.5   32, 448, 900: 39.1 / 41.6   32, 448, 1200: 43.8 / 43.7   32, 80, 1200: 28.0 / 25.4
+//     48, 80, 1200: 29.1 / 29.5   64, 64, 1536: 34.7 / 34.9   64, 64, 2000: 49.6 / 40.7   32, 256, 4096: 79.8 / 55.2
+//     96, 20, 2000: 47.5 / 47.0   128, 16, 2000: 48.4 / 53.3
+//     d 64: 8, 8, 1000: 17.6 / 18.2   16, 256, 1400: 23.9 / 21.9   24, 160, 1400: 23.6 / 22.9   32, 128, 1400: 23.7 / 24.6
+//     64, 32, 3000: 40.8 / 37.6   96, 32, 3000: 42.2 / 44.1
+inline bool rank_spreads(int d, int n_unit, int cache_len, bool small) {
+  if (small && cache_len <= kShortLen)
+    return d == 128 ? n_unit <= (cache_len >= 1000 ? 32 : 16) && cache_len >= 800 : n_unit <= 24 && cache_len >= 1300;
+  if (small || n_unit <= 64) return n_unit <= 64 && cache_len >= (d == 128 ? 800 : 1300);
+  return d == 128 ? n_unit <= (cache_len <= 4096 ? 96 : 128) && cache_len > kShortLen : n_unit <= 96 && cache_len > 4096;
+}
+// Where the ranking is spread, whether the kernel for small work leaves the pruning to it: its own copying workgroups come
+// behind the n_wg attending ones, and wait for a round of their own where those (nearly) fill the compute units.
+// us, pruned by the small kernel / before (n_wg, d 128): 32 units, 80 queries, 1200 rows (160)
+// 25.4 / 26.9; 48, 40, 2000 (144) 35.0 / 35.8; 48, 64, 2000 (192) 38.7 / 36.6; 32, 100, 1200 (224) 32.2 / 29.4;
+// 64, 64, 1536 (256) 37.7 / 34.9; 16, 256, 4096 (256) 46.5 / 41.9.
+inline bool small_pruned_before(long long n_wg) { return n_wg > 160; }
+// Whether selection and pruning share a launch behind launch_score_logits: a workgroup per unit, or several where there are
+// fewer units than compute units.  Up to 256 units; more are not served in one round (fp32 steps, us, two launches / one:
+// 32 units x 585 rows 69.7 / 64.5, 128 x 200 31.9 / 28.1, 256 x 1200 148 / 144, 300 x 1200 185 / 197).
+inline bool select_prunes(int n_unit) { return n_unit <= 256; }
+// The workgroups of a unit that do so: as many as the compute units take at once, and at least 64 rows to each.
+inline int select_parts(int n_unit, int rows) {
+  const int most = n_unit < 256 ? 256 / n_unit : 1, full = (rows + 63) / 64;
+  return most < full ? most : full > 1 ? full : 1;
+}
+// With `prune` the same launch then also prunes (Sec. 3.3): source row idx[t] of k
 // (keys) / prune->v_src (values) goes to row t of the destination caches, and the n_app rows of
 // k_cur / v_cur ([U, n_app, d], NULL: none) are appended behind the keep rows.
 struct PruneTarget {
@@ -101,7 +133,13 @@ struct PruneTarget {
 hipError_t launch_score_select(int dtype, int n_seq, int n_head, int d, const void* q, long long q_unit_stride,
                                WindowRows rows, int n_win, KvView k, int cache_len, float sm_scale,
                                ScoreWorkspace ws, int keep, int32_t* idx, const SelectExtras* extras,
-                               const PruneTarget* prune, hipStream_t stream);
+                               const PruneTarget* prune, bool small, hipStream_t stream);
+// What follows launch_score_logits: log-scores, selection and, with `prune`, the pruning in the same launch as
+// the selection.  hipErrorNotSupported beyond 12288 rows.  Up to 2048 rows the selection forms the log-scores itself: one
+// workgroup takes 4 us per 1024 rows for it, as long as a launch of its own that spreads it over the chip.
+hipError_t launch_select_prune(int dtype, int n_seq, int n_head, int d, int n_win, ScoreWorkspace ws, KvView k,
+                               int cache_len, int keep, int32_t* idx, const SelectExtras* extras, const PruneTarget* prune,
+                               hipStream_t stream);
 // first n_sink and last keep - n_sink positions of every unit (n_sink <= keep <= cache_len)
 hipError_t launch_positional(int n_unit, int cache_len, int n_sink, int keep, int32_t* idx,
                              hipStream_t stream);

@@ -50,12 +50,13 @@ struct ScoreInputs {
   bool past_caches;         // rows_go_past_caches()
 };
 
-// Pruning of one unit by one workgroup: the kept rows (and, if asked, the map's rows behind them)
+// Pruning of one unit by one workgroup, or by `parts` of them: the kept rows (and, if asked, the map's rows behind them)
 // into the destination.
-template <int D, int THREADS>
-__device__ __forceinline__ void prune_unit(const ScoreInputs& si, int unit, int keep, const int32_t* list) {
+// vec_log2: 16-byte vectors per row.
+template <int THREADS>
+__device__ __forceinline__ void prune_unit(const ScoreInputs& si, int unit, int keep, const int32_t* list, int vec_log2,
+                                           int part = 0, int parts = 1) {
   typedef unsigned int vec4 __attribute__((ext_vector_type(4)));
-  constexpr int VPR = D * 2 / 16;  // 16-byte vectors per row
   constexpr int kFly = 4;          // vectors in flight per thread and tensor
   const int tid = threadIdx.x;
   const int seq = unit / si.n_head, head = unit - seq * si.n_head;
@@ -63,24 +64,25 @@ __device__ __forceinline__ void prune_unit(const ScoreInputs& si, int unit, int 
   const vec4* vsrc = (const vec4*)(si.v_src + seq * si.v_seq_stride + head * si.v_head_stride);
   vec4* kdst = (vec4*)(si.k_dst + seq * si.kd_seq_stride + head * si.kd_head_stride);
   vec4* vdst = (vec4*)(si.v_dst + seq * si.vd_seq_stride + head * si.vd_head_stride);
-  const vec4* kcur = (const vec4*)(si.k_cur + (long long)unit * si.n_app * D);
-  const vec4* vcur = (const vec4*)(si.v_cur + (long long)unit * si.n_app * D);
-  const int total = (keep + si.n_app) * VPR;
+  const vec4* kcur = (const vec4*)si.k_cur + ((long long)unit * si.n_app << vec_log2);
+  const vec4* vcur = (const vec4*)si.v_cur + ((long long)unit * si.n_app << vec_log2);
+  const int share = (keep + si.n_app + parts - 1) / parts << vec_log2;
+  const int first = part * share, total = min((keep + si.n_app) << vec_log2, first + share);
   // (the attention reads the kept rows next: plain stores, which may leave them in the caches, unless they are too many.
   // 256 units, 246 of 546 rows, 576 queries, the whole step: 110.8 us with streaming stores, 107.2 so.  Two loops: of
   // two kinds of store in one the compiler makes plain ones.)
   auto copy = [&](auto past) __attribute__((always_inline)) {
 #pragma unroll 1
-    for (int f0 = tid; f0 < total; f0 += THREADS * kFly) {
+    for (int f0 = first + tid; f0 < total; f0 += THREADS * kFly) {
       vec4 a[kFly], b[kFly];
 #pragma unroll
       for (int u = 0; u < kFly; ++u) {
         // (lanes past the end re-read the last vector and store nothing: a branch around the loads
         // costs the kernel 30 registers)
         const int f = min(f0 + u * THREADS, total - 1);
-        const int row = f / VPR, c = f % VPR;
+        const int row = f >> vec_log2, c = f & ((1 << vec_log2) - 1);
         const bool kept = row < keep;
-        const long long o = (long long)(kept ? list[row] : row - keep) * VPR + c;
+        const long long o = ((long long)(kept ? list[row] : row - keep) << vec_log2) + c;
         a[u] = __builtin_nontemporal_load((kept ? ksrc : kcur) + o);
         b[u] = __builtin_nontemporal_load((kept ? vsrc : vcur) + o);
       }
@@ -169,7 +171,7 @@ __global__ __launch_bounds__(THREADS) void rank_short_kernel(int cache_len, int 
   rank_short<D, THREADS, EXTRAS>(si.q + unit * si.q_unit_stride, si.rows, n_win,
                                  si.k + seq * si.k_seq_stride + head * si.k_head_stride, cache_len, keep, si.sm_scale,
                                  ex, short_logits, lds, idx + (long long)unit * keep);
-  if (si.k_dst != nullptr) prune_unit<D, THREADS>(si, unit, keep, lds.list);
+  if (si.k_dst != nullptr) prune_unit<THREADS>(si, unit, keep, lds.list, D == 128 ? 4 : 3);
 }
 
 // The same for longer ones.  256 units, 3350 cached rows, 1622 kept: 138 us, 148 with every logit through
@@ -186,7 +188,79 @@ __global__ __launch_bounds__(1024) void rank_long_kernel(int cache_len, int keep
       si.q + unit * si.q_unit_stride, si.rows, n_win, si.k + seq * si.k_seq_stride + head * si.k_head_stride, cache_len,
       keep, si.sm_scale, ex, long_turn, ws.logits + (long long)unit * ws.len_pad * kMaxWindow, lds,
       idx + (long long)unit * keep);
-  if (si.k_dst != nullptr) prune_unit<D, 1024>(si, unit, keep, list);
+  if (si.k_dst != nullptr) prune_unit<1024>(si, unit, keep, list, D == 128 ? 4 : 3);
+}
+
+// ---- the ranking of a unit spread over workgroups, in three launches: logits, log-scores, selection and pruning.  Where
+// there are few units, one workgroup to a unit leaves most of the chip idle: it forms the unit's logits, 16 exponentials
+// twice for each key, and copies the kept rows, all through one compute unit.
+// Normalisers and log-scores round as they do in rank_short (up to kShortLen rows) and rank_long: groups of 32 keys,
+// merged in the order of those, so that the same rows are selected bit for bit.
+// Bound by three launches and the chains in them: 16 units x 4096 rows, a quarter kept, d 128: 6.6 + 5.1 + 10.2 us, 47.7 by
+// a workgroup per unit; 60 x 1733, d 64: 6.7 + 5.5 + 11.1, 26.0.  The log-scores formed by the workgroups that select, which
+// saves a launch, is as fast up to 1000 rows and slower beyond (8 units x 2000 rows, whole step 27.4 / 29.5).
+constexpr int kSpreadThreads = 256;
+constexpr int kSpreadKeys = kSpreadThreads / 64 * 32;  // per workgroup of the first kernel
+
+// Logits of 32 keys a wave, and their maximum and sum of exponentials for every window row.
+template <int D>
+__global__ __launch_bounds__(kSpreadThreads) void spread_logits_kernel(int cache_len, int n_win, ScoreInputs si,
+                                                                       ScoreWorkspace ws) {
+  const int unit = SCALEKV_WG_Y, lane = threadIdx.x & 63;
+  const int group = SCALEKV_WG_X * (kSpreadThreads / 64) + (threadIdx.x >> 6);
+  if (32 * group >= cache_len) return;
+  const int seq = unit / si.n_head, head = unit - seq * si.n_head;
+  score_bf16x8 qf[D / 32], kf[2][D / 32];
+  score_load_keys<D, 2>(si.k + seq * si.k_seq_stride + head * si.k_head_stride, 32 * group, cache_len, kf);
+  score_load_window<D>(si.q + unit * si.q_unit_stride, si.rows, n_win, qf);
+  score_f32x4 c[2];
+  float m, e;
+  score_products<D, 2>(kf, qf, c);
+  score_statistics<2>(c, 32 * group, cache_len, si.sm_scale, m, e);
+  score_store_logits<2, true>(c, 32 * group, cache_len, ws.logits + (long long)unit * ws.len_pad * kMaxWindow, kMaxWindow);
+  float* const stat = ws.groups + (long long)unit * ws.len_pad + group * (2 * kMaxWindow);
+  if (lane < 2 * kMaxWindow) stat[lane] = lane < kMaxWindow ? m : e;  // (every lane l holds those of row l % 16)
+}
+
+// Log-scores of kSpreadThreads keys.
+__global__ __launch_bounds__(kSpreadThreads) void spread_scores_kernel(int cache_len, int n_win, ScoreWorkspace ws) {
+  static_assert(kSpreadThreads == kVirtualWaves * kMaxWindow, "a thread merges the groups of a virtual wave and row");
+  __shared__ float wave_max[kVirtualWaves][kMaxWindow], wave_sum[kVirtualWaves][kMaxWindow];
+  const int unit = SCALEKV_WG_Y, tid = threadIdx.x, i = tid & 15, g = (tid & 63) >> 4, first = tid / kMaxWindow;
+  const int key = SCALEKV_WG_X * kSpreadThreads + tid, n_group = (cache_len + 31) / 32;
+  const float* const lg = ws.logits + ((long long)unit * ws.len_pad + min(key, cache_len - 1)) * kMaxWindow;
+  float la[kMaxWindow];  // (requested in front of the statistics)
+#pragma unroll
+  for (int j4 = 0; j4 < kMaxWindow; j4 += 4) {
+    const float4 x = *(const float4*)(lg + j4);
+    la[j4] = x.x; la[j4 + 1] = x.y; la[j4 + 2] = x.z; la[j4 + 3] = x.w;
+  }
+  const float* const stat = ws.groups + (long long)unit * ws.len_pad + i;
+  float m_run = -INFINITY, e_run = 0.f;
+  if (first < n_group) {
+    m_run = stat[first * (2 * kMaxWindow)];
+    e_run = stat[first * (2 * kMaxWindow) + kMaxWindow];
+  }
+#pragma unroll 4
+  for (int group = first + kVirtualWaves; group < n_group; group += kVirtualWaves) {
+    const float m = stat[group * (2 * kMaxWindow)], e = stat[group * (2 * kMaxWindow) + kMaxWindow];
+    const float m_new = fmaxf(m_run, m);
+    e_run = e_run * expf(m_run - m_new) + e * expf(m - m_new);
+    m_run = m_new;
+  }
+  wave_max[first][i] = m_run;
+  wave_sum[first][i] = e_run;
+  __syncthreads();
+  float vm[4], ve[4], shift[kMaxWindow];
+#pragma unroll
+  for (int x = 0; x < 4; ++x) {
+    vm[x] = wave_max[4 * g + x][i];
+    ve[x] = wave_sum[4 * g + x][i];
+  }
+  const int turns = (min(n_group, kVirtualWaves) + 3) / 4;
+  row_shifts(cache_len <= kShortLen ? row_shift<false>(vm, ve, turns) : row_shift<true>(vm, ve, turns), shift);
+  const float score = log_sum_rows(la, n_win, shift);
+  if (key < cache_len) ws.scores[(long long)unit * ws.len_pad + key] = score;
 }
 
 template <int D, int PER, bool EXTRAS>
@@ -212,8 +286,10 @@ hipError_t launch_short(int n_unit, int cache_len, int keep, int32_t* idx, int n
   return hipGetLastError();
 }
 
-// Selection alone, for units whose keys fit in LDS (PER rows per thread): from scores, or
-// (FROM_LOGITS) from the logits and chunk statistics of the workspace, log-scores formed here.
+// Selection for units whose keys fit in LDS (PER rows per thread): from scores, or (FROM_LOGITS) from the logits and
+// chunk statistics of the workspace, log-scores formed here; and, if si.k_dst is there, the pruning by the same launch.
+// Every one of a unit's `parts` workgroups selects, the first writes the index list, and each copies its share
+// of the rows.
 template <int PER>
 struct SelectLds {
   __attribute__((aligned(16))) uint32_t hist[4 * 256];
@@ -221,13 +297,16 @@ struct SelectLds {
   uint32_t wave_max[kWaves], wave_min[kWaves];
   uint32_t count[PER * 2 * kWaves];  // as in RankShortLds
 };
-template <int PER, bool FROM_LOGITS>
+template <int PER, bool FROM_LOGITS, bool COPIES>
 __global__ __launch_bounds__(kThreads) void select_lds_kernel(const float* __restrict__ scores, long long score_unit_stride,
                                                               int cache_len, int keep, int32_t* __restrict__ idx,
-                                                              ScoreWorkspace ws, int n_win, SelectExtras ex) {
+                                                              ScoreWorkspace ws, int n_win, SelectExtras ex, ScoreInputs si,
+                                                              int vec_log2, int parts) {
+  extern __shared__ __attribute__((aligned(16))) int32_t select_list[];  // [keep], where rows are copied
   __shared__ SelectLds<PER> lds;
   __shared__ float row_shift[kMaxWindow], stage[FROM_LOGITS ? kStatChunks * 2 * kMaxWindow : 1];
-  const int unit = SCALEKV_WG_X, tid = threadIdx.x;
+  const int wg = xcd_order(SCALEKV_WG_X, gridDim.x);  // (what the workgroups of a unit read meets in one L2)
+  const int unit = wg / parts, part = wg - unit * parts, tid = threadIdx.x;
   lds.hist[tid] = 0;
   if constexpr (FROM_LOGITS) score_row_shifts(ws, unit, n_win, stage, row_shift);
   float own[PER];
@@ -239,26 +318,66 @@ __global__ __launch_bounds__(kThreads) void select_lds_kernel(const float* __res
       else own[c] = scores[unit * score_unit_stride + key];
     }
   }
-  select_scores<kThreads, PER, true>(own, cache_len, keep, ex, lds, nullptr, idx + (long long)unit * keep);
+  if constexpr (COPIES)
+    select_scores<kThreads, PER, true>(own, cache_len, keep, ex, lds, select_list,
+                                       part == 0 ? idx + (long long)unit * keep : nullptr);
+  else
+    select_scores<kThreads, PER, true>(own, cache_len, keep, ex, lds, nullptr, idx + (long long)unit * keep);
+  if constexpr (COPIES) prune_unit<kThreads>(si, unit, keep, select_list, vec_log2, part, parts);
 }
 
-template <bool FROM_LOGITS>
+template <bool FROM_LOGITS, bool COPIES>
 hipError_t launch_select_lds(int n_unit, const float* scores, long long score_unit_stride, int cache_len, int keep,
-                             int32_t* idx, ScoreWorkspace ws, int n_win, const SelectExtras& ex, hipStream_t stream) {
-#define SCALEKV_SELECT(PER)                                                                                      \
-  hipLaunchKernelGGL((select_lds_kernel<PER, FROM_LOGITS>), dim3(n_unit), dim3(kThreads), 0, stream, scores,     \
-                     score_unit_stride, cache_len, keep, idx, ws, n_win, ex)
+                             int32_t* idx, ScoreWorkspace ws, int n_win, const SelectExtras& ex, const ScoreInputs& si,
+                             int vec_log2, hipStream_t stream) {
+  const int parts = COPIES ? select_parts(n_unit, keep + si.n_app) : 1;
+#define SCALEKV_SELECT(PER)                                                                                              \
+  do {                                                                                                                   \
+    static std::atomic<uint64_t> configured{0}; /* LDS above 64 KB per workgroup has to be asked for */                  \
+    const hipError_t e = !COPIES ? hipSuccess                                                                            \
+                                 : allow_dynamic_lds((const void*)select_lds_kernel<PER, FROM_LOGITS, COPIES>,           \
+                                                     PER * kThreads * 4, configured);                                    \
+    if (e != hipSuccess) return e;                                                                                       \
+    hipLaunchKernelGGL((select_lds_kernel<PER, FROM_LOGITS, COPIES>), dim3(n_unit * parts), dim3(kThreads),              \
+                       COPIES ? keep * 4 : 0, stream, scores, score_unit_stride, cache_len, keep, idx, ws, n_win, ex,    \
+                       si, vec_log2, parts);                                                                             \
+  } while (0)
   if (cache_len <= kThreads) SCALEKV_SELECT(1);
   else if (cache_len <= 2 * kThreads) SCALEKV_SELECT(2);
   else if constexpr (!FROM_LOGITS) {
     if (cache_len <= 4 * kThreads) SCALEKV_SELECT(4);
     else if (cache_len <= 8 * kThreads) SCALEKV_SELECT(8);
     else SCALEKV_SELECT(kLdsKeys / kThreads);
-  } else {
-    return hipErrorNotSupported;
   }
 #undef SCALEKV_SELECT
   return hipGetLastError();
+}
+
+bool plain(const SelectExtras& ex) { return ex.n_forced == 0 && ex.pool_w == 1; }
+
+// The part of ScoreInputs that says what is copied.  Rows are counted in elements of two bytes.
+void set_prune(ScoreInputs& si, const PruneTarget& p, KvView k, int n_unit, int n_head, int keep, int row_bytes, int elem,
+               CacheWriter by) {
+  const int x = elem / 2;
+  si.n_head = n_head;
+  si.k = (const uint16_t*)k.ptr; si.k_seq_stride = k.seq_stride * x; si.k_head_stride = k.head_stride * x;
+  si.v_src = (const uint16_t*)p.v_src.ptr;
+  si.v_seq_stride = p.v_src.seq_stride * x; si.v_head_stride = p.v_src.head_stride * x;
+  si.k_dst = (uint16_t*)const_cast<void*>(p.k_dst.ptr); si.v_dst = (uint16_t*)const_cast<void*>(p.v_dst.ptr);
+  si.kd_seq_stride = p.k_dst.seq_stride * x; si.kd_head_stride = p.k_dst.head_stride * x;
+  si.vd_seq_stride = p.v_dst.seq_stride * x; si.vd_head_stride = p.v_dst.head_stride * x;
+  si.k_cur = (const uint16_t*)p.k_cur; si.v_cur = (const uint16_t*)p.v_cur;
+  si.n_app = p.k_cur ? p.n_app : 0;
+  si.past_caches = rows_go_past_caches(by, n_unit, keep + si.n_app, row_bytes);
+}
+int log2_of(int x) { return 31 - __builtin_clz(x); }
+// Selection from ws.scores, and the pruning if `si` says so.
+hipError_t select_from_scores(int n_unit, int cache_len, int keep, int32_t* idx, ScoreWorkspace ws, const SelectExtras& ex,
+                              const ScoreInputs& si, int vec_log2, hipStream_t stream) {
+  return si.k_dst ? launch_select_lds<false, true>(n_unit, ws.scores, ws.len_pad, cache_len, keep, idx, ws, 0, ex, si,
+                                                   vec_log2, stream)
+                  : launch_select_lds<false, false>(n_unit, ws.scores, ws.len_pad, cache_len, keep, idx, ws, 0, ex, si,
+                                                    vec_log2, stream);
 }
 
 __global__ void iota_kernel(int32_t* __restrict__ idx, int keep, long long total) {
@@ -301,28 +420,39 @@ hipError_t launch_select(int n_unit, const float* scores, long long score_unit_s
                        idx, keep, total);
     return hipGetLastError();
   }
-  const ScoreWorkspace none{nullptr, nullptr, 0, 0};
   if (cache_len <= kLdsKeys)
-    return launch_select_lds<false>(n_unit, scores, score_unit_stride, cache_len, keep, idx, none, 0, ex, stream);
+    return launch_select_lds<false, false>(n_unit, scores, score_unit_stride, cache_len, keep, idx, ScoreWorkspace{}, 0, ex,
+                                          ScoreInputs{}, 0, stream);
   hipLaunchKernelGGL(select_far_kernel, dim3(n_unit), dim3(kThreads), 0, stream, scores, score_unit_stride,
                      cache_len, keep, idx, ex);
   return hipGetLastError();
 }
 
-hipError_t launch_select_from_logits(int n_unit, int n_win, ScoreWorkspace ws, int cache_len,
-                                     int keep, int32_t* idx, const SelectExtras* extras,
-                                     hipStream_t stream) {
+hipError_t launch_select_prune(int dtype, int n_seq, int n_head, int d, int n_win, ScoreWorkspace ws, KvView k,
+                               int cache_len, int keep, int32_t* idx, const SelectExtras* extras, const PruneTarget* prune,
+                               hipStream_t stream) {
   SelectExtras ex{};
   ex.pool_w = 1;
   if (extras) ex = *extras;
+  const int n_unit = n_seq * n_head;
+  if (cache_len > kLdsKeys) return hipErrorNotSupported;
   if (n_unit <= 0 || keep <= 0 || cache_len <= 0) return hipSuccess;
-  return launch_select_lds<true>(n_unit, nullptr, 0, cache_len, keep, idx, ws, n_win, ex, stream);
+  const int elem = dtype == 0 ? 4 : 2, vec_log2 = log2_of(d * elem / 16);
+  ScoreInputs si{};
+  if (prune) set_prune(si, *prune, k, n_unit, n_head, keep, d * elem, elem, CacheWriter::kCompact);
+  if (cache_len <= 2 * kThreads)
+    return si.k_dst
+        ? launch_select_lds<true, true>(n_unit, nullptr, 0, cache_len, keep, idx, ws, n_win, ex, si, vec_log2, stream)
+        : launch_select_lds<true, false>(n_unit, nullptr, 0, cache_len, keep, idx, ws, n_win, ex, si, vec_log2, stream);
+  const hipError_t e = launch_score_finalize(n_unit, n_win, cache_len, ws, ws.scores, ws.len_pad, stream);
+  if (e != hipSuccess) return e;
+  return select_from_scores(n_unit, cache_len, keep, idx, ws, ex, si, vec_log2, stream);
 }
 
 hipError_t launch_score_select(int dtype, int n_seq, int n_head, int d, const void* q, long long q_unit_stride,
                                WindowRows rows, int n_win, KvView k, int cache_len, float sm_scale,
                                ScoreWorkspace ws, int keep, int32_t* idx, const SelectExtras* extras,
-                               const PruneTarget* prune, hipStream_t stream) {
+                               const PruneTarget* prune, bool small, hipStream_t stream) {
   SelectExtras ex{};
   ex.pool_w = 1;
   if (extras) ex = *extras;
@@ -333,23 +463,24 @@ hipError_t launch_score_select(int dtype, int n_seq, int n_head, int d, const vo
   si.q = (const uint16_t*)q; si.q_unit_stride = q_unit_stride; si.rows = rows;
   si.k = (const uint16_t*)k.ptr; si.k_seq_stride = k.seq_stride; si.k_head_stride = k.head_stride;
   si.n_head = n_head; si.sm_scale = sm_scale;
-  if (prune) {
-    si.v_src = (const uint16_t*)prune->v_src.ptr;
-    si.v_seq_stride = prune->v_src.seq_stride; si.v_head_stride = prune->v_src.head_stride;
-    si.k_dst = (uint16_t*)const_cast<void*>(prune->k_dst.ptr); si.v_dst = (uint16_t*)const_cast<void*>(prune->v_dst.ptr);
-    si.kd_seq_stride = prune->k_dst.seq_stride; si.kd_head_stride = prune->k_dst.head_stride;
-    si.vd_seq_stride = prune->v_dst.seq_stride; si.vd_head_stride = prune->v_dst.head_stride;
-    si.k_cur = (const uint16_t*)prune->k_cur; si.v_cur = (const uint16_t*)prune->v_cur;
-    si.n_app = prune->k_cur ? prune->n_app : 0;
-    si.past_caches = rows_go_past_caches(CacheWriter::kRanking, n_unit, keep + si.n_app, d * 2);
-  }
   constexpr int kComputeUnits = 256;  // MI355X
-  const bool plain = ex.n_forced == 0 && ex.pool_w == 1;
+  if (rank_spreads(d, n_unit, cache_len, small)) {
+    if (prune) set_prune(si, *prune, k, n_unit, n_head, keep, d * 2, 2, CacheWriter::kRanking);
+    const dim3 logit_grid((cache_len + kSpreadKeys - 1) / kSpreadKeys, n_unit);
+    if (d == 128)
+      hipLaunchKernelGGL(spread_logits_kernel<128>, logit_grid, dim3(kSpreadThreads), 0, stream, cache_len, n_win, si, ws);
+    else
+      hipLaunchKernelGGL(spread_logits_kernel<64>, logit_grid, dim3(kSpreadThreads), 0, stream, cache_len, n_win, si, ws);
+    hipLaunchKernelGGL(spread_scores_kernel, dim3((cache_len + kSpreadThreads - 1) / kSpreadThreads, n_unit),
+                       dim3(kSpreadThreads), 0, stream, cache_len, n_win, ws);
+    return select_from_scores(n_unit, cache_len, keep, idx, ws, ex, si, log2_of(d / 8), stream);
+  }
+  if (prune) set_prune(si, *prune, k, n_unit, n_head, keep, d * 2, 2, CacheWriter::kRanking);
   if (cache_len <= kShortLen) {
 #define SCALEKV_SHORT(T)                                                                             \
-  (d == 128 ? plain ? launch_short<128, T, false>(n_unit, cache_len, keep, idx, n_win, ex, si, stream) \
+  (d == 128 ? plain(ex) ? launch_short<128, T, false>(n_unit, cache_len, keep, idx, n_win, ex, si, stream) \
                     : launch_short<128, T, true>(n_unit, cache_len, keep, idx, n_win, ex, si, stream)  \
-   : plain ? launch_short<64, T, false>(n_unit, cache_len, keep, idx, n_win, ex, si, stream)           \
+   : plain(ex) ? launch_short<64, T, false>(n_unit, cache_len, keep, idx, n_win, ex, si, stream)           \
            : launch_short<64, T, true>(n_unit, cache_len, keep, idx, n_win, ex, si, stream))
     // More units than compute units: 512 threads, of which two workgroups share a compute unit up to about 736 rows
     // (23 KB of LDS and 80 bytes a row of 160 KB), and which wait for fewer waves at each barrier beyond.
@@ -359,7 +490,7 @@ hipError_t launch_score_select(int dtype, int n_seq, int n_head, int d, const vo
 #undef SCALEKV_SHORT
   }
 #define SCALEKV_LONG(D, PER)                                                                           \
-  (plain ? launch_long<D, PER, false>(n_unit, cache_len, keep, idx, n_win, ex, si, ws, stream)       \
+  (plain(ex) ? launch_long<D, PER, false>(n_unit, cache_len, keep, idx, n_win, ex, si, ws, stream)       \
          : launch_long<D, PER, true>(n_unit, cache_len, keep, idx, n_win, ex, si, ws, stream))
   if (cache_len <= kLongInRegisters) return d == 128 ? SCALEKV_LONG(128, 4) : SCALEKV_LONG(64, 4);
   return d == 128 ? SCALEKV_LONG(128, kLongMaxPer) : SCALEKV_LONG(64, kLongMaxPer);

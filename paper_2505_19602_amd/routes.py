@@ -64,14 +64,37 @@ def step_work(keep: int, cache_len: int) -> int:
     return KEEP_ALL if keep else APPEND
 
 
+def rank_spreads(d: int, units: int, cache_len: int, small: bool) -> bool:
+    """Whether several workgroups rank a unit, where ranks_in_one_launch(); small: its attention is in the kernel for
+    small work."""
+    if small and cache_len <= SHORT_LEN:
+        return units <= (32 if cache_len >= 1000 else 16) and cache_len >= 800 if d == 128 else units <= 24 and cache_len >= 1300
+    if small or units <= 64:
+        return units <= 64 and cache_len >= (800 if d == 128 else 1300)
+    return units <= (96 if cache_len <= 4096 else 128) and cache_len > SHORT_LEN if d == 128 else \
+        units <= 96 and cache_len > 4096
+
+
+def step_spreads(dtype: torch.dtype, d: int, units: int, n_cur: int, cache_len: int, budget: int) -> bool:
+    """Whether scalekv_step ranks a unit by several workgroups."""
+    keep = min(budget, cache_len)
+    small = small_tile_rows(dtype, d, units, n_cur, keep + n_cur, step_work(keep, cache_len)) > 0
+    return 0 < keep < cache_len and ranks_in_one_launch(dtype, units, cache_len) and rank_spreads(d, units, cache_len, small)
+
+
 def step_kernel(dtype: torch.dtype, d: int, units: int, n_cur: int, cache_len: int, budget: int) -> str:
     """The same for the attention of scalekv_step; "small" prunes and appends in the same launch."""
     keep = min(budget, cache_len)
-    return attend_kernel(dtype, d, units, n_cur, keep + n_cur, step_work(keep, cache_len))
+    work = step_work(keep, cache_len)
+    if work == RANKED and step_spreads(dtype, d, units, n_cur, cache_len, budget) and \
+            small_tile_rows(dtype, d, units, n_cur, keep + n_cur, work):
+        work = RANKED_BEFORE
+    return attend_kernel(dtype, d, units, n_cur, keep + n_cur, work)
 
 
 def ranks_in_one_launch(dtype: torch.dtype, units: int, cache_len: int) -> bool:
-    """Scores, selection and pruning of a unit by one workgroup (or inside the kernel for small work)."""
+    """Scores, selection and pruning of a unit by one workgroup (or inside the kernel for small work), unless
+    rank_spreads()."""
     return dtype == torch.bfloat16 and cache_len <= 12288 and (units >= 64 or cache_len <= 4096)
 
 

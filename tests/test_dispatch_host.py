@@ -87,3 +87,36 @@ def test_forms_of_the_pipelined_kernel_are_the_rules_of_the_library(tmp_path):
             assert int(next(lines)) == routes.step_work(keep, n), (keep, n)
     assert next(lines, None) is None
     assert seen == {(64, "plain"), (64, "split"), (128, "plain"), (128, "wide"), (128, "split")}
+
+
+SPREAD_PROGRAM = """
+#include <cstdio>
+#include "common.h"
+using namespace scalekv;
+int main() {
+  const int units[] = {%s}, lengths[] = {%s};
+  for (int u : units) for (int n : lengths) for (int d = 64; d <= 128; d += 64)
+    printf("%%d %%d\\n", rank_spreads(d, u, n, true), rank_spreads(d, u, n, false));
+  // a unit's workgroups share its rows and are at most the compute units
+  for (int u : units) for (int n : lengths) {
+    const int parts = select_parts(u, n);
+    if (parts < 1 || (u <= 256 && u * parts > 256) || (parts > 1 && n / (parts - 1) < 64)) return 1;
+  }
+}
+"""
+
+
+def test_spread_ranking_is_the_rule_of_the_library(tmp_path):
+    src, exe = tmp_path / "spread.hip", tmp_path / "spread"
+    units = UNITS + (17, 24, 25, 33, 65, 97)
+    lengths = LENGTHS + (799, 800, 999, 1000, 1299, 1300, 4097, 12288)
+    src.write_text(SPREAD_PROGRAM % tuple(", ".join(map(str, t)) for t in (units, lengths)))
+    cmd = [os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "--offload-host-only", "-std=c++17", f"-I{CSRC}", str(src), "-o", str(exe)]
+    res = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stderr[-3000:]
+    lines = iter(subprocess.run([str(exe)], capture_output=True, text=True, check=True, timeout=60).stdout.splitlines())
+    for u in units:
+        for n in lengths:
+            for d in (64, 128):
+                assert next(lines) == f"{int(routes.rank_spreads(d, u, n, True))} {int(routes.rank_spreads(d, u, n, False))}", (u, n, d)
+    assert next(lines, None) is None

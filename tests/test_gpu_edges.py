@@ -132,6 +132,83 @@ def test_selection_of_short_caches(S, H, n_cur, L, budget, dup):
     _step_against_oracle(S, H, 64, L, budget, n_cur, 16, sorted({0, S * H - 1}), 11, dup)
 
 
+# The ranking of a unit spread over workgroups against a workgroup per unit: a step of many units takes the second, a
+# step of the first `few` of them the first, and both keep the same rows, bit for bit, and copy them.  Lengths around
+# groups of 32, 128 and 256 keys and rounds of 16 groups, rows per thread of the selection, shares of the pruning
+# (1 to 85 workgroups), tied rows; with the attention that appends and the one that does not.
+@pytest.mark.parametrize("d,few,n_cur,L,budget,n_win,dup", [
+    (128, 3, 20, 800, 1, 1, 1), (128, 3, 300, 801, 800, 16, 1), (128, 32, 256, 1023, 77, 7, 1), (128, 1, 16, 1024, 500, 16, 3),
+    (128, 64, 300, 1025, 256, 16, 1), (128, 2, 40, 1535, 129, 9, 1), (128, 64, 300, 1536, 1535, 16, 5), (128, 96, 300, 1537, 300, 16, 1),
+    (128, 3, 20, 2047, 40, 16, 1), (128, 64, 20, 2049, 900, 4, 1), (128, 5, 300, 4096, 1000, 16, 7), (128, 64, 130, 4097, 700, 16, 1),
+    (128, 96, 130, 8191, 600, 16, 1), (128, 64, 20, 12288, 5000, 16, 1),
+    (64, 3, 20, 1300, 64, 16, 1), (64, 64, 1300, 1337, 65, 3, 2), (64, 1, 40, 1536, 1000, 16, 1), (64, 64, 40, 2048, 63, 16, 1),
+    (64, 96, 300, 5000, 1250, 16, 1),
+])
+def test_spread_ranking_keeps_the_same_rows(d, few, n_cur, L, budget, n_win, dup):
+    print(f"spread ranking d={d} few={few} n_cur={n_cur} L={L} budget={budget} n_win={n_win} dup={dup}", flush=True)
+    many, dtype = 130, torch.bfloat16
+    assert routes.step_spreads(dtype, d, few, n_cur, L, budget) and not routes.step_spreads(dtype, d, many, n_cur, L, budget)
+    gen = torch.Generator(device=DEV).manual_seed(L + few)
+    mk = lambda n, scale=1.0: (torch.randn(1, many, n, d, device=DEV, generator=gen) * scale).to(dtype)
+    q, kc, vc, vs = mk(n_cur, 1.5), mk(n_cur), mk(n_cur), mk(L)
+    ks = mk((L + dup - 1) // dup, 1.5).repeat_interleave(dup, 2)[:, :, :L].contiguous()
+    win = list(range(n_cur - n_win, n_cur))
+
+    def run(units):
+        part = lambda t: t[:, :units].clone()
+        shape = skv.Shape(1, units, d, dtype)
+        kd = torch.full((1, units, budget + n_cur + 1, d), 7.0, dtype=dtype, device=DEV); vd = torch.full_like(kd, 7.0)
+        out, idx = torch.zeros(1, units, n_cur, d, dtype=dtype, device=DEV), torch.full((1, units, budget), -1, dtype=torch.int32, device=DEV)
+        ws = torch.empty(skv.workspace_bytes(shape, L, n_cur), dtype=torch.uint8, device=DEV)
+        skv.step(shape, part(q), part(kc), part(vc), win, part(ks), part(vs), L, budget, kd, vd, out, idx, ws)
+        # the literal order: forced window rows, pooled scores, `L` rows in all
+        k_all, v_all = part(ks), part(vs)
+        keep = n_win + min(budget, L - n_win - 1)
+        kn = torch.full((1, units, keep + 1, d), 7.0, dtype=dtype, device=DEV); vn = torch.full_like(kn, 7.0)
+        idx2 = torch.full((1, units, keep), -1, dtype=torch.int32, device=DEV)
+        skv.step_append_first(shape, part(q), part(kc), part(vc), win, 3, k_all, v_all, L - n_cur, keep - n_win, kn, vn, out.clone(),
+                              idx2, ws)
+        torch.cuda.synchronize()
+        return idx, kd, vd, idx2, kn, vn
+
+    for a, b in zip(run(few), run(many)):
+        assert torch.equal(a, b[:, :few])
+
+
+# fp32: selection and pruning in one launch (up to 256 units, one or several workgroups each) against two (257), rows
+# per thread of the selection, log-scores formed in it (up to 2048 rows) or before, the longest for which it holds
+@pytest.mark.parametrize("d,few,L,budget,n_cur", [
+    (128, 256, 2, 1, 20), (64, 256, 300, 299, 17), (128, 3, 1024, 65, 20), (64, 1, 1025, 1000, 20), (128, 100, 2048, 128, 30),
+    (128, 7, 2049, 64, 20), (64, 130, 4097, 129, 20), (64, 20, 8193, 2000, 20), (64, 2, 12288, 300, 20), (64, 2, 12289, 300, 20),
+])
+def test_selection_that_prunes_f32(d, few, L, budget, n_cur):
+    print(f"selection and pruning f32 d={d} few={few} L={L} budget={budget} n_cur={n_cur}", flush=True)
+    many, dtype = 257, torch.float32
+    gen = torch.Generator(device=DEV).manual_seed(L + few)
+    mk = lambda n: torch.randn(1, many, n, d, device=DEV, generator=gen)
+    q, kc, vc, ks, vs = mk(n_cur), mk(n_cur), mk(n_cur), mk(L), mk(L)
+    n_win = min(16, n_cur)
+    win = list(range(n_cur - n_win, n_cur))
+
+    def run(units):
+        part = lambda t: t[:, :units].clone()
+        shape = skv.Shape(1, units, d, dtype)
+        kd = torch.full((1, units, budget + n_cur + 1, d), 7.0, device=DEV); vd = torch.full_like(kd, 7.0)
+        out, idx = torch.zeros(1, units, n_cur, d, device=DEV), torch.full((1, units, budget), -1, dtype=torch.int32, device=DEV)
+        ws = torch.empty(skv.workspace_bytes(shape, L, n_cur), dtype=torch.uint8, device=DEV)
+        skv.step(shape, part(q), part(kc), part(vc), win, part(ks), part(vs), L, budget, kd, vd, out, idx, ws)
+        torch.cuda.synchronize()
+        return idx, kd, vd
+
+    got, want = run(few), run(many)
+    for a, b in zip(got, want):
+        assert torch.equal(a, b[:, :few])
+    rows = got[0].long().unsqueeze(-1).expand(-1, -1, -1, d)
+    for dst, src, cur in ((got[1], ks, kc), (got[2], vs, vc)):
+        assert torch.equal(dst[:, :, :budget], src[:, :few].gather(2, rows))
+        assert torch.equal(dst[:, :, budget:-1], cur[:, :few]) and torch.all(dst[:, :, -1] == 7.0)
+
+
 # Streamed selectivity: rounds of 512 keys, lists that overflow and are cut (keys in ascending order of
 # their scores), ties at the threshold, several parts per unit, one and two blocks of 16 rows, history
 # within a round, K' at its limits and beyond (the route through the logits)
