@@ -50,6 +50,7 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # 2.0: what the same counter reads for a plain copy of known size) plus --pmc WRITE_SIZE (KiB,
 # scale 1.0), three launches each, inside scalekv_step.  The commands and the full per-kernel table are in profiles/step_hbm_traffic.md.
 ATTEND_PIPE_TRAFFIC = {
+    (1, 64): 17.5e6, (4, 65): 19.0e6, (36, 19): 19.4e6,  # every row kept: the cache is copied as well
     (144, 46): 63.1e6, (144, 9): 58.2e6,
     (256, 82): 120.2e6, (256, 16): 108.5e6,
     (400, 146): 176.8e6, (400, 29): 161.5e6,
@@ -639,6 +640,8 @@ def main() -> int:
                 pruned_too, attended_too = append_split(m, append_bytes)
                 m.update(move_bytes=2.0 * 2.0 * keep * d * e * U + (4.0 * keep * U if keep < lens[l] else 0) + pruned_too,
                          append_in_attend=attended_too)
+                if 0 < keep == lens[l] and is_big(m):  # that kernel writes the kept rows as well, which it reads as keys
+                    m["append_in_attend"] += 2.0 * keep * d * e * U
                 # (a step whose pruning is part of the attention kernel has no kernel that these bytes belong to)
                 if 0 < keep < lens[l] and routes.step_kernel(dtype, d, U, n_cur, lens[l], keep) != "small":
                     m["score_bytes"] = (lens[l] * d * e + len(windows[k]) * d * e + 4.0 * lens[l]) * U

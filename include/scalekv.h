@@ -313,7 +313,8 @@ scalekv_status scalekv_pyramid_budgets(int32_t n_layer, int64_t b_uniform, int64
  * Stages that share a kernel share the time of the last of them: where the ranking is one
  * kernel (bf16) it lies between events[0] and events[1], the pruning with it; on small bf16
  * maps one kernel prunes, appends and attends, for caches of up to 1536 rows ranks as
- * well, and lies between events[3] and events[4], so that the slots before are empty.
+ * well, and lies between events[3] and events[4], so that the slots before are empty.  The
+ * pipelined kernel copies a cache that is kept whole, and the slot before it is empty too.
  * Where the attention runs in the pipelined bf16 kernel (all but small maps) the
  * two events around it are not recorded as stream operations of their own but attached
  * to that kernel's dispatch and receive its start and end times, so timing that kernel

@@ -492,15 +492,19 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
   // behind the kept rows itself (it is bound by the matrix pipe, the copy by the HBM, so the
   // two overlap); for the other shapes the pruning appends them.
   const bool fused_append = pipe;
-  if (!pruned && !small)
+  // Where every row is kept it reads those from the source too, and copies both, unless out lies on top of the source.
+  const bool copies_both = pipe && keep > 0 && keep == cache_len && !src_written;
+  if (!pruned && !small && !copies_both)
     SCALEKV_HIP(launch_compact(shape->dtype, shape->n_seq, shape->n_head, shape->head_dim,
                                view(k_src), view(v_src), idx, keep, k_cur, v_cur,
                                fused_append ? 0 : n_cur, view(k_dst), view(v_dst), st),
                 "compact launch");
   if (fused_append) {
     // events 3 and 4 ride on this kernel's dispatch: its own start and end
-    SCALEKV_HIP(launch_attend_pipe(U, shape->n_head, shape->head_dim, q, n_cur, view(k_dst), view(v_dst), keep, k_cur,
-                                   v_cur, n_cur, true, resolve_scale(shape), out, st,
+    const AttendCopy copy{view(k_dst), view(v_dst), copies_both};
+    SCALEKV_HIP(launch_attend_pipe(U, shape->n_head, shape->head_dim, q, n_cur, view(copies_both ? k_src : k_dst),
+                                   view(copies_both ? v_src : v_dst), keep, k_cur, v_cur, n_cur, &copy,
+                                   resolve_scale(shape), out, st,
                                    ev ? static_cast<hipEvent_t>(ev[3]) : nullptr,
                                    ev ? static_cast<hipEvent_t>(ev[4]) : nullptr),
                 "attend launch");
@@ -696,8 +700,9 @@ scalekv_status scalekv_step_append_first(const scalekv_shape* shape, const void*
   // 2. the map attends over history and itself
   if (fused_append) {
     // events 1 and 2 ride on this kernel's dispatch: its own start and end
+    const AttendCopy copy{view(k_cache), view(v_cache), false};
     SCALEKV_HIP(launch_attend_pipe(U, shape->n_head, shape->head_dim, q, n_cur, view(k_cache), view(v_cache), cache_len,
-                                   k_cur, v_cur, n_cur, true, resolve_scale(shape), out, st,
+                                   k_cur, v_cur, n_cur, &copy, resolve_scale(shape), out, st,
                                    ev ? static_cast<hipEvent_t>(ev[1]) : nullptr,
                                    ev ? static_cast<hipEvent_t>(ev[2]) : nullptr),
                 "attend launch");

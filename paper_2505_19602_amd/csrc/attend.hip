@@ -14,7 +14,7 @@ hipError_t launch_attend(int dtype, int n_seq, int n_head, int d, const void* q,
     return launch_attend_f32(n_unit, n_head, d, q, n_q, k, v, kv_len, sm_scale, out, stream);
   const int rows = small_tile_rows(dtype, d, n_unit, n_q, kv_len, SmallWork::kAttend);
   if (rows == 0)
-    return launch_attend_pipe(n_unit, n_head, d, q, n_q, k, v, kv_len, nullptr, nullptr, 0, false, sm_scale, out,
+    return launch_attend_pipe(n_unit, n_head, d, q, n_q, k, v, kv_len, nullptr, nullptr, 0, nullptr, sm_scale, out,
                               stream);
   SmallStep s{};
   s.n_unit = n_unit; s.n_head = n_head; s.d = d;

@@ -82,7 +82,11 @@
 // workgroup also copies its share of the second segment behind the first in the cache
 // (rows len1 .. len1+len2-1): the append of the pruning step, done here because this
 // kernel is bound by the matrix pipe and leaves the HBM idle, while a separate copy
-// kernel would be bound by the HBM and leave the matrix pipe idle.
+// kernel would be bound by the HBM and leave the matrix pipe idle.  Where every cached row is kept, the first segment is
+// read from the source cache and both are copied, tile by tile from the LDS, to the destination (kCopyBoth): the cache is
+// read once, and its copy costs little beside the products.  Steps, us, a copy before / this: 168 units x 529 queries x
+// 4582 rows 403 / 332; 80 x 140 x 4458 124 / 87; 168 x 340 x 569 60.3 / 40.4; 120 x 182 x 153 22.5 / 13.8; 256 x 4096 x
+// 6489 5437 / 5300; head_dim 64, 32 x 700 x 6000 84.5 / 69.1, 60 x 300 x 500 21.5 / 14.7.
 #include <hip/hip_ext.h>
 
 #include "common.h"
@@ -211,13 +215,22 @@ constexpr bool appends_in_loop(long long n_wg) {
   return WAVES == 4 && (SPLIT > 1 ? D == 64 : n_wg > kResident);
 }
 
+// What a launch writes besides its output: nothing, the second segment behind the first, or both segments, into a cache
+// that is not the one it reads.
+enum CopyWhat { kCopyNothing = 0, kCopySecond = 1, kCopyBoth = 2 };
+struct CopyArgs {
+  int what;  // CopyWhat
+  uint16_t *k, *v;
+  long long k_seq_stride, k_head_stride, v_seq_stride, v_head_stride;
+};
+
 template <int D, int WAVES, int SPLIT, bool LOOP>
 __global__ __launch_bounds__(64 * WAVES * SPLIT)
 __attribute__((amdgpu_waves_per_eu(Shape<D, WAVES, SPLIT>::kWavesPerSimd, Shape<D, WAVES, SPLIT>::kWavesPerSimd)))
-void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, long long k_seq_stride,
-                        long long k_head_stride, uint16_t* v, long long v_seq_stride,
+void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, const uint16_t* k, long long k_seq_stride,
+                        long long k_head_stride, const uint16_t* v, long long v_seq_stride,
                         long long v_head_stride, int len1, const uint16_t* __restrict__ k2,
-                        const uint16_t* __restrict__ v2, int len2, int append, int n_head,
+                        const uint16_t* __restrict__ v2, int len2, CopyArgs copy, int n_head,
                         int n_qtile, int n_wg, float scale_log2e, float no_max, uint16_t* __restrict__ out) {
   SCALEKV_STAMP(t_start);
 #if defined(SCALEKV_TIMELINE)
@@ -482,16 +495,24 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   // ---- append in the loop: the second segment goes behind the first in the cache from the LDS, as its
   // tiles pass.  A wave copies the rows that it has brought in itself; turn x of the second segment falls to query tile
   // x mod n_qtile, so that the workgroups of a unit write at different times.
-  [[maybe_unused]] int copy_turn = append ? n_tile1 / SPLIT + qtile : -1;  // the next of this workgroup
-  auto copy_tile = [&](int t, const unsigned char* stages, const unsigned char* cache, auto ofs)
+  // (Both segments: turn x falls to query tile x mod n_qtile from the first turn on.)
+  [[maybe_unused]] unsigned char *kdu = nullptr, *vdu = nullptr;
+  [[maybe_unused]] int copy_turn = -1;  // the next of this workgroup
+  if constexpr (LOOP) {
+    kdu = (unsigned char*)(copy.k + seq * copy.k_seq_stride + head * copy.k_head_stride);
+    vdu = (unsigned char*)(copy.v + seq * copy.v_seq_stride + head * copy.v_head_stride);
+    copy_turn = copy.what == kCopyBoth ? qtile : n_tile1 / SPLIT + qtile;
+  }
+  auto copy_tile = [&](int t, const unsigned char* stages, unsigned char* cache, auto ofs)
                        __attribute__((always_inline)) {
-    const int tile = t * SPLIT + group - n_tile1;
-    if (t >= n_tile || tile < 0) return;
+    const int tile = t * SPLIT + group;
+    if (t >= n_tile || (tile < n_tile1 && copy.what != kCopyBoth)) return;
     // (formed on the spot, and a vector at a time: nothing of it stays in registers through the tile loop)
     const int mine = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
     const unsigned char* const src = stages + t % kStages * kTileBytes + G::kWaveRows * wave * kRowBytes + 16 * mine;
-    unsigned char* const dst = const_cast<unsigned char*>(cache) + (long long)(len1 + tile * TN) * kRowBytes;
-    const int left = len2 - tile * TN - G::kWaveRows * wave - mine / G::kChunks;
+    const int row = tile < n_tile1 ? tile * TN : len1 + (tile - n_tile1) * TN;
+    unsigned char* const dst = cache + (long long)row * kRowBytes;
+    const int left = rows_of(t) - G::kWaveRows * wave - mine / G::kChunks;
 #pragma unroll
     for (int p = 0; p < G::kOps; ++p) {
       const u32x4 val = *(const u32x4*)(src + 1024 * p);
@@ -500,10 +521,10 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
     }
   };
   [[maybe_unused]] auto copy_k = [&](int t) __attribute__((always_inline)) {
-    copy_tile(t, k_lds, ku, [&](int p) { return ld_krow + (ld_kchunk ^ k_step(p)) + 1024 * p; });
+    copy_tile(t, k_lds, kdu, [&](int p) { return ld_krow + (ld_kchunk ^ k_step(p)) + 1024 * p; });
   };
   [[maybe_unused]] auto copy_v = [&](int t) __attribute__((always_inline)) {
-    copy_tile(t, v_lds, vu, [&](int p) { return ld_vofs + 1024 * p; });
+    copy_tile(t, v_lds, vdu, [&](int p) { return ld_vofs + 1024 * p; });
   };
   // Publishes tile t + 1 of K and tile t of V, and requests the tiles kStages further on, in the place of those that
   // all waves have left.  Requests are made in the order V(x), K(x + 1): what may still be under way is those of x > t.
@@ -739,7 +760,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   // as 16-byte vectors.  The vectors of the first round (the whole share when it is at most 256
   // rows) are requested here, before the output is normalised and stored, so that their latency
   // hides behind that work; the registers of the operand fragments are free by now.
-  const int ap_per = !LOOP && append ? (len2 + n_qtile - 1) / n_qtile : 0;
+  const int ap_per = !LOOP && copy.what != kCopyNothing ? (len2 + n_qtile - 1) / n_qtile : 0;
   const int ap_row0 = min(qtile * ap_per, len2);
   const int ap_vec = min(ap_per, len2 - ap_row0) * (kRowBytes / 16);  // per tensor
   const u32x4* ap_ks = (const u32x4*)(k2u + (long long)ap_row0 * kRowBytes);
@@ -843,6 +864,7 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
   // ---- append, second half: store the first round, then whatever is left of a larger share.
   // The other workgroup on the compute unit keeps the matrix pipe busy meanwhile.
   if (ap_vec > 0) {
+    // (copied here, the second segment goes behind the first where that is)
     u32x4* kd = (u32x4*)(const_cast<unsigned char*>(ku) + (long long)(len1 + ap_row0) * kRowBytes);
     u32x4* vd = (u32x4*)(const_cast<unsigned char*>(vu) + (long long)(len1 + ap_row0) * kRowBytes);
 #pragma unroll
@@ -886,8 +908,8 @@ void attend_pipe_kernel(const uint16_t* __restrict__ q, int n_q, uint16_t* k, lo
 
 template <int D, int WAVES, int SPLIT, bool LOOP>
 hipError_t launch_form(int n_unit, int n_head, const void* q, int n_q, KvView k, KvView v, int len1, const void* k2,
-                  const void* v2, int len2, bool append, float sm_scale, void* out, hipStream_t stream,
-                  hipEvent_t start, hipEvent_t stop) {
+                       const void* v2, int len2, const CopyArgs& copy, float sm_scale, void* out, hipStream_t stream,
+                       hipEvent_t start, hipEvent_t stop) {
   using G = Shape<D, WAVES, SPLIT>;
   constexpr int kLds = kLdsBytes<D, WAVES, SPLIT>;
   const auto kernel = attend_pipe_kernel<D, WAVES, SPLIT, LOOP>;
@@ -900,40 +922,46 @@ hipError_t launch_form(int n_unit, int n_head, const void* q, int n_q, KvView k,
   const int n_wg = n_qtile * n_unit;
   if (start || stop)
     hipExtLaunchKernelGGL(kernel, dim3(n_wg), dim3(G::kThreads), kLds, stream, start, stop, 0, (const uint16_t*)q, n_q,
-                          (uint16_t*)const_cast<void*>(k.ptr), k.seq_stride, k.head_stride,
-                          (uint16_t*)const_cast<void*>(v.ptr), v.seq_stride, v.head_stride, len1, (const uint16_t*)k2,
-                          (const uint16_t*)v2, len2, append ? 1 : 0, n_head, n_qtile, n_wg, scale_log2e, no_max,
-                          (uint16_t*)out);
+                          (const uint16_t*)k.ptr, k.seq_stride, k.head_stride, (const uint16_t*)v.ptr, v.seq_stride,
+                          v.head_stride, len1, (const uint16_t*)k2, (const uint16_t*)v2, len2, copy, n_head, n_qtile, n_wg,
+                          scale_log2e, no_max, (uint16_t*)out);
   else
     hipLaunchKernelGGL(kernel, dim3(n_wg), dim3(G::kThreads), kLds, stream, (const uint16_t*)q, n_q,
-                       (uint16_t*)const_cast<void*>(k.ptr), k.seq_stride, k.head_stride,
-                       (uint16_t*)const_cast<void*>(v.ptr), v.seq_stride, v.head_stride, len1, (const uint16_t*)k2,
-                       (const uint16_t*)v2, len2, append ? 1 : 0, n_head, n_qtile, n_wg, scale_log2e, no_max,
-                       (uint16_t*)out);
+                       (const uint16_t*)k.ptr, k.seq_stride, k.head_stride, (const uint16_t*)v.ptr, v.seq_stride,
+                       v.head_stride, len1, (const uint16_t*)k2, (const uint16_t*)v2, len2, copy, n_head, n_qtile, n_wg,
+                       scale_log2e, no_max, (uint16_t*)out);
   return hipGetLastError();
 }
 
 template <int D, int WAVES, int SPLIT>
 hipError_t launch(int n_unit, int n_head, const void* q, int n_q, KvView k, KvView v, int len1, const void* k2,
-                  const void* v2, int len2, bool append, float sm_scale, void* out, hipStream_t stream,
+                  const void* v2, int len2, const CopyArgs& copy, float sm_scale, void* out, hipStream_t stream,
                   hipEvent_t start, hipEvent_t stop) {
   constexpr int kRows = Shape<D, WAVES, SPLIT>::kRows;
-  if constexpr (appends_in_loop<D, WAVES, SPLIT>(1LL << 40))  // (not at all, whatever the number of workgroups)
-    if (append && appends_in_loop<D, WAVES, SPLIT>((long long)n_unit * ((n_q + kRows - 1) / kRows)))
-      return launch_form<D, WAVES, SPLIT, true>(n_unit, n_head, q, n_q, k, v, len1, k2, v2, len2, true, sm_scale, out,
-                                                stream, start, stop);
-  return launch_form<D, WAVES, SPLIT, false>(n_unit, n_head, q, n_q, k, v, len1, k2, v2, len2, append, sm_scale, out,
-                                             stream, start, stop);
+  const bool loop = copy.what == kCopyBoth ||
+                    (copy.what == kCopySecond &&
+                     appends_in_loop<D, WAVES, SPLIT>((long long)n_unit * ((n_q + kRows - 1) / kRows)));
+  return loop ? launch_form<D, WAVES, SPLIT, true>(n_unit, n_head, q, n_q, k, v, len1, k2, v2, len2, copy, sm_scale, out,
+                                                   stream, start, stop)
+              : launch_form<D, WAVES, SPLIT, false>(n_unit, n_head, q, n_q, k, v, len1, k2, v2, len2, copy, sm_scale, out,
+                                                    stream, start, stop);
 }
 
 }  // namespace
 
 hipError_t launch_attend_pipe(int n_unit, int n_head, int d, const void* q, int n_q, KvView k, KvView v,
-                              int len1, const void* k2, const void* v2, int len2, bool append,
+                              int len1, const void* k2, const void* v2, int len2, const AttendCopy* copy_to,
                               float sm_scale, void* out, hipStream_t stream, hipEvent_t start,
                               hipEvent_t stop) {
+  CopyArgs copy{};
+  if (copy_to) {
+    copy.what = copy_to->both ? kCopyBoth : kCopySecond;
+    copy.k = (uint16_t*)const_cast<void*>(copy_to->k.ptr); copy.v = (uint16_t*)const_cast<void*>(copy_to->v.ptr);
+    copy.k_seq_stride = copy_to->k.seq_stride; copy.k_head_stride = copy_to->k.head_stride;
+    copy.v_seq_stride = copy_to->v.seq_stride; copy.v_head_stride = copy_to->v.head_stride;
+  }
 #define SCALEKV_PIPE(D, W, S) \
-  launch<D, W, S>(n_unit, n_head, q, n_q, k, v, len1, k2, v2, len2, append, sm_scale, out, stream, start, stop)
+  launch<D, W, S>(n_unit, n_head, q, n_q, k, v, len1, k2, v2, len2, copy, sm_scale, out, stream, start, stop)
   switch (pipe_form(d, n_unit, n_q, len1 + len2)) {
     case PipeForm::kWide: return SCALEKV_PIPE(128, 8, 1);
     case PipeForm::kSplit: return d == 128 ? SCALEKV_PIPE(128, 4, 2) : SCALEKV_PIPE(64, 4, 3);

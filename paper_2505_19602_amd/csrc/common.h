@@ -248,15 +248,34 @@ inline SmallWork step_work(int keep, int cache_len) {
 // is repeated by every workgroup of a unit: 64 rows pay up to 16 of those, 32 only with head_dim 64 (8 x 2048, 380, 82:
 // 58.7 / 51.5, head_dim 64 33.3 / 36.0).  Without one 64 rows pay while
 // the workgroups leave some compute units to those that copy, which otherwise wait for a round of their
-// own (all kept, 64 x 144 queries, 100 cached, 192 workgroups: 12.9 / 16.8; 64 x 256, 256 workgroups: 19.3 / 18.7;
-// ranked before, 2500 cached, 300 kept: 64 x 144 51.8 / 54.7; 64 x 256 58.8 / 56.1; 16 x 1024 69.2 / 63.9;
-// head_dim 64 copies half as much: 0.71-0.99 of the time up to 256; one workgroup per unit is as fast or faster but
-// around 100 cached rows: 256 x 36 queries, 19, 70, 100, 500: 12.4 / 11.9, 13.5 / 16.8, 18.0 / 17.3, 39.6 / 42.2),
-// 128 rows do not (128 x 200, 100: 26.2 / 21.1).
+// own (ranked before, 2500 cached, 300 kept: 64 x 144 51.8 / 54.7; 64 x 256 58.8 / 56.1; 16 x 1024 69.2 / 63.9), 128 rows do
+// not.
 // Appending alone copies least and gains least: head_dim 64, up to 224 workgroups, 0.86-0.95 of the time over 500
 // keys and more; head_dim 128: 1.00-1.24.
 // More units than compute units: two rounds are paid, which only maps of up to 16 queries stand
 // (320 x 4, 65, 65: 11.7 / 18.2;  512 x 16, 69, 14: 19.9 / 18.7;  320 x 36, 85, 21, 128 rows: 20.5 / 20.1).
+//
+// keep_all_is_pipelined(): where every row is kept, the pipelined kernel copies the tiles that pass through it, while
+// this one has workgroups for that behind the n_wg attending ones, of `rows` query rows, which read everything once
+// more.  Small / pipelined, us (units, queries, cached rows):
+//   64 rows, d 128: 8, 1000, 800: 29.2 / 32.3   40, 200, 200: 16.6 / 14.8   64, 144, 800: 32.0 / 23.4   32, 400, 3000: 76.4 / 56.8
+//     d 64: 8, 1000, 800: 17.4 / 22.3   24, 500, 800 (192): 18.3 / 18.4   16, 900, 800 (240): 26.5 / 22.7
+//   32 rows, d 128: 12, 546, 800 (216): 21.2 / 26.7   48, 100, 800 (192): 22.2 / 23.5   32, 200, 800 (224): 22.9 / 24.0
+//     48, 160, 800 (240): 27.5 / 22.2   24, 300, 200 (240): 16.8 / 15.6   96, 60, 200 (192): 15.2 / 13.0   128, 60, 800: 35.7 / 26.9
+//     d 64: 64, 100, 800: 16.0 / 16.0   96, 60, 200: 10.9 / 9.7   128, 60, 800: 21.4 / 15.7
+//   16 rows, d 128: 96, 30, 800: 24.1 / 24.8   128, 10, 200: 10.8 / 12.5   128, 10, 3000: 82.5 / 71.5   160, 10, 200: 11.8 / 12.7
+//     160, 10, 800: 31.9 / 27.1   200, 10, 60: 7.7 / 7.7   200, 10, 200: 16.1 / 12.5   256, 10, 800: 50.0 / 35.9   512, 4, 20: 11.0 / 8.9
+//     d 64: 128, 20, 200: 6.4 / 9.4   128, 20, 800: 17.1 / 15.2   256, 10, 200: 7.9 / 9.6   256, 10, 800: 26.8 / 20.7
+//     300, 4, 200: 10.6 / 10.7
+//   More units than compute units: a pipelined workgroup to a unit, two of them on a few compute units, which then take
+//   the longest; d 128, 8 queries: 288, 1500: 99.0 / 81.1   288, 3000: 209 / 224   320, 3000: 231 / 235   384, 3000: 280 / 253
+inline bool keep_all_is_pipelined(int d, int n_unit, int rows, long long n_wg, int kv) {
+  if (rows >= 64) return n_wg > (d == 128 ? 128 : 192);
+  if (rows == 32) return n_unit >= 96 || (d == 128 && n_wg > 224);
+  if (d == 128 && n_unit > 256 && n_unit < 320 && kv > 2000) return false;
+  const long long elements = (long long)n_unit * kv * d;
+  return n_unit >= 128 && elements >= (d == 64 ? 5000000 : n_wg >= 200 ? 2000000 : 8000000);
+}
 inline int small_tile_rows(int dtype, int d, int n_unit, int n_q, int kv, SmallWork work) {
   if (dtype != 1) return 0;
   constexpr int kComputeUnits = 256;
@@ -264,13 +283,14 @@ inline int small_tile_rows(int dtype, int d, int n_unit, int n_q, int kv, SmallW
   long long n_wg = 0;
   for (; rows <= 128; rows *= 2)
     if ((n_wg = (long long)n_unit * ((n_q + rows - 1) / rows)) <= kComputeUnits) break;
+  if (work == SmallWork::kKeepAll && keep_all_is_pipelined(d, n_unit, rows > 128 ? 16 : rows, n_wg, kv)) return 0;
   if (rows > 128) return n_q <= 16 ? 16 : 0;
   if (rows == 32 && work == SmallWork::kAttend && kv <= 128) return 0;
   if (rows <= 32) return rows;
   if (rows == 128) return work == SmallWork::kRanked && kv <= 320 ? rows : 0;
   const bool spare = n_wg <= kComputeUnits * 7 / 8;
   const bool pays = (work == SmallWork::kRanked && (d == 64 || n_q <= 1024)) ||
-                    (work == SmallWork::kRankedBefore && spare) || (work == SmallWork::kKeepAll && (d == 64 || spare || n_q <= 64)) ||
+                    (work == SmallWork::kRankedBefore && spare) || work == SmallWork::kKeepAll ||
                     (work == SmallWork::kAppend && d == 64 && spare);
   return pays ? rows : 0;
 }
@@ -308,12 +328,17 @@ inline int pipe_rows(PipeForm form) { return form == PipeForm::kWide ? 256 : 128
 
 // bf16: the pipelined kernel used when there is enough work for it.  Keys and values are the
 // first len1 rows of the caches k, v followed by the len2 rows of the dense tensors k2, v2
-// ([U, len2, d]; may be NULL when len2 == 0).  With `append` the kernel also copies k2, v2 into
-// rows [len1, len1 + len2) of the caches, which must have room for them.  `start` / `stop`
+// ([U, len2, d]; may be NULL when len2 == 0).  With `copy` the kernel also copies the second segment into rows
+// [len1, len1 + len2) of the caches named there, which are k and v, or (`both`) both segments from row 0 on, and the caches
+// are others than those it reads; they must have room for the rows.  `start` / `stop`
 // (either may be NULL): events that receive the kernel's own start and end times; they ride on
 // the kernel's dispatch, so unlike hipEventRecord they put no operation of their own on the stream.
+struct AttendCopy {
+  KvView k, v;
+  bool both;
+};
 hipError_t launch_attend_pipe(int n_unit, int n_head, int d, const void* q, int n_q, KvView k, KvView v,
-                              int len1, const void* k2, const void* v2, int len2, bool append,
+                              int len1, const void* k2, const void* v2, int len2, const AttendCopy* copy,
                               float sm_scale, void* out, hipStream_t stream,
                               hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 

@@ -11,6 +11,17 @@ ATTEND, APPEND, KEEP_ALL, RANKED, RANKED_BEFORE = range(5)   # enum class SmallW
 SHORT_LEN = 1536   # longest cache that is ranked in the launch that attends
 
 
+def keep_all_is_pipelined(d: int, units: int, rows: int, n_wg: int, kv: int) -> bool:
+    """Whether a step that keeps every row takes the pipelined kernel, which copies the tiles that pass."""
+    if rows >= 64:
+        return n_wg > (128 if d == 128 else 192)
+    if rows == 32:
+        return units >= 96 or (d == 128 and n_wg > 224)
+    if d == 128 and 256 < units < 320 and kv > 2000:
+        return False
+    return units >= 128 and units * kv * d >= (5_000_000 if d == 64 else 2_000_000 if n_wg >= 200 else 8_000_000)
+
+
 def small_tile_rows(dtype: torch.dtype, d: int, units: int, n_q: int, kv: int, work: int) -> int:
     """Query rows per workgroup of the kernel for small work, 0 where it is not taken."""
     if dtype != torch.bfloat16:
@@ -20,6 +31,10 @@ def small_tile_rows(dtype: torch.dtype, d: int, units: int, n_q: int, kv: int, w
         if n_wg <= COMPUTE_UNITS:
             break
     else:
+        rows, n_wg = 256, units * -(-n_q // 128)
+    if work == KEEP_ALL and keep_all_is_pipelined(d, units, 16 if rows > 128 else rows, n_wg, kv):
+        return 0
+    if rows > 128:
         return 16 if n_q <= 16 else 0
     if rows == 32 and work == ATTEND and kv <= 128:
         return 0
@@ -29,7 +44,7 @@ def small_tile_rows(dtype: torch.dtype, d: int, units: int, n_q: int, kv: int, w
         return rows if work == RANKED and kv <= 320 else 0
     spare = n_wg <= COMPUTE_UNITS * 7 // 8
     pays = (work == RANKED and (d == 64 or n_q <= 1024)) or (work == RANKED_BEFORE and spare) or \
-        (work == KEEP_ALL and (d == 64 or spare or n_q <= 64)) or (work == APPEND and d == 64 and spare)
+        work == KEEP_ALL or (work == APPEND and d == 64 and spare)
     return rows if pays else 0
 
 

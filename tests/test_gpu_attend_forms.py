@@ -101,6 +101,44 @@ def test_append_of_passing_tiles(form, d, S, H, n_q, cached):
     _check(form, d, S, H, n_q, cached + n_q, 6, cached=cached)
 
 
+# a step that keeps everything: the pipelined kernel reads the source cache and copies the tiles that pass into another
+# one, with strides and rows of its own.  One query tile and several, more of them than tiles, ragged tiles of both
+# segments, one tile in all, groups without a tile, rows that make workgroups repeat their pass
+@pytest.mark.parametrize("form,d,S,H,n_q,cached", [
+    ("plain", 128, 20, 30, 96, 1), ("plain", 128, 16, 16, 30, 64), ("plain", 128, 20, 20, 190, 63), ("plain", 128, 4, 65, 900, 65),
+    ("plain", 64, 20, 41, 65, 130), ("plain", 64, 20, 20, 191, 127), ("plain", 64, 10, 20, 40, 200),
+    ("wide", 128, 16, 16, 129, 1999), ("wide", 128, 16, 16, 200, 2048), ("wide", 128, 8, 16, 500, 1700),
+    ("split", 128, 4, 32, 100, 700), ("split", 128, 4, 10, 600, 257), ("split", 64, 4, 50, 33, 1001), ("split", 64, 8, 16, 100, 320),
+])
+@pytest.mark.parametrize("rise", [0.0, 150.0])
+def test_copy_of_passing_tiles(form, d, S, H, n_q, cached, rise):
+    kv = cached + n_q
+    assert routes.step_kernel(BF16, d, S * H, n_q, cached, cached) == "pipelined" and routes.pipe_form(d, S * H, n_q, kv) == form
+    print(f"copies both: {form} d={d} {S}x{H} units {n_q} queries {cached} cached rise={rise}", flush=True)
+    shape = skv.Shape(S, H, d, BF16)
+    q, kc, vc, k1, v1 = (_rand(70 + i, (S, H, n, d)) for i, n in enumerate((n_q, n_q, n_q, cached + 1, cached + 5)))
+    if rise:
+        q[..., 0] = 8.0
+        k1[..., 0] = 0.0
+        kc[..., 0] = rise * d ** 0.5 / 8.0
+    ks, vs = k1[:, :, :cached].clone(), v1[:, :, :cached].clone()
+    k1[:, :, cached:], v1[:, :, cached:] = float("nan"), float("nan")
+    kd = torch.full((S, H + 1, kv + 2, d), 7.0, dtype=BF16, device=DEV)[:, :H]
+    vd = torch.full((S, H, kv + 7, d), 7.0, dtype=BF16, device=DEV)
+    out, idx = torch.empty_like(q), torch.full((S, H, cached), -1, dtype=torch.int32, device=DEV)
+    skv.step(shape, q, kc, vc, [0], k1, v1, cached, cached, kd, vd, out, idx, None)
+    torch.cuda.synchronize()
+    k, v = torch.cat([ks, kc], 2), torch.cat([vs, vc], 2)
+    assert torch.equal(kd[:, :, :kv], k) and torch.equal(vd[:, :, :kv], v)
+    assert torch.all(kd[:, :, kv:] == 7.0) and torch.all(vd[:, :, kv:] == 7.0)
+    assert torch.equal(idx, torch.arange(cached, dtype=torch.int32, device=DEV).expand(S, H, cached))
+    pick = sorted({0, S * H // 2, S * H - 1})
+    rows = sorted({0, 31, 32, 127, 128, n_q // 2, n_q - 1} & set(range(n_q)))
+    take = lambda t: units(t.reshape(S * H, 1, *t.shape[2:])[pick])
+    check_output(take(out)[:, rows], oracle.attend(take(q)[:, rows], take(k), take(v), d ** -0.5), BF16, form)
+    assert torch.isfinite(out).all()
+
+
 # values whose products with weights far below 1 would be lost; and none
 @pytest.mark.parametrize("value_scale", [2.0 ** -36, 2.0 ** -80, 2.0 ** -110])
 @pytest.mark.parametrize("form,d,S,H,n_q,kv", [("split", 64, 4, 5, 430, 500), ("split", 128, 4, 5, 430, 500),
