@@ -59,6 +59,27 @@ def test_score_f32_edges(d, L, n_win):
     assert np.abs(ls.cpu().numpy().reshape(S * H, L).astype(np.float64) - ref).max() < 2e-4
 
 
+# tiles of 16 keys, waves of 64 and chunks of 256, channels of very different sizes.  A logit is a sum of d products: its
+# error is at most d 2^-24 of the sum of their magnitudes, the row normaliser's as much; exp, log: a few 2^-24 of about 10.
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("L,n_win", [(15, 16), (16, 1), (17, 15), (192, 9), (193, 16), (256, 2), (513, 16)])
+def test_score_f32_tiles(d, L, n_win):
+    S, H = 2, 2
+    print(f"score f32 tiles d={d} L={L} n_win={n_win}", flush=True)
+    shape = skv.Shape(S, H, d, torch.float32)
+    qw, k = _rand(7, (S, H, n_win, d), torch.float32, 1.5), _rand(8, (S, H, L + 1, d), torch.float32, 1.5)
+    qw[:, :, :, ::3] *= 2.0 ** 10
+    k[:, :, :, ::3] *= 2.0 ** -10
+    k[:, :, L:] = float("nan")
+    ls = torch.full((S, H, L), float("nan"), device=DEV)
+    ws = torch.empty(skv.workspace_bytes(shape, L, 16), dtype=torch.uint8, device=DEV)
+    skv.score(shape, qw.to(DEV), k.to(DEV), L, ls, ws)
+    torch.cuda.synchronize()
+    _, ref = oracle.score(units(qw), units(k)[:, :L])
+    bound = (d * 2.0 ** -24 * (qw.abs() @ k[:, :, :L].abs().transpose(2, 3)).max() / d ** 0.5).item()
+    assert np.abs(ls.cpu().numpy().reshape(S * H, L).astype(np.float64) - ref).max() < 2 * bound + 2e-5
+
+
 def _step_against_oracle(S, H, d, L, budget, n_cur, n_win, pick, seed, dup=1, idx_of=None):
     """One step; units `pick` followed by the oracle.  dup > 1: cached rows repeat in runs of that length (ties).
     idx_of: the indices of the same step; it is then called without an index list.  Returns its outputs and indices."""
