@@ -261,20 +261,21 @@ inline SmallWork step_work(int keep, int cache_len) {
 //   64 rows, d 128: 8, 1000, 800: 29.2 / 32.3   40, 200, 200: 16.6 / 14.8   64, 144, 800: 32.0 / 23.4   32, 400, 3000: 76.4 / 56.8
 //     d 64: 8, 1000, 800: 17.4 / 22.3   24, 500, 800 (192): 18.3 / 18.4   16, 900, 800 (240): 26.5 / 22.7
 //   32 rows, d 128: 12, 546, 800 (216): 21.2 / 26.7   48, 100, 800 (192): 22.2 / 23.5   32, 200, 800 (224): 22.9 / 24.0
-//     48, 160, 800 (240): 27.5 / 22.2   24, 300, 200 (240): 16.8 / 15.6   96, 60, 200 (192): 15.2 / 13.0   128, 60, 800: 35.7 / 26.9
-//     d 64: 64, 100, 800: 16.0 / 16.0   96, 60, 200: 10.9 / 9.7   128, 60, 800: 21.4 / 15.7
-//   16 rows, d 128: 96, 30, 800: 24.1 / 24.8   128, 10, 200: 10.8 / 12.5   128, 10, 3000: 82.5 / 71.5   160, 10, 200: 11.8 / 12.7
-//     160, 10, 800: 31.9 / 27.1   200, 10, 60: 7.7 / 7.7   200, 10, 200: 16.1 / 12.5   256, 10, 800: 50.0 / 35.9   512, 4, 20: 11.0 / 8.9
-//     d 64: 128, 20, 200: 6.4 / 9.4   128, 20, 800: 17.1 / 15.2   256, 10, 200: 7.9 / 9.6   256, 10, 800: 26.8 / 20.7
-//     300, 4, 200: 10.6 / 10.7
+//     48, 160, 800 (240): 27.5 / 22.2   128, 60, 800: 35.7 / 26.9   48, 160, 70: 9.9 / 12.5   96, 60, 150: 10.0 / 11.3
+//     128, 60, 150: 11.4 / 11.4 (up to 256 keys no wave has a second chunk: see ONE in step_small.hip)
+//     d 64: 64, 100, 800: 16.0 / 16.0   128, 60, 800: 21.4 / 15.7   128, 60, 150: 7.3 / 8.6
+//   16 rows, d 128: 96, 30, 800: 24.1 / 24.8   128, 20, 200: 10.3 / 12.7   128, 10, 3000: 82.5 / 71.5   160, 10, 800: 31.9 / 27.1
+//     200, 10, 140: 12.4 / 11.0   256, 4, 100: 8.0 / 9.3   256, 4, 140: 13.6 / 11.0   300, 10, 65: 8.6 / 10.5   300, 10, 100: 11.2 / 10.5
+//     512, 4, 30: 9.1 / 8.9   512, 4, 100: 16.0 / 10.8   256, 10, 800: 50.0 / 35.9
+//     d 64: 128, 20, 200: 6.4 / 9.4   128, 20, 800: 17.1 / 15.2   256, 10, 800: 26.8 / 20.7   300, 4, 200: 10.6 / 10.7
 //   More units than compute units: a pipelined workgroup to a unit, two of them on a few compute units, which then take
 //   the longest; d 128, 8 queries: 288, 1500: 99.0 / 81.1   288, 3000: 209 / 224   320, 3000: 231 / 235   384, 3000: 280 / 253
 inline bool keep_all_is_pipelined(int d, int n_unit, int rows, long long n_wg, int kv) {
   if (rows >= 64) return n_wg > (d == 128 ? 128 : 192);
-  if (rows == 32) return n_unit >= 96 || (d == 128 && n_wg > 224);
+  if (rows == 32) return kv > 256 && (n_unit >= 96 || (d == 128 && n_wg > 224));
   if (d == 128 && n_unit > 256 && n_unit < 320 && kv > 2000) return false;
   const long long elements = (long long)n_unit * kv * d;
-  return n_unit >= 128 && elements >= (d == 64 ? 5000000 : n_wg >= 200 ? 2000000 : 8000000);
+  return n_unit >= 128 && elements >= (d == 64 ? 5000000 : n_unit >= 384 ? 2000000 : n_wg >= 200 ? 3700000 : 8000000);
 }
 inline int small_tile_rows(int dtype, int d, int n_unit, int n_q, int kv, SmallWork work) {
   if (dtype != 1) return 0;

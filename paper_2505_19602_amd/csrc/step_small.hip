@@ -15,11 +15,15 @@
 // Measured (16 units; a step of 16 queries over 69 cached rows, 14 kept; before: ranking kernel, then
 // attention kernel): 19.1 -> 11.0 us a step; 9 queries, 967 of 6477 rows kept, 24 units: compaction and
 // attention 53 -> 19 us; 256 units, maps of 16-64 queries: 25-29 -> 13-18 us.
+// Keys through the stage as whole rows instead of as operands, a row per lane (L2 to one compute unit: 37 bytes a
+// nanosecond so, 70-140 of whole rows): 16 units, 1024 queries, 312 of 773 rows 50.8 -> 47.0 us; 16, 3 queries, 2924 rows, all
+// kept 33.2 -> 26.3; 40 x 56, 1218 rows, literal order 35.6 -> 32.6.  One chunk to a wave (ONE), whose fewer registers let two
+// workgroups share a compute unit: 256 units, 4 queries, 65 rows 8.5 -> 6.3; 230, 12, 30 7.2 -> 5.4; 96, 10, 200 9.3 -> 8.2.
 //
 // Both products are formed transposed, on MFMA 16x16x32 (lane = 16g + i):
 //   A (16 x 32): lane holds row i, k-indices 8g..8g+7     B (32 x 16): lane holds column i, same k-indices
 //   C (16 x 16): lane holds column i, rows 4g + v, v = 0..3
-//   S^T[key][query] = K Q^T: A = key rows, 16 bytes per lane straight from global memory
+//   S^T[key][query] = K Q^T: A = key rows, 16 bytes per lane
 //   O^T[chan][query] += V^T P^T over 32 keys.  S^T of the two 16-key blocks leaves keys 4g + v and
 //   16 + 4g + v in lane group g: taken in that order as k-indices 8g..8g+7 they are the B operand;
 //   the A operand then is channel i of the same eight keys, which the transposing LDS load
@@ -76,7 +80,10 @@ struct SmallLds {
   static constexpr int kBytes = kWaves * kWave;
 };
 
-template <int D, int QB, int MODE>
+// ONE: no wave has more than one chunk of keys.  It then takes the keys as operands: the way through the stage is only
+// longer, and a kernel that ends within 5 us is sensitive to its own length (80 units, 3 queries, 40 rows: 4.9 us through
+// the stage, 4.8 with a branch around it).
+template <int D, int QB, int MODE, bool ONE>
 __global__ __launch_bounds__(kThreads) void step_small_kernel(SmallArgs a) {
   constexpr int NSL = D / 32;          // k-slabs of the first product
   constexpr int NCB = D / 16;          // 16-channel blocks of the output
@@ -170,24 +177,18 @@ __global__ __launch_bounds__(kThreads) void step_small_kernel(SmallArgs a) {
     if constexpr (MODE == kRank) return list[t];
     else return list ? list[t] : t;
   };
-  bf16x8 kf[2][NSL];
-  u32x4 vr[NV];
-  auto load_k = [&](int rows) {
-#pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int r = __shfl(rows, 16 * b + i);
-      const uint16_t* row = (r < 0 ? k2 : k1) + (long long)(r & 0x7fffffff) * D + 8 * g;
-#pragma unroll
-      for (int sl = 0; sl < NSL; ++sl) kf[b][sl] = *(const bf16x8*)(row + 32 * sl);
-    }
-  };
-  auto load_v = [&](int rows) {
+  // (keys as values: RPI whole rows to an instruction.  Fetched as operands, a row per lane and 16 bytes of it, every lane
+  // is a request of its own: a quarter of the rate.)
+  u32x4 kr[NV], vr[NV];
+  auto load_rows = [&](int rows, const uint16_t* cached, const uint16_t* own, u32x4 (&x)[NV]) {
 #pragma unroll
     for (int p = 0; p < NV; ++p) {
       const int r = __shfl(rows, RPI * p + lane / VPR);
-      vr[p] = *(const u32x4*)((r < 0 ? v2 : v1) + (long long)(r & 0x7fffffff) * D + 8 * (lane % VPR));
+      x[p] = *(const u32x4*)((r < 0 ? own : cached) + (long long)(r & 0x7fffffff) * D + 8 * (lane % VPR));
     }
   };
+  auto load_k = [&](int rows) { load_rows(rows, k1, k2, kr); };
+  auto load_v = [&](int rows) { load_rows(rows, v1, v2, vr); };
 
   f32x4 o[QB][NCB];
   float m_run[QB], l_run[QB];
@@ -201,43 +202,52 @@ __global__ __launch_bounds__(kThreads) void step_small_kernel(SmallArgs a) {
   unsigned char* const stage = smem + wave * L::kWave;
   const int n_chunk = (kv + kChunk - 1) / kChunk;
   int rows = 0;
+  bf16x8 kf[2][NSL];
   if (split < n_chunk) {
     rows = row_of(split);
-    load_k(rows);
-    load_v(rows);
-    if (split + n_split < n_chunk) rows = row_of(split + n_split);
-  }
-  for (int chunk = split; chunk < n_chunk; chunk += n_split) {
-    const bool more = chunk + n_split < n_chunk;
-    f32x4 s[QB][2];
-#pragma unroll
-    for (int b = 0; b < QB; ++b)
+    if constexpr (ONE) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
-        s[b][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int r = __shfl(rows, 16 * kb + i);
+        const uint16_t* row = (r < 0 ? k2 : k1) + (long long)(r & 0x7fffffff) * D + 8 * g;
+#pragma unroll
+        for (int sl = 0; sl < NSL; ++sl) kf[kb][sl] = *(const bf16x8*)(row + 32 * sl);
+      }
+    } else {
+      load_k(rows);
+    }
+    load_v(rows);
+    if (!ONE && split + n_split < n_chunk) rows = row_of(split + n_split);
+  }
+  for (int chunk = split; chunk < n_chunk; chunk += ONE ? n_chunk : n_split) {
+    const bool more = !ONE && chunk + n_split < n_chunk;
+    // through the wave's stage, the keys first: what a wave asks of the LDS is done in order
+    auto to_stage = [&](const u32x4 (&x)[NV]) {
+#pragma unroll
+      for (int p = 0; p < NV; ++p)
+        *(u32x4*)(stage + (RPI * p + lane / VPR) * L::kRowStride + 16 * (lane % VPR)) = x[p];
+    };
+    if constexpr (!ONE) {
+      to_stage(kr);
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int sl = 0; sl < NSL; ++sl)
-          s[b][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][sl], qf[b][sl], s[b][kb], 0, 0, 0);
-      }
-#pragma unroll
-    for (int p = 0; p < NV; ++p)
-      *(u32x4*)(stage + (RPI * p + lane / VPR) * L::kRowStride + 16 * (lane % VPR)) = vr[p];
+          kf[kb][sl] = *(const bf16x8*)(stage + (16 * kb + i) * L::kRowStride + 64 * sl + 16 * g);
+    }
+    to_stage(vr);
     if constexpr (MODE == kRank) {
       // this chunk's rows into the destination: one wave of one of the unit's workgroups
       if (block == 0 && chunk % a.n_tile == tile) {
         uint16_t* kd = a.kd + seq * a.kd_seq + head * a.kd_head;
         uint16_t* vd = a.vd + seq * a.vd_seq + head * a.vd_head;
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-          const int t = chunk * kChunk + 16 * kb + i;
-          if (t < kv)
-#pragma unroll
-            for (int sl = 0; sl < NSL; ++sl) *(bf16x8*)(kd + (long long)t * D + 32 * sl + 8 * g) = kf[kb][sl];
-        }
-#pragma unroll
         for (int p = 0; p < NV; ++p) {
           const int t = chunk * kChunk + RPI * p + lane / VPR;
-          if (t < kv) *(u32x4*)(vd + (long long)t * D + 8 * (lane % VPR)) = vr[p];
+          if (t < kv) {
+            *(u32x4*)(kd + (long long)t * D + 8 * (lane % VPR)) = kr[p];
+            *(u32x4*)(vd + (long long)t * D + 8 * (lane % VPR)) = vr[p];
+          }
         }
       }
     }
@@ -248,6 +258,16 @@ __global__ __launch_bounds__(kThreads) void step_small_kernel(SmallArgs a) {
       if (chunk + 2 * n_split < n_chunk) rows = row_of(chunk + 2 * n_split);
     }
     __builtin_amdgcn_sched_barrier(0);
+    f32x4 s[QB][2];
+#pragma unroll
+    for (int b = 0; b < QB; ++b)
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        s[b][kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int sl = 0; sl < NSL; ++sl)
+          s[b][kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][sl], qf[b][sl], s[b][kb], 0, 0, 0);
+      }
     if ((chunk + 1) * kChunk > kv) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
@@ -350,12 +370,12 @@ __global__ __launch_bounds__(kThreads) void step_small_kernel(SmallArgs a) {
   }
 }
 
-template <int D, int QB, int MODE>
+template <int D, int QB, int MODE, bool ONE>
 hipError_t launch(const SmallArgs& a, int n_wg, int lds, hipStream_t stream) {
   static std::atomic<uint64_t> configured{0};  // LDS above 64 KB per workgroup has to be asked for
-  const hipError_t e = allow_dynamic_lds((const void*)step_small_kernel<D, QB, MODE>, 128 * 1024, configured);
+  const hipError_t e = allow_dynamic_lds((const void*)step_small_kernel<D, QB, MODE, ONE>, 128 * 1024, configured);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((step_small_kernel<D, QB, MODE>), dim3(n_wg), dim3(kThreads), lds, stream, a);
+  hipLaunchKernelGGL((step_small_kernel<D, QB, MODE, ONE>), dim3(n_wg), dim3(kThreads), lds, stream, a);
   return hipGetLastError();
 }
 
@@ -394,8 +414,10 @@ hipError_t launch_step_small(const SmallStep& s, hipStream_t stream) {
   }
   int lds = d == 128 ? SmallLds<128>::kBytes : SmallLds<64>::kBytes;
   if (s.cache_len) lds = lds > rank_short_logit_bytes(s.cache_len) ? lds : rank_short_logit_bytes(s.cache_len);
-#define SCALEKV_SMALL(D, Q) \
-  (s.cache_len ? launch<D, Q, kRank>(a, n_wg, lds, stream) : launch<D, Q, kGiven>(a, n_wg, lds, stream))
+  const bool one = (s.len1 + s.len2 + kChunk - 1) / kChunk <= kWaves >> a.blocks_log2;
+#define SCALEKV_SMALL(D, Q)                                                                                     \
+  (s.cache_len ? launch<D, Q, kRank, false>(a, n_wg, lds, stream)                                               \
+   : one ? launch<D, Q, kGiven, true>(a, n_wg, lds, stream) : launch<D, Q, kGiven, false>(a, n_wg, lds, stream))
   if (d == 128) return QB == 2 ? SCALEKV_SMALL(128, 2) : SCALEKV_SMALL(128, 1);
   return QB == 2 ? SCALEKV_SMALL(64, 2) : SCALEKV_SMALL(64, 1);
 #undef SCALEKV_SMALL

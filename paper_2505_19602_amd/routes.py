@@ -16,10 +16,11 @@ def keep_all_is_pipelined(d: int, units: int, rows: int, n_wg: int, kv: int) -> 
     if rows >= 64:
         return n_wg > (128 if d == 128 else 192)
     if rows == 32:
-        return units >= 96 or (d == 128 and n_wg > 224)
+        return kv > 256 and (units >= 96 or (d == 128 and n_wg > 224))
     if d == 128 and 256 < units < 320 and kv > 2000:
         return False
-    return units >= 128 and units * kv * d >= (5_000_000 if d == 64 else 2_000_000 if n_wg >= 200 else 8_000_000)
+    return units >= 128 and units * kv * d >= (
+        5_000_000 if d == 64 else 2_000_000 if units >= 384 else 3_700_000 if n_wg >= 200 else 8_000_000)
 
 
 def small_tile_rows(dtype: torch.dtype, d: int, units: int, n_q: int, kv: int, work: int) -> int:

@@ -141,6 +141,21 @@ def test_small_step_edges(d, S, H, L, budget, n_cur, n_win, dup):
         assert torch.equal(a, b)
 
 
+# The kernel for small work where the kept rows are known before it: one chunk of 32 keys to each of its eight (64 query
+# rows: four) waves at most, and the first length with which one has two; some without any; rows kept by a ranking (few
+# of many, through the index list) and whole caches; 16, 32 and 64 query rows to a workgroup
+@pytest.mark.parametrize("d,S,H,L,budget,n_cur", [
+    (d, 1, 3, L, budget, n) for d in (64, 128) for L, budget, n in (
+        (1700, 235, 20), (1700, 236, 20), (1700, 237, 20), (2000, 1, 1), (1, 1, 1), (31, 31, 1), (32, 32, 1), (235, 235, 20),
+        (236, 236, 20), (237, 237, 20), (500, 500, 17))
+] + [(128, 2, 50, 216, 216, 40), (128, 2, 20, 217, 217, 100), (64, 2, 50, 215, 215, 40), (64, 2, 48, 57, 57, 70),
+     (64, 2, 48, 58, 58, 70), (64, 2, 48, 59, 59, 70)])
+def test_one_chunk_to_a_wave(d, S, H, L, budget, n_cur):
+    print(f"one chunk to a wave d={d} S={S} H={H} L={L} budget={budget} n_cur={n_cur}", flush=True)
+    assert routes.step_kernel(torch.bfloat16, d, S * H, n_cur, L, budget) == "small"
+    _step_against_oracle(S, H, d, L, budget, n_cur, min(16, n_cur), sorted({0, S * H // 2, S * H - 1}), 21)
+
+
 # Short caches are selected by counting, four lanes or two to a row (512 threads: up to 128 and 256 rows; the ranking
 # kernel with 1024: 256): shares of four keys and their remainders, the first length beyond; runs of equal rows that
 # the border cuts or not, and rows that are all equal, which the search decides.
