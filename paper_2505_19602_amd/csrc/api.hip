@@ -493,7 +493,8 @@ scalekv_status step_impl(const scalekv_shape* shape, const void* q, const void* 
   // two overlap); for the other shapes the pruning appends them.
   const bool fused_append = pipe;
   // Where every row is kept it reads those from the source too, and copies both, unless out lies on top of the source.
-  const bool copies_both = pipe && keep > 0 && keep == cache_len && !src_written;
+  const bool copies_both = pipe && keep > 0 && keep == cache_len && !src_written &&
+                           pipe_copies_cache(shape->head_dim, U, n_cur, cache_len);
   if (!pruned && !small && !copies_both)
     SCALEKV_HIP(launch_compact(shape->dtype, shape->n_seq, shape->n_head, shape->head_dim,
                                view(k_src), view(v_src), idx, keep, k_cur, v_cur,

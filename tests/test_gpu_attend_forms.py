@@ -107,7 +107,7 @@ def test_append_of_passing_tiles(form, d, S, H, n_q, cached):
 @pytest.mark.parametrize("form,d,S,H,n_q,cached", [
     ("plain", 128, 20, 30, 96, 1), ("plain", 128, 16, 16, 30, 260), ("plain", 128, 20, 20, 190, 63), ("plain", 128, 4, 65, 900, 65),
     ("plain", 64, 20, 41, 65, 130), ("plain", 64, 20, 20, 191, 127), ("plain", 64, 10, 20, 40, 200),
-    ("wide", 128, 16, 16, 129, 1999), ("wide", 128, 16, 16, 200, 2048), ("wide", 128, 8, 16, 500, 1700),
+    ("wide", 128, 16, 16, 129, 1999), ("wide", 128, 16, 16, 200, 2048), ("wide", 128, 8, 16, 500, 1700), ("wide", 128, 8, 16, 2040, 1020), ("wide", 128, 8, 16, 2040, 1019),
     ("split", 128, 4, 32, 100, 700), ("split", 128, 4, 10, 600, 257), ("split", 64, 4, 50, 33, 1001), ("split", 64, 8, 16, 100, 320),
 ])
 @pytest.mark.parametrize("rise", [0.0, 150.0])
