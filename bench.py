@@ -50,7 +50,7 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # 2.0: what the same counter reads for a plain copy of known size) plus --pmc WRITE_SIZE (KiB,
 # scale 1.0), three launches each, inside scalekv_step.  The commands and the full per-kernel table are in profiles/step_hbm_traffic.md.
 ATTEND_PIPE_TRAFFIC = {
-    (1, 64): 17.5e6, (4, 65): 19.0e6, (36, 19): 19.4e6,  # every row kept: the cache is copied as well
+    (36, 19): 19.4e6,  # every row kept: the cache is copied as well
     (144, 46): 63.1e6, (144, 9): 58.2e6,
     (256, 82): 120.2e6, (256, 16): 108.5e6,
     (400, 146): 176.8e6, (400, 29): 161.5e6,
