@@ -257,25 +257,46 @@ inline SmallWork step_work(int keep, int cache_len) {
 //
 // keep_all_is_pipelined(): where every row is kept, the pipelined kernel copies the tiles that pass through it, while
 // this one has workgroups for that behind the n_wg attending ones, of `rows` query rows, which read everything once
-// more.  Small / pipelined, us (units, queries, cached rows):
-//   64 rows, d 128: 8, 1000, 800: 29.2 / 32.3   40, 200, 200: 16.6 / 14.8   64, 144, 800: 32.0 / 23.4   32, 400, 3000: 76.4 / 56.8
-//     d 64: 8, 1000, 800: 17.4 / 22.3   24, 500, 800 (192): 18.3 / 18.4   16, 900, 800 (240): 26.5 / 22.7
-//   32 rows, d 128: 12, 546, 800 (216): 21.2 / 26.7   48, 100, 800 (192): 22.2 / 23.5   32, 200, 800 (224): 22.9 / 24.0
-//     48, 160, 800 (240): 27.5 / 22.2   128, 60, 800: 35.7 / 26.9   48, 160, 70: 9.9 / 12.5   96, 60, 150: 10.0 / 11.3
-//     128, 60, 150: 11.4 / 11.4 (up to 256 keys no wave has a second chunk: see ONE in step_small.hip)
-//     d 64: 64, 100, 800: 16.0 / 16.0   128, 60, 800: 21.4 / 15.7   128, 60, 150: 7.3 / 8.6
-//   16 rows, d 128: 96, 30, 800: 24.1 / 24.8   128, 20, 200: 10.3 / 12.7   128, 10, 3000: 82.5 / 71.5   160, 10, 800: 31.9 / 27.1
-//     200, 10, 140: 12.4 / 11.0   256, 4, 100: 8.0 / 9.3   256, 4, 140: 13.6 / 11.0   300, 10, 65: 8.6 / 10.5   300, 10, 100: 11.2 / 10.5
-//     512, 4, 30: 9.1 / 8.9   512, 4, 100: 16.0 / 10.8   256, 10, 800: 50.0 / 35.9
-//     d 64: 128, 20, 200: 6.4 / 9.4   128, 20, 800: 17.1 / 15.2   256, 10, 800: 26.8 / 20.7   300, 4, 200: 10.6 / 10.7
-//   More units than compute units: a pipelined workgroup to a unit, two of them on a few compute units, which then take
-//   the longest; d 128, 8 queries: 288, 1500: 99.0 / 81.1   288, 3000: 209 / 224   320, 3000: 231 / 235   384, 3000: 280 / 253
-inline bool keep_all_is_pipelined(int d, int n_unit, int rows, long long n_wg, int kv) {
+// more.  The pipelined kernel has n_pipe workgroups, of 128 rows, each of which walks all keys: where they are few it loses by
+// the length of the cache what it gains by copying.  Small / pipelined, us (units, queries, cached rows):
+//   64 rows, d 128: 8, 1000, 800 (n_wg 128): 24.8 / 31.9   24, 465, 69 (168): 16.0 / 16.3   40, 200, 200 (160): 14.0 / 14.5
+//     64, 144, 800 (192): 27.6 / 23.0   32, 400, 3000 (224): 64.3 / 55.9
+//     d 64: 8, 1000, 800: 16.2 / 21.5   24, 500, 800 (192): 17.2 / 17.7   96, 103, 438 (192): 14.9 / 11.8   20, 650, 101 (220):
+//     12.5 / 13.5   16, 900, 800 (240): 24.3 / 21.4
+//   32 rows, d 128 (n_wg, n_pipe): 16, 485, 230 (256, 64): 16.4 / 17.5   16, 485, 4009: 54.0 / 72.4   32, 254, 300 (256, 64):
+//     16.0 / 15.5   32, 254, 1700: 36.9 / 39.0   32, 254, 4473: 67.6 / 85.6   60, 108, 550 (240, 60): 22.1 / 19.5   60, 108, 1700: 39.7 / 43.9
+//     12, 546, 800 (216, 60): 17.4 / 26.1   32, 200, 800 (224, 64): 19.7 / 23.2   48, 100, 800 (192, 48): 19.6 / 24.0
+//     40, 173, 221 (240, 80): 15.2 / 13.7   48, 160, 800 (240, 96): 24.9 / 21.8   128, 60, 800 (256, 128): 34.2 / 26.2
+//     few keys, no wave of this kernel has a second chunk (ONE in step_small.hip): 48, 160, 70: 9.5 / 12.1
+//     96, 60, 150: 9.7 / 11.1   128, 60, 150: 11.2 / 11.1
+//     d 64: 64, 100, 800: 15.4 / 15.6   96, 60, 300: 10.9 / 9.7   96, 37, 1812: 24.6 / 26.9   120, 52, 4951: 73.8 / 61.6
+//     128, 60, 800: 20.3 / 17.2   128, 60, 150: 7.0 / 8.5
+//   16 rows, a pipelined workgroup to a unit.  Little work is done sooner in this kernel; how little depends on the idle
+//   compute units, which it sends to copy.  d 128: 96, 30, 800: 23.0 / 24.9   128, 10, 800: 25.3 / 25.6   128, 10, 3000: 82.7 / 71.1
+//     160, 10, 400: 20.4 / 18.0   192, 10, 200: 12.9 / 12.7   256, 4, 100: 7.7 / 9.2   256, 4, 140: 13.5 / 10.6   300, 10, 65: 8.2 / 10.2
+//     300, 10, 100: 11.1 / 10.2   512, 4, 30: 8.9 / 8.7   512, 4, 100: 15.9 / 12.2   256, 10, 800: 50.0 / 35.8
+//     d 64: 128, 10, 900: 15.2 / 19.2   144, 10, 900: 18.2 / 18.5   168, 10, 800: 19.4 / 17.0   192, 10, 400: 12.1 / 11.0   224, 10, 400:
+//     12.9 / 11.9   256, 10, 800: 26.5 / 20.2   300, 4, 200: 8.9 / 10.4   384, 10, 200: 10.0 / 10.7
+//   A new cache (keys and values, 4 bytes an element) beyond the last-level cache of 256 MB is written to the HBM while the
+//   source is read from it.  This kernel keeps all compute units at that; the pipelined one those that have a unit, in the
+//   last round too: taken where five eighths of the units' rounds over the chip are filled or more (at that line either is up
+//   to 7 % the faster, by the cache's length).  8 queries, d 128:
+//   128, 5000: 136.7 / 167.1   160, 3400: 120.6 / 129.6   160, 4200: 163.3 / 148.6   168, 3148: 119.5 / 124.7   168, 4200: 179.8 / 150.6
+//     208, 4200: 237 / 179   256, 3000: 188 / 164   272, 3000: 195 / 218   288, 3000: 202 / 224   320, 2000: 162.1 / 161.2
+//     320, 3000: 225 / 235   336, 3000: 240.5 / 239.0   384, 3000: 277 / 251      within: 288, 1500: 99.0 / 81.3
+//     d 64: 272, 5000: 158 / 173      within: 160, 6000: 103.4 / 79.3
+inline bool keep_all_is_pipelined(int d, int n_unit, int n_q, int rows, long long n_wg, int kv) {
+  const long long n_pipe = (long long)n_unit * ((n_q + 127) / 128);  // pipelined workgroups
   if (rows >= 64) return n_wg > (d == 128 ? 128 : 192);
-  if (rows == 32) return kv > 256 && (n_unit >= 96 || (d == 128 && n_wg > 224));
-  if (d == 128 && n_unit > 256 && n_unit < 320 && kv > 2000) return false;
-  const long long elements = (long long)n_unit * kv * d;
-  return n_unit >= 128 && elements >= (d == 64 ? 5000000 : n_unit >= 384 ? 2000000 : n_wg >= 200 ? 3700000 : 8000000);
+  if (rows == 32 && n_pipe >= (d == 128 ? 96 : 112)) return kv > 256;
+  if (rows == 32) return kv > 256 && kv <= 1024 && (n_unit >= 96 || (d == 128 && n_unit >= 32 && n_wg > 224));
+  const long long elements = (long long)n_unit * kv * d;  // of the new keys, and as many values
+  if (4 * elements > (256 << 20)) {
+    const int rounds = (n_unit + 255) / 256;
+    return 16 * n_unit >= 10 * 256 * rounds;
+  }
+  const bool idle = (d == 64 ? n_unit : n_wg) < 192;
+  return n_unit >= 128 && elements >= (idle ? 8000000 : d == 64 ? 5000000 : n_unit >= 384 ? 2000000 : 3850000);
 }
 inline int small_tile_rows(int dtype, int d, int n_unit, int n_q, int kv, SmallWork work) {
   if (dtype != 1) return 0;
@@ -284,7 +305,7 @@ inline int small_tile_rows(int dtype, int d, int n_unit, int n_q, int kv, SmallW
   long long n_wg = 0;
   for (; rows <= 128; rows *= 2)
     if ((n_wg = (long long)n_unit * ((n_q + rows - 1) / rows)) <= kComputeUnits) break;
-  if (work == SmallWork::kKeepAll && keep_all_is_pipelined(d, n_unit, rows > 128 ? 16 : rows, n_wg, kv)) return 0;
+  if (work == SmallWork::kKeepAll && keep_all_is_pipelined(d, n_unit, n_q, rows > 128 ? 16 : rows, n_wg, kv)) return 0;
   if (rows > 128) return n_q <= 16 ? 16 : 0;
   if (rows == 32 && work == SmallWork::kAttend && kv <= 128) return 0;
   if (rows <= 32) return rows;

@@ -11,16 +11,21 @@ ATTEND, APPEND, KEEP_ALL, RANKED, RANKED_BEFORE = range(5)   # enum class SmallW
 SHORT_LEN = 1536   # longest cache that is ranked in the launch that attends
 
 
-def keep_all_is_pipelined(d: int, units: int, rows: int, n_wg: int, kv: int) -> bool:
+def keep_all_is_pipelined(d: int, units: int, n_q: int, rows: int, n_wg: int, kv: int) -> bool:
     """Whether a step that keeps every row takes the pipelined kernel, which copies the tiles that pass."""
+    n_pipe = units * -(-n_q // 128)
     if rows >= 64:
         return n_wg > (128 if d == 128 else 192)
+    if rows == 32 and n_pipe >= (96 if d == 128 else 112):
+        return kv > 256
     if rows == 32:
-        return kv > 256 and (units >= 96 or (d == 128 and n_wg > 224))
-    if d == 128 and 256 < units < 320 and kv > 2000:
-        return False
-    return units >= 128 and units * kv * d >= (
-        5_000_000 if d == 64 else 2_000_000 if units >= 384 else 3_700_000 if n_wg >= 200 else 8_000_000)
+        return 256 < kv <= 1024 and (units >= 96 or (d == 128 and units >= 32 and n_wg > 224))
+    elements = units * kv * d
+    if 4 * elements > 256 << 20:
+        return 16 * units >= 10 * COMPUTE_UNITS * -(-units // COMPUTE_UNITS)
+    idle = (units if d == 64 else n_wg) < 192
+    return units >= 128 and elements >= (
+        8_000_000 if idle else 5_000_000 if d == 64 else 2_000_000 if units >= 384 else 3_850_000)
 
 
 def small_tile_rows(dtype: torch.dtype, d: int, units: int, n_q: int, kv: int, work: int) -> int:
@@ -33,7 +38,7 @@ def small_tile_rows(dtype: torch.dtype, d: int, units: int, n_q: int, kv: int, w
             break
     else:
         rows, n_wg = 256, units * -(-n_q // 128)
-    if work == KEEP_ALL and keep_all_is_pipelined(d, units, 16 if rows > 128 else rows, n_wg, kv):
+    if work == KEEP_ALL and keep_all_is_pipelined(d, units, n_q, 16 if rows > 128 else rows, n_wg, kv):
         return 0
     if rows > 128:
         return 16 if n_q <= 16 else 0
