@@ -33,6 +33,16 @@ struct RankShortLds {
 // dynamic LDS for the logits
 inline int rank_short_logit_bytes(int len) { return round_up(len, 32) * kLogitStride * 4; }
 
+// Maximum m and sum e of exponentials (above the maximum) of a window row over some keys, joined with those of others.  Every
+// form joins by this function, and its roundings are written out: with them left to the compiler, forms that select the
+// same rows today need not tomorrow.
+__device__ __forceinline__ void join_keys(float& m, float& e, float m_more, float e_more) {
+#pragma clang fp contract(off)
+  const float top = fmaxf(m, m_more);
+  e = fmaf(e, expf(m - top), e_more * expf(m_more - top));
+  m = top;
+}
+
 // Rows in ascending order: thread tid holds the keys kk[c] of rows tid + c THREADS < len.  Those above T,
 // the first need_eq equal to T and those whose bit c of `forced` is set go to list[] (LDS) and idx[], each
 // if it is not NULL.  count: one word of LDS per 64 rows.  One barrier; the caller's next one publishes the list.
@@ -354,8 +364,8 @@ __device__ __forceinline__ void rank_short(const uint16_t* qu, const WindowRows&
         for (int x = 0; x < 4; ++x) {
           const int group = first + 4 * g + x;
           const float m = lds.group_max[min(group, n_group - 1)][i], e = lds.group_sum[min(group, n_group - 1)][i];
-          const float m_new = fmaxf(vm[x], m);
-          const float e_new = ve[x] * expf(vm[x] - m_new) + e * expf(m - m_new);
+          float m_new = vm[x], e_new = ve[x];
+          join_keys(m_new, e_new, m, e);
           vm[x] = group < n_group ? m_new : vm[x];
           ve[x] = group < n_group ? e_new : ve[x];
         }
@@ -430,11 +440,6 @@ __device__ __forceinline__ const int32_t* rank_long(const uint16_t* qu, const Wi
   const int i = lane & 15, g = lane >> 4;
   score_f32x4 c[kLongRounds][2];
   float m_run = -INFINITY, e_run = 0.f;
-  auto join = [&](float m, float e) {
-    const float m_new = fmaxf(m_run, m);
-    e_run = e_run * expf(m_run - m_new) + e * expf(m - m_new);
-    m_run = m_new;
-  };
   {
     score_bf16x8 qf[D / 32], kf[2][D / 32];
     score_load_window<D>(qu, rows, n_win, qf);
@@ -449,7 +454,7 @@ __device__ __forceinline__ const int32_t* rank_long(const uint16_t* qu, const Wi
         __builtin_amdgcn_sched_barrier(0);
         float m, e;
         score_statistics<2>(c[r], key0, len, sm_scale, m, e);
-        join(m, e);
+        join_keys(m_run, e_run, m, e);
       }
     }
     if constexpr (kFar) {
@@ -462,7 +467,7 @@ __device__ __forceinline__ const int32_t* rank_long(const uint16_t* qu, const Wi
         float m, e;
         score_statistics<2>(far, key0, len, sm_scale, m, e);
         score_store_logits<2, true>(far, key0, len, logits_far, kMaxWindow);
-        join(m, e);
+        join_keys(m_run, e_run, m, e);
       }
     }
   }

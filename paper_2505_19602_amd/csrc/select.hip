@@ -242,12 +242,8 @@ __global__ __launch_bounds__(kSpreadThreads) void spread_scores_kernel(int cache
     e_run = stat[first * (2 * kMaxWindow) + kMaxWindow];
   }
 #pragma unroll 4
-  for (int group = first + kVirtualWaves; group < n_group; group += kVirtualWaves) {
-    const float m = stat[group * (2 * kMaxWindow)], e = stat[group * (2 * kMaxWindow) + kMaxWindow];
-    const float m_new = fmaxf(m_run, m);
-    e_run = e_run * expf(m_run - m_new) + e * expf(m - m_new);
-    m_run = m_new;
-  }
+  for (int group = first + kVirtualWaves; group < n_group; group += kVirtualWaves)
+    join_keys(m_run, e_run, stat[group * (2 * kMaxWindow)], stat[group * (2 * kMaxWindow) + kMaxWindow]);
   wave_max[first][i] = m_run;
   wave_sum[first][i] = e_run;
   __syncthreads();
