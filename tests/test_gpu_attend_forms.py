@@ -23,7 +23,8 @@ def _rand(key, shape):
 
 
 def _check(form, d, S, H, n_q, kv, key, rise=0.0, rise_from=0, cached=None, value_scale=1.0):
-    """One attention of S x H units; with `cached` as a step that keeps that many rows and appends the others."""
+    """One attention of S x H units; with `cached` as a step that keeps that many of one more cached rows (none of none) and
+    appends the others."""
     assert routes.attend_kernel(BF16, d, S * H, n_q, kv) == "pipelined"
     assert routes.pipe_form(d, S * H, n_q, kv) == form
     print(f"{form} d={d} {S}x{H} units {n_q} queries {kv} keys rise={rise} from {rise_from} cached={cached}", flush=True)
@@ -38,11 +39,23 @@ def _check(form, d, S, H, n_q, kv, key, rise=0.0, rise_from=0, cached=None, valu
     if cached is None:
         skv.attend(shape, q, k, v, kv, out)
     else:
-        rows = max(cached, 1)
-        parts = [t.contiguous() for t in (k[:, :, cached:], v[:, :, cached:], k[:, :, :rows], v[:, :, :rows])]
-        kd, vd = torch.zeros_like(k), torch.zeros_like(v)
-        skv.step(shape, q, parts[0], parts[1], [0], parts[2], parts[3], cached, cached, kd, vd, out, None, None)
-        assert torch.equal(kd, k) and torch.equal(vd, v)
+        # (a step that keeps every row would copy both segments: test_copy_of_passing_tiles)
+        held = cached + 1 if cached else 0
+        assert routes.step_kernel(BF16, d, S * H, n_q, held, cached) == "pipelined"
+        kc, vc = k[:, :, cached:].contiguous(), v[:, :, cached:].contiguous()
+        ks, vs = (_rand(10 * key + 5 + i, (S, H, cached + 1, d)) for i in range(2))
+        if rise:
+            ks[..., 0] = 0.0
+        idx = torch.full((S, H, cached), -1, dtype=torch.int32, device=DEV)
+        kd, vd = (torch.full((S, H, kv + 1, d), 7.0, dtype=BF16, device=DEV) for _ in range(2))
+        ws = torch.empty(skv.workspace_bytes(shape, cached + 1, n_q), dtype=torch.uint8, device=DEV)
+        skv.step(shape, q, kc, vc, [0, n_q - 1], ks, vs, held, cached, kd, vd, out, idx, ws)
+        took = idx.long().unsqueeze(-1).expand(-1, -1, -1, d)
+        k, v = (torch.cat([src.gather(2, took), cur], 2) for src, cur in ((ks, kc), (vs, vc)))
+        if cached:
+            assert idx.min() >= 0 and idx.max() <= cached and torch.all(idx.diff(dim=2) > 0)
+        assert torch.equal(kd[:, :, :kv], k) and torch.equal(vd[:, :, :kv], v)
+        assert torch.all(kd[:, :, kv:] == 7.0) and torch.all(vd[:, :, kv:] == 7.0)
     torch.cuda.synchronize()
     pick = sorted({0, S * H // 2, S * H - 1})
     rows = sorted({0, 31, 32, 127, 128, n_q // 2, n_q - 33, n_q - 1} & set(range(n_q)))
@@ -81,24 +94,27 @@ def test_scores_far_above_the_first_block_in_each_form(form, d, S, H, n_q, kv, r
 
 
 @pytest.mark.parametrize("form,d,S,H,n_q,cached", [("split", 64, 4, 10, 430, 101), ("split", 128, 4, 10, 430, 64),
-                                                   ("split", 128, 4, 10, 430, 129), ("wide", 128, 16, 16, 200, 1999)])
-def test_step_of_two_segments_in_each_form(form, d, S, H, n_q, cached):
-    assert routes.step_kernel(BF16, d, S * H, n_q, cached, cached) == "pipelined"
-    _check(form, d, S, H, n_q, cached + n_q, 4, cached=cached)
+                                                   ("split", 128, 4, 10, 430, 129), ("wide", 128, 16, 16, 200, 1999),
+                                                   ("split", 128, 4, 10, 430, 1), ("wide", 128, 16, 16, 129, 2048)])
+@pytest.mark.parametrize("rise", [0.0, 150.0])   # 150: workgroups repeat their pass, and append as well
+def test_step_of_two_segments_in_each_form(form, d, S, H, n_q, cached, rise):
+    _check(form, d, S, H, n_q, cached + n_q, 4, rise, max(cached, 100), cached=cached)
 
 
 # more workgroups than the compute units hold at once, and the split form of head_dim 64: tiles are appended as they
-# pass through the loop; one query tile and several, no kept rows, ragged tiles of both segments
+# pass through the loop; one query tile and several, no kept rows, ragged tiles of both segments, kept rows of fewer tiles
+# than groups and of a number that the groups do not share evenly
 @pytest.mark.parametrize("form,d,S,H,n_q,cached", [
     ("plain", 128, 20, 30, 96, 0), ("plain", 128, 20, 30, 97, 1), ("plain", 128, 20, 30, 128, 64),
     ("plain", 128, 20, 20, 190, 63), ("plain", 128, 20, 20, 193, 65), ("plain", 128, 15, 20, 385, 130),
     ("plain", 64, 20, 41, 65, 0), ("plain", 64, 20, 41, 127, 3), ("plain", 64, 20, 20, 191, 128),
     ("plain", 64, 20, 30, 258, 61),
-    ("split", 64, 4, 10, 449, 0), ("split", 64, 4, 10, 385, 191), ("split", 64, 4, 10, 500, 1),
+    ("split", 64, 4, 10, 449, 0), ("split", 64, 4, 10, 385, 191), ("split", 64, 4, 10, 500, 1), ("split", 64, 4, 10, 385, 100),
+    ("split", 64, 4, 10, 400, 257), ("split", 64, 4, 10, 430, 448),
 ])
-def test_append_of_passing_tiles(form, d, S, H, n_q, cached):
-    assert routes.step_kernel(BF16, d, S * H, n_q, cached, cached) == "pipelined"
-    _check(form, d, S, H, n_q, cached + n_q, 6, cached=cached)
+@pytest.mark.parametrize("rise", [0.0, 150.0])
+def test_append_of_passing_tiles(form, d, S, H, n_q, cached, rise):
+    _check(form, d, S, H, n_q, cached + n_q, 6, rise, max(cached, 64), cached=cached)
 
 
 # a step that keeps everything: the pipelined kernel reads the source cache and copies the tiles that pass into another
@@ -137,6 +153,34 @@ def test_copy_of_passing_tiles(form, d, S, H, n_q, cached, rise):
     take = lambda t: units(t.reshape(S * H, 1, *t.shape[2:])[pick])
     check_output(take(out)[:, rows], oracle.attend(take(q)[:, rows], take(k), take(v), d ** -0.5), BF16, form)
     assert torch.isfinite(out).all()
+
+
+# The same with out on top of the map's keys or values or of the source cache: the kernel must not read (and copy) what
+# other workgroups store their results over, so that the cache is written before.
+@pytest.mark.parametrize("over", ["k_cur", "v_cur", "k_src", "v_src"])
+@pytest.mark.parametrize("form,d,S,H,n_q,cached", [
+    ("plain", 128, 10, 13, 300, 40), ("plain", 64, 20, 20, 191, 200), ("split", 128, 4, 10, 600, 257), ("split", 64, 8, 16, 100, 320),
+    ("wide", 128, 8, 16, 500, 1700),
+])
+def test_copy_of_passing_tiles_under_the_output(form, d, S, H, n_q, cached, over):
+    kv = cached + n_q
+    assert routes.step_kernel(BF16, d, S * H, n_q, cached, cached) == "pipelined" and routes.pipe_form(d, S * H, n_q, kv) == form
+    assert form != "wide" or 2 * cached >= n_q   # the sizes at which that form copies both segments
+    print(f"copies both under out over {over}: {form} d={d} {S}x{H} units {n_q} queries {cached} cached", flush=True)
+    shape = skv.Shape(S, H, d, BF16)
+    q, kc, vc = (_rand(130 + i, (S, H, n_q, d)) for i in range(3))
+    ks, vs = (_rand(133 + i, (S, H, max(cached, n_q), d)) for i in range(2))
+    k, v = torch.cat([ks[:, :, :cached], kc], 2), torch.cat([vs[:, :, :cached], vc], 2)
+    out = {"k_cur": kc, "v_cur": vc, "k_src": ks, "v_src": vs}[over].view(-1)[:q.numel()].view_as(q)
+    kd, vd = (torch.full((S, H, kv + 1, d), 7.0, dtype=BF16, device=DEV) for _ in range(2))
+    skv.step(shape, q, kc, vc, [0], ks, vs, cached, cached, kd, vd, out, None, None)
+    torch.cuda.synchronize()
+    assert torch.equal(kd[:, :, :kv], k) and torch.equal(vd[:, :, :kv], v)
+    assert torch.all(kd[:, :, kv:] == 7.0) and torch.all(vd[:, :, kv:] == 7.0)
+    pick = sorted({0, S * H // 2, S * H - 1})
+    take = lambda t: units(t.reshape(S * H, 1, *t.shape[2:])[pick])
+    rows = sorted({0, 31, n_q // 2, n_q - 1})
+    check_output(take(out)[:, rows], oracle.attend(take(q)[:, rows], take(k), take(v), d ** -0.5), BF16, form)
 
 
 # values whose products with weights far below 1 would be lost; and none
