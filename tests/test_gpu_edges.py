@@ -122,8 +122,9 @@ def _step_against_oracle(S, H, d, L, budget, n_cur, n_win, pick, seed, dup=1, id
     return kd, vd, out, idx
 
 
-# One-launch steps: groups of 32 keys, rounds of 512 keys, the longest cache ranked in LDS and the
-# first beyond it; 16-query blocks, several blocks per workgroup (many units), ties.
+# Small steps: groups of 32 keys, rounds of 512 keys, the longest cache ranked in LDS and the first beyond it (with few
+# units, from 800 rows on, head_dim 64 from 1300, ranked by several workgroups to a unit; one launch at those lengths:
+# test_one_launch_ranking_of_longer_caches); 16-query blocks, several blocks per workgroup (many units), ties.
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("S,H,L,budget,n_cur,n_win,dup", [
     (1, 2, 2, 1, 1, 1, 1), (1, 3, 31, 30, 15, 15, 1), (1, 2, 33, 1, 16, 16, 1), (2, 2, 64, 32, 17, 3, 1),
@@ -154,6 +155,19 @@ def test_one_chunk_to_a_wave(d, S, H, L, budget, n_cur):
     print(f"one chunk to a wave d={d} S={S} H={H} L={L} budget={budget} n_cur={n_cur}", flush=True)
     assert routes.step_kernel(torch.bfloat16, d, S * H, n_cur, L, budget) == "small"
     _step_against_oracle(S, H, d, L, budget, n_cur, min(16, n_cur), sorted({0, S * H // 2, S * H - 1}), 21)
+
+
+# Caches of 800 to 1536 rows that are ranked in the launch that attends: more units than rank_spreads() takes.
+@pytest.mark.parametrize("d,S,H,L,budget,n_cur,n_win,dup", [
+    (128, 1, 17, 800, 60, 20, 16, 1), (128, 1, 32, 999, 300, 16, 5, 1), (128, 3, 11, 1025, 77, 64, 16, 1), (128, 1, 33, 1200, 333, 36, 16, 7),
+    (128, 3, 11, 1535, 400, 128, 16, 1), (128, 1, 33, 1536, 1535, 20, 16, 1), (128, 3, 11, 1536, 700, 420, 16, 1),
+    (64, 1, 25, 1300, 60, 20, 16, 1), (64, 5, 5, 1535, 400, 128, 16, 1), (64, 5, 5, 1536, 1535, 20, 16, 1),
+])
+def test_one_launch_ranking_of_longer_caches(d, S, H, L, budget, n_cur, n_win, dup):
+    print(f"one launch d={d} S={S} H={H} L={L} budget={budget} n_cur={n_cur} n_win={n_win} dup={dup}", flush=True)
+    assert routes.step_kernel(torch.bfloat16, d, S * H, n_cur, L, budget) == "small"
+    assert not routes.step_spreads(torch.bfloat16, d, S * H, n_cur, L, budget)
+    _step_against_oracle(S, H, d, L, budget, n_cur, n_win, sorted({0, S * H // 2, S * H - 1}), 31, dup)
 
 
 # Short caches are selected by counting, four lanes or two to a row (512 threads: up to 128 and 256 rows; the ranking
@@ -245,9 +259,6 @@ def test_selection_that_prunes_f32(d, few, L, budget, n_cur):
         assert torch.equal(dst[:, :, budget:-1], cur[:, :few]) and torch.all(dst[:, :, -1] == 7.0)
 
 
-# Streamed selectivity: rounds of 512 keys, lists that overflow and are cut (keys in ascending order of
-# their scores), ties at the threshold, several parts per unit, one and two blocks of 16 rows, history
-# within a round, K' at its limits and beyond (the route through the logits)
 # four lanes to a row up to 128 rows, two up to 256 (1024 threads, as with the 150 units x 300 queries: 256 and 256),
 # then one; windows that leave some of those lanes without a row of their own
 @pytest.mark.parametrize("d", [64, 128])
@@ -259,6 +270,9 @@ def test_window_sizes_of_short_rankings(d, S, H, n_cur, L, budget, n_win):
     _step_against_oracle(S, H, d, L, budget, n_cur, n_win, sorted({0, S * H - 1}), 71 + L + n_win)
 
 
+# Streamed selectivity: rounds of 512 keys, lists that overflow and are cut (keys in ascending order of
+# their scores), ties at the threshold, several parts per unit, one and two blocks of 16 rows, history
+# within a round, K' at its limits and beyond (the route through the logits)
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("S,H,n_samp,hist,cur,top_k,kind", [
     (1, 2, 1, 1, 1, 1, "normal"), (1, 2, 16, 0, 40, 64, "normal"), (1, 2, 17, 511, 1, 64, "normal"),
@@ -344,11 +358,15 @@ def test_select_with_forced_rows_edges(L, kind, pool_w):
                     assert pooled[u][rest].min() >= pooled[u][out].max() - 8 * 2.0 ** -19
 
 
-# out in the place of q: the workgroups of a unit must not read the window after a neighbour has written
-@pytest.mark.parametrize("d,L,budget,n_cur", [(64, 700, 90, 200), (128, 1536, 300, 128), (128, 90, 20, 16)])
-def test_small_step_writes_over_its_queries(d, L, budget, n_cur):
-    S, H, dtype = 1, 12, torch.bfloat16
-    print(f"out over q d={d} L={L} budget={budget} n_cur={n_cur}", flush=True)
+# out in the place of q: the workgroups of a unit must not read the window after a neighbour has written (12 units, 1536
+# rows: ranked by launches of their own in any case)
+@pytest.mark.parametrize("d,L,budget,n_cur,H", [(64, 700, 90, 200, 12), (128, 1536, 300, 128, 12), (128, 1536, 300, 128, 40),
+                                                (128, 90, 20, 16, 12)])
+def test_small_step_writes_over_its_queries(d, L, budget, n_cur, H):
+    S, dtype = 1, torch.bfloat16
+    print(f"out over q d={d} H={H} L={L} budget={budget} n_cur={n_cur}", flush=True)
+    assert routes.step_kernel(dtype, d, H, n_cur, L, budget) == "small"
+    assert routes.step_spreads(dtype, d, H, n_cur, L, budget) == ((H, L) == (12, 1536))
     shape = skv.Shape(S, H, d, dtype)
     q, kc, vc, ks, vs = (_rand(60 + i, (S, H, n, d), dtype, 1.3).to(DEV) for i, n in enumerate((n_cur,) * 3 + (L,) * 2))
     ws = torch.empty(skv.workspace_bytes(shape, L, n_cur), dtype=torch.uint8, device=DEV)
