@@ -199,7 +199,7 @@ def test_attend_scores_far_above_the_first_tile(where, H, d, n_q):
     ref = oracle.attend(units(q)[pick][:, rows], units(ks)[pick], units(vs)[pick]) * post
     check_output(units(out.float() * post)[pick][:, rows], ref, dtype, f"attend {where}")
     # the same keys as cache + current map through the step (budget = len1 keeps every cached row):
-    # two key segments, and the kernel appends the map's K/V itself
+    # two key segments, both of which the kernel copies itself
     kd = torch.zeros(S, H, len1 + len2 + 2, d, dtype=dtype, device=DEV); vd = torch.zeros_like(kd)
     out2 = torch.full_like(out, float("nan"))
     new_len = skv.step(shape, q.to(DEV), kc.to(DEV), vc.to(DEV), [0], ks[:, :, :len1].contiguous().to(DEV),
@@ -412,14 +412,18 @@ def test_step_with_caches_that_are_views_of_larger_buffers(n_cur, S, H):
     check_output(sub(out), ref["out"], dtype, "strided step")
 
 
-@pytest.mark.parametrize("S,H,n_cur,kernel", [(1, 4, 200, "small"), (4, 65, 60, "pipelined")])
-def test_step_can_be_captured_in_a_graph_and_replayed(S, H, n_cur, kernel):
+# ranked by a workgroup to a unit, by several (pruned by the small kernel, and before it), and kept whole
+@pytest.mark.parametrize("S,H,n_cur,L,budget,kernel", [
+    (1, 4, 200, 300, 120, "small"), (4, 65, 60, 300, 120, "pipelined"), (1, 4, 200, 900, 120, "small"), (1, 8, 400, 900, 120, "small"),
+    (1, 64, 300, 900, 120, "pipelined"), (4, 65, 60, 300, 300, "pipelined")])
+def test_step_can_be_captured_in_a_graph_and_replayed(S, H, n_cur, L, budget, kernel):
     # The library neither allocates nor synchronises, so a step can be recorded into a HIP graph;
     # every replay (with eager work and synchronisations in between) must reproduce the eager bits.
-    d, L, budget = 128, 300, 120
+    d = 128
     dtype = torch.bfloat16
     _note(f"step under graph capture, {kernel} attention")
     assert routes.step_kernel(dtype, d, S * H, n_cur, L, budget) == kernel
+    assert budget == L or routes.step_spreads(dtype, d, S * H, n_cur, L, budget) == (L == 900)
     shape = skv.Shape(S, H, d, dtype)
     q, kc, vc = (_rand(70 + i, (S, H, n_cur, d), dtype).to(DEV) for i in range(3))
     ks, vs = _rand(73, (S, H, L, d), dtype).to(DEV), _rand(74, (S, H, L, d), dtype).to(DEV)

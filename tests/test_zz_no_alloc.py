@@ -6,6 +6,7 @@ import torch
 
 import paper_2505_19602_amd as skv
 import workloads as W
+from paper_2505_19602_amd import routes
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda"
@@ -59,14 +60,19 @@ def test_step_static_matches_step_on_two_calls_in_a_row():
 
 @pytest.mark.parametrize("with_idx", [True, False])   # False: the index list is in the scratch as well
 def test_step_static_finds_an_earlier_calls_scratch(with_idx):
-    # every route that writes the scratch array, each call smaller than the one before: logits, statistics, scores
-    # and indices by launches of their own (few units, more than 4096 rows), the ranking kernel with logits
-    # beyond its registers (64 units), the same below (indices alone), and fp32
-    for case, (S, H, d, n_cur, L, budget, dtype) in enumerate((
-            (1, 64, 128, 300, 4400, 250, torch.bfloat16), (1, 64, 64, 40, 4200, 17, torch.bfloat16),
-            (2, 3, 128, 300, 6100, 250, torch.bfloat16), (1, 2, 64, 40, 4100, 17, torch.bfloat16),
-            (1, 5, 128, 40, 1700, 100, torch.bfloat16), (5, 53, 128, 20, 90, 30, torch.bfloat16),
-            (1, 5, 64, 70, 2100, 400, torch.float32), (1, 2, 128, 40, 200, 60, torch.float32))):
+    # every route that writes the scratch array, each call smaller than the one before: the ranking kernel with logits
+    # beyond its registers, the ranking by several workgroups to a unit (statistics where the indices go later), logits,
+    # statistics, scores and indices by launches of their own (few units, more than 4096 rows), the ranking kernel without
+    # logits of its own (indices alone), and fp32
+    for case, (S, H, d, n_cur, L, budget, dtype, ranking) in enumerate((
+            (1, 130, 128, 300, 4400, 250, torch.bfloat16, "unit"), (1, 100, 64, 40, 4300, 17, torch.bfloat16, "unit"),
+            (1, 64, 128, 300, 4400, 250, torch.bfloat16, "spread"), (1, 64, 64, 40, 4200, 17, torch.bfloat16, "spread"),
+            (2, 3, 128, 300, 6100, 250, torch.bfloat16, "stages"), (1, 2, 64, 40, 4100, 17, torch.bfloat16, "stages"),
+            (1, 5, 128, 40, 1700, 100, torch.bfloat16, "spread"), (1, 5, 128, 40, 900, 100, torch.bfloat16, "spread"),
+            (5, 53, 128, 20, 90, 30, torch.bfloat16, "unit"),
+            (1, 5, 64, 70, 2100, 400, torch.float32, "stages"), (1, 2, 128, 40, 200, 60, torch.float32, "stages"))):
+        assert ranking == ("stages" if not routes.ranks_in_one_launch(dtype, S * H, L) else
+                           "spread" if routes.step_spreads(dtype, d, S * H, n_cur, L, budget) else "unit")
         print(f"step_static: {S}x{H} units, {n_cur} queries, {L} cached rows, {dtype} d{d}", flush=True)
         _both_ways(10 + case, S, H, d, n_cur, L, budget, dtype, with_idx)
 
