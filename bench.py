@@ -64,8 +64,8 @@ ATTEND_PIPE_TRAFFIC = {
 
 VARIANTS = ("scalekv", "literal", "pyramid", "sliding", "sinks", "calibrated")
 # stages between consecutive events of one call, per variant
-# ("score" holds the whole ranking where the selection kernel streams the keys itself: one launch;
-# "select" is then only what lies between two events.  Small maps: "attend" holds the pruning as well and,
+# ("score" holds the whole ranking, and the pruning, where the library ranks from the keys (routes.ranks_in_one_launch);
+# "select" is then only what lies between two events.  Small maps: "attend" mostly holds the pruning as well and,
 # for caches of up to 1536 rows, the ranking: the stages before it are then empty)
 STAGES = {
     "scalekv": ("score", "select", "compact", "attend"),
@@ -640,7 +640,8 @@ def main() -> int:
                 pruned_too, attended_too = append_split(m, append_bytes)
                 m.update(move_bytes=2.0 * 2.0 * keep * d * e * U + (4.0 * keep * U if keep < lens[l] else 0) + pruned_too,
                          append_in_attend=attended_too)
-                if 0 < keep == lens[l] and is_big(m):  # that kernel writes the kept rows as well, which it reads as keys
+                # (that kernel writes the kept rows as well, which it reads as keys)
+                if 0 < keep == lens[l] and is_big(m) and routes.pipe_copies_cache(d, U, n_cur, keep):
                     m["append_in_attend"] += 2.0 * keep * d * e * U
                 # (a step whose pruning is part of the attention kernel has no kernel that these bytes belong to)
                 if 0 < keep < lens[l] and routes.step_kernel(dtype, d, U, n_cur, lens[l], keep) != "small":
@@ -770,11 +771,10 @@ def main() -> int:
             per_scale_ms[k] += sum(t)
             attend_all["ms"] += t[att]; attend_all["flops"] += 4.0 * m["n_cur"] * m["kv_len"] * d * U
             if m["score_bytes"] > 0 and "score" in stages:
-                # a step that ranks before its attention: score, select and the gather of the kept rows run in ONE kernel, so the
-                # streaming bytes of all three are priced against the time of the three event slots together
-                # (where the library ranks in one launch -- bf16, and enough units or a short cache -- the
-                # "score" slot brackets exactly that kernel and the other two slots hold nothing but the
-                # next event's own cost)
+                # a step that ranks before its attention: the streaming bytes of score, select and the gather of the kept
+                # rows are priced against the time of the three event slots together (where the library ranks from the
+                # keys -- bf16, and enough units or a short cache -- the "score" slot holds all of it, in one launch or
+                # three, and the other two slots nothing but the next event's own cost)
                 one_launch = routes.ranks_in_one_launch(dtype, U, m["cache_len"])
                 t_rank = t[stages.index("score")] if one_launch else \
                     sum(t[stages.index(n)] for n in ("score", "select", "compact"))

@@ -310,11 +310,19 @@ scalekv_status scalekv_pyramid_budgets(int32_t n_layer, int64_t b_uniform, int64
  * anyway).  A NULL entry is left out, so {0,0,0,e3,e4} brackets the attend kernel
  * alone.  scalekv_step_append_first records them too: events[0] before the first
  * kernel, events[1..4] after its append, attend, score+select and compact kernels.
- * Stages that share a kernel share the time of the last of them: where the ranking is one
- * kernel (bf16) it lies between events[0] and events[1], the pruning with it; on small bf16
- * maps one kernel prunes, appends and attends, for caches of up to 1536 rows ranks as
- * well, and lies between events[3] and events[4], so that the slots before are empty.  The
- * pipelined kernel copies a cache that is kept whole, and the slot before it is empty too.
+ * Stages that share a launch share a slot, and slots that nothing is left for are empty:
+ *   - bf16, with enough units for the length of the cache (always up to 4096 rows): the whole
+ *     ranking, one launch or three, lies between events[0] and events[1], and the pruning
+ *     with it, unless the kernel for small maps does that;
+ *   - otherwise (fp32; long caches of few units) the logits lie between events[0] and
+ *     events[1], and log-scores and selection between events[1] and events[2], with the
+ *     pruning where there are up to 256 units and 12288 rows, unless the kernel for small maps does it;
+ *   - small bf16 maps: one kernel, between events[3] and events[4], appends and attends; it
+ *     prunes as well, unless the ranking before it has, and ranks as well, unless the cache
+ *     is too long for that (1536 rows), or several workgroups rank a unit;
+ *   - a cache that is kept whole is mostly copied by the kernel that attends (bf16), and by
+ *     one of its own, between events[2] and events[3], where out lies on top of an input or
+ *     few cached rows stand beside a large map.
  * Where the attention runs in the pipelined bf16 kernel (all but small maps) the
  * two events around it are not recorded as stream operations of their own but attached
  * to that kernel's dispatch and receive its start and end times, so timing that kernel

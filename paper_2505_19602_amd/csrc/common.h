@@ -70,36 +70,38 @@ hipError_t launch_score_finalize(int n_unit, int n_win, int cache_len, ScoreWork
 hipError_t launch_select(int n_unit, const float* scores, long long score_unit_stride,
                          int cache_len, int keep, int32_t* idx, const SelectExtras* extras,
                          hipStream_t stream);
-// The whole ranking step in one launch (bf16 only): one workgroup per unit forms the logits of
-// the window rows against the unit's cached keys, the row normalisers and the log-scores
-// (Eq. 5) and selects.  Returns hipErrorNotSupported where score_select_fits() says no (and for fp32 or
+// The whole ranking step (bf16 only), by a workgroup per unit in one launch, or by several in three launches where
+// rank_spreads(): the logits of the window rows against the unit's cached keys, the row normalisers and the log-scores
+// (Eq. 5), and the selection.  Returns hipErrorNotSupported where score_select_fits() says no (and for fp32 or
 // very long caches), and the caller takes the launches of the single stages, which fill the chip whatever the units.
-// The logits part of `ws` is used, the chunk statistics are not.
-// Ranked steps of 300 queries that keep a quarter, us, one launch / several (d 128; units x rows):
-//   16 x 600: 24.3 / 24.2   16 x 1600: 39.7 / 31.9   16 x 4096: 68.5 / 41.7   16 x 6400: 103 / 54
-//   64 x 600: 34.8 / 36.1   64 x 1600: 52.9 / 47.3   64 x 4096: 97 / 76   64 x 6400: 153 / 106   64 x 12000: 270 / 173
-//   128 x 1600: 64.8 / 70.0   128 x 4096: 126 / 124   128 x 6400: 190 / 173     256 x 600: 65 / 75   256 x 4096: 188 / 222
-//   256 x 12000: 527 / 574    d 64: 60 x 1600: 36.6 / 37.2   60 x 4096: 62 / 53   128 x 4096: 79 / 83   256 x 12000: 292 / 338
-// Inside this line rank_spreads() says how the one ranking is launched; the several launches outside of it round the row
-// normalisers by chunks of 256 keys, so that rows at the border of a selection may differ in the last bit of their score.
+// Of `ws` the logits are used, and where the ranking is spread the scores and, for statistics, the place of the indices.
+// Ranked steps of 300 queries that keep a quarter, us, this ranking / the single stages (d 128; units x rows; 16 x 6400 and
+// 60 x 12000 lie beyond the line):
+//   16 x 600: 22.0 / 21.9   16 x 1600: 26.7 / 28.6   16 x 4096: 39.4 / 38.4   16 x 6400: 51.9 / 51.0   60 x 12000: 167 / 164
+//   64 x 600: 34.2 / 33.1   64 x 1600: 44.4 / 43.4   64 x 4096: 71.9 / 70.2   64 x 6400: 99.5 / 97.6   64 x 12000: 172 / 168
+//   128 x 1600: 62.3 / 61.8   128 x 4096: 115.5 / 114.5   128 x 6400: 168 / 168     256 x 600: 56.5 / 60.8   256 x 4096: 185 / 218
+//   256 x 12000: 545 / 577    d 64: 60 x 1600: 34.2 / 34.2   60 x 4096: 53.1 / 50.0   128 x 4096: 76.7 / 75.7   256 x 12000: 290 / 331
+// Up to 128 units the two are close, so that there the line decides little about time; it stays where it is because the
+// single stages round the row normalisers by chunks of 256 keys: rows at the border of a selection may differ in the last
+// bit of their score.
 inline bool score_select_fits(int dtype, int d, int n_unit, int cache_len) {
   return dtype == 1 && (d == 64 || d == 128) && cache_len <= 12288 && (n_unit >= 64 || cache_len <= 4096);
 }
 // Whether the ranking of a unit is spread over workgroups (three launches instead of one, the same rows bit for bit),
 // where score_select_fits().  `small`: the attention goes to the kernel for small work, which ranks up to kShortLen rows in
 // its own launch, and prunes.  Whole steps that keep a quarter, us, a workgroup per unit / spread:
-//   300 queries, d 128: 8 units x 600: 21.4 / 21.5   8 x 800: 24.8 / 22.9   8 x 1600: 36.5 / 26.7   8 x 4096: 65.6 / 35.9
-//     32 x 800: 33.9 / 32.4   32 x 1600: 47.3 / 40.3   64 x 800: 39.8 / 36.1   64 x 1600: 53.9 / 45.9   64 x 10000: 235 / 151
-//     96 x 1000: 48.5 / 47.0   96 x 1600: 61.9 / 58.7   96 x 4096: 115.5 / 102.8   128 x 1600: 64.8 / 66.2   128 x 4096: 118.4 / 119.9
-//     128 x 6000: 180 / 166   192 x 6000: 240 / 255
-//   d 64: 8 x 1000: 18.9 / 19.3   32 x 1000: 24.7 / 25.2   32 x 1600: 32.7 / 29.4   64 x 1600: 39.2 / 36.2   96 x 1600: 44.5 / 44.7
-//     96 x 4096: 77.4 / 76.8   96 x 6000: 112.8 / 102.6
-//   small, units, queries, rows, d 128: 16, 8, 600: 17.8 / 18.3   16, 8, 800: 21.4 / 19.1   16, 256, 900: 26.2 / 25.4
-//     32, 100, 900: 25.1 / 25.5   32, 448, 900: 39.1 / 41.6   32, 448, 1200: 43.8 / 43.7   32, 80, 1200: 28.0 / 25.4
-//     48, 80, 1200: 29.1 / 29.5   64, 64, 1536: 34.7 / 34.9   64, 64, 2000: 49.6 / 40.7   32, 256, 4096: 79.8 / 55.2
-//     96, 20, 2000: 47.5 / 47.0   128, 16, 2000: 48.4 / 53.3
-//     d 64: 8, 8, 1000: 17.6 / 18.2   16, 256, 1400: 23.9 / 21.9   24, 160, 1400: 23.6 / 22.9   32, 128, 1400: 23.7 / 24.6
-//     64, 32, 3000: 40.8 / 37.6   96, 32, 3000: 42.2 / 44.1
+//   300 queries, d 128: 8 units x 600: 19.2 / 19.9   8 x 800: 21.8 / 20.3   8 x 1600: 32.8 / 23.0   8 x 4096: 59.3 / 31.0
+//     32 x 800: 29.6 / 29.2   32 x 1600: 43.1 / 36.3   64 x 800: 37.8 / 34.9   64 x 1600: 52.5 / 44.8   64 x 10000: 226 / 147
+//     96 x 1000: 45.4 / 44.8   96 x 1600: 60.4 / 57.0   96 x 4096: 112 / 100   128 x 1600: 61.9 / 63.5   128 x 4096: 116 / 117
+//     128 x 6000: 174 / 163   192 x 6000: 236 / 251
+//   d 64: 8 x 1000: 16.5 / 17.5   32 x 1000: 22.5 / 24.3   32 x 1600: 30.4 / 27.6   64 x 1600: 37.3 / 34.8   96 x 1600: 43.2 / 43.4
+//     96 x 4096: 74.7 / 75.0   96 x 6000: 109 / 100
+//   small, units, queries, rows, d 128: 16, 8, 600: 16.3 / 17.6   16, 8, 800: 19.0 / 18.8   16, 256, 900: 23.0 / 22.1
+//     32, 100, 900: 21.7 / 21.9   32, 448, 900: 33.3 / 37.0   32, 80, 1200: 24.6 / 23.1   32, 448, 1200: 37.6 / 40.7 (the kernel
+//     for small work has become faster since the line was drawn)   48, 80, 1200: 25.7 / 27.5   64, 64, 1536: 29.9 / 32.0
+//     64, 64, 2000: 46.6 / 37.4   32, 256, 4096: 73.9 / 49.3   96, 20, 2000: 44.7 / 44.7   128, 16, 2000: 46.7 / 52.3
+//     d 64: 8, 8, 1000: 15.4 / 18.2   16, 256, 1400: 20.9 / 19.6   24, 160, 1400: 20.4 / 20.6   32, 128, 1400: 20.7 / 21.4
+//     64, 32, 3000: 38.9 / 36.1   96, 32, 3000: 41.6 / 45.3
 inline bool rank_spreads(int d, int n_unit, int cache_len, bool small) {
   if (small && cache_len <= kShortLen)
     return d == 128 ? n_unit <= (cache_len >= 1000 ? 32 : 16) && cache_len >= 800 : n_unit <= 24 && cache_len >= 1300;
@@ -109,8 +111,8 @@ inline bool rank_spreads(int d, int n_unit, int cache_len, bool small) {
 // Where the ranking is spread, whether the kernel for small work leaves the pruning to it: its own copying workgroups come
 // behind the n_wg attending ones, and wait for a round of their own where those (nearly) fill the compute units.
 // us, pruned by the small kernel / before (n_wg, d 128): 32 units, 80 queries, 1200 rows (160)
-// 25.4 / 26.9; 48, 40, 2000 (144) 35.0 / 35.8; 48, 64, 2000 (192) 38.7 / 36.6; 32, 100, 1200 (224) 32.2 / 29.4;
-// 64, 64, 1536 (256) 37.7 / 34.9; 16, 256, 4096 (256) 46.5 / 41.9.
+// 23.6 / 25.3; 48, 40, 2000 (144) 33.8 / 33.0; 48, 64, 2000 (192) 36.4 / 34.8; 32, 100, 1200 (224) 29.6 / 26.2;
+// 64, 64, 1536 (256) 30.0 / 29.9; 16, 256, 4096 (256) 40.8 / 37.2.
 inline bool small_pruned_before(long long n_wg) { return n_wg > 160; }
 // Whether selection and pruning share a launch behind launch_score_logits: a workgroup per unit, or several where there are
 // fewer units than compute units.  Up to 256 units; more are not served in one round (fp32 steps, us, two launches / one:
@@ -235,25 +237,25 @@ inline SmallWork step_work(int keep, int cache_len) {
 // are the better ones.  A workgroup of it fills a compute unit, and its time grows with the rows it
 // carries, so: the fewest rows with which the chip's 256 compute units take the launch in one round.
 // Measured against ranking + pruning + pipelined attention (us, d 128; units, queries, cached, kept; this kernel's
-// time stands first, also where the rule takes the other side):
-//   16 rows:   16 x 144, 340, 80: 16.4 / 25.0       16 x 144, 5000, 5000: 60.8 / 88.6     16 x 256, 1200, 300: 28.1 / 42.5
-//   32 rows:   32 x 256, 380, 82: 21.8 / 28.0       16 x 400, 1500, 1500: 27.0 / 39.5     8 x 1024, 1500, 700: 45.5 / 65.1
-//   64 rows:   16 x 1024, 820, 390: 49.7 / 52.4     64 x 256, 380, 82: 26.3 / 28.6        16 x 576, 1200, 300: 43.2 / 46.6
-//              16 x 1024, 400, 80: 40.7 / 39.3      (the narrowest; head_dim 64, 16 x 1024, 820, 390: 31.3 / 37.3)
-//   128 rows:  256 x 128, 300, 60: 28.5 / 28.4      (equal by now; up to 320 keys)
-//              128 x 256, 380, 82: 33.9 / 32.2      128 x 144, 5000, 5000: 295 / 202     (longer: not worth it)
+// time stands first, also where the rule takes the other side; every row kept: see below):
+//   16 rows:   16 x 144, 340, 80: 15.1 / 24.0       16 x 256, 1200, 300: 24.5 / 31.0
+//   32 rows:   32 x 256, 380, 82: 20.0 / 26.0       8 x 1024, 1500, 700: 38.5 / 45.2
+//   64 rows:   64 x 256, 380, 82: 24.7 / 27.0       16 x 1024, 400, 80: 35.3 / 36.0
+//              16 x 576, 1200, 300, ranked before: 35.4 / 34.6  (the narrowest; head_dim 64, 16 x 1024, 820, 390: 30.0 / 34.2)
+//   128 rows:  256 x 128, 300, 60: 25.4 / 27.6      (up to 320 keys)
+//              128 x 256, 380, 82: 30.3 / 30.4      (longer: not worth it)
 // From 64 rows on it is what the launch does besides the attention that pays: the attention alone is then faster in the
-// pipelined kernel (64 x 144 queries, 300 keys: 13.6 / 10.6; 128 x 144, 300 keys, 128 rows: 19.8 / 11.5), and with few
-// keys from 32 rows on (8 x 700, 64 keys: 7.3 / 5.2; 130: 8.3 / 8.0; 400: 11.4 / 11.9).  A ranking in the same launch
+// pipelined kernel (64 x 144 queries, 300 keys: 12.1 / 10.2; 128 x 144, 300 keys, 128 rows: 17.9 / 10.4), and with few
+// keys from 32 rows on (8 x 700, 64 keys: 7.1 / 5.3; 130: 8.0 / 7.9; 400: 10.3 / 11.7).  A ranking in the same launch
 // is repeated by every workgroup of a unit: 64 rows pay up to 16 of those, 32 only with head_dim 64 (8 x 2048, 380, 82:
-// 58.7 / 51.5, head_dim 64 33.3 / 36.0).  Without one 64 rows pay while
+// 50.1 / 47.8, head_dim 64 33.5 / 35.2).  Without one 64 rows pay while
 // the workgroups leave some compute units to those that copy, which otherwise wait for a round of their
-// own (ranked before, 2500 cached, 300 kept: 64 x 144 51.8 / 54.7; 64 x 256 58.8 / 56.1; 16 x 1024 69.2 / 63.9), 128 rows do
+// own (ranked before, 2500 cached, 300 kept: 64 x 144 44.8 / 45.0; 64 x 256 49.1 / 46.0; 16 x 1024 51.2 / 45.4), 128 rows do
 // not.
-// Appending alone copies least and gains least: head_dim 64, up to 224 workgroups, 0.86-0.95 of the time over 500
-// keys and more; head_dim 128: 1.00-1.24.
+// Appending alone copies least and gains least: head_dim 64, up to 224 workgroups (64 rows: 56 x 200, 500 keys: 11.5 / 12.5;
+// 64 x 256, 256 workgroups: 16.2 / 12.3; thousands of keys: 224 x 62, 4035: 42.1 / 39.1); head_dim 128: 64 x 144, 500: 17.3 / 16.3.
 // More units than compute units: two rounds are paid, which only maps of up to 16 queries stand
-// (320 x 4, 65, 65: 11.7 / 18.2;  512 x 16, 69, 14: 19.9 / 18.7;  320 x 36, 85, 21, 128 rows: 20.5 / 20.1).
+// (320 x 4, 65, 65: 8.1 / 10.1;  512 x 16, 69, 14: 18.1 / 18.4).
 //
 // keep_all_is_pipelined(): where every row is kept, the pipelined kernel copies the tiles that pass through it, while
 // this one has workgroups for that behind the n_wg attending ones, of `rows` query rows, which read everything once

@@ -1,7 +1,8 @@
-// Top-k of Sec. 3.3 for one (sequence, head) unit per workgroup.
+// Top-k of Sec. 3.3: a workgroup selects for one (sequence, head) unit.  Where it prunes as well, several may share a
+// unit: each selects the same rows and copies a part of them.
 //
-// Scores are mapped to order-preserving unsigned keys; a 4-pass, 8-bit radix
-// select finds the key T of the keep-th largest score; one stable pass then
+// Scores are mapped to order-preserving unsigned keys; an 8-bit radix
+// select of up to four passes finds the key T of the keep-th largest score; one stable pass then
 // emits, in ascending index order, every index with key > T and the first
 // (keep - #greater) indices with key == T.  Only integer compares are involved,
 // so the result is deterministic and ties always go to the lower index.
@@ -9,8 +10,8 @@
 // Two optional parts of the paper's selection are folded into the key set-up:
 // average pooling of the scores along the cache axis (odd width, zeros beyond the
 // ends; done on log-scores as a log-sum-exp, which ranks the same), and positions
-// that are preserved whatever their score (the observation window): those get the
-// largest key, and `keep` counts them.
+// that are preserved whatever their score (the observation window): those take no part in
+// the search, are emitted with the others, and `keep` counts them.
 #include <type_traits>
 
 #include "common.h"

@@ -73,6 +73,11 @@ def pipe_form(d: int, units: int, n_q: int, kv: int) -> str:
     return "wide" if -(-wide // COMPUTE_UNITS) * 9600 <= plain_rounds * 100 else "plain"
 
 
+def pipe_copies_cache(d: int, units: int, n_q: int, cached: int) -> bool:
+    """Whether the pipelined kernel copies the rows of a cache that is kept whole; otherwise a launch before it does."""
+    return pipe_form(d, units, n_q, cached + n_q) != "wide" or 2 * cached >= n_q
+
+
 def pipe_rows(form: str) -> int:
     """Query rows per workgroup."""
     return 256 if form == "wide" else 128
@@ -104,7 +109,7 @@ def step_spreads(dtype: torch.dtype, d: int, units: int, n_cur: int, cache_len: 
 
 
 def step_kernel(dtype: torch.dtype, d: int, units: int, n_cur: int, cache_len: int, budget: int) -> str:
-    """The same for the attention of scalekv_step; "small" prunes and appends in the same launch."""
+    """The same for the attention of scalekv_step; "small" appends in the same launch, and prunes unless the ranking has."""
     keep = min(budget, cache_len)
     work = step_work(keep, cache_len)
     if work == RANKED and step_spreads(dtype, d, units, n_cur, cache_len, budget) and \

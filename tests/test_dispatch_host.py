@@ -68,9 +68,9 @@ int main() {
   for (int u : units) for (int q : queries) for (int k : keys)
     for (int d = 64; d <= 128; d += 64) {
       const PipeForm f = pipe_form(d, u, q, k);
-      printf("%%s %%d %%d %%d %%d\\n", f == PipeForm::kPlain ? "plain" : f == PipeForm::kWide ? "wide" : "split", pipe_rows(f),
+      printf("%%s %%d %%d %%d %%d %%d\\n", f == PipeForm::kPlain ? "plain" : f == PipeForm::kWide ? "wide" : "split", pipe_rows(f),
              small_tile_rows(1, d, u, q, k, SmallWork::kRankedBefore), rows_go_past_caches(CacheWriter::kRanking, u, k, 2 * d),
-             rows_go_past_caches(CacheWriter::kCompact, u, k, 2 * d));
+             rows_go_past_caches(CacheWriter::kCompact, u, k, 2 * d), pipe_copies_cache(d, u, q, k));
     }
   const int lengths[] = {%s};
   for (int n : lengths) for (int keep : {0, 1, n - 1, n}) printf("%%d\\n", (int)step_work(keep, n));
@@ -95,7 +95,8 @@ def test_forms_of_the_pipelined_kernel_are_the_rules_of_the_library(tmp_path):
                     seen.add((d, form))
                     rows = routes.small_tile_rows(torch.bfloat16, d, u, q, k, routes.RANKED_BEFORE)
                     past = [int(routes.rows_go_past_caches(ranking, u, k, 2 * d)) for ranking in (True, False)]
-                    assert next(lines) == f"{form} {routes.pipe_rows(form)} {rows} {past[0]} {past[1]}", (u, q, k, d)
+                    copies = int(routes.pipe_copies_cache(d, u, q, k))
+                    assert next(lines) == f"{form} {routes.pipe_rows(form)} {rows} {past[0]} {past[1]} {copies}", (u, q, k, d)
     for n in LENGTHS:
         for keep in (0, 1, n - 1, n):
             assert int(next(lines)) == routes.step_work(keep, n), (keep, n)
