@@ -364,10 +364,7 @@ __device__ __forceinline__ void rank_short(const uint16_t* qu, const WindowRows&
         for (int x = 0; x < 4; ++x) {
           const int group = first + 4 * g + x;
           const float m = lds.group_max[min(group, n_group - 1)][i], e = lds.group_sum[min(group, n_group - 1)][i];
-          float m_new = vm[x], e_new = ve[x];
-          join_keys(m_new, e_new, m, e);
-          vm[x] = group < n_group ? m_new : vm[x];
-          ve[x] = group < n_group ? e_new : ve[x];
+          if (group < n_group) join_keys(vm[x], ve[x], m, e);
         }
       }
     own_shift = row_shift<false>(vm, ve, (min(n_group, kVirtualWaves) + 3) / 4);
