@@ -52,13 +52,13 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 ATTEND_PIPE_TRAFFIC = {
     (36, 19): 19.4e6,  # every row kept: the cache is copied as well
     (144, 46): 63.1e6, (144, 9): 58.2e6,
-    (256, 82): 120.2e6, (256, 16): 108.5e6,
-    (400, 146): 176.8e6, (400, 29): 161.5e6,
+    (256, 82): 123.1e6, (256, 16): 113.7e6,
+    (400, 146): 176.9e6, (400, 29): 161.5e6,
     (576, 246): 264.4e6, (576, 49): 236.2e6,
     (1024, 390): 454.1e6, (1024, 78): 413.3e6,
-    (1600, 646): 764.7e6, (1600, 129): 678.8e6,
-    (2304, 1046): 1277.9e6, (2304, 209): 1125.4e6,
-    (4096, 1622): 1947.1e6, (4096, 324): 1777.3e6,
+    (1600, 646): 764.8e6, (1600, 129): 680.6e6,
+    (2304, 1046): 1278.1e6, (2304, 209): 1124.2e6,
+    (4096, 1622): 1944.8e6, (4096, 324): 1753.4e6,
 }
 
 
