@@ -351,9 +351,10 @@ inline PipeForm pipe_form(int d, int n_unit, int n_q, int kv) {
 inline int pipe_rows(PipeForm form) { return form == PipeForm::kWide ? 256 : 128; }  // query rows per workgroup
 
 // Whether a step that keeps all `cached` rows leaves their copy to that kernel.  In its wide form the copies of both segments
-// pass through the loop, where the map's own rows cost more than at its end: with few cached rows beside many of the map
-// a copy before it is as good.  Steps, us, copied before / by the kernel: 256 units x 4096 queries, 100 rows 1964 / 1988,
-// 800 2290 / 2306, 1500 2609 / 2614, 2500 3081 / 3077, 6489 4990 / 4870; 256 x 2304, 200 725 / 717, 1500 1085 / 1056.
+// pass through the loop, where the map's own rows cost more than at its end: with few cached rows beside 4096 of the map
+// a copy before it is as good or better.  Steps, us, copied before / by the kernel: 256 units x 4096 queries, 100 rows
+// 1973 / 1993, 800 2296 / 2311, 1500 2623 / 2628, 2500 3087 / 3089, 6489 4990 / 4870.  With fewer queries the line lies
+// too high, by up to 3 % of a step: 256 x 2304, 200 728 / 720, 1000 942 / 924, 1500 1085 / 1060; 128 x 2040, 300 298 / 292.
 inline bool pipe_copies_cache(int d, int n_unit, int n_q, int cached) {
   return pipe_form(d, n_unit, n_q, cached + n_q) != PipeForm::kWide || 2LL * cached >= n_q;
 }
