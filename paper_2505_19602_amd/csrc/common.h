@@ -263,8 +263,9 @@ inline SmallWork step_work(int keep, int cache_len) {
 // the length of the cache what it gains by copying.  Small / pipelined, us (units, queries, cached rows):
 //   64 rows, d 128: 8, 1000, 800 (n_wg 128): 24.8 / 31.9   24, 465, 69 (168): 16.0 / 16.3   40, 200, 200 (160): 14.0 / 14.5
 //     64, 144, 800 (192): 27.6 / 23.0   32, 400, 3000 (224): 64.3 / 55.9
-//     d 64: 8, 1000, 800: 16.2 / 21.5   24, 500, 800 (192): 17.2 / 17.7   96, 103, 438 (192): 14.9 / 11.8   20, 650, 101 (220):
-//     12.5 / 13.5   16, 900, 800 (240): 24.3 / 21.4
+//     d 64: 8, 1000, 800: 16.2 / 21.5   24, 500, 800 (192): 17.2 / 17.7   96, 103, 438 (192): 14.9 / 11.8   16, 900, 800 (240): 24.3 / 21.4
+//     up to 223 workgroups with few keys, n_pipe 120: 20, 650, 101 (220): 12.6 / 13.5   24, 525, 26 (216): 11.0 / 12.2   (more keys:
+//     40, 265, 1201 (200): 22.1 / 19.5; n_pipe 200: 200, 40, 200: 12.2 / 9.5)
 //   32 rows, d 128 (n_wg, n_pipe): 16, 485, 230 (256, 64): 16.4 / 17.5   16, 485, 4009: 54.0 / 72.4   32, 254, 300 (256, 64):
 //     16.0 / 15.5   32, 254, 1700: 36.9 / 39.0   32, 254, 4473: 67.6 / 85.6   60, 108, 550 (240, 60): 22.1 / 19.5   60, 108, 1700: 39.7 / 43.9
 //     12, 546, 800 (216, 60): 17.4 / 26.1   32, 200, 800 (224, 64): 19.7 / 23.2   48, 100, 800 (192, 48): 19.6 / 24.0
@@ -289,9 +290,9 @@ inline SmallWork step_work(int keep, int cache_len) {
 //     d 64: 272, 5000: 158 / 173      within: 160, 6000: 103.4 / 79.3
 inline bool keep_all_is_pipelined(int d, int n_unit, int n_q, int rows, long long n_wg, int kv) {
   const long long n_pipe = (long long)n_unit * ((n_q + 127) / 128);  // pipelined workgroups
-  if (rows >= 64) return n_wg > (d == 128 ? 128 : 192);
+  if (rows >= 64) return d == 128 ? n_wg > 128 : n_wg > 192 && (n_wg >= 224 || n_pipe > 128 || kv >= 1024);
   if (rows == 32 && n_pipe >= (d == 128 ? 96 : 112)) return kv > 256;
-  if (rows == 32) return kv > 256 && kv <= 1024 && (n_unit >= 96 || (d == 128 && n_unit >= 32 && n_wg > 224));
+  if (rows == 32) return kv > 256 && kv <= 1280 && (n_unit >= 96 || (d == 128 && n_unit >= 32 && n_wg > 224));
   const long long elements = (long long)n_unit * kv * d;  // of the new keys, and as many values
   if (4 * elements > (256 << 20)) {
     const int rounds = (n_unit + 255) / 256;

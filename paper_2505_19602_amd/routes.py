@@ -15,11 +15,11 @@ def keep_all_is_pipelined(d: int, units: int, n_q: int, rows: int, n_wg: int, kv
     """Whether a step that keeps every row takes the pipelined kernel, which copies the tiles that pass."""
     n_pipe = units * -(-n_q // 128)
     if rows >= 64:
-        return n_wg > (128 if d == 128 else 192)
+        return n_wg > 128 if d == 128 else n_wg > 192 and (n_wg >= 224 or n_pipe > 128 or kv >= 1024)
     if rows == 32 and n_pipe >= (96 if d == 128 else 112):
         return kv > 256
     if rows == 32:
-        return 256 < kv <= 1024 and (units >= 96 or (d == 128 and units >= 32 and n_wg > 224))
+        return 256 < kv <= 1280 and (units >= 96 or (d == 128 and units >= 32 and n_wg > 224))
     elements = units * kv * d
     if 4 * elements > 256 << 20:
         return 16 * units >= 10 * COMPUTE_UNITS * -(-units // COMPUTE_UNITS)

@@ -11,7 +11,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 UNITS = (1, 2, 9, 16, 31, 32, 40, 48, 63, 64, 80, 96, 111, 112, 127, 128, 129, 160, 161, 191, 192, 199, 200, 224, 225, 256, 257, 300,
          319, 320, 321, 383, 384, 512, 4000)
 QUERIES = (1, 4, 16, 17, 32, 33, 64, 65, 100, 128, 129, 200, 256, 300, 448, 576, 1024, 1025, 2049, 4096)
-KEYS = (1, 60, 117, 118, 256, 257, 320, 321, 326, 511, 512, 976, 977, 1024, 1025, 1400, 2000, 2001, 2999, 3000, 4096, 4097, 6500, 12288, 12289, 60000)
+KEYS = (1, 60, 117, 118, 256, 257, 320, 321, 326, 511, 512, 976, 977, 1023, 1024, 1280, 1281, 1400, 2000, 2001, 2999, 3000, 4096, 4097, 6500, 12288, 12289, 60000)
 LENGTHS = (1, 2, 1535, 1536, 1537, 4096)   # cached rows: ranked in the launch that attends up to 1536
 PROGRAM = """
 #include <cstdio>
@@ -52,7 +52,7 @@ def test_routes_are_the_rules_of_the_library(tmp_path):
 def test_long_caches_that_are_kept_whole_go_where_the_chip_is_filled():
     kernel = lambda d, units, n, cached: routes.step_kernel(torch.bfloat16, d, units, n, cached, cached)
     for case in ((128, 128, 16, 5000), (128, 152, 5, 4200), (128, 272, 8, 3000), (128, 304, 5, 2500), (64, 272, 5, 5000),
-                 (128, 16, 485, 4009), (128, 32, 254, 4473), (128, 64, 109, 2176), (64, 96, 37, 1812), (64, 128, 5, 800)):
+                 (128, 16, 485, 4009), (128, 32, 254, 4473), (128, 64, 109, 2176), (64, 96, 37, 1812), (64, 128, 5, 800), (64, 20, 650, 101)):
         assert kernel(*case) == "small", case
     for case in ((128, 128, 10, 3000), (128, 168, 8, 4200), (128, 256, 8, 3000), (128, 288, 8, 1500), (128, 384, 8, 3000),
                  (64, 160, 8, 6000), (128, 48, 160, 800), (128, 40, 173, 221), (64, 128, 60, 800), (64, 168, 10, 800)):
